@@ -799,21 +799,13 @@ void launch_bbox(Dev& d, const BuildCfg& c, const double* pos, const double* mas
 }
 
 void launch_keys(Dev& d, const BuildCfg& c, const double* pos, int nblk, hipStream_t s) {
-    // with an odd number of sort passes the keys start in keys_alt, so that the
-    // sorted keys and permutation end in (keys, perm) without a copy
-    uint64_t* out = (radix_passes(3 * c.D + c.cbits) & 1) ? d.keys_alt : d.keys;
     hipLaunchKernelGGL(k_keys, dim3(nblk), dim3(BB_T), 0, s, pos, (const int64_t*)d.blk_range,
-                       (const int32_t*)d.blk_cluster, (const double*)d.cl_box, c.D, out);
+                       (const int32_t*)d.blk_cluster, (const double*)d.cl_box, c.D,
+                       sort_iota_in_alt(c.n) ? d.keys_alt : d.keys);
 }
 
 void launch_key_sort(Dev& d, const BuildCfg& c, hipStream_t s) {
-    const int nbits = 3 * c.D + c.cbits;
-    if (radix_passes(nbits) & 1)
-        radix_sort_pairs(d.keys_alt, d.vals_alt, d.keys, d.perm, c.n, nbits, d.rs_hist, d.scan_tmp, s,
-                         true, nullptr, true);
-    else
-        radix_sort_pairs(d.keys, d.perm, d.keys_alt, d.vals_alt, c.n, nbits, d.rs_hist, d.scan_tmp, s,
-                         true);
+    sort_iota(d.keys, d.perm, d.keys_alt, d.vals_alt, c.n, 3 * c.D + c.cbits, d.rs_hist, d.scan_tmp, d.sort_tmp, s);
 }
 
 void launch_gather(Dev& d, const BuildCfg& c, const double* pos, const double* mass, hipStream_t s) {

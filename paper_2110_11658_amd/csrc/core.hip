@@ -490,8 +490,8 @@ void launch_core(const CoreLaunch& c, hipStream_t s) {
     hipLaunchKernelGGL(k_core_radius, dim3(1), dim3(kStatT), 0, s, nc, (const double*)c.bsum, c.stats);
     const int64_t nb = (n + 255) / 256;
     hipLaunchKernelGGL(k_core_dist, dim3((unsigned)(nb < kDistGrid ? nb : kDistGrid)), dim3(256), 0, s, n, c.pos,
-                       (const double*)c.stats, c.keys, c.ncore);
-    radix_sort_pairs(c.keys, c.vals, c.keys_alt, c.vals_alt, n, 64, c.hist, c.scan_tmp, s, true);
+                       (const double*)c.stats, sort_iota_in_alt(n) ? c.keys_alt : c.keys, c.ncore);
+    sort_iota(c.keys, c.vals, c.keys_alt, c.vals_alt, n, 64, c.hist, c.scan_tmp, c.sort_tmp, s);
     const int64_t nblk = (n + kCrossBlk - 1) / kCrossBlk;
     hipLaunchKernelGGL(k_core_bsum, dim3((unsigned)nblk), dim3(kCrossBlk), 0, s, n, (const int32_t*)c.vals,
                        c.mass, c.bsum);

@@ -243,7 +243,8 @@ pbh_status ensure_buffers(pbh_ctx* ctx) {
               dalloc(ctx, &d.g.lo, 3 * G) && dalloc(ctx, &d.g.hi, 3 * G) && dalloc(ctx, &d.fill_list, G) &&
               dalloc(ctx, &d.stage_k, n) &&
               dalloc(ctx, &d.scan_tmp, scan_len) &&
-              dalloc(ctx, &d.rs_hist, radix_hist_need(big) + 1) && dalloc(ctx, &d.nbr_cnt, n) &&
+              dalloc(ctx, &d.rs_hist, radix_hist_need(big) + 1) &&
+              dalloc(ctx, &d.sort_tmp, sort_scratch_need(n)) && dalloc(ctx, &d.nbr_cnt, n) &&
               dalloc(ctx, &d.stack, stack) && dalloc(ctx, &d.cnt, kNumCounters) &&
               dalloc(ctx, &d.queues, 32) &&
               dalloc(ctx, &d.wave_log, 2 * (stack / kStackCap)) &&
@@ -1224,6 +1225,7 @@ pbh_status pbh_core(pbh_ctx* ctx, const double* pos, const double* mass, int64_t
     c.vals_alt = d.core_vals_alt;
     c.hist = d.rs_hist;
     c.scan_tmp = d.scan_tmp;
+    c.sort_tmp = d.sort_tmp;
     c.bsum = d.core_bsum;
     c.ncore = d.core_cnt;
     c.err = d.core_cnt + 1;

@@ -165,6 +165,7 @@ struct Dev {
     int64_t scan_tmp_len = 0;
     // radix-sort histogram scratch
     int64_t* rs_hist = nullptr;
+    int32_t* sort_tmp = nullptr;     // sample-sort scratch
     int64_t rs_hist_len = 0;
     // neighbour counts
     int32_t* nbr_cnt = nullptr;
@@ -222,6 +223,15 @@ int radix_passes(int nbits);
 void radix_sort_pairs(uint64_t* keys, int32_t* vals, uint64_t* keys_alt, int32_t* vals_alt,
                       int64_t n, int nbits, int64_t* hist, int64_t* scan_tmp, hipStream_t s,
                       bool vals_are_iota, const int32_t* n_dev = nullptr, bool to_alt = false);
+
+// Stable sort of (key, position) on bits [0, nbits): the keys are in `keys` on
+// entry (in `keys_alt` when sort_iota_in_alt(n)); sorted in `keys`, vals[k] = the original position of the k-th; keys_alt and
+// vals_alt are scratch of the same size, `scratch` holds sort_scratch_need(n)
+// words, hist and scan_tmp are the radix sort's (used above 2^22 keys).
+int64_t sort_scratch_need(int64_t n);
+bool sort_iota_in_alt(int64_t n);
+void sort_iota(uint64_t* keys, int32_t* vals, uint64_t* keys_alt, int32_t* vals_alt, int64_t n, int nbits,
+               int64_t* hist, int64_t* scan_tmp, int32_t* scratch, hipStream_t s);
 
 // threads per workgroup of the per-level moment kernels (the host sizes their grids)
 constexpr int kMomT = 64;   // 32, 128 and 256 built slower at 2^20
@@ -321,6 +331,7 @@ struct CoreLaunch {
     int32_t* vals_alt = nullptr;
     int64_t* hist = nullptr;           // radix-sort scratch of the build
     int64_t* scan_tmp = nullptr;
+    int32_t* sort_tmp = nullptr;
     double* bsum = nullptr;            // [core_bsum_len(n)]
     unsigned long long* ncore = nullptr;
     unsigned long long* err = nullptr;
