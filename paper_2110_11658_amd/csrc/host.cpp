@@ -245,8 +245,9 @@ pbh_status ensure_buffers(pbh_ctx* ctx) {
               dalloc(ctx, &d.scan_tmp, scan_len) &&
               dalloc(ctx, &d.rs_hist, radix_hist_need(big) + 1) &&
               dalloc(ctx, &d.sort_tmp, sort_scratch_need(n)) && dalloc(ctx, &d.nbr_cnt, n) &&
-              dalloc(ctx, &d.stack, stack) && dalloc(ctx, &d.cnt, kNumCounters) &&
-              dalloc(ctx, &d.queues, 32) &&
+              dalloc(ctx, &d.stack, stack) && dalloc(ctx, &d.cnt, kNumCounters + kQueueWords) &&
+              dalloc(ctx, (char**)&d.part_sum, (int64_t)kWalkSlots * kWalkSlotBytes) &&
+              dalloc(ctx, &d.part_done, kWalkShared) &&
               dalloc(ctx, &d.wave_log, 2 * (stack / kStackCap)) &&
               dalloc(ctx, &d.wave_log_nbr, 2 * (stack / kStackCap)) &&
               dalloc(ctx, &d.wave_cyc, stack / kStackCap);
@@ -254,6 +255,7 @@ pbh_status ensure_buffers(pbh_ctx* ctx) {
         free_all(ctx);
         return fail(ctx, PBH_E_OOM, "device allocation failed");
     }
+    d.queues = d.cnt + kNumCounters;
     d.scan_tmp_len = scan_len;
     d.stack_len = stack;
     ++ctx->alloc_gen;
@@ -415,7 +417,7 @@ pbh_status launch_build(pbh_ctx* ctx, const double* pos, const double* mass, hip
 void enqueue_build(pbh_ctx* ctx, const double* pos, const double* mass, hipStream_t s) {
     Dev& d = ctx->d;
     const BuildCfg& c = ctx->cfg;
-    launch_zero_u64(d.cnt, kNumCounters - 5, s);   // keep the KDK slots (>= 11)
+    launch_zero_counts(d.cnt, s);   // keeps the KDK slots (>= 11)
     launch_bbox(d, c, pos, mass, ctx->nblk_box, s);
     launch_keys(d, c, pos, ctx->nblk_box, s);
     launch_key_sort(d, c, s);
@@ -1495,20 +1497,18 @@ pbh_status pbh_get_stats(pbh_ctx* ctx, pbh_stats* out) {
         out->error_flags = (int64_t)(f << 8);
     }
     if (!ctx->d.cnt) return PBH_OK;
-    unsigned long long h[kNumCounters];
-    HIP_TRY(hipMemcpy(h, ctx->d.cnt, sizeof(h), hipMemcpyDeviceToHost));
+    std::vector<unsigned long long> h(kNumCounters + kQueueWords);
+    HIP_TRY(hipMemcpy(h.data(), ctx->d.cnt, h.size() * sizeof(h[0]), hipMemcpyDeviceToHost));
     out->n = ctx->cfg.n;
     out->n_clusters = ctx->cfg.n_clusters;
     out->n_nodes = (int64_t)h[kCntNodes];
     out->n_leaves = (int64_t)h[kCntLeaves];
     out->n_groups = (int64_t)h[kCntGroups];
     out->max_level = (int64_t)h[kCntMaxLevel];
-    out->n_pn = (int64_t)h[kCntPN];
-    out->n_pp_far = (int64_t)h[kCntFar];
-    out->n_pp_near = (int64_t)h[kCntNear];
-    out->lane_slots_pn = (int64_t)h[kCntSlotPN];
-    out->lane_slots_far = (int64_t)h[kCntSlotFar];
-    out->lane_slots_near = (int64_t)h[kCntSlotNear];
+    int64_t* const sums[6] = {&out->n_pn, &out->n_pp_far, &out->n_pp_near, &out->lane_slots_pn,
+                              &out->lane_slots_far, &out->lane_slots_near};
+    for (int l = 0; l < kWalkCntLines; ++l)
+        for (int k = 0; k < 6; ++k) *sums[k] += (int64_t)h[kNumCounters + kWalkCntAt + l * kQueueStride + k];
     out->error_flags |= (int64_t)h[kErr];
     if (ctx->ev_build) out->ms_build = event_ms(ctx->ev[0], ctx->ev[1]);
     if (ctx->ev_walk) out->ms_walk = event_ms(ctx->ev[2], ctx->ev[3]);

@@ -45,7 +45,7 @@ struct NbrParams {
     int32_t* stack;
     int stack_cap;
     unsigned long long* cnt;
-    unsigned long long* queues;    // [kQueues] of this pass
+    unsigned long long* queues;    // heads of this pass, kQueueStride apart
     unsigned long long* wave_log;  // per workgroup: groups done, clock ticks
 };
 
@@ -257,7 +257,7 @@ NbrParams make_params(Dev& d, const BuildCfg& c, int stack_cap) {
     p.stack = d.stack;
     p.stack_cap = stack_cap;
     p.cnt = d.cnt;
-    p.queues = d.queues + kQueues;
+    p.queues = d.queues + kFillQueuesAt;
     p.wave_log = d.wave_log_nbr;
     (void)c;
     return p;
@@ -281,7 +281,6 @@ void launch_nbr_fill(Dev& d, const BuildCfg& c, int grid, int stack_cap, const i
     p.off = off;
     p.idx = idx;
     p.cap = cap;
-    p.queues = d.queues + 2 * kQueues;
     hipLaunchKernelGGL(k_nbr_fill, dim3(grid), dim3(64), 0, s, p);
 }
 

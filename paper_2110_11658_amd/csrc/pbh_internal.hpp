@@ -35,11 +35,20 @@ enum : unsigned long long {
 };
 
 // slots of the device counter array
-// kCntSlot*: wave-instruction slots of the walk's evaluation loops (64 lanes
-// per loop iteration), beside the interactions they carried (kCntPN, ...)
-enum { kCntNodes = 0, kCntPN = 1, kCntFar = 2, kCntNear = 3, kCntNbrTotal = 4, kErr = 5,
-       kCntSlotPN = 6, kCntSlotFar = 7, kCntSlotNear = 8,
+enum { kCntNodes = 0, kCntNbrTotal = 4, kErr = 5,
        kCntMaxLevel = 9, kCntLeaves = 10, kCntGroups = 12, kCntFill = 13, kNumCounters = 16 };
+
+// Behind the counters, on lines of their own (thousands of waves meet there):
+// the heads of the walk's group queues (one per XCD), the walk's interaction
+// counters (lines of six: multipole, far and near interactions, then the lane
+// slots of their evaluation loops, 64 per loop iteration; a wave adds to line
+// blockIdx mod kWalkCntLines), and the heads of the neighbour fill's queues.
+constexpr int kQueues = 8;
+constexpr int kQueueStride = 32;
+constexpr int kWalkCntLines = 64;
+constexpr int kWalkCntAt = kQueues * kQueueStride;
+constexpr int kFillQueuesAt = kWalkCntAt + kWalkCntLines * kQueueStride;
+constexpr int kQueueWords = kFillQueuesAt + kQueues * kQueueStride;
 
 struct alignas(16) WNode {
     double lo[3];
@@ -106,6 +115,11 @@ struct BuildCfg {
 inline int group_hist_reps(int n_clusters) {
     return n_clusters >= 256 ? 1 : (n_clusters > 4 ? 256 / n_clusters : 64);
 }
+
+// Most groups of a walk that two waves share, and their (group, part) pairs.
+constexpr int kWalkShared = 8192;
+constexpr int kWalkSlots = 2 * kWalkShared;
+constexpr int kWalkSlotBytes = 64 * 32;
 
 // Staging rows are interleaved by 64 particles: entry t of sorted particle i
 // sits at stage_index(i, t, cap). The walk's lanes append entries with
@@ -195,10 +209,12 @@ struct Dev {
     // walk stacks
     int32_t* stack = nullptr;
     int64_t stack_len = 0;
+    // groups walked by two waves: their partial sums and arrivals
+    void* part_sum = nullptr;        // [kWalkSlots] x 64 lanes x 32 B
+    unsigned* part_done = nullptr;   // [kWalkShared]
     // counters
     unsigned long long* cnt = nullptr;
-    // group work queues: walk [0, 8), neighbour count [8, 16), neighbour fill [16, 24)
-    unsigned long long* queues = nullptr;
+    unsigned long long* queues = nullptr;   // cnt + kNumCounters: [kQueueWords]
     // per persistent workgroup of the last walk / neighbour count: groups, clock ticks
     unsigned long long* wave_log = nullptr;
     unsigned long long* wave_log_nbr = nullptr;
@@ -388,6 +404,8 @@ void launch_drift(double* pos, const double* vel, double dt, int64_t n, hipStrea
 void launch_energy(const double* vel, const double* mass, const double* pot, int64_t n,
                    double* partial, int nblk, double* out, hipStream_t s);
 void launch_zero_u64(unsigned long long* p, int n, hipStream_t s);
+// the counters of a build and force call (all but those kept across builds) and the queue words
+void launch_zero_counts(unsigned long long* cnt, hipStream_t s);
 // one wave per block, 32 * iters + 32 VALU instructions per wave (counted in
 // the kernel's gfx950 assembly): a known count for instruction counters
 void launch_valu_probe(int64_t blocks, int iters, float* out, hipStream_t s);

@@ -90,7 +90,8 @@ struct WalkParams {
     int32_t* stack;
     int stack_cap;
     unsigned long long* cnt;
-    unsigned long long* queues;     // [kQueues] group queue heads
+    unsigned long long* queues;     // [kQueues] group queue heads, kQueueStride apart
+    unsigned long long* walk_cnt;   // [kWalkCntLines] lines of six interaction counters
     unsigned long long* wave_log;   // per workgroup: groups walked, steady-clock ticks
     unsigned long long* wave_cyc;   // per workgroup: core clock cycles over the same span
     int32_t* nbr_cnt;               // neighbour counts per caller index, or null
@@ -101,6 +102,8 @@ struct WalkParams {
     int max_copies;                 // most sub-wave copies of a small group (1..64)
     const double* cpos;             // caller's pos [n][3] and mass [n]: compared with the
     const double* cmass;            // build's sorted copy (changed in place: kErrStale), or null
+    void* part_sum;                 // partial sums of the shared groups' waves, [slot][word][lane]
+    unsigned* part_done;            // waves of a shared group that have stored theirs
 };
 
 __device__ inline void two_sum_acc(float& hi, float& lo, float v) {
@@ -134,6 +137,9 @@ struct Acc<float> {
     __device__ void store(float* w) const {
         w[0] = hx; w[1] = lx; w[2] = hy; w[3] = ly; w[4] = hz; w[5] = lz; w[6] = hp; w[7] = lp;
     }
+    __device__ void load(const float* w) {
+        hx = w[0]; lx = w[1]; hy = w[2]; ly = w[3]; hz = w[4]; lz = w[5]; hp = w[6]; lp = w[7];
+    }
     // adds another (hi, lo) set: TwoSum of the high parts, plain sum of the low parts
     __device__ void merge(const float* w) {
         two_sum_acc(hx, lx, w[0]); lx += w[1];
@@ -156,6 +162,7 @@ struct Acc<double> {
     }
     __device__ void add(const Part<double>& q) { add(q.x, q.y, q.z, q.p); }
     __device__ void store(double* w) const { w[0] = x; w[1] = y; w[2] = z; w[3] = p; }
+    __device__ void load(const double* w) { x = w[0]; y = w[1]; z = w[2]; p = w[3]; }
     __device__ void merge(const double* w) { x += w[0]; y += w[1]; z += w[2]; p += w[3]; }
     __device__ double gx() const { return x; }
     __device__ double gy() const { return y; }
@@ -331,7 +338,7 @@ __device__ inline bool is_neighbour(double xj, double yj, double zj, double xi, 
 // `scap` entries, kStageStride apart).
 template <typename R, int TC>
 __device__ inline Part<R> eval_near(const Tiles<R, TC>& T, int cnt, int ksub, int sub, R px, R py, R pz,
-                                    R eps2, int self, const NearK<R>& K, bool count_nbr, int me,
+                                    R eps2, int self, const NearK<R>& K, bool count_nbr, bool force, int me,
                                     double rlist2, int& nbr, int32_t* srow, int scap) {
     const double xi = K.x[me], yi = K.y[me], zi = K.z[me];
     R ax = 0, ay = 0, az = 0, ph = 0;
@@ -344,6 +351,7 @@ __device__ inline Part<R> eval_near(const Tiles<R, TC>& T, int cnt, int ksub, in
             if (nb && nbr < scap) srow[nbr * kStageStride] = oj;
             nbr += nb ? 1 : 0;
         }
+        if (!force) return;
         const R dx = q[0] - px, dy = q[1] - py, dz = q[2] - pz;
         const R s2 = dx * dx + dy * dy + dz * dz + eps2;
         const R inv = rsq(s2);
@@ -365,20 +373,38 @@ __device__ inline Part<R> eval_near(const Tiles<R, TC>& T, int cnt, int ksub, in
     return Part<R>{ax, ay, az, ph};
 }
 
+// Whether the near pair e (dr = r^2 - R^2 in FP32) is inside the list radius:
+// FP32 decides outside the band (where it provably agrees with the FP64
+// definition), the FP64 test inside it.
+template <int TC>
+__device__ inline bool near_listed(const Tiles<float, TC>& T, int e, float dr, const NearK<float>& K, int me,
+                                   double rlist2) {
+    const double* __restrict__ gx = K.x;
+    const double* __restrict__ gy = K.y;
+    const double* __restrict__ gz = K.z;
+    const bool band = fabsf(dr) <= K.band;
+    bool nb = dr < 0.f;
+    if (__ballot(band)) {
+        if (band) {
+            const int js = T.nears[e];
+            nb = is_neighbour(gx[js], gy[js], gz[js], gx[me], gy[me], gz[me], rlist2);
+        }
+    }
+    return nb;
+}
+
 // FP32 form without per-lane branches: the neighbour count and the pole
 // terms (-d0/s + l1 ln s, present when r_in > 0) are compile-time switches,
 // ln s = log2(s) ln 2, and the boundary cases of W and Phi_R are selects.
 // Each entry yields a force factor f and a potential term, taken either from
 // the far-pair formula (every lane beyond the list radius) or from the
 // changeover forms; the sums are updated in one place after either.
-template <bool CNT, bool POLE, int TC>
+// Without FORCE only the neighbours are found.
+template <bool CNT, bool FORCE, bool POLE, int TC>
 __device__ inline Part<float> eval_near_f32(const Tiles<float, TC>& T, int cnt, int ksub, int sub,
                                             float px, float py, float pz, float eps2, int self,
                                             const NearK<float>& K, int me, double rlist2, int& nbr,
                                             int32_t* srow, int scap) {
-    const double* __restrict__ gx = K.x;
-    const double* __restrict__ gy = K.y;
-    const double* __restrict__ gz = K.z;
     float ax = 0.f, ay = 0.f, az = 0.f, ph = 0.f;
     const float l1 = K.l1 * 0.693147180559945309f;
     const float x0 = -K.r_in * K.inv_delta;   // x = (s - r_in) / delta = s / delta + x0
@@ -392,6 +418,15 @@ __device__ inline Part<float> eval_near_f32(const Tiles<float, TC>& T, int cnt, 
         const float r2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
         const float s2 = r2 + e2;
         const float dr = r2 - K.rlist2f;
+        if (!FORCE) {
+            if (__ballot(dr <= K.band) == 0) return;
+            const int oj = T.nearj[e];
+            bool nb = near_listed(T, e, dr, K, me, rlist2);
+            nb = nb & (oj != self);
+            if (nb & (nbr < scap)) srow[nbr * kStageStride] = oj;
+            nbr += nb ? 1 : 0;
+            return;
+        }
         const float inv = __builtin_amdgcn_rsqf(s2);
         float f, pt;
         if (__ballot(dr <= K.band) == 0) {
@@ -423,16 +458,7 @@ __device__ inline Part<float> eval_near_f32(const Tiles<float, TC>& T, int cnt, 
             const int oj = T.nearj[e];
             const bool other = oj != self;
             if (CNT) {
-                // FP32 decides outside the band (where it provably agrees with the
-                // FP64 definition), the FP64 test inside it
-                const bool band = fabsf(dr) <= K.band;
-                bool nb = dr < 0.f;
-                if (__ballot(band)) {
-                    if (band) {
-                        const int js = T.nears[e];
-                        nb = is_neighbour(gx[js], gy[js], gz[js], gx[me], gy[me], gz[me], rlist2);
-                    }
-                }
+                bool nb = near_listed(T, e, dr, K, me, rlist2);
                 nb = nb & other;
                 if (nb & (nbr < scap)) srow[nbr * kStageStride] = oj;
                 nbr += nb ? 1 : 0;
@@ -467,20 +493,103 @@ __device__ inline Part<float> eval_far(const Tiles<float, TC>& T, int cnt, int k
 template <int TC>
 __device__ inline Part<float> eval_near(const Tiles<float, TC>& T, int cnt, int ksub, int sub,
                                         float px, float py, float pz, float eps2, int self,
-                                        const NearK<float>& K, bool count_nbr, int me, double rlist2,
+                                        const NearK<float>& K, bool count_nbr, bool force, int me, double rlist2,
                                         int& nbr, int32_t* srow, int scap) {
+    if (!force)   // (only with count_nbr)
+        return eval_near_f32<true, false, false, TC>(T, cnt, ksub, sub, px, py, pz, eps2, self, K, me, rlist2,
+                                                     nbr, srow, scap);
     if (count_nbr) {
         if (K.pole)
-            return eval_near_f32<true, true, TC>(T, cnt, ksub, sub, px, py, pz, eps2, self, K, me, rlist2,
-                                                 nbr, srow, scap);
-        return eval_near_f32<true, false, TC>(T, cnt, ksub, sub, px, py, pz, eps2, self, K, me, rlist2,
-                                              nbr, srow, scap);
+            return eval_near_f32<true, true, true, TC>(T, cnt, ksub, sub, px, py, pz, eps2, self, K, me, rlist2,
+                                                       nbr, srow, scap);
+        return eval_near_f32<true, true, false, TC>(T, cnt, ksub, sub, px, py, pz, eps2, self, K, me, rlist2,
+                                                    nbr, srow, scap);
     }
     if (K.pole)
-        return eval_near_f32<false, true, TC>(T, cnt, ksub, sub, px, py, pz, eps2, self, K, me, rlist2,
-                                              nbr, srow, scap);
-    return eval_near_f32<false, false, TC>(T, cnt, ksub, sub, px, py, pz, eps2, self, K, me, rlist2, nbr,
-                                           srow, scap);
+        return eval_near_f32<false, true, true, TC>(T, cnt, ksub, sub, px, py, pz, eps2, self, K, me, rlist2,
+                                                    nbr, srow, scap);
+    return eval_near_f32<false, true, false, TC>(T, cnt, ksub, sub, px, py, pz, eps2, self, K, me, rlist2, nbr,
+                                                 srow, scap);
+}
+
+// How many groups at the end of each queue are shared by two waves. With few
+// groups the chip is idle but for the longest one, so all are; with many, sharing
+// the last ones makes the end of the walk finer-grained (a group is up to a
+// millisecond of one wave) at the price of traversing for them twice, which costs
+// the FP64 walk less. q: groups per queue, w: waves per queue (512 for the mixed
+// walk). Walk times in us, sharing none / the rule's / all:
+//   215 groups 245 / 205 / 205, 1523: 461 / 374 / 375, 3177: 552 / 521 / 576,
+//   6141: 892 / 805 / 899, 26611: 5128 / 5098 / -, FP64 4782: 2012 / 1786 / 1835
+// and with 103236 groups sharing only costs (14090 / 14150).
+template <bool MIXED>
+__device__ inline int walk_shared(int64_t G) {
+    const int64_t q = (G + kQueues - 1) / kQueues, w = gridDim.x / kQueues;
+    if (q > 8 * w) return 0;
+    const int64_t t = 8 * q <= 5 * w ? q : (MIXED ? q * 3 / 8 : q * 5 / 8);
+    return (int)(t < kWalkShared / kQueues ? t : kWalkShared / kQueues);
+}
+
+// The next work item of a persistent wave. A queue (one contiguous range of
+// groups, one per XCD) hands out its groups one by one; its last `tail` groups
+// are handed out twice, to the two waves that share them.
+struct WalkItem {
+    int64_t g;        // group, < 0: no work left
+    int part, parts;  // this wave's part of it
+    int slot;         // its place among the shared groups' partial sums (parts > 1)
+};
+
+// A wave's first item is its own by its place in the grid, with no queue access
+// (4096 waves starting on one line of queue heads waited 50 us for it, and every
+// other access to that memory channel with them); the heads count from there
+// on, each on a line of its own.
+__device__ inline WalkItem walk_next(unsigned long long* q, int64_t G, int tail, int& home, bool first,
+                                     int lane) {
+    WalkItem it;
+    it.part = 0;
+    it.parts = 1;
+    it.slot = 0;
+    for (int k = 0; k < kQueues; ++k) {
+        const int qi = (home + k) % kQueues;
+        const int64_t lo = G * qi / kQueues, hi = G * (qi + 1) / kQueues;
+        const int64_t shared = hi - lo < tail ? hi - lo : tail, single = hi - lo - shared;
+        const int64_t given = ((int64_t)gridDim.x - qi + kQueues - 1) / kQueues;   // first items of its waves
+        const int64_t items = single + 2 * shared;
+        int64_t t;
+        if (first && k == 0) {
+            t = blockIdx.x / kQueues;
+        } else {
+            if (items <= given) continue;   // nothing queued beyond the first items
+            unsigned long long* head = q + qi * kQueueStride;
+            if (k > 0 && (int64_t)__builtin_amdgcn_readfirstlane((int)(*head + given < (unsigned long long)items)) == 0)
+                continue;   // range already drained: skip the atomic
+            t = given + (int64_t)uni((int)atomicAdd(head, lane == 0 ? 1ull : 0ull));
+        }
+        if (t < items) {
+            home = qi;
+            if (t < single) {
+                it.g = lo + t;
+            } else {
+                const int u = (int)(t - single), j = u >> 1;
+                it.g = lo + single + j;
+                it.part = u & 1;
+                it.parts = 2;
+                it.slot = (qi * tail + j) * 2;
+            }
+            return it;
+        }
+    }
+    it.g = -1;
+    return it;
+}
+
+// The kernel's arguments, read again where they are used: the empty asm keeps
+// the compiler from loading all of them at the start, which spilled 150 scalar
+// registers into vector ones.
+typedef const __attribute__((address_space(4))) WalkParams* WalkArgs;
+__device__ inline WalkArgs walk_args() {
+    WalkArgs a = (WalkArgs)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(a));
+    return a;
 }
 
 // Four waves per SIMD (16 per compute unit, which the 64-entry mixed walk's
@@ -501,49 +610,43 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
     const int64_t G = (int64_t)*p.G;
     const unsigned long long t_start = wall_clock64();
     const unsigned long long c_start = clock64();
+    const int tail = walk_shared<MIXED>(G);
     int n_walked = 0;
+    // interaction counts of this wave, added to the counters once at its end
+    unsigned long long sum_pn = 0, sum_far = 0, sum_near = 0, slot_pn = 0, slot_far = 0, slot_near = 0;
+    bool first = true;
 
     for (;;) {
-        const int64_t g = queue_next(p.queues, G, home, lane);
-        if (g < 0) break;
-        ++n_walked;
+        const WalkItem item = walk_next(p.queues, G, tail, home, first, lane);
+        first = false;
+        if (item.g < 0) break;
+        const int64_t g = item.g;
+        // A group's sums are kept in two: A0 takes three of five multipole tiles
+        // and the far tiles, A1 the other multipole tiles and the near ones, and
+        // the two are added at the end. In a shared group each wave computes one
+        // of them: both traverse the tree (the order of the tile entries is the
+        // traversal's), each fills and evaluates only the tiles of its own sum, and
+        // part 0 finds the neighbours. So the sums do not depend on which groups
+        // are shared.
+        const int part = uni(item.part), parts = uni(item.parts);
+        const bool lead = part == 0;
+        n_walked += lead ? 1 : 0;
 
-        const int gb = uni(p.g_begin[g]), gcnt = uni(p.g_count[g]), root = uni(p.g_root[g]);
-        const int cl = uni(p.g_cluster[g]);
+        const WalkArgs a = walk_args();
+        const int gb = uni(a->g_begin[g]), gcnt = uni(a->g_count[g]), root = uni(a->g_root[g]);
+        const int cl = uni(a->g_cluster[g]);
         double glo[3], ghi[3], ctr[3];
         for (int k = 0; k < 3; ++k) {
-            glo[k] = p.g_lo[3 * g + k];
-            ghi[k] = p.g_hi[3 * g + k];
+            glo[k] = a->g_lo[3 * g + k];
+            ghi[k] = a->g_hi[3 * g + k];
             ctr[k] = (glo[k] + ghi[k]) * 0.5;
         }
-        const ClusterParams& cp = p.cp[cl];
-        const double rlist2 = cp.rlist2;   // neighbour-list radius R = r_out + r_buff, squared
-        NearK<R> K;
-        if (MIXED) {
-            K.r_in = cp.f_r_in; K.r_out = cp.f_r_out; K.inv_delta = cp.f_inv_delta;
-            K.c0 = cp.f_c0; K.d0 = cp.f_d0; K.l1 = cp.f_l1; K.inner = cp.f_inner;
-            for (int k = 0; k < 6; ++k) K.e[k] = cp.f_e[k];
-        } else {
-            K.r_in = cp.r_in; K.r_out = cp.r_out; K.inv_delta = cp.inv_delta;
-            K.c0 = cp.c0; K.d0 = cp.d0; K.l1 = cp.l1; K.inner = cp.inner;
-            for (int k = 0; k < 6; ++k) K.e[k] = cp.e[k];
-        }
-        K.pole = cp.d0 != 0.0;
-        {
-            // Band of the FP32 neighbour pre-test against the list radius R.
-            // Relative coordinates are FP64 differences rounded once to FP32, so
-            // with |p| <= h (group box half side) and a pair at r <= 2 R each
-            // component of d errs by at most 2^-24 (2h + 2.01 r); with h <= 64 R
-            // the error of r^2 (squares, FMA rounding, R^2 in FP32) stays below
-            // 928 * 2^-24 R^2, and for r > 2 R far below r^2 - R^2. The band is
-            // 2048 * 2^-24 R^2; larger groups always take the FP64 test.
-            double h = 0.0;
-            for (int k = 0; k < 3; ++k) h = fmax(h, (ghi[k] - glo[k]) * 0.5);
-            K.rlist2f = (float)rlist2;
-            K.x = p.x; K.y = p.y; K.z = p.z;
-            K.band = (h <= 64.0 * cp.rlist) ? (float)(2048.0 * 0x1p-24 * rlist2) : INFINITY;
-        }
-
+        // a group this large against the list radius R takes every neighbour test in
+        // FP64 (see the band in flush_near)
+        double h = 0.0;
+        for (int k = 0; k < 3; ++k) h = fmax(h, (ghi[k] - glo[k]) * 0.5);
+        const bool near_exact = __builtin_amdgcn_readfirstlane((int)(h > 64.0 * a->cp[cl].rlist)) != 0;
+        const double rlist2 = a->cp[cl].rlist2;   // neighbour-list radius R = r_out + r_buff, squared
         // Lane roles. By default a group of g particles takes one pass over
         // every tile with ksub = min(64 / g, cap) copies, lane = copy * g +
         // particle (see for_entries; lanes beyond ksub * g repeat copy 0 and
@@ -560,7 +663,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
         int kB = 0;
         if (rB >= 1 && rB <= 21) {
             const int kfit = 64 / rB;
-            kB = kfit < p.max_copies ? kfit : p.max_copies;
+            kB = kfit < a->max_copies ? kfit : a->max_copies;
             kB = kB < 8 ? kB : 8;
         }
         const bool split = kB >= 3;
@@ -577,7 +680,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
             subB = cB < kB ? cB : 0;
         } else {
             const int kfit = 64 / gcnt;
-            ksubA = kfit < p.max_copies ? kfit : p.max_copies;
+            ksubA = kfit < a->max_copies ? kfit : a->max_copies;
             copyA = lane / gcnt;
             plA = lane - copyA * gcnt;
             subA = copyA < ksubA ? copyA : 0;
@@ -588,45 +691,45 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
         const int ksubN = split ? 1 : ksubA;
         const int subN = split ? 0 : subA;
         const int me = gb + own;
-        const int orig_me = p.perm[me];
-        if (p.cpos) {
+        const int orig_me = a->perm[me];
+        if (a->cpos && lead) {
             // the caller's arrays must still hold what the build sorted
             const int64_t o3 = 3 * (int64_t)orig_me;
-            const bool stale = active && (p.cpos[o3] != p.x[me] || p.cpos[o3 + 1] != p.y[me] ||
-                                          p.cpos[o3 + 2] != p.z[me] || p.cmass[orig_me] != p.m[me]);
-            if (__ballot(stale)) atomicOr(&p.cnt[kErr], lane == 0 ? kErrStale : 0ull);
+            const bool stale = active && (a->cpos[o3] != a->x[me] || a->cpos[o3 + 1] != a->y[me] ||
+                                          a->cpos[o3 + 2] != a->z[me] || a->cmass[orig_me] != a->m[me]);
+            if (__ballot(stale)) atomicOr(&a->cnt[kErr], lane == 0 ? kErrStale : 0ull);
         }
-        // Neighbour staging. A particle's row holds p.scap entries; a lane
+        // Neighbour staging. A particle's row holds a->scap entries; a lane
         // that holds it whole (ksubN = 1) uses it whole, copies of a small group
-        // each get a sub-row of wrow = p.scap / ksubN entries (joined into one
+        // each get a sub-row of wrow = a->scap / ksubN entries (joined into one
         // list after the walk). Lanes that hold no particle of their own, or
         // repeat copy 0, store nothing (scap = 0).
         const bool real = split ? active : copyA < ksubA;
-        const int wrow = p.scap / ksubN;
-        const int scap = (p.stage == nullptr || !real) ? 0 : (ksubN == 1 ? p.scap : wrow);
-        int32_t* srow = p.stage != nullptr
-                            ? p.stage + stage_index(me, (ksubN == 1 ? 0 : subN * wrow), p.scap)
-                            : nullptr;
+        const int wrow = a->scap / ksubN;
+        const int scap = (a->stage == nullptr || !real) ? 0 : (ksubN == 1 ? a->scap : wrow);
         // positions relative to the group centre: pass A (also the far and
         // near tiles, except on lanes >= 32 of a split group) and pass B
-        const R pAx = (R)(p.x[gb + plA] - ctr[0]);
-        const R pAy = (R)(p.y[gb + plA] - ctr[1]);
-        const R pAz = (R)(p.z[gb + plA] - ctr[2]);
+        const R pAx = (R)(a->x[gb + plA] - ctr[0]);
+        const R pAy = (R)(a->y[gb + plA] - ctr[1]);
+        const R pAz = (R)(a->z[gb + plA] - ctr[2]);
         const int pbi = split ? gb + plB : me;
-        const R pBx = (R)(p.x[pbi] - ctr[0]);
-        const R pBy = (R)(p.y[pbi] - ctr[1]);
-        const R pBz = (R)(p.z[pbi] - ctr[2]);
+        const R pBx = (R)(a->x[pbi] - ctr[0]);
+        const R pBy = (R)(a->y[pbi] - ctr[1]);
+        const R pBz = (R)(a->z[pbi] - ctr[2]);
         const unsigned rcpA = rounds_rcp(ksubA), rcpB = split ? rounds_rcp(kB) : 0u,
                        rcpN = rounds_rcp(ksubN);
         const bool hiB = split && lane >= 32;   // lanes whose own particle is pass B's copy 0
         const bool ownerB = hiB && active;
-        const bool count_nbr = p.nbr_cnt != nullptr;
+        const bool count_nbr = a->nbr_cnt != nullptr && lead;
+        // the tiles this wave fills and evaluates
+        int pn_tile = 0, pn_own = 0;                     // multipole tile being filled and its accumulator
+        const bool far_mine = lead, near_force = parts == 1 || !lead, near_mine = near_force || count_nbr;
         int npn = 0, nfar = 0, nnear = 0;
         unsigned c_pn = 0, c_far = 0, c_near = 0;   // per group: far below 2^32
         // loop iterations of the evaluations (each occupies all 64 lanes)
         unsigned it_pn = 0, it_far = 0, it_near = 0;
         int nbr = 0;
-        Acc<R> A;
+        Acc<R> A0, A1;
         // one flush of each tile kind; every lane runs it (it_* counts the
         // loop iterations, each of which occupies the 64 lanes)
         auto flush_pn = [&](int cnt) {
@@ -656,16 +759,50 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
                 __syncthreads();
                 if (hiB) pa = sb;   // idle lanes add zero
             }
-            A.add(pa);
+            if (pn_own == 0) A0.add(pa);
+            else A1.add(pa);
         };
         auto flush_far = [&](int cnt) {
             it_far += entry_rounds(cnt, ksubN, rcpN);
-            A.add(eval_far(T, cnt, ksubN, subN, hiB ? pBx : pAx, hiB ? pBy : pAy, hiB ? pBz : pAz, eps2));
+            A0.add(eval_far(T, cnt, ksubN, subN, hiB ? pBx : pAx, hiB ? pBy : pAy, hiB ? pBz : pAz, eps2));
         };
         auto flush_near = [&](int cnt) {
-            it_near += entry_rounds(cnt, ksubN, rcpN);
-            A.add(eval_near(T, cnt, ksubN, subN, hiB ? pBx : pAx, hiB ? pBy : pAy, hiB ? pBz : pAz, eps2,
-                            orig_me, K, count_nbr, me, rlist2, nbr, srow, scap));
+            // The changeover constants are read for each flush of a near tile (about ten a
+            // group): kept in registers they would crowd the multipole loop. The
+            // empty asm keeps the loads here.
+            const ClusterParams* cpp = p.cp + cl;
+            asm volatile("" : "+s"(cpp));
+            const ClusterParams& cp = *cpp;
+            NearK<R> K;
+            if (MIXED) {
+                K.r_in = cp.f_r_in; K.r_out = cp.f_r_out; K.inv_delta = cp.f_inv_delta;
+                K.c0 = cp.f_c0; K.d0 = cp.f_d0; K.l1 = cp.f_l1; K.inner = cp.f_inner;
+                for (int k = 0; k < 6; ++k) K.e[k] = cp.f_e[k];
+            } else {
+                K.r_in = cp.r_in; K.r_out = cp.r_out; K.inv_delta = cp.inv_delta;
+                K.c0 = cp.c0; K.d0 = cp.d0; K.l1 = cp.l1; K.inner = cp.inner;
+                for (int k = 0; k < 6; ++k) K.e[k] = cp.e[k];
+            }
+            K.pole = cp.d0 != 0.0;
+            {
+                // Band of the FP32 neighbour pre-test against the list radius R.
+                // Relative coordinates are FP64 differences rounded once to FP32, so
+                // with |p| <= h (group box half side) and a pair at r <= 2 R each
+                // component of d errs by at most 2^-24 (2h + 2.01 r); with h <= 64 R
+                // the error of r^2 (squares, FMA rounding, R^2 in FP32) stays below
+                // 928 * 2^-24 R^2, and for r > 2 R far below r^2 - R^2. The band is
+                // 2048 * 2^-24 R^2; larger groups always take the FP64 test.
+                K.rlist2f = (float)rlist2;
+                K.x = p.x; K.y = p.y; K.z = p.z;
+                K.band = near_exact ? INFINITY : (float)(2048.0 * 0x1p-24 * rlist2);
+            }
+            if (near_force) it_near += entry_rounds(cnt, ksubN, rcpN);
+            int32_t* srow = p.stage != nullptr
+                                ? p.stage + stage_index(me, (ksubN == 1 ? 0 : subN * wrow), p.scap)
+                                : nullptr;
+            const Part<R> v = eval_near(T, cnt, ksubN, subN, hiB ? pBx : pAx, hiB ? pBy : pAy, hiB ? pBz : pAz,
+                                        eps2, p.perm[me], K, count_nbr, near_force, me, rlist2, nbr, srow, scap);
+            if (near_force) A1.add(v);
         };
         stack.put(0, root);   // every lane stores the same value
         int top = 1;
@@ -675,10 +812,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
             // multipole tile: evaluated here, where no node state is live,
             // once it could not take another step's entries (up to 64)
             if (npn > TCAP - 32) {
-                __syncthreads();
-                flush_pn(npn);
+                if (parts == 1 || pn_own == part) {
+                    __syncthreads();
+                    flush_pn(npn);
+                    __syncthreads();
+                }
                 npn = 0;
-                __syncthreads();
+                pn_tile = pn_tile < 4 ? pn_tile + 1 : 0;
+                pn_own = pn_tile < 3 ? 0 : 1;
             }
             __threadfence_block();
             const int npop = uni(top < 64 ? top : 64);
@@ -697,7 +838,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
             const uint64_t mk = __ballot(accept);
             if (mk) {
                 const int k = uni(__popcll(mk));
-                if (accept) {
+                if (accept && (parts == 1 || pn_own == part)) {
                     R* e = T.pn[npn + popc_below(mk)];
                     e[0] = (R)(w.com[0] - ctr[0]);
                     e[1] = (R)(w.com[1] - ctr[1]);
@@ -752,12 +893,15 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
                     const int add = (total - base) < 64 ? (total - base) : 64;
                     if (fill + add > TCAP) {
                         __syncthreads();
-                        if (cls == 0) flush_far(fill);
-                        else flush_near(fill);
+                        if (cls == 0) {
+                            if (far_mine) flush_far(fill);
+                        } else {
+                            if (near_mine) flush_near(fill);
+                        }
                         fill = 0;
                         __syncthreads();
                     }
-                    if (s < total) {
+                    if (s < total && (cls == 0 ? far_mine : near_mine)) {
                         R* e = cls == 0 ? T.far[fill + lane] : T.nearp[fill + lane];
                         e[0] = (R)(p.x[j] - ctr[0]);
                         e[1] = (R)(p.y[j] - ctr[1]);
@@ -780,28 +924,31 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
             }
         }
         __syncthreads();
-        if (npn) flush_pn(npn);
-        if (nfar) flush_far(nfar);
-        if (nnear) flush_near(nnear);
+        if (npn && (parts == 1 || pn_own == part)) flush_pn(npn);
+        if (nfar && far_mine) flush_far(nfar);
+        if (nnear && near_mine) flush_near(nnear);
         __syncthreads();
 
+        const WalkArgs e = walk_args();
         // a row that overflowed sends the group's lists to the fill pass
         const bool row_full = count_nbr && real && nbr > scap;
-        const bool need_fill = count_nbr && (p.stage == nullptr || __ballot(row_full) != 0);
+        const bool need_fill = count_nbr && (e->stage == nullptr || __ballot(row_full) != 0);
         if (!split && ksubA > 1) {
             const int ksub = ksubA;
             // merge the copies' partial sums in copy order, into copy 0
             R* red = &T.pn[0][0];
             constexpr int W = Acc<R>::kWords + 1;   // odd stride: no LDS bank conflicts
-            A.store(red + W * lane);
+            A0.store(red + W * lane);
+            A1.store(red + W * (64 + lane));
             T.nearj[lane] = nbr;
             __syncthreads();
             // (the barrier also makes the copies' staged entries visible)
             if (active) {
                 const bool join = count_nbr && !need_fill;
-                int32_t* base = join ? p.stage + stage_index(me, 0, p.scap) : nullptr;
+                int32_t* base = join ? e->stage + stage_index(me, 0, e->scap) : nullptr;
                 for (int c = 1; c < ksub; ++c) {
-                    A.merge(red + W * (c * gcnt + lane));
+                    A0.merge(red + W * (c * gcnt + lane));
+                    A1.merge(red + W * (64 + c * gcnt + lane));
                     const int nc = T.nearj[c * gcnt + lane];
                     // move copy c's sub-row down to follow the list so far;
                     // targets lie below sources, loads of a batch precede its stores
@@ -823,40 +970,88 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
             }
             __syncthreads();
         }
-        if (overflow) atomicOr(&p.cnt[kErr], lane == 0 ? kErrWalkStack : 0ull);
+        if (overflow) atomicOr(&e->cnt[kErr], lane == 0 ? kErrWalkStack : 0ull);
         if (count_nbr) {
             // lists this walk did not stage completely go to the fill pass
             if (need_fill) {
                 // all lanes issue the atomic (lane 0 adds 1): no lane-0-only branch
                 const unsigned long long slot =
-                    atomicAdd(&p.cnt[kCntFill], lane == 0 ? 1ull : 0ull);
-                if (lane == 0) p.fill_list[slot] = (int32_t)g;
+                    atomicAdd(&e->cnt[kCntFill], lane == 0 ? 1ull : 0ull);
+                if (lane == 0) e->fill_list[slot] = (int32_t)g;
             }
-            if (active) p.stage_k[me] = (int8_t)(need_fill ? 0 : 1);
+            if (active) e->stage_k[me] = (int8_t)(need_fill ? 0 : 1);
         }
-        if (active) {
-            const int orig = orig_me;
-            if (count_nbr) p.nbr_cnt[orig] = nbr;
-            p.acc[3 * (int64_t)orig] = A.gx();
-            p.acc[3 * (int64_t)orig + 1] = A.gy();
-            p.acc[3 * (int64_t)orig + 2] = A.gz();
-            p.pot[orig] = A.gp();
+        if (active && count_nbr) e->nbr_cnt[e->perm[me]] = nbr;
+        bool last = true;
+        if (parts == 1) {
+            R w[Acc<R>::kWords];
+            A1.store(w);
+            A0.merge(w);
+        } else {
+            // The wave that comes last adds up both sums, as one wave would. They
+            // cross XCDs, whose L2s are not coherent with each other: device-scope
+            // accesses, and the count is raised only after the stores have arrived
+            // (a fence at that scope would write back and invalidate a whole L2).
+            R* sum = reinterpret_cast<R*>(e->part_sum) + (int64_t)item.slot * (Acc<R>::kWords * 64);
+            R w[Acc<R>::kWords];
+            if (!lead) A0 = A1;
+            A0.store(w);
+#pragma unroll
+            for (int k = 0; k < Acc<R>::kWords; ++k)
+                __hip_atomic_store(sum + (part * Acc<R>::kWords + k) * 64 + lane, w[k], __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            last = uni((int)atomicAdd(e->part_done + item.slot / 2, lane == 0 ? 1u : 0u)) == 1;
+            if (last) {
+#pragma unroll
+                for (int k = 0; k < Acc<R>::kWords; ++k)
+                    w[k] = __hip_atomic_load(sum + ((part ^ 1) * Acc<R>::kWords + k) * 64 + lane, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+                // (the first sum takes the second)
+                Acc<R> B;
+                B.load(w);
+                if (lead) {
+                    A0.merge(w);
+                } else {
+                    A0.store(w);
+                    B.merge(w);
+                    A0 = B;
+                }
+            }
         }
-        // interaction counters: one contribution per wave (lane 0), others add 0
-        const unsigned long long l0 = lane == 0 ? (unsigned long long)gcnt : 0ull;
-        atomicAdd(&p.cnt[kCntPN], (unsigned long long)c_pn * l0);
-        atomicAdd(&p.cnt[kCntFar], (unsigned long long)c_far * l0);
-        atomicAdd(&p.cnt[kCntNear], (unsigned long long)c_near * l0);
-        const unsigned long long w0 = lane == 0 ? 64ull : 0ull;
-        atomicAdd(&p.cnt[kCntSlotPN], (unsigned long long)it_pn * w0);
-        atomicAdd(&p.cnt[kCntSlotFar], (unsigned long long)it_far * w0);
-        atomicAdd(&p.cnt[kCntSlotNear], (unsigned long long)it_near * w0);
+        if (active && last) {
+            const int orig = e->perm[me];
+            e->acc[3 * (int64_t)orig] = A0.gx();
+            e->acc[3 * (int64_t)orig + 1] = A0.gy();
+            e->acc[3 * (int64_t)orig + 2] = A0.gz();
+            e->pot[orig] = A0.gp();
+        }
+        if (lead) {
+            sum_pn += (unsigned long long)c_pn * gcnt;
+            sum_far += (unsigned long long)c_far * gcnt;
+            sum_near += (unsigned long long)c_near * gcnt;
+        }
+        slot_pn += it_pn;
+        slot_far += it_far;
+        slot_near += it_near;
     }
-    if (p.wave_log) {
+    const WalkArgs z = walk_args();
+    if (!first && (slot_pn | slot_far | slot_near)) {
+        // one contribution per wave (lane 0, the others add 0), spread over lines
+        unsigned long long* c = z->walk_cnt + (blockIdx.x % kWalkCntLines) * kQueueStride;
+        const unsigned long long l0 = lane == 0 ? 1ull : 0ull;
+        atomicAdd(c, sum_pn * l0);
+        atomicAdd(c + 1, sum_far * l0);
+        atomicAdd(c + 2, sum_near * l0);
+        atomicAdd(c + 3, slot_pn * 64ull * l0);
+        atomicAdd(c + 4, slot_far * 64ull * l0);
+        atomicAdd(c + 5, slot_near * 64ull * l0);
+    }
+    if (z->wave_log) {
         const unsigned long long c_end = clock64();
-        p.wave_log[2 * blockIdx.x] = (unsigned long long)n_walked;
-        p.wave_log[2 * blockIdx.x + 1] = wall_clock64() - t_start;
-        p.wave_cyc[blockIdx.x] = c_end - c_start;
+        z->wave_log[2 * blockIdx.x] = (unsigned long long)n_walked;
+        z->wave_log[2 * blockIdx.x + 1] = wall_clock64() - t_start;
+        z->wave_cyc[blockIdx.x] = c_end - c_start;
     }
 }
 
@@ -864,14 +1059,16 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
 // |COM - box centre|; also clears the per-call counters and queues.
 __global__ void k_rcrit(WNode* __restrict__ node, const unsigned long long* __restrict__ n_dev,
                         double theta, unsigned long long* __restrict__ cnt,
-                        unsigned long long* __restrict__ queues) {
+                        unsigned long long* __restrict__ queues, unsigned* __restrict__ part_done, int n_part) {
 #pragma clang fp contract(off)
     const int64_t n = (int64_t)*n_dev;
-    if (blockIdx.x == 0 && threadIdx.x < 3 * kQueues) queues[threadIdx.x] = 0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        cnt[kCntPN] = 0; cnt[kCntFar] = 0; cnt[kCntNear] = 0; cnt[kCntFill] = 0;
-        cnt[kCntSlotPN] = 0; cnt[kCntSlotFar] = 0; cnt[kCntSlotNear] = 0;
+    if (blockIdx.x == 0) {   // the queue heads, then the counter lines
+        for (int k = threadIdx.x; k < kQueueWords; k += blockDim.x) queues[k] = 0;
+        if (threadIdx.x == 0) cnt[kCntFill] = 0;
     }
+    for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < n_part;
+         b += (int64_t)gridDim.x * blockDim.x)
+        part_done[b] = 0u;
     for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < n;
          b += (int64_t)gridDim.x * blockDim.x) {
         WNode& w = node[b];
@@ -892,7 +1089,7 @@ void launch_rcrit(Dev& d, const BuildCfg& c, double theta, hipStream_t s) {
     int64_t nb = (c.node_cap + 255) / 256;
     if (nb > 4096) nb = 4096;
     hipLaunchKernelGGL(k_rcrit, dim3(nb), dim3(256), 0, s, d.node,
-                       (const unsigned long long*)(d.cnt + kCntNodes), theta, d.cnt, d.queues);
+                       (const unsigned long long*)(d.cnt + kCntNodes), theta, d.cnt, d.queues, d.part_done, kWalkShared);
 }
 
 template <bool MIXED>
@@ -927,6 +1124,7 @@ void launch_walk(Dev& d, const BuildCfg& c, const WalkCfg& w, double* acc, doubl
     p.stack_cap = w.stack_cap;
     p.cnt = d.cnt;
     p.queues = d.queues;
+    p.walk_cnt = d.queues + kWalkCntAt;
     p.wave_log = d.wave_log;
     p.wave_cyc = d.wave_cyc;
     p.nbr_cnt = w.count_nbr ? d.nbr_cnt : nullptr;
@@ -937,6 +1135,8 @@ void launch_walk(Dev& d, const BuildCfg& c, const WalkCfg& w, double* acc, doubl
     p.max_copies = w.max_copies;
     p.cpos = w.cpos;
     p.cmass = w.cmass;
+    p.part_sum = d.part_sum;
+    p.part_done = d.part_done;
     if (w.mixed) hipLaunchKernelGGL(walk_kernel<true>(w.tile), dim3(w.grid), dim3(64), 0, s, p);
     else hipLaunchKernelGGL(walk_kernel<false>(w.tile), dim3(w.grid), dim3(64), 0, s, p);
 }

@@ -37,8 +37,6 @@ __device__ inline int last_lane(int v) { return __builtin_amdgcn_readlane(v, 63)
 // its XCD's range first (neighbouring groups share tree nodes in that XCD's
 // L2) and then helps the other ranges. All lanes issue the atomic (lane 0
 // adds 1, the others 0): no lane-0-only branch precedes the broadcast.
-constexpr int kQueues = 8;
-
 // Workgroup id -> logical block in chunks of `chunk` consecutive blocks:
 // workgroups go to XCDs round-robin by id, and XCD x runs the chunks
 // x, x + 8, x + 16, ... in order, so every XCD's L2 serves a few compact
@@ -50,15 +48,16 @@ __device__ inline unsigned xcd_chunk_block(unsigned b, unsigned chunk) {
     return ((j / chunk) * kQueues + x) * chunk + j % chunk;
 }
 
-__device__ inline int64_t queue_next(unsigned long long* q /* [kQueues] */, int64_t G, int& home,
+__device__ inline int64_t queue_next(unsigned long long* q, int64_t G, int& home,
                                      int lane) {
     for (int k = 0; k < kQueues; ++k) {
         const int qi = (home + k) % kQueues;
         const int64_t lo = G * qi / kQueues, hi = G * (qi + 1) / kQueues;
         if (hi <= lo) continue;   // empty range (G < kQueues, or nothing queued)
-        if (k > 0 && (int64_t)__builtin_amdgcn_readfirstlane((int)(q[qi] < (unsigned long long)(hi - lo))) == 0)
+        unsigned long long* head = q + qi * kQueueStride;
+        if (k > 0 && (int64_t)__builtin_amdgcn_readfirstlane((int)(*head < (unsigned long long)(hi - lo))) == 0)
             continue;   // range already drained: skip the atomic
-        const unsigned long long r = atomicAdd(&q[qi], lane == 0 ? 1ull : 0ull);
+        const unsigned long long r = atomicAdd(head, lane == 0 ? 1ull : 0ull);
         const int64_t t = lo + (int64_t)uni((int)r);
         if (t < hi) {
             home = qi;
