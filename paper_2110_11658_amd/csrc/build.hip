@@ -330,7 +330,7 @@ __global__ void k_invert(const int32_t* __restrict__ bfs2pre, const int32_t* __r
 __global__ void k_nodes_init(const int32_t* __restrict__ bfs2pre, const int32_t* __restrict__ pre2bfs,
                              const int32_t* __restrict__ n_dev, int64_t cap,
                              const int32_t* __restrict__ pre_begin, const int32_t* __restrict__ pre_count,
-                             const int32_t* __restrict__ pre_nchild, WNode* __restrict__ node,
+                             const int32_t* __restrict__ pre_nchild, NodePlanes node,
                              unsigned long long* __restrict__ cnt) {
     const int64_t n = min(cap, (int64_t)*n_dev);
     unsigned long long leaves = 0;
@@ -339,11 +339,7 @@ __global__ void k_nodes_init(const int32_t* __restrict__ bfs2pre, const int32_t*
         const int32_t p = bfs2pre[b];
         // pre-order: the first child follows its parent (guarded for a truncated node list)
         const int32_t nc = (p + 1 < n) ? pre_nchild[p] : 0;
-        WNode& w = node[b];
-        w.begin = pre_begin[p];
-        w.count = pre_count[p];
-        w.nchild = nc;
-        w.first_child = nc ? pre2bfs[p + 1] : -1;
+        node.set_range(b, make_int4(pre_begin[p], pre_count[p], nc ? pre2bfs[p + 1] : -1, nc));
         leaves += (nc == 0);
     }
     // one atomic per block: a single counter serialises same-address atomics
@@ -374,8 +370,7 @@ struct MomOut {
 
 __device__ inline void moments_small(const WNode& w, bool leaf, int nsub, const double* __restrict__ x,
                                      const double* __restrict__ y, const double* __restrict__ z,
-                                     const double* __restrict__ m, const WNode* __restrict__ node,
-                                     const Mom64* __restrict__ q64, MomOut& o) {
+                                     const double* __restrict__ m, NodePlanes node, Mom64Planes q64, MomOut& o) {
 #pragma clang fp contract(off)
     double mu[kMomFast], cu[3][kMomFast], lu[3][kMomFast], hu[3][kMomFast];
 #pragma unroll
@@ -387,12 +382,11 @@ __device__ inline void moments_small(const WNode& w, bool leaf, int nsub, const 
             for (int d = 0; d < 3; ++d) { lu[d][k] = cu[d][k]; hu[d][k] = cu[d][k]; }
         } else {
             const int c = w.first_child + u;
-            mu[k] = q64[c].M;
-            for (int d = 0; d < 3; ++d) {
-                cu[d][k] = node[c].com[d];
-                lu[d][k] = node[c].lo[d];
-                hu[d][k] = node[c].hi[d];
-            }
+            mu[k] = q64.mass(c);
+            double cc[3], cl[3], ch[3];
+            node.com(c, cc);
+            node.box(c, cl, ch);
+            for (int d = 0; d < 3; ++d) { cu[d][k] = cc[d]; lu[d][k] = cl[d]; hu[d][k] = ch[d]; }
         }
     }
     double M = 0.0, sx = 0.0, sy = 0.0, sz = 0.0;
@@ -422,7 +416,7 @@ __device__ inline void moments_small(const WNode& w, bool leaf, int nsub, const 
         if (leaf) {
             for (int e = 0; e < 6; ++e) qc[e][k] = 0.0;
         } else {
-            const Mom64 mc = q64[w.first_child + u];
+            const Mom64 mc = q64.load(w.first_child + u);
             qc[0][k] = mc.qxx; qc[1][k] = mc.qyy; qc[2][k] = mc.qzz;
             qc[3][k] = mc.qxy; qc[4][k] = mc.qxz; qc[5][k] = mc.qyz;
         }
@@ -446,8 +440,7 @@ __device__ inline void moments_small(const WNode& w, bool leaf, int nsub, const 
 
 __device__ inline void moments_loop(const WNode& w, bool leaf, int nsub, const double* __restrict__ x,
                                     const double* __restrict__ y, const double* __restrict__ z,
-                                    const double* __restrict__ m, const WNode* __restrict__ node,
-                                    const Mom64* __restrict__ q64, MomOut& o) {
+                                    const double* __restrict__ m, NodePlanes node, Mom64Planes q64, MomOut& o) {
 #pragma clang fp contract(off)
     double M = 0.0, sx = 0.0, sy = 0.0, sz = 0.0;
     for (int u = 0; u < nsub; ++u) {
@@ -458,12 +451,9 @@ __device__ inline void moments_loop(const WNode& w, bool leaf, int nsub, const d
             for (int k = 0; k < 3; ++k) { lu[k] = cu[k]; hu[k] = cu[k]; }
         } else {
             const int c = w.first_child + u;
-            mu = q64[c].M;
-            for (int k = 0; k < 3; ++k) {
-                cu[k] = node[c].com[k];
-                lu[k] = node[c].lo[k];
-                hu[k] = node[c].hi[k];
-            }
+            mu = q64.mass(c);
+            node.com(c, cu);
+            node.box(c, lu, hu);
         }
         M = M + mu;
         sx = sx + mu * cu[0];
@@ -489,9 +479,9 @@ __device__ inline void moments_loop(const WNode& w, bool leaf, int nsub, const d
             for (int e = 0; e < 6; ++e) qc[e] = 0.0;
         } else {
             const int c = w.first_child + u;
-            const Mom64 mc = q64[c];
+            const Mom64 mc = q64.load(c);
             mu = mc.M;
-            for (int k = 0; k < 3; ++k) cu[k] = node[c].com[k];
+            node.com(c, cu);
             qc[0] = mc.qxx; qc[1] = mc.qyy; qc[2] = mc.qzz;
             qc[3] = mc.qxy; qc[4] = mc.qxz; qc[5] = mc.qyz;
         }
@@ -509,35 +499,31 @@ __device__ inline void moments_loop(const WNode& w, bool leaf, int nsub, const d
 
 __device__ inline void moments_node(int64_t b, const double* __restrict__ x, const double* __restrict__ y,
                                     const double* __restrict__ z, const double* __restrict__ m,
-                                    WNode* __restrict__ node, Mom64* __restrict__ q64,
-                                    Mom32* __restrict__ q32) {
-    const WNode w = node[b];
+                                    NodePlanes node, Mom64Planes q64, Mom32Planes q32) {
+    WNode w;
+    const int4 rg = node.range(b);
+    w.begin = rg.x; w.count = rg.y; w.first_child = rg.z; w.nchild = rg.w;
     const bool leaf = w.nchild == 0;
     const int nsub = leaf ? w.count : w.nchild;
     MomOut o;
     if (nsub <= kMomFast) moments_small(w, leaf, nsub, x, y, z, m, node, q64, o);
     else moments_loop(w, leaf, nsub, x, y, z, m, node, q64, o);
-    for (int k = 0; k < 3; ++k) {
-        node[b].lo[k] = o.lo[k];
-        node[b].hi[k] = o.hi[k];
-        node[b].com[k] = o.com[k];
-    }
+    node.set_geometry(b, o.lo, o.hi, o.com);
     Mom64 r;
     r.M = o.M; r.qxx = o.q[0]; r.qyy = o.q[1]; r.qzz = o.q[2]; r.qxy = o.q[3]; r.qxz = o.q[4];
     r.qyz = o.q[5];
     r.pad = 0.0;
-    q64[b] = r;
+    q64.store(b, r);
     Mom32 f;
     f.M = (float)o.M; f.qxx = (float)o.q[0]; f.qyy = (float)o.q[1]; f.qzz = (float)o.q[2];
     f.qxy = (float)o.q[3]; f.qxz = (float)o.q[4]; f.qyz = (float)o.q[5]; f.pad = 0.0f;
-    q32[b] = f;
+    q32.store(b, f);
 }
 
 __global__ __launch_bounds__(kMomT) void k_moments_level(const int32_t* __restrict__ lvl_off, int level,
                                 const double* __restrict__ x, const double* __restrict__ y,
                                 const double* __restrict__ z, const double* __restrict__ m,
-                                WNode* __restrict__ node, Mom64* __restrict__ q64,
-                                Mom32* __restrict__ q32) {
+                                NodePlanes node, Mom64Planes q64, Mom32Planes q32) {
     const int64_t b0 = lvl_off[level], b1 = lvl_off[level + 1];
     for (int64_t b = b0 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < b1;
          b += (int64_t)gridDim.x * blockDim.x)
@@ -548,8 +534,8 @@ __global__ __launch_bounds__(kMomT) void k_moments_level(const int32_t* __restri
 __global__ __launch_bounds__(kMomT) void k_moments_levels(const int32_t* __restrict__ lvl_off, int l_hi,
                                  int l_lo, const double* __restrict__ x,
                                  const double* __restrict__ y, const double* __restrict__ z,
-                                 const double* __restrict__ m, WNode* __restrict__ node,
-                                 Mom64* __restrict__ q64, Mom32* __restrict__ q32) {
+                                 const double* __restrict__ m, NodePlanes node,
+                                 Mom64Planes q64, Mom32Planes q32) {
     for (int l = l_hi; l >= l_lo; --l) {
         const int64_t b0 = lvl_off[l], b1 = lvl_off[l + 1];
         for (int64_t b = b0 + threadIdx.x; b < b1; b += blockDim.x)
@@ -600,7 +586,7 @@ __device__ inline void emit_group(int begin, int count, double ext, unsigned* hi
 }
 
 template <bool HIST>
-__global__ __launch_bounds__(256) void k_group_pass(const WNode* __restrict__ node, const uint64_t* __restrict__ lvl,
+__global__ __launch_bounds__(256) void k_group_pass(NodePlanes node, const uint64_t* __restrict__ lvl,
                              const unsigned long long* __restrict__ n_dev,
                              const uint64_t* __restrict__ keys, int D, int n_crit,
                              const double* __restrict__ x, const double* __restrict__ y,
@@ -610,7 +596,10 @@ __global__ __launch_bounds__(256) void k_group_pass(const WNode* __restrict__ no
     const int64_t nn = (int64_t)*n_dev;
     for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < nn;
          b += (int64_t)gridDim.x * blockDim.x) {
-        const WNode w = node[b];
+        WNode w;
+        node.box(b, w.lo, w.hi);
+        const int4 rg = node.range(b);
+        w.begin = rg.x; w.count = rg.y; w.first_child = rg.z; w.nchild = rg.w;
         const int c = cluster_of(keys[w.begin], D);
         const double S = HIST ? INFINITY : cl_S[c];
         unsigned* h = hist + ((int64_t)(b % reps) * nc + c) * kOctaves;
@@ -648,10 +637,10 @@ __global__ __launch_bounds__(256) void k_group_pass(const WNode* __restrict__ no
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             if (u < nch) {
-                const WNode& ch = node[w.first_child + u];
-                for (int k = 0; k < 3; ++k) { alo[u][k] = ch.lo[k]; ahi[u][k] = ch.hi[k]; }
-                acnt[u] = ch.count;
-                abeg[u] = ch.begin;
+                node.box(w.first_child + u, alo[u], ahi[u]);
+                const int4 cr = node.range(w.first_child + u);
+                acnt[u] = cr.y;
+                abeg[u] = cr.x;
             }
         }
 #pragma unroll
@@ -867,14 +856,14 @@ void launch_groups(Dev& d, const BuildCfg& c, hipStream_t s) {
     const int reps = group_hist_reps(c.n_clusters);
     const int64_t hist_len = (int64_t)reps * c.n_clusters * kOctaves;
     hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(hist_len, 256)), dim3(256), 0, s, d.g_hist, hist_len);
-    hipLaunchKernelGGL(k_group_pass<true>, dim3(gb), dim3(256), 0, s, (const WNode*)d.node,
+    hipLaunchKernelGGL(k_group_pass<true>, dim3(gb), dim3(256), 0, s, d.node,
                        (const uint64_t*)d.lvl_key, n_nodes, (const uint64_t*)d.keys, c.D, c.n_crit,
                        (const double*)d.x, (const double*)d.y, (const double*)d.z,
                        (const double*)d.cl_S, d.g_hist, c.n_clusters, reps, d.g_flag, d.g_len);
     hipLaunchKernelGGL(k_group_limit, dim3(c.n_clusters), dim3(kLimitT), 0, s,
                        (const unsigned*)d.g_hist, c.n_clusters, reps, d.cl_S);
     hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(n + 1, 256)), dim3(256), 0, s, d.g_flag, n + 1, 0);
-    hipLaunchKernelGGL(k_group_pass<false>, dim3(gb), dim3(256), 0, s, (const WNode*)d.node,
+    hipLaunchKernelGGL(k_group_pass<false>, dim3(gb), dim3(256), 0, s, d.node,
                        (const uint64_t*)d.lvl_key, n_nodes, (const uint64_t*)d.keys, c.D, c.n_crit,
                        (const double*)d.x, (const double*)d.y, (const double*)d.z,
                        (const double*)d.cl_S, d.g_hist, c.n_clusters, reps, d.g_flag, d.g_len);

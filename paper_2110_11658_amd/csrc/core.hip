@@ -34,7 +34,7 @@ struct CoreParams {
     int64_t n;
     int64_t ns;
     const int32_t* sample;   // [ns] caller indices
-    const WNode* node;       // breadth-first nodes of the last build, root 0
+    NodePlanes node;         // breadth-first nodes of the last build, root 0
     const double* x;         // sorted coordinates
     const double* y;
     const double* z;
@@ -159,7 +159,10 @@ __global__ __launch_bounds__(64) void k_core_knn(CoreParams p) {
         const bool has = lane < npop;
         const int nd = has ? s_stack[top + lane] : 0;
         __syncthreads();
-        const WNode w = p.node[nd];
+        WNode w;
+        p.node.box(nd, w.lo, w.hi);
+        const int4 rg = p.node.range(nd);
+        w.begin = rg.x; w.count = rg.y; w.first_child = rg.z; w.nchild = rg.w;
         const double c[3] = {xi, yi, zi};
         const bool open = has && !(box_pt_d2(w.lo, w.hi, c) > T.bound());
         const bool leaf = w.nchild == 0;

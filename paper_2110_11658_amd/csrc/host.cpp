@@ -234,8 +234,9 @@ pbh_status ensure_buffers(pbh_ctx* ctx) {
               dalloc(ctx, &d.pre_nchild, cap) && dalloc(ctx, &d.lvl_key, cap) &&
               dalloc(ctx, &d.lvl_key_alt, cap) && dalloc(ctx, &d.lvl_val, cap) &&
               dalloc(ctx, &d.bfs2pre, cap) && dalloc(ctx, &d.pre2bfs, cap) &&
-              dalloc(ctx, &d.lvl_off, 32) && dalloc(ctx, &d.node, cap) &&
-              dalloc(ctx, &d.q64, cap) && dalloc(ctx, &d.q32, cap) &&
+              dalloc(ctx, &d.lvl_off, 32) && dalloc(ctx, &d.node.p, cap * NodePlanes::kPlanes) &&
+              dalloc(ctx, &d.q64.p, cap * Mom64Planes::kPlanes) &&
+              dalloc(ctx, &d.q32.p, cap * Mom32Planes::kPlanes) &&
               dalloc(ctx, &d.g_flag, n + 1) && dalloc(ctx, &d.g_len, n) &&
               dalloc(ctx, &d.g_hist, (int64_t)128 * C * group_hist_reps((int)C)) && dalloc(ctx, &d.cl_S, C) &&
               dalloc(ctx, &d.g.begin, G) && dalloc(ctx, &d.g.count, G) &&
@@ -256,6 +257,7 @@ pbh_status ensure_buffers(pbh_ctx* ctx) {
         return fail(ctx, PBH_E_OOM, "device allocation failed");
     }
     d.queues = d.cnt + kNumCounters;
+    d.node.cap = d.q64.cap = d.q32.cap = cap;
     d.scan_tmp_len = scan_len;
     d.stack_len = stack;
     ++ctx->alloc_gen;
@@ -1629,30 +1631,31 @@ pbh_status pbh_debug_tree(pbh_ctx* ctx, int32_t* order, uint64_t* keys, int64_t 
     if (keys) HIP_TRY(hipMemcpy(keys, ctx->d.keys, sizeof(uint64_t) * n, hipMemcpyDeviceToHost));
     if (!nodes_i && !nodes_d) return PBH_OK;
     if (cap < nn) return fail(ctx, PBH_E_ARG, "node buffer too small");
-    std::vector<WNode> w(nn);
-    std::vector<Mom64> q(nn);
-    std::vector<int32_t> lvl(nn);
-    HIP_TRY(hipMemcpy(w.data(), ctx->d.node, sizeof(WNode) * nn, hipMemcpyDeviceToHost));
-    HIP_TRY(hipMemcpy(q.data(), ctx->d.q64, sizeof(Mom64) * nn, hipMemcpyDeviceToHost));
+    std::vector<double2> w(NodePlanes::kPlanes * nn), q(Mom64Planes::kPlanes * nn);
+    for (int k = 0; k < NodePlanes::kPlanes; ++k)
+        HIP_TRY(hipMemcpy(w.data() + k * nn, ctx->d.node.plane(k), sizeof(double2) * nn, hipMemcpyDeviceToHost));
+    for (int k = 0; k < Mom64Planes::kPlanes; ++k)
+        HIP_TRY(hipMemcpy(q.data() + k * nn, ctx->d.q64.p + k * ctx->d.q64.cap, sizeof(double2) * nn,
+                          hipMemcpyDeviceToHost));
     std::vector<uint64_t> lk(nn);
     HIP_TRY(hipMemcpy(lk.data(), ctx->d.lvl_key, sizeof(uint64_t) * nn, hipMemcpyDeviceToHost));
     for (int64_t k = 0; k < nn; ++k) {
         if (nodes_i) {
-            nodes_i[4 * k] = w[k].begin;
-            nodes_i[4 * k + 1] = w[k].count;
-            nodes_i[4 * k + 2] = w[k].nchild;
+            int32_t r[4];   // begin, count, first_child, nchild
+            std::memcpy(r, &w[5 * nn + k], sizeof(r));
+            nodes_i[4 * k] = r[0];
+            nodes_i[4 * k + 1] = r[1];
+            nodes_i[4 * k + 2] = r[3];
             nodes_i[4 * k + 3] = (int64_t)lk[k];
         }
         if (nodes_d) {
             double* o = nodes_d + 16 * k;
-            o[0] = q[k].M;
-            for (int j = 0; j < 3; ++j) {
-                o[1 + j] = w[k].com[j];
-                o[10 + j] = w[k].lo[j];
-                o[13 + j] = w[k].hi[j];
-            }
-            o[4] = q[k].qxx; o[5] = q[k].qyy; o[6] = q[k].qzz;
-            o[7] = q[k].qxy; o[8] = q[k].qxz; o[9] = q[k].qyz;
+            o[0] = q[k].x;
+            o[1] = w[3 * nn + k].x; o[2] = w[3 * nn + k].y; o[3] = w[4 * nn + k].x;
+            o[4] = q[k].y; o[5] = q[nn + k].x; o[6] = q[nn + k].y;
+            o[7] = q[2 * nn + k].x; o[8] = q[2 * nn + k].y; o[9] = q[3 * nn + k].x;
+            o[10] = w[k].x; o[11] = w[k].y; o[12] = w[nn + k].x;
+            o[13] = w[nn + k].y; o[14] = w[2 * nn + k].x; o[15] = w[2 * nn + k].y;
         }
     }
     return PBH_OK;

@@ -25,7 +25,7 @@ namespace {
 constexpr int NCAP = 128;   // candidate tile: < 64 left over + 64 new
 
 struct NbrParams {
-    const WNode* node;
+    NodePlanes node;
     const double* x;
     const double* y;
     const double* z;
@@ -114,7 +114,10 @@ __global__ __launch_bounds__(64) void k_nbr_fill(NbrParams p) {
                 const bool has = lane < npop;
                 const int nd = has ? stack.get(top + lane) : root;
                 __threadfence_block();
-                const WNode w = p.node[nd];
+                WNode w;
+                p.node.box(nd, w.lo, w.hi);
+                const int4 rg = p.node.range(nd);
+                w.begin = rg.x; w.count = rg.y; w.first_child = rg.z; w.nchild = rg.w;
                 const bool near = has && box_box_d2(glo, ghi, w.lo, w.hi) < rlist2;
                 const bool leaf = w.nchild == 0;
                 const int nch = (near && !leaf) ? w.nchild : 0;

@@ -67,9 +67,9 @@ struct alignas(16) Tiles : NearExtra<R, TC> {
 };
 
 struct WalkParams {
-    const WNode* node;
-    const Mom32* q32;
-    const Mom64* q64;
+    NodePlanes node;
+    Mom32Planes q32;
+    Mom64Planes q64;
     const double* x;
     const double* y;
     const double* z;
@@ -827,7 +827,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
             const bool has = lane < npop;
             const int nd = has ? stack.get(top + lane) : root;
             __threadfence_block();
-            const WNode w = p.node[nd];
+            const WNode w = p.node.load(nd);
+            // (the moments along with the node: one latency a step, and siblings' moments
+            // lie side by side, whether or not all of them are accepted)
+            Mom32 q32 = {};
+            if (MIXED) q32 = p.q32.load(nd);
             const double dbox2 = box_box_d2(glo, ghi, w.lo, w.hi);
             const bool near = (dbox2 < rlist2) || (dbox2 == 0.0);
             const bool accept = has && !near && p.use_theta && (box_pt_d2(glo, ghi, w.com) > w.rcrit2);
@@ -845,11 +849,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
                     e[2] = (R)(w.com[2] - ctr[2]);
                     if (MIXED) {
                         // quadrupole scaled by 2.5 (see eval_pn<float>)
-                        const Mom32 q = p.q32[nd];
-                        e[3] = q.M; e[4] = 2.5f * q.qxx; e[5] = 2.5f * q.qyy; e[6] = 2.5f * q.qzz;
-                        e[7] = 2.5f * q.qxy; e[8] = 2.5f * q.qxz; e[9] = 2.5f * q.qyz;
+                        e[3] = q32.M; e[4] = 2.5f * q32.qxx; e[5] = 2.5f * q32.qyy; e[6] = 2.5f * q32.qzz;
+                        e[7] = 2.5f * q32.qxy; e[8] = 2.5f * q32.qxz; e[9] = 2.5f * q32.qyz;
                     } else {
-                        const Mom64 q = p.q64[nd];
+                        const Mom64 q = p.q64.load(nd);
                         e[3] = q.M; e[4] = q.qxx; e[5] = q.qyy; e[6] = q.qzz;
                         e[7] = q.qxy; e[8] = q.qxz; e[9] = q.qyz;
                     }
@@ -866,7 +869,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
                 overflow = true;
                 break;
             }
-            for (int k = 0; k < nch; ++k) stack.put(top + incl - nch + k, w.first_child + k);
+            if (top + tot <= kWalkStackLds) {   // (wave-uniform; the usual case)
+                int* dst = s_stack + top + incl - nch;
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+                    if (k < nch) dst[k] = w.first_child + k;
+            } else {
+                for (int k = 0; k < nch; ++k) stack.put(top + incl - nch + k, w.first_child + k);
+            }
             top = uni(top + tot);
 
             // leaves: far ones (W = 1) and near ones (changeover)
@@ -1057,7 +1067,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
 
 // rcrit^2 = (l/theta + delta)^2 per node, l = largest box extent, delta =
 // |COM - box centre|; also clears the per-call counters and queues.
-__global__ void k_rcrit(WNode* __restrict__ node, const unsigned long long* __restrict__ n_dev,
+__global__ void k_rcrit(NodePlanes node, const unsigned long long* __restrict__ n_dev,
                         double theta, unsigned long long* __restrict__ cnt,
                         unsigned long long* __restrict__ queues, unsigned* __restrict__ part_done, int n_part) {
 #pragma clang fp contract(off)
@@ -1071,7 +1081,9 @@ __global__ void k_rcrit(WNode* __restrict__ node, const unsigned long long* __re
         part_done[b] = 0u;
     for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < n;
          b += (int64_t)gridDim.x * blockDim.x) {
-        WNode& w = node[b];
+        WNode w;
+        node.box(b, w.lo, w.hi);
+        node.com(b, w.com);
         double l = 0.0;
         for (int k = 0; k < 3; ++k)
             if (w.hi[k] - w.lo[k] > l) l = w.hi[k] - w.lo[k];
@@ -1079,7 +1091,7 @@ __global__ void k_rcrit(WNode* __restrict__ node, const unsigned long long* __re
         for (int k = 0; k < 3; ++k) dd[k] = w.com[k] - (w.lo[k] + w.hi[k]) * 0.5;
         const double delta = sqrt(dd[0] * dd[0] + dd[1] * dd[1] + dd[2] * dd[2]);
         const double rc = theta > 0.0 ? l / theta + delta : 0.0;
-        w.rcrit2 = rc * rc;
+        node.set_rcrit2(b, rc * rc);
     }
 }
 
