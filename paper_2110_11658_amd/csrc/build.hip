@@ -1,22 +1,28 @@
 // build.hip -- octree construction on gfx950.
 //
 // Steps (Barnes-Hut tree of Section 2.4 of Arnold, Baumgardt & Wang 2021):
-//   bbox     per-cluster bounding box and NaN/Inf check (two-level reduction)
+//   bbox     per-cluster bounding box and NaN/Inf check (per-block partial boxes,
+//            reduced again by every workgroup of the keys)
 //   keys     cluster id above D-bit-per-axis Morton codes (x, y, z interleaved)
-//   sort     stable radix sort (sort.hip) -> sorted keys and permutation
-//   gather   sorted FP64 SoA copies of x, y, z, m
+//   sort     stable sort (sort.hip) -> sorted keys and permutation
 //   topology a node is a run of sorted particles sharing a key prefix whose
 //            parent holds more than n_leaf particles; each particle knows the
-//            levels of the nodes it starts, so one scan numbers the nodes in
-//            pre-order; a one-pass counting sort by level then gives the
-//            breadth-first order in which every node's children are contiguous
-//   moments  bottom-up, one launch per level: M, centre of mass, traceless
-//            quadrupole about it (parallel-axis sums over children), tight box
+//            levels of the nodes it starts, so a count per tile and level, one
+//            scan of those counts and ballots within a tile give every node its
+//            place in breadth-first order, in which children are contiguous
+//   moments  bottom-up inside tiles of particles, then the nodes that straddle
+//            tiles: M, centre of mass, traceless quadrupole about it
+//            (parallel-axis sums over children), tight box
 //   groups   tree-bounded runs of <= n_crit sorted particles (rule at k_group_pass)
+//
+// A build is 13 launches up to 8192 particles and 20 beyond (there were 43 and
+// 53): with kernels of a few microseconds the launches, and the scans between
+// them, were most of its time.
 //
 // FP64 arithmetic that decides the tree (keys, moments) is evaluated without
 // fused multiply-add so it rounds exactly as written.
 #include "pbh_internal.hpp"
+#include "wave.hpp"
 
 namespace pbh {
 
@@ -25,70 +31,52 @@ namespace {
 constexpr int BB_T = 256;
 
 // ------------------------------------------------------------------ bbox
+__device__ inline double wave_min_f64(double v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, 64));
+    return v;
+}
+
+// box[6] (lo, -hi) of the workgroup's threads, in thread 0 .. all (min is exact,
+// so the order does not matter); s has 6 entries per wave
+__device__ inline void block_box(double (&v)[6], double (*s)[6]) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    for (int k = 0; k < 6; ++k) v[k] = wave_min_f64(v[k]);
+    if (lane == 0)
+        for (int k = 0; k < 6; ++k) s[w][k] = v[k];
+    __syncthreads();
+    for (int k = 0; k < 6; ++k) {
+        double m = s[0][k];
+        for (int q = 1; q < BB_T / 64; ++q) m = fmin(m, s[q][k]);
+        v[k] = m;
+    }
+}
+
+// Partial boxes of the blocks of the cluster table, and the zeroing of the
+// build's counters (see launch_zero_counts).
 __global__ __launch_bounds__(BB_T) void k_bbox_part(const double* __restrict__ pos,
                                                     const double* __restrict__ mass,
                                                     const int64_t* __restrict__ range,
-                                                    double* __restrict__ part,
-                                                    int32_t* __restrict__ bad) {
-    __shared__ double s_v[6][BB_T];
-    __shared__ int s_bad;
+                                                    double* __restrict__ part, int32_t* __restrict__ bad,
+                                                    unsigned long long* __restrict__ cnt) {
+    __shared__ double s_v[BB_T / 64][6];
     const int t = threadIdx.x;
-    if (t == 0) s_bad = 0;
+    for (int i = blockIdx.x * BB_T + t; i < kNumCounters + kQueueWords; i += gridDim.x * BB_T)
+        if (i < 11 || i >= kNumCounters) cnt[i] = 0ull;   // slots 11 .. outlive a build
     const int64_t b0 = range[2 * blockIdx.x], b1 = range[2 * blockIdx.x + 1];
-    double lo0 = INFINITY, lo1 = INFINITY, lo2 = INFINITY;
-    double hi0 = -INFINITY, hi1 = -INFINITY, hi2 = -INFINITY;
+    double v[6] = {INFINITY, INFINITY, INFINITY, INFINITY, INFINITY, INFINITY};
     int nf = 0;
+#pragma unroll 8
     for (int64_t i = b0 + t; i < b1; i += BB_T) {
         const double x = pos[3 * i], y = pos[3 * i + 1], z = pos[3 * i + 2], mm = mass[i];
         nf |= !(isfinite(x) && isfinite(y) && isfinite(z) && isfinite(mm));
-        lo0 = fmin(lo0, x); lo1 = fmin(lo1, y); lo2 = fmin(lo2, z);
-        hi0 = fmax(hi0, x); hi1 = fmax(hi1, y); hi2 = fmax(hi2, z);
+        v[0] = fmin(v[0], x); v[1] = fmin(v[1], y); v[2] = fmin(v[2], z);
+        v[3] = fmin(v[3], -x); v[4] = fmin(v[4], -y); v[5] = fmin(v[5], -z);
     }
-    s_v[0][t] = lo0; s_v[1][t] = lo1; s_v[2][t] = lo2;
-    s_v[3][t] = hi0; s_v[4][t] = hi1; s_v[5][t] = hi2;
-    __syncthreads();
-    if (nf) atomicOr(&s_bad, 1);
-    for (int o = BB_T / 2; o > 0; o >>= 1) {
-        if (t < o) {
-            for (int k = 0; k < 3; ++k) s_v[k][t] = fmin(s_v[k][t], s_v[k][t + o]);
-            for (int k = 3; k < 6; ++k) s_v[k][t] = fmax(s_v[k][t], s_v[k][t + o]);
-        }
-        __syncthreads();
-    }
-    if (t < 6) part[6 * blockIdx.x + t] = s_v[t][0];
-    if (t == 0) bad[blockIdx.x] = s_bad;
-}
-
-// one block per cluster; blocks of cluster c are [cblk[c], cblk[c+1]). min and
-// max are exact, so the reduction order does not matter.
-__global__ __launch_bounds__(BB_T) void k_bbox_final(const double* __restrict__ part,
-                                                     const int32_t* __restrict__ bad,
-                                                     const int32_t* __restrict__ cblk, int nc,
-                                                     double* __restrict__ box,
-                                                     unsigned long long* __restrict__ cnt) {
-    __shared__ double s_v[6][BB_T];
-    __shared__ int s_bad;
-    const int c = blockIdx.x, t = threadIdx.x;
-    if (t == 0) s_bad = 0;
-    double v[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
-    int nf = 0;
-    for (int b = cblk[c] + t; b < cblk[c + 1]; b += BB_T) {
-        for (int k = 0; k < 3; ++k) v[k] = fmin(v[k], part[6 * b + k]);
-        for (int k = 3; k < 6; ++k) v[k] = fmax(v[k], part[6 * b + k]);
-        nf |= bad[b];
-    }
-    for (int k = 0; k < 6; ++k) s_v[k][t] = v[k];
-    __syncthreads();
-    if (nf) atomicOr(&s_bad, 1);
-    for (int o = BB_T / 2; o > 0; o >>= 1) {
-        if (t < o) {
-            for (int k = 0; k < 3; ++k) s_v[k][t] = fmin(s_v[k][t], s_v[k][t + o]);
-            for (int k = 3; k < 6; ++k) s_v[k][t] = fmax(s_v[k][t], s_v[k][t + o]);
-        }
-        __syncthreads();
-    }
-    if (t < 6) box[6 * c + t] = s_v[t][0];
-    if (t == 0 && s_bad) atomicOr(&cnt[kErr], kErrNonFinite);
+    const int any = __syncthreads_or(nf);
+    block_box(v, s_v);
+    if (t < 6) part[6 * blockIdx.x + t] = t == 0 ? v[0] : t == 1 ? v[1] : t == 2 ? v[2] : t == 3 ? v[3] : t == 4 ? v[4] : v[5];
+    if (t == 0) bad[blockIdx.x] = any;
 }
 
 // ------------------------------------------------------------------ keys
@@ -103,47 +91,48 @@ __device__ inline uint64_t spread_bits3(uint64_t v) {
     return v;
 }
 
+// The cluster's box from its blocks' partial boxes (cluster c: blocks
+// [cblk[c], cblk[c+1])), then the keys of the block's particles.
 __global__ __launch_bounds__(BB_T) void k_keys(const double* __restrict__ pos,
                                                const int64_t* __restrict__ range,
                                                const int32_t* __restrict__ blk_cluster,
-                                               const double* __restrict__ box, int D,
-                                               uint64_t* __restrict__ keys) {
+                                               const int32_t* __restrict__ cblk,
+                                               const double* __restrict__ part, const int32_t* __restrict__ bad,
+                                               int D, uint64_t* __restrict__ keys,
+                                               unsigned long long* __restrict__ cnt) {
 #pragma clang fp contract(off)
+    __shared__ double s_v[BB_T / 64][6];
     const int c = blk_cluster[blockIdx.x];
+    const int p0 = cblk[c], p1 = cblk[c + 1];
+    double v[6] = {INFINITY, INFINITY, INFINITY, INFINITY, INFINITY, INFINITY};
+    int nf = 0;
+    for (int b = p0 + threadIdx.x; b < p1; b += BB_T) {
+        for (int k = 0; k < 6; ++k) v[k] = fmin(v[k], part[6 * (int64_t)b + k]);
+        nf |= bad[b];
+    }
+    const int any = __syncthreads_or(nf);
+    if (any && threadIdx.x == 0 && (int)blockIdx.x == p0) atomicOr(&cnt[kErr], kErrNonFinite);
+    block_box(v, s_v);
     const int64_t b0 = range[2 * blockIdx.x], b1 = range[2 * blockIdx.x + 1];
-    const double lo0 = box[6 * c], lo1 = box[6 * c + 1], lo2 = box[6 * c + 2];
     double L = 0.0;
     for (int k = 0; k < 3; ++k) {
-        const double e = box[6 * c + 3 + k] - box[6 * c + k];
+        const double e = -v[3 + k] - v[k];
         if (e > L) L = e;
     }
     if (L == 0.0) L = 1.0;
     const double scale = ldexp(1.0, D) / L;
     const int64_t maxc = ((int64_t)1 << D) - 1;
     const uint64_t cid = (uint64_t)c << (3 * D);
+#pragma unroll 4
     for (int64_t i = b0 + threadIdx.x; i < b1; i += BB_T) {
-        const double v[3] = {pos[3 * i], pos[3 * i + 1], pos[3 * i + 2]};
-        const double lo[3] = {lo0, lo1, lo2};
+        const double x[3] = {pos[3 * i], pos[3 * i + 1], pos[3 * i + 2]};
         uint64_t key = 0;
         for (int k = 0; k < 3; ++k) {
-            int64_t q = (int64_t)floor((v[k] - lo[k]) * scale);
+            int64_t q = (int64_t)floor((x[k] - v[k]) * scale);
             q = q > maxc ? maxc : (q < 0 ? 0 : q);
             key |= spread_bits3((uint64_t)q) << (2 - k);
         }
         keys[i] = cid | key;
-    }
-}
-
-__global__ void k_gather(const double* __restrict__ pos, const double* __restrict__ mass,
-                         const int32_t* __restrict__ perm, int64_t n, double* __restrict__ x,
-                         double* __restrict__ y, double* __restrict__ z, double* __restrict__ m) {
-    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n;
-         k += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t i = perm[k];
-        x[k] = pos[3 * i];
-        y[k] = pos[3 * i + 1];
-        z[k] = pos[3 * i + 2];
-        m[k] = mass[i];
     }
 }
 
@@ -153,393 +142,536 @@ __device__ inline uint64_t prefix(uint64_t key, int l, int D) { return key >> (3
 
 __device__ inline int cluster_of(uint64_t key, int D) { return (int)(key >> (3 * D)); }
 
-// Number of nodes started by sorted particle i and the first level.
-__global__ void k_topo_count(const uint64_t* __restrict__ keys, const int64_t* __restrict__ cl_off,
-                             int64_t n, int D, int n_leaf, int32_t* __restrict__ p_first,
-                             int32_t* __restrict__ p_nn) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x) {
+// Topology runs over tiles of kTopoT particles. A particle i carries the first
+// level at which its key differs from that of i - 1 (0 at the start of a
+// cluster, D + 1 for equal keys): level-l runs start exactly at the particles
+// whose first level is at most l. It starts nodes at the levels first .. last
+// (last < first: none).
+constexpr int kTopoT = 256;
+constexpr int kTopoW = kTopoT / 64;
+
+__device__ inline int lv_first(int lv) { return lv & 255; }
+__device__ inline int lv_last(int lv) { return (lv >> 8) - 1; }
+
+// Levels of every particle's nodes, and the nodes per tile and level:
+// table[l][tile]. Sorts the particles into place on the way (x, y, z, m) and
+// clears the group flags and histograms.
+__global__ __launch_bounds__(kTopoT) void k_topo_count(const uint64_t* __restrict__ keys,
+                                                       const int64_t* __restrict__ cl_off, int64_t n, int D,
+                                                       int n_leaf, int32_t* __restrict__ lv_out, int64_t ntile,
+                                                       int32_t* __restrict__ table, const double* __restrict__ pos,
+                                                       const double* __restrict__ mass,
+                                                       const int32_t* __restrict__ perm, double* __restrict__ x,
+                                                       double* __restrict__ y, double* __restrict__ z,
+                                                       double* __restrict__ m, int32_t* __restrict__ g_flag,
+                                                       unsigned* __restrict__ hist, int64_t hist_len) {
+    __shared__ int s_c[kTopoW][64];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    for (int64_t k = (int64_t)blockIdx.x * kTopoT + t; k < hist_len; k += (int64_t)gridDim.x * kTopoT) hist[k] = 0u;
+    const int64_t i = (int64_t)blockIdx.x * kTopoT + t;
+    int first = D + 1, last = D;   // (beyond n: no nodes)
+    if (i < n) {
+        const int64_t src = perm[i];
+        const double px = pos[3 * src], py = pos[3 * src + 1], pz = pos[3 * src + 2], pm = mass[src];
         const uint64_t key = keys[i];
         const int c = cluster_of(key, D);
         const int64_t cs = cl_off[c], ce = cl_off[c + 1];
-        int lf;
+        bool starts = true;
         if (i == cs) {
-            lf = 0;
+            first = 0;
         } else {
-            const uint64_t x = key ^ keys[i - 1];
-            if (x == 0) {
-                p_first[i] = D + 1;
-                p_nn[i] = 0;
-                continue;
-            }
-            const int h = 63 - __clzll(x);
-            lf = D - h / 3;
-            // the parent run (level lf-1) contains i-1 and i: it must hold more than n_leaf
-            const uint64_t pp = prefix(key, lf - 1, D);
-            int64_t a = i - 1, b = i + 1;
-            while (a > cs && b - a <= n_leaf && prefix(keys[a - 1], lf - 1, D) == pp) --a;
-            while (b < ce && b - a <= n_leaf && prefix(keys[b], lf - 1, D) == pp) ++b;
-            if (b - a <= n_leaf) {
-                p_first[i] = lf;
-                p_nn[i] = 0;
-                continue;
-            }
-        }
-        // levels lf+1.. exist while the run of level l-1 starting at i holds > n_leaf
-        int last = lf;
-        for (int l = lf + 1; l <= D; ++l) {
-            const int64_t j = i + n_leaf;
-            if (j < ce && prefix(keys[j], l - 1, D) == prefix(key, l - 1, D)) last = l;
-            else break;
-        }
-        p_first[i] = lf;
-        p_nn[i] = last - lf + 1;
-    }
-}
-
-// end of the level-l run that starts at i (exclusive)
-__device__ inline int64_t run_end(const uint64_t* keys, int64_t i, int64_t ce, int l, int D) {
-    if (l == 0) return ce;
-    const uint64_t p = prefix(keys[i], l, D);
-    int64_t step = 1, lo = i, hi;
-    // exponential search for the first index with a different prefix
-    for (;;) {
-        hi = lo + step;
-        if (hi >= ce || prefix(keys[hi], l, D) != p) break;
-        lo = hi;
-        step <<= 1;
-    }
-    if (hi > ce) hi = ce;
-    // invariant: keys[lo] has prefix p; keys[hi] (if < ce) does not
-    while (hi - lo > 1) {
-        const int64_t mid = lo + (hi - lo) / 2;
-        if (prefix(keys[mid], l, D) == p) lo = mid; else hi = mid;
-    }
-    return hi;
-}
-
-// start of the level-l run containing i
-__device__ inline int64_t run_start(const uint64_t* keys, int64_t i, int64_t cs, int l, int D) {
-    if (l == 0) return cs;
-    const uint64_t p = prefix(keys[i], l, D);
-    int64_t step = 1, hi = i, lo;
-    for (;;) {
-        lo = hi - step;
-        if (lo < cs || prefix(keys[lo], l, D) != p) break;
-        hi = lo;
-        step <<= 1;
-    }
-    if (lo < cs - 1) lo = cs - 1;
-    // keys[hi] has prefix p; keys[lo] (if >= cs) does not
-    while (hi - lo > 1) {
-        const int64_t mid = lo + (hi - lo) / 2;
-        if (prefix(keys[mid], l, D) == p) hi = mid; else lo = mid;
-    }
-    return hi;
-}
-
-// One thread per node (pre-order index v): its first particle i is the last
-// with p_base[i] <= v (binary search), and it is i's (v - p_base[i])-th node
-// from level p_first[i] down. (A particle that starts nodes on many levels --
-// the first of a cluster starts one on every level -- would otherwise search
-// the runs of all of them in turn.)
-__global__ void k_topo_emit(const uint64_t* __restrict__ keys, const int64_t* __restrict__ cl_off,
-                            int64_t n, int D, int n_leaf, const int32_t* __restrict__ p_first,
-                            const int32_t* __restrict__ p_base, int64_t cap,
-                            int32_t* __restrict__ pre_begin, int32_t* __restrict__ pre_count,
-                            int32_t* __restrict__ pre_level, int32_t* __restrict__ pre_nchild,
-                            uint64_t* __restrict__ lvl_key, unsigned long long* __restrict__ cnt) {
-    const int64_t total = p_base[n];
-    if (total > cap && blockIdx.x == 0 && threadIdx.x == 0) atomicOr(&cnt[kErr], kErrNodeCap);
-    const int64_t m = total < cap ? total : cap;
-    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < m;
-         v += (int64_t)gridDim.x * blockDim.x) {
-        int64_t lo = 0, hi = n;   // p_base[lo] <= v < p_base[hi]
-        while (hi - lo > 1) {
-            const int64_t mid = lo + (hi - lo) / 2;
-            if ((int64_t)p_base[mid] <= v) lo = mid;
-            else hi = mid;
-        }
-        const int64_t i = lo;
-        const int k = (int)(v - p_base[i]);
-        const uint64_t key = keys[i];
-        const int c = cluster_of(key, D);
-        const int64_t cs = cl_off[c], ce = cl_off[c + 1];
-        const int l = p_first[i] + k;
-        const int64_t e = run_end(keys, i, ce, l, D);
-        pre_begin[v] = (int32_t)i;
-        pre_count[v] = (int32_t)(e - i);
-        pre_level[v] = l;
-        lvl_key[v] = (uint64_t)l;
-        // register with the parent: its node index is known from the particle
-        // that starts it (i itself for k > 0)
-        if (l > 0) {
-            int64_t parent;
-            if (k > 0) {
-                parent = v - 1;
+            const uint64_t q = key ^ keys[i - 1];
+            if (q == 0) {
+                starts = false;
             } else {
-                const int64_t s = run_start(keys, i, cs, l - 1, D);
-                parent = (int64_t)p_base[s] + (l - 1 - p_first[s]);
+                first = D - (63 - __clzll(q)) / 3;
+                // the parent run (level first - 1) contains i - 1 and i: it must hold more than n_leaf
+                const uint64_t pp = prefix(key, first - 1, D);
+                int64_t a = i - 1, b = i + 1;
+                while (a > cs && b - a <= n_leaf && prefix(keys[a - 1], first - 1, D) == pp) --a;
+                while (b < ce && b - a <= n_leaf && prefix(keys[b], first - 1, D) == pp) ++b;
+                starts = b - a > n_leaf;
             }
-            if (parent < cap) atomicAdd(&pre_nchild[parent], 1);
         }
+        last = first - 1;
+        if (starts) {
+            // levels first + 1 .. exist while the run of level l - 1 starting at i holds > n_leaf:
+            // while particle i + n_leaf is in it
+            last = first;
+            const int64_t j = i + n_leaf;
+            if (j < ce) {
+                const uint64_t q = key ^ keys[j];
+                const int same = q == 0 ? D : D - 1 - (63 - __clzll(q)) / 3;   // deepest common level
+                if (same + 1 > last) last = same + 1 < D ? same + 1 : D;
+            }
+        }
+        lv_out[i] = first | (last + 1) << 8;
+        x[i] = px;
+        y[i] = py;
+        z[i] = pz;
+        m[i] = pm;
+        g_flag[i] = 0;
+    }
+    int cnt = 0;
+    for (int l = 0; l <= D; ++l) {
+        const int c = __popcll(__ballot(first <= l && l <= last));
+        cnt = lane == l ? c : cnt;
+    }
+    s_c[w][lane] = cnt;
+    __syncthreads();
+    if (t <= D) {
+        int c = 0;
+        for (int q = 0; q < kTopoW; ++q) c += s_c[q][t];
+        table[(int64_t)t * (ntile + 1) + blockIdx.x] = c;
     }
 }
 
-__global__ void k_fill_i32(int32_t* __restrict__ p, int64_t n, int32_t v) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = v;
+// Exclusive scan of a level's counts over the tiles, its total behind them (one
+// workgroup a level).
+__global__ __launch_bounds__(1024) void k_topo_scan(int64_t ntile, int32_t* __restrict__ table) {
+    __shared__ int s_w[16];
+    int32_t* row = table + (int64_t)blockIdx.x * (ntile + 1);
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    int carry = 0;
+    for (int64_t c0 = 0; c0 < ntile; c0 += 4096) {
+        int v[4], sum = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t k = c0 + 4 * t + u;
+            v[u] = k < ntile ? row[k] : 0;
+            sum += v[u];
+        }
+        const int inc = wave_incl_scan(sum, lane);
+        __syncthreads();
+        if (lane == 63) s_w[w] = inc;
+        __syncthreads();
+        int run = carry + inc - sum;
+        for (int q = 0; q < 16; ++q) {
+            if (q < w) run += s_w[q];
+            carry += s_w[q];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t k = c0 + 4 * t + u;
+            if (k < ntile) row[k] = run;
+            run += v[u];
+        }
+    }
+    if (t == 0) row[ntile] = carry;
 }
 
-__global__ void k_zero_i32(int32_t* __restrict__ p, const int32_t* __restrict__ n_dev, int64_t cap) {
-    const int64_t n = min(cap, (int64_t)*n_dev);
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = 0;
-}
-
-// breadth-first level offsets: lvl_off[l] = first sorted slot with level >= l
-__global__ void k_level_offsets(const uint64_t* __restrict__ lvl_sorted,
-                                const int32_t* __restrict__ n_dev, int64_t cap,
-                                int32_t* __restrict__ lvl_off, unsigned long long* __restrict__ cnt) {
+// First node of every level, s_off[0 .. D + 1] (the levels' totals stand at
+// table[l][ntile]); more nodes than the capacity: all zero. Threads 0 .. 63.
+__device__ inline void level_offsets(const int32_t* __restrict__ table, int64_t ntile, int D, int64_t cap,
+                                     int* s_off) {
     const int l = threadIdx.x;
-    const int64_t n = min(cap, (int64_t)*n_dev);
-    if (l <= kMaxLevels) {
-        int64_t lo = 0, hi = n;
-        while (lo < hi) {
-            const int64_t mid = (lo + hi) / 2;
-            if (lvl_sorted[mid] < (uint64_t)l) lo = mid + 1; else hi = mid;
+    const int v = l <= D ? table[(int64_t)l * (ntile + 1) + ntile] : 0;
+    const int inc = wave_incl_scan(v, l);
+    const bool over = (int64_t)last_lane(inc) > cap;   // (node capacities stay below 2^31)
+    if (l <= D + 1) s_off[l] = over ? 0 : inc - v;
+}
+
+// End (exclusive) of the level-l run that contains particle a, by the 8 lanes of
+// an aligned lane group that share (a, l): each step probes 8 places, first at
+// growing distances, then evenly between the last particle known inside and the
+// first known outside. Every lane of the wave takes part; groups with on = false
+// return a at once.
+__device__ inline int64_t run_end8(const uint64_t* __restrict__ keys, bool on, int64_t a, int64_t ce, int l, int D) {
+    const int lane = threadIdx.x & 63, g = lane & 7, sh = lane & 56;
+    const uint64_t p = on ? prefix(keys[a], l, D) : 0;
+    int64_t lo = a, hi = on ? ce : a + 1;
+    bool grow = true;
+    while (__ballot(hi - lo > 1)) {
+        int64_t q;
+        if (grow) q = a + ((int64_t)1 << (3 * g));
+        else if (hi - lo <= 9) q = lo + 1 + g;
+        else q = lo + (hi - lo) * (g + 1) / 9;
+        const bool in = hi - lo > 1 && q < hi && prefix(keys[q], l, D) == p;
+        const int c = __popc((unsigned)((__ballot(in) >> sh) & 255u));   // probes inside (they come first)
+        const int64_t q0 = __shfl(q, sh + (c > 0 ? c - 1 : 0), 64), q1 = __shfl(q, sh + (c < 8 ? c : 7), 64);
+        if (hi - lo > 1) {
+            if (c > 0) lo = q0;
+            if (c < 8 && q1 < hi) hi = q1;
         }
-        lvl_off[l] = (int32_t)lo;
+        grow = false;
     }
-    if (l == 0) {
-        cnt[kCntNodes] = (unsigned long long)n;
-        cnt[kCntMaxLevel] = n ? lvl_sorted[n - 1] : 0ull;
-    }
+    return on ? hi : a;
 }
 
-__global__ void k_invert(const int32_t* __restrict__ bfs2pre, const int32_t* __restrict__ n_dev,
-                         int64_t cap, int32_t* __restrict__ pre2bfs) {
-    const int64_t n = min(cap, (int64_t)*n_dev);
-    for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < n;
-         b += (int64_t)gridDim.x * blockDim.x)
-        pre2bfs[bfs2pre[b]] = (int32_t)b;
-}
-
-__global__ void k_nodes_init(const int32_t* __restrict__ bfs2pre, const int32_t* __restrict__ pre2bfs,
-                             const int32_t* __restrict__ n_dev, int64_t cap,
-                             const int32_t* __restrict__ pre_begin, const int32_t* __restrict__ pre_count,
-                             const int32_t* __restrict__ pre_nchild, NodePlanes node,
-                             unsigned long long* __restrict__ cnt) {
-    const int64_t n = min(cap, (int64_t)*n_dev);
-    unsigned long long leaves = 0;
-    for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < n;
-         b += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t p = bfs2pre[b];
-        // pre-order: the first child follows its parent (guarded for a truncated node list)
-        const int32_t nc = (p + 1 < n) ? pre_nchild[p] : 0;
-        node.set_range(b, make_int4(pre_begin[p], pre_count[p], nc ? pre2bfs[p + 1] : -1, nc));
-        leaves += (nc == 0);
+// The nodes of a tile's particles, at their places in breadth-first order: the
+// level's offset, its count in the tiles before, then the nodes of the level
+// before this particle in the tile. A run ends before the next particle whose
+// first level is no deeper, found in the tile's masks, or by a search beyond
+// the tile. The first child of a node that holds more than n_leaf particles is
+// the node of the next level that the same particle starts; the number of
+// children is a difference of places when the node ends in the tile, and left
+// to the moments (-1) when it does not.
+__global__ __launch_bounds__(kTopoT) void k_topo_emit(const uint64_t* __restrict__ keys,
+                                                      const int64_t* __restrict__ cl_off, int64_t n, int D,
+                                                      int n_leaf, const int32_t* __restrict__ lv_in, int64_t ntile,
+                                                      const int32_t* __restrict__ table, int64_t cap,
+                                                      NodePlanes node, int32_t* __restrict__ lvl_off,
+                                                      unsigned long long* __restrict__ cnt) {
+    __shared__ int s_off[64];
+    __shared__ uint64_t s_run[kMaxLevels + 1][kTopoW];  // particles that start a run of level l
+    __shared__ uint64_t s_node[kMaxLevels + 1][kTopoW]; // ... a node
+    __shared__ int s_pre[kMaxLevels + 1][kTopoW + 1];   // place of a wave's first node of a level
+    __shared__ int64_t s_end[kMaxLevels + 1];           // end of the run that reaches out of the tile
+    __shared__ int s_leaves;
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    if (t < 64) level_offsets(table, ntile, D, cap, s_off);
+    if (t == 0) s_leaves = 0;
+    const int64_t t0 = (int64_t)blockIdx.x * kTopoT, i = t0 + t;
+    const int lv = i < n ? lv_in[i] : (D + 1) | (D + 1) << 8;
+    const int first = lv_first(lv), last = lv_last(lv);
+    for (int l = 0; l <= D; ++l) {
+        const uint64_t r = __ballot(first <= l), q = __ballot(first <= l && l <= last);
+        if (lane == 0) {
+            s_run[l][w] = r;
+            s_node[l][w] = q;
+        }
     }
-    // one atomic per block: a single counter serialises same-address atomics
-    __shared__ unsigned long long s_leaves;
-    if (threadIdx.x == 0) s_leaves = 0;
     __syncthreads();
+    if (t <= D) {
+        int c = s_off[t] + table[(int64_t)t * (ntile + 1) + blockIdx.x];
+        for (int q = 0; q < kTopoW; ++q) {
+            s_pre[t][q] = c;
+            c += __popcll(s_node[t][q]);
+        }
+        s_pre[t][kTopoW] = c;
+    }
+    // Where the last run of a level that starts in the tile is a node and reaches
+    // beyond the tile, its end is searched here, 8 lanes a level.
+    static_assert(8 * (kMaxLevels + 1) <= kTopoT, "8 threads a level");
+    {
+        const int l = t >> 3;
+        bool on = false;
+        const int64_t last_p = t0 + kTopoT - 1;
+        if (l <= D && t0 + kTopoT < n) {
+            for (int q = kTopoW - 1; q >= 0; --q)
+                if (s_run[l][q]) {
+                    on = (s_node[l][q] >> (63 - __clzll(s_run[l][q]))) & 1ull;
+                    break;
+                }
+        }
+        const int64_t pe = on ? cl_off[cluster_of(keys[last_p], D) + 1] : 0;
+        const int64_t e = run_end8(keys, on, last_p, pe, l <= D ? l : D, D);
+        if (on && (t & 7) == 0) s_end[l] = e;
+    }
+    if (blockIdx.x == 0) {
+        if (t <= kMaxLevels) lvl_off[t] = s_off[t <= D + 1 ? t : D + 1];
+        if (t == 0) {
+            int64_t total = 0;
+            int deepest = 0;
+            for (int l = 0; l <= D; ++l) {
+                const int v = table[(int64_t)l * (ntile + 1) + ntile];
+                total += v;
+                if (v) deepest = l;
+            }
+            if (total > cap) atomicOr(&cnt[kErr], kErrNodeCap);
+            cnt[kCntNodes] = total > cap ? 0ull : (unsigned long long)total;
+            cnt[kCntMaxLevel] = (unsigned long long)deepest;
+        }
+    }
+    if (s_off[D + 1] == 0) return;   // beyond the capacity (workgroup-uniform: a build has a root)
+    __syncthreads();
+    // place of the first node of level l that starts at or behind particle p of the tile
+    auto before = [&](int l, int p) {
+        const int pw = p >> 6;
+        return s_pre[l][pw] + ((p & 63) ? __popcll(s_node[l][pw] & (~0ull >> (64 - (p & 63)))) : 0);
+    };
+    int leaves = 0;
+    int place = first <= last ? before(first, t) : 0;
+    for (int l = first; l <= last; ++l) {
+        // the next start of a level-l run in the tile
+        int e = -1;
+        const uint64_t m = lane < 63 ? s_run[l][w] >> (lane + 1) : 0ull;
+        if (m) e = t + 1 + (__ffsll((unsigned long long)m) - 1);
+        for (int q = w + 1; e < 0 && q < kTopoW; ++q)
+            if (s_run[l][q]) e = 64 * q + __ffsll((unsigned long long)s_run[l][q]) - 1;
+        int64_t end;
+        if (e >= 0) {
+            end = t0 + e;
+        } else if (t0 + kTopoT >= n) {
+            end = n;   // the run reaches the end of the last cluster
+        } else {
+            end = s_end[l];
+        }
+        const int count = (int)(end - i);
+        const bool inner = count > n_leaf && l < D;
+        int child = -1, nch = 0;
+        if (inner) {
+            child = before(l + 1, t);
+            nch = e >= 0 ? before(l + 1, e) - child : (end == t0 + kTopoT ? before(l + 1, kTopoT) - child : -1);
+        }
+        node.set_range(place, make_int4((int)i, count, child, nch));
+        leaves += inner ? 0 : 1;
+        place = child;
+    }
     for (int o = 32; o > 0; o >>= 1) leaves += __shfl_xor(leaves, o, 64);
-    if ((threadIdx.x & 63) == 0 && leaves) atomicAdd(&s_leaves, leaves);
+    if (lane == 0 && leaves) atomicAdd(&s_leaves, leaves);
     __syncthreads();
-    if (threadIdx.x == 0 && s_leaves) atomicAdd(&cnt[kCntLeaves], s_leaves);
+    // one atomic per workgroup: a single counter serialises same-address atomics
+    if (t == 0 && s_leaves) atomicAdd(&cnt[kCntLeaves], (unsigned long long)s_leaves);
 }
 
 // ----------------------------------------------------------------- moments
-// One node per thread for the nodes of one level. Leaves sum their particles,
-// inner nodes their (contiguous) children, in order: M, the mass-weighted
-// centre, the tight box, then the traceless quadrupole about the new centre
-// (children's own quadrupoles shifted by the parallel-axis terms).
+// Leaves sum their particles, inner nodes their (contiguous) children, in order:
+// M, the mass-weighted centre, the tight box, then the traceless quadrupole about
+// the new centre (children's own quadrupoles shifted by the parallel-axis terms).
 //
-// A node with at most 8 parts (every inner node; leaves up to n_leaf = 8)
-// loads all parts first, with indices clamped into the node so every load is
-// valid and can be issued at once; the sums then run over the parts in order,
-// exactly as in the general loop below, so both paths round alike.
-constexpr int kMomFast = 8;
-
-struct MomOut {
-    double M, com[3], lo[3], hi[3], q[6];
+// Eight lanes a node: lane k loads part k (siblings are neighbours in memory) and
+// forms its products, which pass through LDS to the lane that sums a component
+// over the parts in order, so every sum rounds as one thread's loop would. A
+// thread for a whole node waited for three dependent loads and a chain of eight
+// parts' sums on every level: 3.8 us a level against 1.9.
+struct MomLds {
+    double v[10][66];     // component, 8 * node of the wave + part (padded: a component a lane, other banks)
+    double r[10][8];      // component, node: M, sums or centre (3), box lo (3), hi (3)
+    double q[6][8];
 };
 
-__device__ inline void moments_small(const WNode& w, bool leaf, int nsub, const double* __restrict__ x,
-                                     const double* __restrict__ y, const double* __restrict__ z,
-                                     const double* __restrict__ m, NodePlanes node, Mom64Planes q64, MomOut& o) {
+__device__ inline void lds_order() {
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Moments of the node b (range rg) of this lane group; `on`: the group has one.
+// kids_end: end of the next level's nodes. A node whose children were not counted
+// (-1 of them) holds those that start inside it. All lanes of the wave take part.
+__device__ inline void moments_group(MomLds& L, bool on, int b, int4 rg, int kids_end,
+                                     const double* __restrict__ x, const double* __restrict__ y,
+                                     const double* __restrict__ z, const double* __restrict__ m, NodePlanes node,
+                                     Mom64Planes q64, Mom32Planes q32) {
 #pragma clang fp contract(off)
-    double mu[kMomFast], cu[3][kMomFast], lu[3][kMomFast], hu[3][kMomFast];
-#pragma unroll
-    for (int k = 0; k < kMomFast; ++k) {
-        const int u = k < nsub ? k : nsub - 1;
-        if (leaf) {
-            const int j = w.begin + u;
-            mu[k] = m[j]; cu[0][k] = x[j]; cu[1][k] = y[j]; cu[2][k] = z[j];
-            for (int d = 0; d < 3; ++d) { lu[d][k] = cu[d][k]; hu[d][k] = cu[d][k]; }
-        } else {
-            const int c = w.first_child + u;
-            mu[k] = q64.mass(c);
-            double cc[3], cl[3], ch[3];
-            node.com(c, cc);
-            node.box(c, cl, ch);
-            for (int d = 0; d < 3; ++d) { cu[d][k] = cc[d]; lu[d][k] = cl[d]; hu[d][k] = ch[d]; }
+    const int lane = threadIdx.x & 63, g = lane & 7, nd = lane >> 3;
+    const bool leaf = rg.z < 0;
+    int nsub = leaf ? rg.y : rg.w;
+    double M = 0.0, c[3] = {0.0, 0.0, 0.0}, lo[3] = {0.0, 0.0, 0.0}, hi[3] = {0.0, 0.0, 0.0};
+    Mom64 mq = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    const int kid = rg.z + g < kids_end ? rg.z + g : kids_end - 1;   // (inner nodes: the level has nodes)
+    if (on && leaf) {
+        if (g < nsub) {
+            const int j = rg.x + g;
+            M = m[j];
+            c[0] = x[j]; c[1] = y[j]; c[2] = z[j];
+            for (int d = 0; d < 3; ++d) { lo[d] = c[d]; hi[d] = c[d]; }
+        }
+    } else if (on) {
+        mq = q64.load(kid);
+        M = mq.M;
+        node.com(kid, c);
+        node.box(kid, lo, hi);
+    }
+    const bool uncounted = on && !leaf && rg.w < 0;
+    if (__ballot(uncounted)) {
+        const bool in = uncounted && rg.z + g < kids_end && node.range(kid).x < rg.x + rg.y;
+        const uint64_t k = __ballot(in);
+        if (uncounted) {
+            nsub = __popc((unsigned)((k >> (lane & 56)) & 255u));   // the children come first
+            if (g == 0) node.set_range(b, make_int4(rg.x, rg.y, rg.z, nsub));
         }
     }
-    double M = 0.0, sx = 0.0, sy = 0.0, sz = 0.0;
+    // parts beyond 8 (leaves of more than 8 particles) are summed by every lane in turn below
+    const int n8 = nsub < 8 ? nsub : 8;
+    L.v[0][lane] = M;
+    for (int d = 0; d < 3; ++d) {
+        L.v[1 + d][lane] = M * c[d];
+        L.v[4 + d][lane] = lo[d];
+        L.v[7 + d][lane] = hi[d];
+    }
+    lds_order();
+    for (int pass = 0; pass < 2; ++pass) {
+        const int k = pass == 0 ? g : 8 + g;   // the component of this lane
+        if (k < 10) {
+            double a = k < 4 ? 0.0 : L.v[k][8 * nd];
+            double u[8];
 #pragma unroll
-    for (int k = 0; k < kMomFast; ++k) {
-        if (k < nsub) {
-            M = M + mu[k];
-            sx = sx + mu[k] * cu[0][k];
-            sy = sy + mu[k] * cu[1][k];
-            sz = sz + mu[k] * cu[2][k];
-            for (int d = 0; d < 3; ++d) {
-                if (k == 0 || lu[d][k] < o.lo[d]) o.lo[d] = lu[d][k];
-                if (k == 0 || hu[d][k] > o.hi[d]) o.hi[d] = hu[d][k];
+            for (int p = 0; p < 8; ++p) u[p] = L.v[k][8 * nd + p];
+#pragma unroll
+            for (int p = 0; p < 8; ++p) {
+                if (p < n8) {
+                    if (k < 4) a = a + u[p];
+                    else if (k < 7) a = u[p] < a ? u[p] : a;
+                    else a = u[p] > a ? u[p] : a;
+                }
+            }
+            if (on && leaf) {
+                for (int p = 8; p < nsub; ++p) {
+                    const int j = rg.x + p;
+                    if (k == 0) {
+                        a = a + m[j];
+                    } else {
+                        const int d = k < 4 ? k - 1 : (k < 7 ? k - 4 : k - 7);
+                        const double w = d == 0 ? x[j] : (d == 1 ? y[j] : z[j]);
+                        if (k < 4) a = a + m[j] * w;
+                        else if (k < 7) a = w < a ? w : a;
+                        else a = w > a ? w : a;
+                    }
+                }
+            }
+            L.r[k][nd] = a;
+        }
+    }
+    lds_order();
+    const double Ms = L.r[0][nd];
+    if (g >= 1 && g < 4) {
+        const double s = L.r[g][nd];
+        L.r[g][nd] = Ms > 0.0 ? s / Ms : (L.r[3 + g][nd] + L.r[6 + g][nd]) * 0.5;
+    }
+    lds_order();
+    const double com[3] = {L.r[1][nd], L.r[2][nd], L.r[3][nd]};
+    {
+        const double dx = c[0] - com[0], dy = c[1] - com[1], dz = c[2] - com[2];
+        const double r2 = dx * dx + dy * dy + dz * dz;
+        L.v[0][lane] = mq.qxx + M * (3.0 * dx * dx - r2);
+        L.v[1][lane] = mq.qyy + M * (3.0 * dy * dy - r2);
+        L.v[2][lane] = mq.qzz + M * (3.0 * dz * dz - r2);
+        L.v[3][lane] = mq.qxy + M * (3.0 * dx * dy);
+        L.v[4][lane] = mq.qxz + M * (3.0 * dx * dz);
+        L.v[5][lane] = mq.qyz + M * (3.0 * dy * dz);
+    }
+    lds_order();
+    if (g < 6) {
+        double a = 0.0;
+        double u[8];
+#pragma unroll
+        for (int p = 0; p < 8; ++p) u[p] = L.v[g][8 * nd + p];
+#pragma unroll
+        for (int p = 0; p < 8; ++p)
+            if (p < n8) a = a + u[p];
+        if (on && leaf) {
+            for (int p = 8; p < nsub; ++p) {
+                const int j = rg.x + p;
+                const double dx = x[j] - com[0], dy = y[j] - com[1], dz = z[j] - com[2];
+                const double r2 = dx * dx + dy * dy + dz * dz, mj = m[j];
+                const double e = g == 0 ? 3.0 * dx * dx - r2 : g == 1 ? 3.0 * dy * dy - r2 : g == 2 ? 3.0 * dz * dz - r2
+                                 : g == 3 ? 3.0 * dx * dy : g == 4 ? 3.0 * dx * dz : 3.0 * dy * dz;
+                a = a + (0.0 + mj * e);
             }
         }
+        L.q[g][nd] = a;
     }
-    if (M > 0.0) {
-        o.com[0] = sx / M; o.com[1] = sy / M; o.com[2] = sz / M;
-    } else {
-        for (int d = 0; d < 3; ++d) o.com[d] = (o.lo[d] + o.hi[d]) * 0.5;
-    }
-    o.M = M;
-    double qc[6][kMomFast];
-#pragma unroll
-    for (int k = 0; k < kMomFast; ++k) {
-        const int u = k < nsub ? k : nsub - 1;
-        if (leaf) {
-            for (int e = 0; e < 6; ++e) qc[e][k] = 0.0;
-        } else {
-            const Mom64 mc = q64.load(w.first_child + u);
-            qc[0][k] = mc.qxx; qc[1][k] = mc.qyy; qc[2][k] = mc.qzz;
-            qc[3][k] = mc.qxy; qc[4][k] = mc.qxz; qc[5][k] = mc.qyz;
+    lds_order();
+    if (on) {   // the pieces of the results, a plane or two a lane
+        auto R = [&](int k) { return L.r[k][nd]; };
+        auto Q = [&](int k) { return L.q[k][nd]; };
+        switch (g) {
+            case 0: node.plane(0)[b] = make_double2(R(4), R(5)); break;
+            case 1: node.plane(1)[b] = make_double2(R(6), R(7)); break;
+            case 2: node.plane(2)[b] = make_double2(R(8), R(9)); break;
+            case 3:
+                node.plane(3)[b] = make_double2(R(1), R(2));
+                reinterpret_cast<double*>(node.plane(4) + b)[0] = R(3);
+                break;
+            case 4: q64.p[b] = make_double2(R(0), Q(0)); break;
+            case 5: q64.p[q64.cap + b] = make_double2(Q(1), Q(2)); break;
+            case 6:
+                q64.p[2 * q64.cap + b] = make_double2(Q(3), Q(4));
+                q64.p[3 * q64.cap + b] = make_double2(Q(5), 0.0);
+                break;
+            default:
+                q32.p[b] = make_float4((float)R(0), (float)Q(0), (float)Q(1), (float)Q(2));
+                q32.p[q32.cap + b] = make_float4((float)Q(3), (float)Q(4), (float)Q(5), 0.0f);
         }
     }
-    double q[6] = {0, 0, 0, 0, 0, 0};
-#pragma unroll
-    for (int k = 0; k < kMomFast; ++k) {
-        if (k < nsub) {
-            const double dx = cu[0][k] - o.com[0], dy = cu[1][k] - o.com[1], dz = cu[2][k] - o.com[2];
-            const double r2 = dx * dx + dy * dy + dz * dz;
-            q[0] = q[0] + (qc[0][k] + mu[k] * (3.0 * dx * dx - r2));
-            q[1] = q[1] + (qc[1][k] + mu[k] * (3.0 * dy * dy - r2));
-            q[2] = q[2] + (qc[2][k] + mu[k] * (3.0 * dz * dz - r2));
-            q[3] = q[3] + (qc[3][k] + mu[k] * (3.0 * dx * dy));
-            q[4] = q[4] + (qc[4][k] + mu[k] * (3.0 * dx * dz));
-            q[5] = q[5] + (qc[5][k] + mu[k] * (3.0 * dy * dz));
-        }
-    }
-    for (int e = 0; e < 6; ++e) o.q[e] = q[e];
+    lds_order();
 }
 
-__device__ inline void moments_loop(const WNode& w, bool leaf, int nsub, const double* __restrict__ x,
-                                    const double* __restrict__ y, const double* __restrict__ z,
-                                    const double* __restrict__ m, NodePlanes node, Mom64Planes q64, MomOut& o) {
-#pragma clang fp contract(off)
-    double M = 0.0, sx = 0.0, sy = 0.0, sz = 0.0;
-    for (int u = 0; u < nsub; ++u) {
-        double mu, cu[3], lu[3], hu[3];
-        if (leaf) {
-            const int j = w.begin + u;
-            mu = m[j]; cu[0] = x[j]; cu[1] = y[j]; cu[2] = z[j];
-            for (int k = 0; k < 3; ++k) { lu[k] = cu[k]; hu[k] = cu[k]; }
-        } else {
-            const int c = w.first_child + u;
-            mu = q64.mass(c);
-            node.com(c, cu);
-            node.box(c, lu, hu);
-        }
-        M = M + mu;
-        sx = sx + mu * cu[0];
-        sy = sy + mu * cu[1];
-        sz = sz + mu * cu[2];
-        for (int k = 0; k < 3; ++k) {
-            if (u == 0 || lu[k] < o.lo[k]) o.lo[k] = lu[k];
-            if (u == 0 || hu[k] > o.hi[k]) o.hi[k] = hu[k];
-        }
+// A node's children start inside it, so the nodes that lie inside one tile of
+// kMomTiles topology tiles (1024 particles) depend on no other tile: a workgroup
+// takes them level by level, with barriers for launches.
+constexpr int kMomTiles = 4;
+constexpr int kMomT = 512;
+__global__ __launch_bounds__(kMomT) void k_moments_tile(int64_t n, int D, int64_t ntile, int64_t cap,
+                                                        const int32_t* __restrict__ table,
+                                                        const double* __restrict__ x, const double* __restrict__ y,
+                                                        const double* __restrict__ z, const double* __restrict__ m,
+                                                        NodePlanes node, Mom64Planes q64, Mom32Planes q32) {
+    __shared__ MomLds s_m[kMomT / 64];
+    __shared__ int s_off[64];
+    __shared__ int s_b[kMaxLevels + 1][2];
+    const int t = threadIdx.x;
+    if (t < 64) level_offsets(table, ntile, D, cap, s_off);
+    __syncthreads();
+    if (s_off[D + 1] == 0) return;
+    const int64_t a = (int64_t)blockIdx.x * kMomTiles, e = a + kMomTiles < ntile ? a + kMomTiles : ntile;
+    if (t <= D) {
+        s_b[t][0] = s_off[t] + table[(int64_t)t * (ntile + 1) + a];
+        s_b[t][1] = s_off[t] + table[(int64_t)t * (ntile + 1) + e];
     }
-    if (M > 0.0) {
-        o.com[0] = sx / M; o.com[1] = sy / M; o.com[2] = sz / M;
-    } else {
-        for (int k = 0; k < 3; ++k) o.com[k] = (o.lo[k] + o.hi[k]) * 0.5;
-    }
-    o.M = M;
-    double q[6] = {0, 0, 0, 0, 0, 0};
-    for (int u = 0; u < nsub; ++u) {
-        double mu, cu[3], qc[6];
-        if (leaf) {
-            const int j = w.begin + u;
-            mu = m[j]; cu[0] = x[j]; cu[1] = y[j]; cu[2] = z[j];
-            for (int e = 0; e < 6; ++e) qc[e] = 0.0;
-        } else {
-            const int c = w.first_child + u;
-            const Mom64 mc = q64.load(c);
-            mu = mc.M;
-            node.com(c, cu);
-            qc[0] = mc.qxx; qc[1] = mc.qyy; qc[2] = mc.qzz;
-            qc[3] = mc.qxy; qc[4] = mc.qxz; qc[5] = mc.qyz;
+    __syncthreads();
+    const int64_t pend = e * kTopoT < n ? e * kTopoT : n;
+    for (int l = D; l >= 0; --l) {
+        const int b0 = s_b[l][0], b1 = s_b[l][1];
+        if (b0 == b1) continue;   // workgroup-uniform
+        const int kids_end = s_off[l + 2 <= D + 1 ? l + 2 : D + 1];
+        for (int w0 = b0 + (t >> 6) * 8; w0 < b1; w0 += kMomT / 8) {   // 8 nodes a wave
+            const int b = w0 + ((t & 63) >> 3);
+            const int4 rg = node.range(b < b1 ? b : b1 - 1);
+            const bool on = b < b1 && (int64_t)rg.x + rg.y <= pend;
+            moments_group(s_m[t >> 6], on, b, rg, kids_end, x, y, z, m, node, q64, q32);
         }
-        const double dx = cu[0] - o.com[0], dy = cu[1] - o.com[1], dz = cu[2] - o.com[2];
-        const double r2 = dx * dx + dy * dy + dz * dz;
-        q[0] = q[0] + (qc[0] + mu * (3.0 * dx * dx - r2));
-        q[1] = q[1] + (qc[1] + mu * (3.0 * dy * dy - r2));
-        q[2] = q[2] + (qc[2] + mu * (3.0 * dz * dz - r2));
-        q[3] = q[3] + (qc[3] + mu * (3.0 * dx * dy));
-        q[4] = q[4] + (qc[4] + mu * (3.0 * dx * dz));
-        q[5] = q[5] + (qc[5] + mu * (3.0 * dy * dz));
+        __syncthreads();
     }
-    for (int e = 0; e < 6; ++e) o.q[e] = q[e];
 }
 
-__device__ inline void moments_node(int64_t b, const double* __restrict__ x, const double* __restrict__ y,
-                                    const double* __restrict__ z, const double* __restrict__ m,
-                                    NodePlanes node, Mom64Planes q64, Mom32Planes q32) {
-    WNode w;
-    const int4 rg = node.range(b);
-    w.begin = rg.x; w.count = rg.y; w.first_child = rg.z; w.nchild = rg.w;
-    const bool leaf = w.nchild == 0;
-    const int nsub = leaf ? w.count : w.nchild;
-    MomOut o;
-    if (nsub <= kMomFast) moments_small(w, leaf, nsub, x, y, z, m, node, q64, o);
-    else moments_loop(w, leaf, nsub, x, y, z, m, node, q64, o);
-    node.set_geometry(b, o.lo, o.hi, o.com);
-    Mom64 r;
-    r.M = o.M; r.qxx = o.q[0]; r.qyy = o.q[1]; r.qzz = o.q[2]; r.qxy = o.q[3]; r.qxz = o.q[4];
-    r.qyz = o.q[5];
-    r.pad = 0.0;
-    q64.store(b, r);
-    Mom32 f;
-    f.M = (float)o.M; f.qxx = (float)o.q[0]; f.qyy = (float)o.q[1]; f.qzz = (float)o.q[2];
-    f.qxy = (float)o.q[3]; f.qxz = (float)o.q[4]; f.qyz = (float)o.q[5]; f.pad = 0.0f;
-    q32.store(b, f);
-}
-
-__global__ __launch_bounds__(kMomT) void k_moments_level(const int32_t* __restrict__ lvl_off, int level,
-                                const double* __restrict__ x, const double* __restrict__ y,
-                                const double* __restrict__ z, const double* __restrict__ m,
-                                NodePlanes node, Mom64Planes q64, Mom32Planes q32) {
-    const int64_t b0 = lvl_off[level], b1 = lvl_off[level + 1];
-    for (int64_t b = b0 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < b1;
-         b += (int64_t)gridDim.x * blockDim.x)
-        moments_node(b, x, y, z, m, node, q64, q32);
-}
-
-// one workgroup, levels l_hi down to l_lo in order (a barrier between levels)
-__global__ __launch_bounds__(kMomT) void k_moments_levels(const int32_t* __restrict__ lvl_off, int l_hi,
-                                 int l_lo, const double* __restrict__ x,
-                                 const double* __restrict__ y, const double* __restrict__ z,
-                                 const double* __restrict__ m, NodePlanes node,
-                                 Mom64Planes q64, Mom32Planes q32) {
-    for (int l = l_hi; l >= l_lo; --l) {
-        const int64_t b0 = lvl_off[l], b1 = lvl_off[l + 1];
-        for (int64_t b = b0 + threadIdx.x; b < b1; b += blockDim.x)
-            moments_node(b, x, y, z, m, node, q64, q32);
+// The nodes that reach beyond a unit of `inner` topology tiles but not beyond
+// one of `outer`: of a level, only the last node that starts in a unit can reach
+// beyond it. One workgroup per outer unit, eight lanes per inner unit, level by
+// level; levels without such nodes are skipped.
+constexpr int kStradT = 512;
+constexpr int kStradU = kStradT / 8;   // inner units at a time
+__global__ __launch_bounds__(kStradT) void k_moments_straddle(int64_t n, int D, int64_t ntile, int64_t cap,
+                                                              int64_t inner, int64_t outer,
+                                                              const int32_t* __restrict__ table,
+                                                              const double* __restrict__ x,
+                                                              const double* __restrict__ y,
+                                                              const double* __restrict__ z,
+                                                              const double* __restrict__ m, NodePlanes node,
+                                                              Mom64Planes q64, Mom32Planes q32) {
+    __shared__ MomLds s_m[kStradT / 64];
+    __shared__ int s_off[64];
+    __shared__ unsigned s_levels;   // levels at which some unit has such a node
+    const int t = threadIdx.x, g = t & 7;
+    if (t < 64) level_offsets(table, ntile, D, cap, s_off);
+    if (t == 0) s_levels = 0u;
+    __syncthreads();
+    if (s_off[D + 1] == 0) return;
+    const int64_t o0 = (int64_t)blockIdx.x * outer, o1 = o0 + outer < ntile ? o0 + outer : ntile;
+    const int64_t oend = o1 * kTopoT < n ? o1 * kTopoT : n;
+    const int64_t units = (o1 - o0 + inner - 1) / inner;
+    // the last node of level l that starts in unit u and its range; -1 unless it
+    // reaches out of the unit and not out of the outer one
+    auto candidate = [&](int64_t u, int l, int4& rg) -> int {
+        const int64_t a = o0 + u * inner, e = a + inner < o1 ? a + inner : o1;
+        const int c0 = table[(int64_t)l * (ntile + 1) + a], c1 = table[(int64_t)l * (ntile + 1) + e];
+        if (c1 == c0) return -1;
+        const int b = s_off[l] + c1 - 1;
+        rg = node.range(b);
+        const int64_t end = (int64_t)rg.x + rg.y;
+        return end > e * kTopoT && end <= oend ? b : -1;
+    };
+    for (int64_t u = t >> 3; u < units; u += kStradU) {   // a lane group's levels, 8 at a time
+        unsigned mask = 0;
+        int4 rg;
+        for (int l = g; l <= D; l += 8) mask |= candidate(u, l, rg) >= 0 ? 1u << l : 0u;
+        if (mask) atomicOr(&s_levels, mask);
+    }
+    __syncthreads();
+    unsigned levels = s_levels;
+    while (levels) {
+        const int l = 31 - __clz(levels);
+        levels &= ~(1u << l);
+        const int kids_end = s_off[l + 2 <= D + 1 ? l + 2 : D + 1];
+        for (int64_t u0 = (t >> 6) * 8; u0 < units; u0 += kStradU) {
+            const int64_t u = u0 + ((t & 63) >> 3);
+            int4 rg = make_int4(0, 0, -1, 0);
+            const int b = u < units ? candidate(u, l, rg) : -1;
+            if (__ballot(b >= 0))
+                moments_group(s_m[t >> 6], b >= 0, b, rg, kids_end, x, y, z, m, node, q64, q32);
+        }
         __syncthreads();
     }
 }
@@ -575,24 +707,28 @@ __device__ inline int octave_index(double x) {
 // emit one group: first pass -> octave histogram of its box size; second
 // pass -> flag its first particle and store its length
 template <bool HIST>
-__device__ inline void emit_group(int begin, int count, double ext, unsigned* hist, int32_t* flag,
-                                  int32_t* len) {
+__device__ inline void emit_group(int begin, int count, const double* lo, const double* hi, unsigned* hist,
+                                  int32_t* flag, int32_t* len, double* box) {
     if (HIST) {
-        atomicAdd(&hist[octave_index(ext)], 1u);
+        atomicAdd(&hist[octave_index(box_extent(lo, hi))], 1u);
     } else {
         flag[begin] = 1;
         len[begin] = count;
+        for (int k = 0; k < 3; ++k) {
+            box[6 * (int64_t)begin + k] = lo[k];
+            box[6 * (int64_t)begin + 3 + k] = hi[k];
+        }
     }
 }
 
 template <bool HIST>
-__global__ __launch_bounds__(256) void k_group_pass(NodePlanes node, const uint64_t* __restrict__ lvl,
+__global__ __launch_bounds__(256) void k_group_pass(NodePlanes node,
                              const unsigned long long* __restrict__ n_dev,
                              const uint64_t* __restrict__ keys, int D, int n_crit,
                              const double* __restrict__ x, const double* __restrict__ y,
                              const double* __restrict__ z, const double* __restrict__ cl_S,
                              unsigned* __restrict__ hist, int nc, int reps, int32_t* __restrict__ flag,
-                             int32_t* __restrict__ len) {
+                             int32_t* __restrict__ len, double* __restrict__ box) {
     const int64_t nn = (int64_t)*n_dev;
     for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < nn;
          b += (int64_t)gridDim.x * blockDim.x) {
@@ -605,11 +741,14 @@ __global__ __launch_bounds__(256) void k_group_pass(NodePlanes node, const uint6
         unsigned* h = hist + ((int64_t)(b % reps) * nc + c) * kOctaves;
         const double ext = box_extent(w.lo, w.hi);
         const bool big = w.count > n_crit || ext > S;
-        if (lvl[b] == 0 && !big) emit_group<HIST>(w.begin, w.count, ext, h, flag, len);
+        if (b < nc && !big) emit_group<HIST>(w.begin, w.count, w.lo, w.hi, h, flag, len, box);
         if (!big) continue;
         if (w.nchild == 0) {
             if (ext > S) {
-                for (int j = w.begin; j < w.begin + w.count; ++j) emit_group<HIST>(j, 1, 0.0, h, flag, len);
+                for (int j = w.begin; j < w.begin + w.count; ++j) {
+                    const double v[3] = {x[j], y[j], z[j]};
+                    emit_group<HIST>(j, 1, v, v, h, flag, len, box);
+                }
             } else {
                 for (int s0 = w.begin; s0 < w.begin + w.count; s0 += n_crit) {
                     const int e0 = min(s0 + n_crit, w.begin + w.count);
@@ -621,7 +760,7 @@ __global__ __launch_bounds__(256) void k_group_pass(NodePlanes node, const uint6
                             if (j == s0 || v[k] > hi[k]) hi[k] = v[k];
                         }
                     }
-                    emit_group<HIST>(s0, e0 - s0, box_extent(lo, hi), h, flag, len);
+                    emit_group<HIST>(s0, e0 - s0, lo, hi, h, flag, len, box);
                 }
             }
             continue;
@@ -650,7 +789,7 @@ __global__ __launch_bounds__(256) void k_group_pass(NodePlanes node, const uint6
             const double chi[3] = {ahi[u][0], ahi[u][1], ahi[u][2]};
             const int cc = acnt[u];
             if (cc > n_crit || box_extent(clo, chi) > S) {
-                if (run_count > 0) emit_group<HIST>(run_begin, run_count, box_extent(rlo, rhi), h, flag, len);
+                if (run_count > 0) emit_group<HIST>(run_begin, run_count, rlo, rhi, h, flag, len, box);
                 run_count = 0;
                 continue;
             }
@@ -660,7 +799,7 @@ __global__ __launch_bounds__(256) void k_group_pass(NodePlanes node, const uint6
                 uhi[k] = (run_count > 0 && rhi[k] > chi[k]) ? rhi[k] : chi[k];
             }
             if (run_count > 0 && (run_count + cc > n_crit || box_extent(ulo, uhi) > S)) {
-                emit_group<HIST>(run_begin, run_count, box_extent(rlo, rhi), h, flag, len);
+                emit_group<HIST>(run_begin, run_count, rlo, rhi, h, flag, len, box);
                 run_count = 0;
                 for (int k = 0; k < 3; ++k) { ulo[k] = clo[k]; uhi[k] = chi[k]; }
             }
@@ -668,7 +807,7 @@ __global__ __launch_bounds__(256) void k_group_pass(NodePlanes node, const uint6
             run_count += cc;
             for (int k = 0; k < 3; ++k) { rlo[k] = ulo[k]; rhi[k] = uhi[k]; }
         }
-        if (run_count > 0) emit_group<HIST>(run_begin, run_count, box_extent(rlo, rhi), h, flag, len);
+        if (run_count > 0) emit_group<HIST>(run_begin, run_count, rlo, rhi, h, flag, len, box);
     }
 }
 
@@ -712,58 +851,90 @@ __global__ __launch_bounds__(kLimitT) void k_group_limit(const unsigned* __restr
     else if (i == 0 && need == 0) cl_S[c] = ldexp(1.0, -64 + kGroupLimitLog2);
 }
 
-__global__ void k_fill_u32(unsigned* __restrict__ p, int64_t n) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = 0u;
-}
+// Groups in particle order: the flags of a tile of kGrpT * kGrpI particles are
+// counted, then (second launch) ranked, behind the counts of the tiles before,
+// and every group found is copied to its place. Level-0 nodes are the clusters'
+// roots in cluster order. Block 0 hands the build's error
+// bits to the host.
+constexpr int kGrpT = 256;
+constexpr int kGrpI = 4;
+constexpr int kGrpTile = kGrpT * kGrpI;
 
-__global__ void k_group_fill(const int32_t* __restrict__ gid, const int32_t* __restrict__ len,
-                             const uint64_t* __restrict__ keys, const int64_t* __restrict__ cl_off,
-                             int64_t n, int D, const int32_t* __restrict__ p_base,
-                             const int32_t* __restrict__ pre2bfs, GroupArrays g,
-                             unsigned long long* __restrict__ cnt) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        if (gid[i + 1] == gid[i]) continue;   // not the first particle of a group
-        const int32_t k = gid[i];
-        const int c = cluster_of(keys[i], D);
-        g.begin[k] = (int32_t)i;
-        g.count[k] = len[i];
-        g.cluster[k] = c;
-        g.root[k] = pre2bfs[p_base[cl_off[c]]];   // level-0 node started by the cluster's first particle
+__global__ __launch_bounds__(kGrpT) void k_group_count(const int32_t* __restrict__ flag, int64_t n,
+                                                       int32_t* __restrict__ tmp) {
+    __shared__ int s_w[kGrpT / 64];
+    const int64_t base = (int64_t)blockIdx.x * kGrpTile;
+    int c = 0;
+#pragma unroll
+    for (int k = 0; k < kGrpI; ++k) {
+        const int64_t i = base + k * kGrpT + threadIdx.x;
+        c += __popcll(__ballot(i < n && flag[i] != 0));
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) cnt[kCntGroups] = (unsigned long long)gid[n];
+    if ((threadIdx.x & 63) == 0) s_w[threadIdx.x >> 6] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int v = 0;
+        for (int q = 0; q < kGrpT / 64; ++q) v += s_w[q];
+        tmp[blockIdx.x] = v;
+    }
 }
 
-// One wave per group (persistent over the device-side group count): tight box.
-__global__ __launch_bounds__(64) void k_group_box(const unsigned long long* __restrict__ g_dev,
-                                                  const double* __restrict__ x,
-                                                  const double* __restrict__ y,
-                                                  const double* __restrict__ z, GroupArrays g) {
-    const int64_t G = (int64_t)*g_dev;
-    const int lane = threadIdx.x;
-    for (int64_t gi = blockIdx.x; gi < G; gi += gridDim.x) {
-        const int b = g.begin[gi];
-        const int cntg = g.count[gi];
-        double v[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
-        for (int k = lane; k < cntg; k += 64) {
-            const double p[3] = {x[b + k], y[b + k], z[b + k]};
-            for (int d = 0; d < 3; ++d) {
-                v[d] = fmin(v[d], p[d]);
-                v[3 + d] = fmax(v[3 + d], p[d]);
-            }
+__global__ __launch_bounds__(kGrpT) void k_group_fill(const int32_t* __restrict__ flag,
+                                                      const int32_t* __restrict__ len, int64_t n,
+                                                      const int32_t* __restrict__ tmp, int64_t nb,
+                                                      const uint64_t* __restrict__ keys, int D,
+                                                      const double* __restrict__ box, GroupArrays g,
+                                                      unsigned long long* __restrict__ cnt,
+                                                      unsigned long long* __restrict__ host_err) {
+    __shared__ int s_w[kGrpT / 64];
+    __shared__ int s_first[kGrpTile];   // the tile's groups: first particle in the tile
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    int part = 0;
+    for (int64_t k = t; k < (int64_t)blockIdx.x; k += kGrpT) part += tmp[k];
+    for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o, 64);
+    if (lane == 0) s_w[w] = part;
+    __syncthreads();
+    int off = 0;
+    for (int q = 0; q < kGrpT / 64; ++q) off += s_w[q];
+    __syncthreads();
+    // a wave holds kGrpI * 64 consecutive particles
+    const int64_t base = (int64_t)blockIdx.x * kGrpTile;
+    const int p0 = w * (kGrpI * 64) + lane;
+    uint64_t ball[kGrpI];
+    int c = 0;
+#pragma unroll
+    for (int k = 0; k < kGrpI; ++k) {
+        const int64_t i = base + p0 + 64 * k;
+        ball[k] = __ballot(i < n && flag[i] != 0);
+        c += __popcll(ball[k]);
+    }
+    if (lane == 0) s_w[w] = c;
+    __syncthreads();
+    int at = 0, total = 0;
+    for (int q = 0; q < kGrpT / 64; ++q) {
+        at += q < w ? s_w[q] : 0;
+        total += s_w[q];
+    }
+#pragma unroll
+    for (int k = 0; k < kGrpI; ++k) {
+        if ((ball[k] >> lane) & 1ull) s_first[at + popc_below(ball[k])] = p0 + 64 * k;
+        at += __popcll(ball[k]);
+    }
+    __syncthreads();
+    if ((int64_t)blockIdx.x == nb - 1 && t == 0) cnt[kCntGroups] = (unsigned long long)(off + total);
+    if (blockIdx.x == 0 && t == 0) *host_err = cnt[kErr];   // (every kernel that sets a bit is done)
+    for (int q = t; q < total; q += kGrpT) {
+        const int64_t b = base + s_first[q];
+        const int64_t gi = (int64_t)off + q;
+        const int c = cluster_of(keys[b], D);
+        for (int k = 0; k < 3; ++k) {
+            g.lo[3 * gi + k] = box[6 * b + k];
+            g.hi[3 * gi + k] = box[6 * b + 3 + k];
         }
-        for (int o = 32; o > 0; o >>= 1) {
-            for (int d = 0; d < 3; ++d) {
-                v[d] = fmin(v[d], __shfl_xor(v[d], o, 64));
-                v[3 + d] = fmax(v[3 + d], __shfl_xor(v[3 + d], o, 64));
-            }
-        }
-        if (lane < 3) {
-            g.lo[3 * gi + lane] = lane == 0 ? v[0] : (lane == 1 ? v[1] : v[2]);
-            g.hi[3 * gi + lane] = lane == 0 ? v[3] : (lane == 1 ? v[4] : v[5]);
-        }
+        g.begin[gi] = (int32_t)b;
+        g.count[gi] = len[b];
+        g.cluster[gi] = c;
+        g.root[gi] = c;
     }
 }
 
@@ -778,103 +949,76 @@ inline int grid_for(int64_t n, int threads, int maxb = 4096) {
 
 void launch_bbox(Dev& d, const BuildCfg& c, const double* pos, const double* mass, int nblk,
                  hipStream_t s) {
+    (void)c;
     hipLaunchKernelGGL(k_bbox_part, dim3(nblk), dim3(BB_T), 0, s, pos, mass,
-                       (const int64_t*)d.blk_range, d.blk_part, d.blk_bad);
-    // d.blk_cluster is followed by the per-cluster block offsets (see host setup)
-    const int32_t* cblk = d.blk_cluster + nblk;
-    hipLaunchKernelGGL(k_bbox_final, dim3(c.n_clusters), dim3(BB_T), 0, s,
-                       (const double*)d.blk_part, (const int32_t*)d.blk_bad, cblk, c.n_clusters,
-                       d.cl_box, d.cnt);
+                       (const int64_t*)d.blk_range, d.blk_part, d.blk_bad, d.cnt);
 }
 
 void launch_keys(Dev& d, const BuildCfg& c, const double* pos, int nblk, hipStream_t s) {
+    // d.blk_cluster is followed by the per-cluster block offsets (see host setup)
     hipLaunchKernelGGL(k_keys, dim3(nblk), dim3(BB_T), 0, s, pos, (const int64_t*)d.blk_range,
-                       (const int32_t*)d.blk_cluster, (const double*)d.cl_box, c.D,
-                       sort_iota_in_alt(c.n) ? d.keys_alt : d.keys);
+                       (const int32_t*)d.blk_cluster, (const int32_t*)(d.blk_cluster + nblk),
+                       (const double*)d.blk_part, (const int32_t*)d.blk_bad, c.D,
+                       sort_iota_in_alt(c.n) ? d.keys_alt : d.keys, d.cnt);
 }
 
 void launch_key_sort(Dev& d, const BuildCfg& c, hipStream_t s) {
     sort_iota(d.keys, d.perm, d.keys_alt, d.vals_alt, c.n, 3 * c.D + c.cbits, d.rs_hist, d.scan_tmp, d.sort_tmp, s);
 }
 
-void launch_gather(Dev& d, const BuildCfg& c, const double* pos, const double* mass, hipStream_t s) {
-    hipLaunchKernelGGL(k_gather, dim3(grid_for(c.n, 256)), dim3(256), 0, s, pos, mass,
-                       (const int32_t*)d.perm, c.n, d.x, d.y, d.z, d.m);
-}
+int64_t topo_table_need(int64_t n) { return (kMaxLevels + 1) * ((n + kTopoT - 1) / kTopoT + 1); }
 
-void launch_topology(Dev& d, const BuildCfg& c, hipStream_t s) {
-    const int64_t n = c.n;
-    const int64_t cap = c.node_cap;
-    hipLaunchKernelGGL(k_topo_count, dim3(grid_for(n, 256)), dim3(256), 0, s,
-                       (const uint64_t*)d.keys, (const int64_t*)d.cl_off, n, c.D, c.n_leaf,
-                       d.p_first, d.p_nn);
-    exclusive_scan_i32(d.p_nn, d.p_nn, n, d.scan_tmp, s);   // p_nn[n] = node count
-    const int32_t* n_nodes = d.p_nn + n;
-    hipLaunchKernelGGL(k_zero_i32, dim3(grid_for(cap, 256)), dim3(256), 0, s, d.pre_nchild,
-                       n_nodes, cap);
-    hipLaunchKernelGGL(k_topo_emit, dim3(grid_for(n, 256)), dim3(256), 0, s,
-                       (const uint64_t*)d.keys, (const int64_t*)d.cl_off, n, c.D, c.n_leaf,
-                       (const int32_t*)d.p_first, (const int32_t*)d.p_nn, cap, d.pre_begin,
-                       d.pre_count, d.pre_level, d.pre_nchild, d.lvl_key_alt, d.cnt);
-    // breadth-first order: stable sort of pre-order nodes by level (one 8-bit
-    // pass, from lvl_key_alt into (lvl_key, bfs2pre))
-    radix_sort_pairs(d.lvl_key_alt, d.lvl_val, d.lvl_key, d.bfs2pre, cap, 8, d.rs_hist, d.scan_tmp,
-                     s, true, n_nodes, true);
-    hipLaunchKernelGGL(k_level_offsets, dim3(1), dim3(64), 0, s, (const uint64_t*)d.lvl_key,
-                       n_nodes, cap, d.lvl_off, d.cnt);
-    hipLaunchKernelGGL(k_invert, dim3(grid_for(cap, 256)), dim3(256), 0, s,
-                       (const int32_t*)d.bfs2pre, n_nodes, cap, d.pre2bfs);
-    hipLaunchKernelGGL(k_nodes_init, dim3(grid_for(cap, 256, 1024)), dim3(256), 0, s,
-                       (const int32_t*)d.bfs2pre, (const int32_t*)d.pre2bfs, n_nodes, cap,
-                       (const int32_t*)d.pre_begin, (const int32_t*)d.pre_count,
-                       (const int32_t*)d.pre_nchild, d.node, d.cnt);
+void launch_topology(Dev& d, const BuildCfg& c, const double* pos, const double* mass, hipStream_t s) {
+    const int64_t ntile = (c.n + kTopoT - 1) / kTopoT;
+    const int64_t hist_len = (int64_t)group_hist_reps(c.n_clusters) * c.n_clusters * kOctaves;
+    hipLaunchKernelGGL(k_topo_count, dim3((unsigned)ntile), dim3(kTopoT), 0, s, (const uint64_t*)d.keys,
+                       (const int64_t*)d.cl_off, c.n, c.D, c.n_leaf, d.p_lv, ntile, d.topo_table, pos, mass,
+                       (const int32_t*)d.perm, d.x, d.y, d.z, d.m, d.g_flag, d.g_hist, hist_len);
+    hipLaunchKernelGGL(k_topo_scan, dim3(c.D + 1), dim3(1024), 0, s, ntile, d.topo_table);
+    hipLaunchKernelGGL(k_topo_emit, dim3((unsigned)ntile), dim3(kTopoT), 0, s, (const uint64_t*)d.keys,
+                       (const int64_t*)d.cl_off, c.n, c.D, c.n_leaf, (const int32_t*)d.p_lv, ntile,
+                       (const int32_t*)d.topo_table, c.node_cap, d.node, d.lvl_off, d.cnt);
 }
 
 void launch_moments(Dev& d, const BuildCfg& c, hipStream_t s) {
-    const int hi = c.mom_hi < c.D ? c.mom_hi : c.D;
-    const int lo = c.mom_lo;
-    if (hi < c.D)
-        hipLaunchKernelGGL(k_moments_levels, dim3(1), dim3(kMomT), 0, s, (const int32_t*)d.lvl_off, c.D,
-                           hi + 1, (const double*)d.x, (const double*)d.y, (const double*)d.z,
-                           (const double*)d.m, d.node, d.q64, d.q32);
-    for (int l = hi; l > lo; --l) {
-        const int grid = c.mom_grid[l] > 0 ? c.mom_grid[l] : grid_for(c.node_cap, kMomT, 2048);
-        hipLaunchKernelGGL(k_moments_level, dim3(grid), dim3(kMomT), 0, s,
-                           (const int32_t*)d.lvl_off, l, (const double*)d.x, (const double*)d.y,
+    const int64_t ntile = (c.n + kTopoT - 1) / kTopoT;
+    hipLaunchKernelGGL(k_moments_tile, dim3((unsigned)((ntile + kMomTiles - 1) / kMomTiles)), dim3(kMomT), 0, s,
+                       c.n, c.D, ntile, c.node_cap, (const int32_t*)d.topo_table, (const double*)d.x,
+                       (const double*)d.y, (const double*)d.z, (const double*)d.m, d.node, d.q64, d.q32);
+    // units of 1024 particles, then of 64 times that; the last launch takes all
+    for (int64_t inner = kMomTiles; inner < ntile; inner *= kStradU) {
+        const int64_t outer = inner * kStradU;
+        const bool all = outer >= ntile || inner > kMomTiles;
+        hipLaunchKernelGGL(k_moments_straddle, dim3(all ? 1u : (unsigned)((ntile + outer - 1) / outer)),
+                           dim3(kStradT), 0, s, c.n, c.D, ntile, c.node_cap, inner, all ? ntile : outer,
+                           (const int32_t*)d.topo_table, (const double*)d.x, (const double*)d.y,
                            (const double*)d.z, (const double*)d.m, d.node, d.q64, d.q32);
+        if (all) break;
     }
-    if (lo >= 0)
-        hipLaunchKernelGGL(k_moments_levels, dim3(1), dim3(kMomT), 0, s, (const int32_t*)d.lvl_off, lo, 0,
-                           (const double*)d.x, (const double*)d.y, (const double*)d.z,
-                           (const double*)d.m, d.node, d.q64, d.q32);
 }
+
+int64_t group_tmp_need(int64_t n) { return (n + kGrpTile - 1) / kGrpTile; }
 
 void launch_groups(Dev& d, const BuildCfg& c, hipStream_t s) {
     const int64_t n = c.n;
     const unsigned long long* n_nodes = d.cnt + kCntNodes;
-    const int gb = grid_for(c.node_cap, 256, 2048);
+    const int gb = grid_for(n, 256, 2048);   // about half as many nodes as particles
     const int reps = group_hist_reps(c.n_clusters);
-    const int64_t hist_len = (int64_t)reps * c.n_clusters * kOctaves;
-    hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(hist_len, 256)), dim3(256), 0, s, d.g_hist, hist_len);
-    hipLaunchKernelGGL(k_group_pass<true>, dim3(gb), dim3(256), 0, s, d.node,
-                       (const uint64_t*)d.lvl_key, n_nodes, (const uint64_t*)d.keys, c.D, c.n_crit,
-                       (const double*)d.x, (const double*)d.y, (const double*)d.z,
-                       (const double*)d.cl_S, d.g_hist, c.n_clusters, reps, d.g_flag, d.g_len);
+    hipLaunchKernelGGL(k_group_pass<true>, dim3(gb), dim3(256), 0, s, d.node, n_nodes,
+                       (const uint64_t*)d.keys, c.D, c.n_crit, (const double*)d.x, (const double*)d.y,
+                       (const double*)d.z, (const double*)d.cl_S, d.g_hist, c.n_clusters, reps, d.g_flag, d.g_len,
+                       d.g_box);
     hipLaunchKernelGGL(k_group_limit, dim3(c.n_clusters), dim3(kLimitT), 0, s,
                        (const unsigned*)d.g_hist, c.n_clusters, reps, d.cl_S);
-    hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(n + 1, 256)), dim3(256), 0, s, d.g_flag, n + 1, 0);
-    hipLaunchKernelGGL(k_group_pass<false>, dim3(gb), dim3(256), 0, s, d.node,
-                       (const uint64_t*)d.lvl_key, n_nodes, (const uint64_t*)d.keys, c.D, c.n_crit,
-                       (const double*)d.x, (const double*)d.y, (const double*)d.z,
-                       (const double*)d.cl_S, d.g_hist, c.n_clusters, reps, d.g_flag, d.g_len);
-    exclusive_scan_i32(d.g_flag, d.g_flag, n, d.scan_tmp, s);   // g_flag[n] = group count
-    hipLaunchKernelGGL(k_group_fill, dim3(grid_for(n, 256)), dim3(256), 0, s,
-                       (const int32_t*)d.g_flag, (const int32_t*)d.g_len, (const uint64_t*)d.keys,
-                       (const int64_t*)d.cl_off, n, c.D, (const int32_t*)d.p_nn,
-                       (const int32_t*)d.pre2bfs, d.g, d.cnt);
-    hipLaunchKernelGGL(k_group_box, dim3(grid_for(n, 64, 32768)), dim3(64), 0, s,
-                       (const unsigned long long*)(d.cnt + kCntGroups), (const double*)d.x,
-                       (const double*)d.y, (const double*)d.z, d.g);
+    hipLaunchKernelGGL(k_group_pass<false>, dim3(gb), dim3(256), 0, s, d.node, n_nodes,
+                       (const uint64_t*)d.keys, c.D, c.n_crit, (const double*)d.x, (const double*)d.y,
+                       (const double*)d.z, (const double*)d.cl_S, d.g_hist, c.n_clusters, reps, d.g_flag, d.g_len,
+                       d.g_box);
+    const int64_t nb = group_tmp_need(n);
+    hipLaunchKernelGGL(k_group_count, dim3((unsigned)nb), dim3(kGrpT), 0, s, (const int32_t*)d.g_flag, n, d.g_tmp);
+    hipLaunchKernelGGL(k_group_fill, dim3((unsigned)nb), dim3(kGrpT), 0, s, (const int32_t*)d.g_flag,
+                       (const int32_t*)d.g_len, n, (const int32_t*)d.g_tmp, nb, (const uint64_t*)d.keys, c.D,
+                       (const double*)d.g_box, d.g, d.cnt, d.host_err);
 }
 
 }  // namespace pbh

@@ -21,7 +21,8 @@ using namespace pbh;
 
 namespace {
 
-constexpr int kBoxChunk = 2048;      // particles per bbox/key block (512 blocks per 2^20)
+// particles per bbox/key block: 256 blocks or more from 2^17 particles on
+constexpr int kBoxChunk = 2048, kBoxChunkMin = 512;
 constexpr int kStackCap = 16384;     // traversal stack entries per persistent wave (LDS + spill)
 constexpr int kCntKdkStep = 11;      // counter slot: KDK energy output index
 constexpr int64_t kIrrPackRatio = 32;  // target lists of >= n/32 use the key-order records
@@ -113,7 +114,7 @@ struct pbh_ctx {
     hipGraph_t graph = nullptr;
     hipGraphExec_t gexec = nullptr;
     // the build's kernel sequence, captured once per (buffers, sizes, parameters)
-    std::vector<int32_t> lvl_count;   // nodes per level of the last build (moment grids)
+    unsigned long long* build_err = nullptr;   // host-coherent pinned: error bits of the last build
     hipGraph_t bgraph = nullptr;
     hipGraphExec_t bexec = nullptr;
     std::vector<double> bkey;
@@ -220,31 +221,26 @@ pbh_status ensure_buffers(pbh_ctx* ctx) {
         return PBH_OK;
     free_all(ctx);
     Dev& d = ctx->d;
-    const int64_t big = std::max(n, cap);
-    const int64_t scan_len = scan_tmp_need(std::max(big, radix_hist_need(big)) + 1);
+    const int64_t scan_len = scan_tmp_need(std::max(n, radix_hist_need(n)) + 1);
     bool ok = dalloc(ctx, &d.x, n) && dalloc(ctx, &d.y, n) && dalloc(ctx, &d.z, n) &&
               dalloc(ctx, &d.m, n) && dalloc(ctx, &d.perm, n) && dalloc(ctx, &d.keys, n) &&
-              dalloc(ctx, &d.keys_alt, n) && dalloc(ctx, &d.vals_alt, big) &&
-              dalloc(ctx, &d.cl_off, C + 1) && dalloc(ctx, &d.cl_box, 6 * C) &&
+              dalloc(ctx, &d.keys_alt, n) && dalloc(ctx, &d.vals_alt, n) &&
+              dalloc(ctx, &d.cl_off, C + 1) &&
               dalloc(ctx, &d.blk_cluster, nblk + C + 1) && dalloc(ctx, &d.blk_range, 2 * nblk) &&
               dalloc(ctx, &d.blk_part, 6 * nblk) && dalloc(ctx, &d.blk_bad, nblk) &&
-              dalloc(ctx, &d.cparams, C) && dalloc(ctx, &d.p_first, n) &&
-              dalloc(ctx, &d.p_nn, n + 1) && dalloc(ctx, &d.pre_begin, cap) &&
-              dalloc(ctx, &d.pre_count, cap) && dalloc(ctx, &d.pre_level, cap) &&
-              dalloc(ctx, &d.pre_nchild, cap) && dalloc(ctx, &d.lvl_key, cap) &&
-              dalloc(ctx, &d.lvl_key_alt, cap) && dalloc(ctx, &d.lvl_val, cap) &&
-              dalloc(ctx, &d.bfs2pre, cap) && dalloc(ctx, &d.pre2bfs, cap) &&
+              dalloc(ctx, &d.cparams, C) && dalloc(ctx, &d.p_lv, n) &&
+              dalloc(ctx, &d.topo_table, topo_table_need(n)) &&
               dalloc(ctx, &d.lvl_off, 32) && dalloc(ctx, &d.node.p, cap * NodePlanes::kPlanes) &&
               dalloc(ctx, &d.q64.p, cap * Mom64Planes::kPlanes) &&
               dalloc(ctx, &d.q32.p, cap * Mom32Planes::kPlanes) &&
-              dalloc(ctx, &d.g_flag, n + 1) && dalloc(ctx, &d.g_len, n) &&
+              dalloc(ctx, &d.g_flag, n) && dalloc(ctx, &d.g_tmp, group_tmp_need(n)) && dalloc(ctx, &d.g_len, n) && dalloc(ctx, &d.g_box, 6 * n) &&
               dalloc(ctx, &d.g_hist, (int64_t)128 * C * group_hist_reps((int)C)) && dalloc(ctx, &d.cl_S, C) &&
               dalloc(ctx, &d.g.begin, G) && dalloc(ctx, &d.g.count, G) &&
               dalloc(ctx, &d.g.root, G) && dalloc(ctx, &d.g.cluster, G) &&
               dalloc(ctx, &d.g.lo, 3 * G) && dalloc(ctx, &d.g.hi, 3 * G) && dalloc(ctx, &d.fill_list, G) &&
               dalloc(ctx, &d.stage_k, n) &&
               dalloc(ctx, &d.scan_tmp, scan_len) &&
-              dalloc(ctx, &d.rs_hist, radix_hist_need(big) + 1) &&
+              dalloc(ctx, &d.rs_hist, radix_hist_need(n) + 1) &&
               dalloc(ctx, &d.sort_tmp, sort_scratch_need(n)) && dalloc(ctx, &d.nbr_cnt, n) &&
               dalloc(ctx, &d.stack, stack) && dalloc(ctx, &d.cnt, kNumCounters + kQueueWords) &&
               dalloc(ctx, (char**)&d.part_sum, (int64_t)kWalkSlots * kWalkSlotBytes) &&
@@ -257,6 +253,7 @@ pbh_status ensure_buffers(pbh_ctx* ctx) {
         return fail(ctx, PBH_E_OOM, "device allocation failed");
     }
     d.queues = d.cnt + kNumCounters;
+    d.host_err = ctx->build_err;
     d.node.cap = d.q64.cap = d.q32.cap = cap;
     d.scan_tmp_len = scan_len;
     d.stack_len = stack;
@@ -316,41 +313,20 @@ pbh_status setup_build(pbh_ctx* ctx, int64_t n, int32_t C, const int64_t* offset
     // n_crit 0: 32 below 2^18 particles (more, smaller groups keep all CUs busy), else 64
     c.n_crit = ctx->params.n_crit ? ctx->params.n_crit : (n < (1 << 18) ? 32 : 64);
     c.node_cap = node_capacity(n, D, c.n_leaf, C);
-    for (int l = 0; l < 32; ++l) {
-        c.mom_grid[l] = 0;
-        if (l < (int)ctx->lvl_count.size()) {
-            // power-of-two bucket of 1.5x the last count (few distinct graphs)
-            const int64_t want = (ctx->lvl_count[l] * 3 / 2 + kMomT - 1) / kMomT;
-            int g = 1;
-            while (g < want && g < 2048) g <<= 1;
-            c.mom_grid[l] = g;
-        }
-    }
-    c.mom_hi = D;
-    c.mom_lo = -1;
-    if (!ctx->lvl_count.empty()) {
-        // deepest level that held nodes, and the top levels that held few
-        int hi = 0;
-        for (int l = 0; l < (int)ctx->lvl_count.size() && l <= D; ++l)
-            if (ctx->lvl_count[l] > 0) hi = l;
-        int lo = -1;
-        while (lo + 1 <= hi && ctx->lvl_count[lo + 1] <= 128) ++lo;   // one node per thread
-        if (lo >= hi) lo = hi - 1;   // at least the deepest non-empty level runs on its own
-        c.mom_hi = hi;
-        c.mom_lo = lo;
-    }
     if (c.node_cap >= (1ll << 31)) return fail(ctx, PBH_E_ARG, "too many particles for int32 node indices");
     ctx->cl_off_h.assign(offsets, offsets + C + 1);
     std::vector<int32_t> blk_cluster;
     std::vector<int64_t> blk_range;
     std::vector<int32_t> cblk(C + 1, 0);
+    int64_t chunk = kBoxChunk;
+    while (chunk > kBoxChunkMin && n < 256 * chunk) chunk >>= 1;
     for (int k = 0; k < C; ++k) {
         const int64_t a = offsets[k], b = offsets[k + 1];
         cblk[k] = (int32_t)blk_cluster.size();
-        for (int64_t q = a; q < b; q += kBoxChunk) {
+        for (int64_t q = a; q < b; q += chunk) {
             blk_cluster.push_back(k);
             blk_range.push_back(q);
-            blk_range.push_back(std::min(b, q + kBoxChunk));
+            blk_range.push_back(std::min(b, q + chunk));
         }
     }
     cblk[C] = (int32_t)blk_cluster.size();
@@ -382,8 +358,8 @@ pbh_status setup_build(pbh_ctx* ctx, int64_t n, int32_t C, const int64_t* offset
 
 void enqueue_build(pbh_ctx* ctx, const double* pos, const double* mass, hipStream_t s);
 
-// The build issues about 90 small kernels; launched one by one, the host's
-// launch rate rather than the GPU sets the build time. The sequence is captured
+// The build is 13 to 20 small kernels; launched one by one, the host's launch
+// rate rather than the GPU would set the build time. The sequence is captured
 // into a graph once per set of buffers, sizes and parameters (the block tables
 // it reads are uploaded before each launch) and replayed.
 pbh_status launch_build(pbh_ctx* ctx, const double* pos, const double* mass, hipStream_t s) {
@@ -392,15 +368,7 @@ pbh_status launch_build(pbh_ctx* ctx, const double* pos, const double* mass, hip
     const std::vector<double> key = {(double)(uintptr_t)pos, (double)(uintptr_t)mass, (double)c.n,
                                      (double)c.n_clusters, (double)c.D, (double)c.cbits,
                                      (double)c.n_leaf, (double)c.n_crit, (double)c.node_cap,
-                                     (double)ctx->nblk_box, (double)ctx->alloc_gen,
-                                     (double)c.mom_grid[0], (double)c.mom_grid[1], (double)c.mom_grid[2],
-                                     (double)c.mom_grid[3], (double)c.mom_grid[4], (double)c.mom_grid[5],
-                                     (double)c.mom_grid[6], (double)c.mom_grid[7], (double)c.mom_grid[8],
-                                     (double)c.mom_grid[9], (double)c.mom_grid[10], (double)c.mom_grid[11],
-                                     (double)c.mom_grid[12], (double)c.mom_grid[13], (double)c.mom_grid[14],
-                                     (double)c.mom_grid[15], (double)c.mom_grid[16], (double)c.mom_grid[17],
-                                     (double)c.mom_grid[18], (double)c.mom_grid[19], (double)c.mom_grid[20],
-                                     (double)c.mom_grid[21], (double)c.mom_hi, (double)c.mom_lo};
+                                     (double)ctx->nblk_box, (double)ctx->alloc_gen};
     if (!ctx->bexec || ctx->bkey != key) {
         if (ctx->bexec) { (void)hipGraphExecDestroy(ctx->bexec); ctx->bexec = nullptr; }
         if (ctx->bgraph) { (void)hipGraphDestroy(ctx->bgraph); ctx->bgraph = nullptr; }
@@ -419,12 +387,10 @@ pbh_status launch_build(pbh_ctx* ctx, const double* pos, const double* mass, hip
 void enqueue_build(pbh_ctx* ctx, const double* pos, const double* mass, hipStream_t s) {
     Dev& d = ctx->d;
     const BuildCfg& c = ctx->cfg;
-    launch_zero_counts(d.cnt, s);   // keeps the KDK slots (>= 11)
     launch_bbox(d, c, pos, mass, ctx->nblk_box, s);
     launch_keys(d, c, pos, ctx->nblk_box, s);
     launch_key_sort(d, c, s);
-    launch_gather(d, c, pos, mass, s);
-    launch_topology(d, c, s);
+    launch_topology(d, c, pos, mass, s);
     launch_moments(d, c, s);
     launch_groups(d, c, s);
 }
@@ -527,19 +493,14 @@ pbh_status check_radii(pbh_ctx* ctx, double r_in, double r_out) {
 }
 
 pbh_status finish_build(pbh_ctx* ctx, hipStream_t s) {
-    unsigned long long h[kNumCounters];
-    int32_t lo[32];
-    HIP_TRY(hipMemcpyAsync(h, ctx->d.cnt, sizeof(h), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(lo, ctx->d.lvl_off, sizeof(lo), hipMemcpyDeviceToHost, s));
+    // the build's last kernel wrote its error bits to pinned memory: no copy to wait for
     HIP_TRY(hipStreamSynchronize(s));
-    const int D = ctx->cfg.D;
-    ctx->lvl_count.assign(D + 1, 0);
-    for (int l = 0; l <= D; ++l) ctx->lvl_count[l] = lo[l + 1] - lo[l];
-    if (h[kErr] & kErrNonFinite) {
+    const unsigned long long err = *(volatile unsigned long long*)ctx->build_err;
+    if (err & kErrNonFinite) {
         ctx->built = false;
         return fail(ctx, PBH_E_NONFINITE, "non-finite position or mass");
     }
-    if (h[kErr] & kErrNodeCap) {
+    if (err & kErrNodeCap) {
         ctx->built = false;
         return fail(ctx, PBH_E_INTERNAL, "node capacity exceeded");
     }
@@ -926,14 +887,20 @@ pbh_status pbh_create(int device, const pbh_params* params, pbh_ctx** out) {
     }
     ctx->device = device;
     if (hipSetDevice(device) != hipSuccess ||
-        hipDeviceGetAttribute(&ctx->cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess ||
+        hipHostMalloc((void**)&ctx->build_err, sizeof(unsigned long long), hipHostMallocCoherent) != hipSuccess) {
+        delete ctx;
+        return PBH_E_HIP;
+    }
+    if (hipDeviceGetAttribute(&ctx->cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess ||
         hipStreamCreateWithFlags(&ctx->cap_stream, hipStreamNonBlocking) != hipSuccess) {
+        (void)hipHostFree(ctx->build_err);
         delete ctx;
         return PBH_E_HIP;
     }
     // the allocation-free entry point's scratch on this device (set up once)
     if (!na_scratch_setup(device)) {
         (void)hipStreamDestroy(ctx->cap_stream);
+        (void)hipHostFree(ctx->build_err);
         delete ctx;
         return PBH_E_HIP;
     }
@@ -954,6 +921,7 @@ void pbh_destroy(pbh_ctx* ctx) {
     if (ctx->k_pot) (void)hipFree(ctx->k_pot);
     if (ctx->k_epart) (void)hipFree(ctx->k_epart);
     if (ctx->irr_err) (void)hipFree(ctx->irr_err);
+    (void)hipHostFree(ctx->build_err);
     for (void* q : ctx->herm.mem) (void)hipFree(q);
     if (ctx->herm.gexec) (void)hipGraphExecDestroy(ctx->herm.gexec);
     if (ctx->herm.graph) (void)hipGraphDestroy(ctx->herm.graph);
@@ -1637,8 +1605,8 @@ pbh_status pbh_debug_tree(pbh_ctx* ctx, int32_t* order, uint64_t* keys, int64_t 
     for (int k = 0; k < Mom64Planes::kPlanes; ++k)
         HIP_TRY(hipMemcpy(q.data() + k * nn, ctx->d.q64.p + k * ctx->d.q64.cap, sizeof(double2) * nn,
                           hipMemcpyDeviceToHost));
-    std::vector<uint64_t> lk(nn);
-    HIP_TRY(hipMemcpy(lk.data(), ctx->d.lvl_key, sizeof(uint64_t) * nn, hipMemcpyDeviceToHost));
+    std::vector<int32_t> lo(kMaxLevels + 1);   // first node of each level
+    HIP_TRY(hipMemcpy(lo.data(), ctx->d.lvl_off, sizeof(int32_t) * lo.size(), hipMemcpyDeviceToHost));
     for (int64_t k = 0; k < nn; ++k) {
         if (nodes_i) {
             int32_t r[4];   // begin, count, first_child, nchild
@@ -1646,7 +1614,7 @@ pbh_status pbh_debug_tree(pbh_ctx* ctx, int32_t* order, uint64_t* keys, int64_t 
             nodes_i[4 * k] = r[0];
             nodes_i[4 * k + 1] = r[1];
             nodes_i[4 * k + 2] = r[3];
-            nodes_i[4 * k + 3] = (int64_t)lk[k];
+            nodes_i[4 * k + 3] = (int64_t)(std::upper_bound(lo.begin(), lo.end(), (int32_t)k) - lo.begin()) - 1;
         }
         if (nodes_d) {
             double* o = nodes_d + 16 * k;

@@ -62,11 +62,6 @@ __global__ void k_zero_u64(unsigned long long* p, int n) {
     if (i < n) p[i] = 0ull;
 }
 
-__global__ __launch_bounds__(256) void k_zero_counts(unsigned long long* cnt) {
-    const int i = blockIdx.x * 256 + threadIdx.x;   // slots 11 .. outlive a build
-    if (i < 11 || (i >= kNumCounters && i < kNumCounters + kQueueWords)) cnt[i] = 0ull;
-}
-
 inline int grid_for(int64_t n) {
     int64_t b = (n + 255) / 256;
     if (b < 1) b = 1;
@@ -114,10 +109,6 @@ void launch_energy(const double* vel, const double* mass, const double* pot, int
 
 void launch_zero_u64(unsigned long long* p, int n, hipStream_t s) {
     hipLaunchKernelGGL(k_zero_u64, dim3((n + 255) / 256), dim3(256), 0, s, p, n);
-}
-
-void launch_zero_counts(unsigned long long* cnt, hipStream_t s) {
-    hipLaunchKernelGGL(k_zero_counts, dim3((kNumCounters + kQueueWords + 255) / 256), dim3(256), 0, s, cnt);
 }
 
 }  // namespace pbh

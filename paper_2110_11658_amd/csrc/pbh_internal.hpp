@@ -89,13 +89,6 @@ struct NodePlanes {
         const double2 a = plane(3)[b];
         c[0] = a.x; c[1] = a.y; c[2] = reinterpret_cast<const double*>(plane(4) + b)[0];
     }
-    __device__ void set_geometry(int64_t b, const double* lo, const double* hi, const double* c) const {
-        plane(0)[b] = make_double2(lo[0], lo[1]);
-        plane(1)[b] = make_double2(lo[2], hi[0]);
-        plane(2)[b] = make_double2(hi[1], hi[2]);
-        plane(3)[b] = make_double2(c[0], c[1]);
-        reinterpret_cast<double*>(plane(4) + b)[0] = c[2];
-    }
     __device__ void set_rcrit2(int64_t b, double v) const { reinterpret_cast<double*>(plane(4) + b)[1] = v; }
     __device__ WNode load(int64_t b) const {
         WNode w;
@@ -115,16 +108,9 @@ struct Mom64Planes {
     double2* p = nullptr;
     int64_t cap = 0;
     static constexpr int kPlanes = 4;
-    __device__ double mass(int64_t b) const { return reinterpret_cast<const double*>(p + b)[0]; }
     __device__ Mom64 load(int64_t b) const {
         const double2 a = p[b], c = p[cap + b], d = p[2 * cap + b], e = p[3 * cap + b];
         return Mom64{a.x, a.y, c.x, c.y, d.x, d.y, e.x, e.y};
-    }
-    __device__ void store(int64_t b, const Mom64& m) const {
-        p[b] = make_double2(m.M, m.qxx);
-        p[cap + b] = make_double2(m.qyy, m.qzz);
-        p[2 * cap + b] = make_double2(m.qxy, m.qxz);
-        p[3 * cap + b] = make_double2(m.qyz, m.pad);
     }
 };
 struct Mom32Planes {
@@ -134,10 +120,6 @@ struct Mom32Planes {
     __device__ Mom32 load(int64_t b) const {
         const float4 a = p[b], c = p[cap + b];
         return Mom32{a.x, a.y, a.z, a.w, c.x, c.y, c.z, c.w};
-    }
-    __device__ void store(int64_t b, const Mom32& m) const {
-        p[b] = make_float4(m.M, m.qxx, m.qyy, m.qzz);
-        p[cap + b] = make_float4(m.qxy, m.qxz, m.qyz, m.pad);
     }
 };
 
@@ -174,14 +156,6 @@ struct BuildCfg {
     int32_t n_crit = 64;
     int64_t node_cap = 0;
     int64_t n_groups = 0;
-    // workgroups of the moment pass per level (0: sized for the node capacity).
-    // Taken from the previous build's level sizes; any size is correct (the
-    // kernel strides), a good guess avoids dispatching thousands of idle groups.
-    int32_t mom_grid[32] = {0};
-    // levels [mom_hi+1, D] and [0, mom_lo] are each done by one workgroup that
-    // walks its levels in order (they held few or no nodes last time);
-    // mom_hi = D and mom_lo = -1 launch every level on its own
-    int32_t mom_hi = 21, mom_lo = -1;
 };
 
 // Scratch and arrays of one built forest.
@@ -221,33 +195,25 @@ struct Dev {
     int32_t* vals_alt = nullptr;
     // clusters
     int64_t* cl_off = nullptr;       // [C+1]
-    double* cl_box = nullptr;        // [C][6] lo xyz, hi xyz
     int32_t* blk_cluster = nullptr;  // bbox/key block table: cluster of block
     int64_t* blk_range = nullptr;    // [nblk][2]
     double* blk_part = nullptr;      // [nblk][6] partial boxes
     int32_t* blk_bad = nullptr;      // [nblk] non-finite flags
     ClusterParams* cparams = nullptr;
-    // topology scratch (pre-order)
-    int32_t* p_first = nullptr;      // [n] first level started at i
-    int32_t* p_nn = nullptr;         // [n+1] nodes started at i, then exclusive scan
-    int32_t* pre_begin = nullptr;    // [cap]
-    int32_t* pre_count = nullptr;
-    int32_t* pre_level = nullptr;
-    int32_t* pre_nchild = nullptr;
-    uint64_t* lvl_key = nullptr;     // [cap] level as a sort key
-    int32_t* lvl_val = nullptr;      // [cap] pre-order index
-    uint64_t* lvl_key_alt = nullptr;
-    int32_t* bfs2pre = nullptr;      // [cap]
-    int32_t* pre2bfs = nullptr;      // [cap]
-    int32_t* lvl_off = nullptr;      // [kMaxLevels+1] breadth-first level offsets
+    // topology
+    int32_t* p_lv = nullptr;         // [n] first and last level of the nodes a particle starts
+    int32_t* topo_table = nullptr;   // [level][tile + 1] nodes per tile, then their exclusive scan
+    int32_t* lvl_off = nullptr;      // [kMaxLevels+1] breadth-first level offsets (debug export)
     // nodes (breadth-first)
     NodePlanes node;
     Mom64Planes q64;
     Mom32Planes q32;
     // groups (capacity n: the count is data dependent, kept in cnt[kCntGroups])
     GroupArrays g;
-    int32_t* g_flag = nullptr;   // [n+1] 1 at the first particle of a group, then scanned
+    int32_t* g_flag = nullptr;   // [n] 1 at the first particle of a group
+    int32_t* g_tmp = nullptr;    // groups per tile of particles
     int32_t* g_len = nullptr;    // [n] group length at its first particle
+    double* g_box = nullptr;     // [n][6] its tight box there
     unsigned* g_hist = nullptr;  // [reps][C][128] octave histograms of first-pass group sizes
     double* cl_S = nullptr;      // [C] group size limit per cluster
     // generic scan scratch
@@ -288,6 +254,8 @@ struct Dev {
     // groups walked by two waves: their partial sums and arrivals
     void* part_sum = nullptr;        // [kWalkSlots] x 64 lanes x 32 B
     unsigned* part_done = nullptr;   // [kWalkShared]
+    // the build's error bits, in host-coherent pinned memory
+    unsigned long long* host_err = nullptr;
     // counters
     unsigned long long* cnt = nullptr;
     unsigned long long* queues = nullptr;   // cnt + kNumCounters: [kQueueWords]
@@ -301,21 +269,7 @@ struct Dev {
 // scan.hip / sort.hip
 int64_t scan_tmp_need(int64_t n);
 void exclusive_scan_i32_to_i64(const int32_t* in, int64_t* out, int64_t n, int64_t* tmp, hipStream_t s);
-void exclusive_scan_i32(const int32_t* in, int32_t* out, int64_t n, int64_t* tmp, hipStream_t s);
 int64_t radix_hist_need(int64_t n);
-// Stable LSD radix sort of (key, val) on bits [0, nbits). The input is in
-// (keys, vals); the result ends in (keys, vals), or with to_alt in (keys_alt,
-// vals_alt), the other pair being scratch of the same size. The passes
-// alternate between the pairs, so the result needs no final copy when the
-// pass count (radix_passes) is even and to_alt is false, or odd and to_alt is
-// true. With vals_are_iota the input values are taken to be 0..n-1 (vals not
-// read). If n_dev is given the element count is min(n, *n_dev), read on the
-// device.
-int radix_passes(int nbits);
-void radix_sort_pairs(uint64_t* keys, int32_t* vals, uint64_t* keys_alt, int32_t* vals_alt,
-                      int64_t n, int nbits, int64_t* hist, int64_t* scan_tmp, hipStream_t s,
-                      bool vals_are_iota, const int32_t* n_dev = nullptr, bool to_alt = false);
-
 // Stable sort of (key, position) on bits [0, nbits): the keys are in `keys` on
 // entry (in `keys_alt` when sort_iota_in_alt(n)); sorted in `keys`, vals[k] = the original position of the k-th; keys_alt and
 // vals_alt are scratch of the same size, `scratch` holds sort_scratch_need(n)
@@ -325,17 +279,16 @@ bool sort_iota_in_alt(int64_t n);
 void sort_iota(uint64_t* keys, int32_t* vals, uint64_t* keys_alt, int32_t* vals_alt, int64_t n, int nbits,
                int64_t* hist, int64_t* scan_tmp, int32_t* scratch, hipStream_t s);
 
-// threads per workgroup of the per-level moment kernels (the host sizes their grids)
-constexpr int kMomT = 64;   // 32, 128 and 256 built slower at 2^20
-
 // build.hip
 void launch_bbox(Dev& d, const BuildCfg& c, const double* pos, const double* mass, int nblk,
                  hipStream_t s);
 void launch_keys(Dev& d, const BuildCfg& c, const double* pos, int nblk, hipStream_t s);
 // the key sort of a build: (keys, perm) sorted by key, perm the caller order
 void launch_key_sort(Dev& d, const BuildCfg& c, hipStream_t s);
-void launch_gather(Dev& d, const BuildCfg& c, const double* pos, const double* mass, hipStream_t s);
-void launch_topology(Dev& d, const BuildCfg& c, hipStream_t s);
+// the tree's nodes, and the particles in key order
+void launch_topology(Dev& d, const BuildCfg& c, const double* pos, const double* mass, hipStream_t s);
+int64_t topo_table_need(int64_t n);
+int64_t group_tmp_need(int64_t n);
 void launch_moments(Dev& d, const BuildCfg& c, hipStream_t s);
 void launch_groups(Dev& d, const BuildCfg& c, hipStream_t s);
 
@@ -480,8 +433,6 @@ void launch_drift(double* pos, const double* vel, double dt, int64_t n, hipStrea
 void launch_energy(const double* vel, const double* mass, const double* pot, int64_t n,
                    double* partial, int nblk, double* out, hipStream_t s);
 void launch_zero_u64(unsigned long long* p, int n, hipStream_t s);
-// the counters of a build and force call (all but those kept across builds) and the queue words
-void launch_zero_counts(unsigned long long* cnt, hipStream_t s);
 // one wave per block, 32 * iters + 32 VALU instructions per wave (counted in
 // the kernel's gfx950 assembly): a known count for instruction counters
 void launch_valu_probe(int64_t blocks, int iters, float* out, hipStream_t s);

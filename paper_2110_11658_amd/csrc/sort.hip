@@ -6,8 +6,7 @@
 // beyond that a single workgroup scans the tile sums in a launch between).
 //
 // Sorts: a sample sort for the (key, position) pairs of a build and of the core
-// quantities up to 2^22 of them; an LSD radix sort beyond that and for the one
-// 8-bit pass over node levels.
+// quantities up to 2^22 of them, an LSD radix sort beyond that.
 //
 // Radix sort: 8-bit digits. Per pass a tile
 // histogram (LDS atomics), a scan of the digit-major histogram table, and a
@@ -210,12 +209,10 @@ constexpr int RS_MAX_BINS = 256;    // bins of the widest digit used
 // Tile histogram of one digit (BITS wide, at `shift`), digit-major table.
 template <int BITS>
 __global__ __launch_bounds__(RS_T) void k_rs_hist(const uint64_t* __restrict__ keys, int64_t n,
-                                                  const int32_t* __restrict__ n_dev, int shift,
-                                                  int64_t* __restrict__ hist, int64_t nblk) {
+                                                  int shift, int64_t* __restrict__ hist, int64_t nblk) {
     constexpr int BINS = 1 << BITS;
     constexpr unsigned MASK = BINS - 1;
     __shared__ int s_h[BINS];
-    if (n_dev) n = min(n, (int64_t)*n_dev);
     for (int d = threadIdx.x; d < BINS; d += RS_T) s_h[d] = 0;
     __syncthreads();
     const int64_t base = (int64_t)blockIdx.x * RS_TILE;
@@ -243,13 +240,12 @@ __global__ __launch_bounds__(RS_T) void k_rs_scatter(const uint64_t* __restrict_
                                                      const int32_t* __restrict__ vin,
                                                      uint64_t* __restrict__ kout,
                                                      int32_t* __restrict__ vout, int64_t n,
-                                                     const int32_t* __restrict__ n_dev, int shift,
+                                                     int shift,
                                                      const int64_t* __restrict__ hist,
                                                      int64_t nblk, int iota) {
     constexpr int BINS = 1 << BITS;
     constexpr unsigned MASK = BINS - 1;
     constexpr int PER = BINS / RS_T;   // bins per thread
-    if (n_dev) n = min(n, (int64_t)*n_dev);
     __shared__ int64_t s_goff[BINS];
     __shared__ int s_run[BINS];
     __shared__ int s_wc[RS_T / 64][BINS];
@@ -315,9 +311,7 @@ __global__ __launch_bounds__(RS_T) void k_rs_scatter(const uint64_t* __restrict_
 }
 
 __global__ void k_copy_pairs(const uint64_t* __restrict__ ks, const int32_t* __restrict__ vs,
-                             uint64_t* __restrict__ kd, int32_t* __restrict__ vd, int64_t n,
-                             const int32_t* __restrict__ n_dev) {
-    if (n_dev) n = min(n, (int64_t)*n_dev);
+                             uint64_t* __restrict__ kd, int32_t* __restrict__ vd, int64_t n) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x) {
         kd[i] = ks[i];
@@ -888,10 +882,6 @@ void exclusive_scan_i32_to_i64(const int32_t* in, int64_t* out, int64_t n, int64
     scan_impl<int32_t, int64_t>(in, out, n, tmp, s);
 }
 
-void exclusive_scan_i32(const int32_t* in, int32_t* out, int64_t n, int64_t* tmp, hipStream_t s) {
-    scan_impl<int32_t, int32_t>(in, out, n, tmp, s);
-}
-
 int64_t radix_hist_need(int64_t n) {
     const int64_t nblk = (n + RS_TILE - 1) / RS_TILE;
     return nblk * RS_MAX_BINS + 1;
@@ -901,36 +891,29 @@ int64_t radix_hist_need(int64_t n) {
 // but cost more per pass than that pass at 2^20)
 constexpr int RS_BITS = 8;
 
-int radix_passes(int nbits) { return (nbits + RS_BITS - 1) / RS_BITS; }
-
-void radix_sort_pairs(uint64_t* keys, int32_t* vals, uint64_t* keys_alt, int32_t* vals_alt,
-                      int64_t n, int nbits, int64_t* hist, int64_t* scan_tmp, hipStream_t s,
-                      bool vals_are_iota, const int32_t* n_dev, bool to_alt) {
-    if (n <= 0) return;
+// Stable LSD radix sort of the n keys on bits [0, nbits), vals[k] = the original
+// position of the k-th; the alternate pair is scratch, in which an odd number
+// of passes ends.
+static void radix_sort_iota(uint64_t* keys, int32_t* vals, uint64_t* keys_alt, int32_t* vals_alt, int64_t n,
+                            int nbits, int64_t* hist, int64_t* scan_tmp, hipStream_t s) {
     const int64_t nblk = (n + RS_TILE - 1) / RS_TILE;
-    const int passes = radix_passes(nbits);
+    const int passes = (nbits + RS_BITS - 1) / RS_BITS;
     uint64_t* ki = keys;
     int32_t* vi = vals;
     uint64_t* ko = keys_alt;
     int32_t* vo = vals_alt;
     for (int p = 0; p < passes; ++p) {
         const int shift = RS_BITS * p;
-        const int iota = (int)(vals_are_iota && p == 0);
-        hipLaunchKernelGGL(k_rs_hist<RS_BITS>, dim3(nblk), dim3(RS_T), 0, s, (const uint64_t*)ki, n, n_dev,
-                           shift, hist, nblk);
+        hipLaunchKernelGGL(k_rs_hist<RS_BITS>, dim3(nblk), dim3(RS_T), 0, s, (const uint64_t*)ki, n, shift, hist, nblk);
         scan_impl<int64_t, int64_t>(hist, hist, nblk << RS_BITS, scan_tmp, s);
         hipLaunchKernelGGL(k_rs_scatter<RS_BITS>, dim3(nblk), dim3(RS_T), 0, s, (const uint64_t*)ki,
-                           (const int32_t*)vi, ko, vo, n, n_dev, shift, (const int64_t*)hist, nblk, iota);
+                           (const int32_t*)vi, ko, vo, n, shift, (const int64_t*)hist, nblk, (int)(p == 0));
         uint64_t* tk = ki; ki = ko; ko = tk;
         int32_t* tv = vi; vi = vo; vo = tv;
     }
-    uint64_t* kd = to_alt ? keys_alt : keys;
-    int32_t* vd = to_alt ? vals_alt : vals;
-    if (ki != kd) {
-        const int nb = (int)((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096);
-        hipLaunchKernelGGL(k_copy_pairs, dim3(nb), dim3(256), 0, s, (const uint64_t*)ki,
-                           (const int32_t*)vi, kd, vd, n, n_dev);
-    }
+    if (ki != keys)
+        hipLaunchKernelGGL(k_copy_pairs, dim3(4096), dim3(256), 0, s, (const uint64_t*)ki, (const int32_t*)vi, keys,
+                           vals, n);
 }
 
 // Scratch of sort_iota in int32 words for any array of up to n keys: samples,
@@ -972,7 +955,7 @@ void sort_iota(uint64_t* keys, int32_t* vals, uint64_t* keys_alt, int32_t* vals_
                int64_t* hist, int64_t* scan_tmp, int32_t* scratch, hipStream_t s) {
     if (n <= 0) return;
     if (n > kSsMaxN) {
-        radix_sort_pairs(keys, vals, keys_alt, vals_alt, n, nbits, hist, scan_tmp, s, true);
+        radix_sort_iota(keys, vals, keys_alt, vals_alt, n, nbits, hist, scan_tmp, s);
         return;
     }
     if (n <= kSsCap) {
