@@ -427,8 +427,7 @@ __global__ __launch_bounds__(kTopoT) void k_topo_emit(const uint64_t* __restrict
 // parts' sums on every level: 3.8 us a level against 1.9.
 struct MomLds {
     double v[10][66];     // component, 8 * node of the wave + part (padded: a component a lane, other banks)
-    double r[10][8];      // component, node: M, sums or centre (3), box lo (3), hi (3)
-    double q[6][8];
+    double r[17][8];      // component, node: M, sums or centre (3), box lo (3), hi (3), quadrupole (6), 0
 };
 
 __device__ inline void lds_order() {
@@ -482,37 +481,34 @@ __device__ inline void moments_group(MomLds& L, bool on, int b, int4 rg, int kid
         L.v[7 + d][lane] = hi[d];
     }
     lds_order();
-    for (int pass = 0; pass < 2; ++pass) {
-        const int k = pass == 0 ? g : 8 + g;   // the component of this lane
-        if (k < 10) {
-            double a = k < 4 ? 0.0 : L.v[k][8 * nd];
-            double u[8];
+    {
+        // lanes 0 .. 3 sum M and M c, every lane but those of M takes a box side: lanes
+        // 1 .. 3 lo, 4 .. 6 hi (min of the negatives: exact)
+        const int ks = g < 4 ? g : 3, kb = g >= 1 && g < 7 ? 3 + g : 4;
+        const double flip = kb < 7 ? 1.0 : -1.0;
+        double a = 0.0, e = INFINITY, u[8], v[8];
 #pragma unroll
-            for (int p = 0; p < 8; ++p) u[p] = L.v[k][8 * nd + p];
-#pragma unroll
-            for (int p = 0; p < 8; ++p) {
-                if (p < n8) {
-                    if (k < 4) a = a + u[p];
-                    else if (k < 7) a = u[p] < a ? u[p] : a;
-                    else a = u[p] > a ? u[p] : a;
-                }
-            }
-            if (on && leaf) {
-                for (int p = 8; p < nsub; ++p) {
-                    const int j = rg.x + p;
-                    if (k == 0) {
-                        a = a + m[j];
-                    } else {
-                        const int d = k < 4 ? k - 1 : (k < 7 ? k - 4 : k - 7);
-                        const double w = d == 0 ? x[j] : (d == 1 ? y[j] : z[j]);
-                        if (k < 4) a = a + m[j] * w;
-                        else if (k < 7) a = w < a ? w : a;
-                        else a = w > a ? w : a;
-                    }
-                }
-            }
-            L.r[k][nd] = a;
+        for (int p = 0; p < 8; ++p) {
+            u[p] = L.v[ks][8 * nd + p];
+            v[p] = L.v[kb][8 * nd + p];
         }
+#pragma unroll
+        for (int p = 0; p < 8; ++p) {
+            a = p < n8 ? a + u[p] : a;
+            e = p < n8 ? fmin(e, v[p] * flip) : e;
+        }
+        if (on && leaf) {
+            for (int p = 8; p < nsub; ++p) {   // (leaves of more than 8 particles)
+                const int j = rg.x + p;
+                const double mj = m[j], xs = g == 1 ? x[j] : (g == 2 ? y[j] : z[j]);
+                const double xb = kb % 3 == 1 ? x[j] : (kb % 3 == 2 ? y[j] : z[j]);
+                a = g == 0 ? a + mj : a + mj * xs;
+                e = fmin(e, xb * flip);
+            }
+        }
+        if (g < 4) L.r[g][nd] = a;
+        if (g >= 1 && g < 7) L.r[kb][nd] = e * flip;
+        if (g == 7) L.r[16][nd] = 0.0;
     }
     lds_order();
     const double Ms = L.r[0][nd];
@@ -551,29 +547,24 @@ __device__ inline void moments_group(MomLds& L, bool on, int b, int4 rg, int kid
                 a = a + (0.0 + mj * e);
             }
         }
-        L.q[g][nd] = a;
+        L.r[10 + g][nd] = a;
     }
     lds_order();
-    if (on) {   // the pieces of the results, a plane or two a lane
-        auto R = [&](int k) { return L.r[k][nd]; };
-        auto Q = [&](int k) { return L.q[k][nd]; };
-        switch (g) {
-            case 0: node.plane(0)[b] = make_double2(R(4), R(5)); break;
-            case 1: node.plane(1)[b] = make_double2(R(6), R(7)); break;
-            case 2: node.plane(2)[b] = make_double2(R(8), R(9)); break;
-            case 3:
-                node.plane(3)[b] = make_double2(R(1), R(2));
-                reinterpret_cast<double*>(node.plane(4) + b)[0] = R(3);
-                break;
-            case 4: q64.p[b] = make_double2(R(0), Q(0)); break;
-            case 5: q64.p[q64.cap + b] = make_double2(Q(1), Q(2)); break;
-            case 6:
-                q64.p[2 * q64.cap + b] = make_double2(Q(3), Q(4));
-                q64.p[3 * q64.cap + b] = make_double2(Q(5), 0.0);
-                break;
-            default:
-                q32.p[b] = make_float4((float)R(0), (float)Q(0), (float)Q(1), (float)Q(2));
-                q32.p[q32.cap + b] = make_float4((float)Q(3), (float)Q(4), (float)Q(5), 0.0f);
+    if (on) {
+        // the results in pieces of two: lane 0 .. 3 the node's first four planes, lane 4
+        // .. 7 the four of the FP64 moments; then the rest of the centre and the FP32
+        // moments
+        const int i0 = (int)((0xfdb01864u >> (4 * g)) & 15u);   // 4 6 8 1 | 0 11 13 15
+        int i1 = (int)((0x0eca2975u >> (4 * g)) & 15u);         // 5 7 9 2 | 10 12 14 -
+        if (g == 7) i1 = 16;
+        double2* dst = g < 4 ? node.p + (int64_t)g * node.cap + b : q64.p + (int64_t)(g - 4) * q64.cap + b;
+        *dst = make_double2(L.r[i0][nd], L.r[i1][nd]);
+        if (g == 0) reinterpret_cast<double*>(node.plane(4) + b)[0] = L.r[3][nd];
+        if (g == 1 || g == 2) {
+            const double f = L.r[g == 1 ? 0 : 13][nd];
+            const int k1 = g == 1 ? 10 : 14;
+            q32.p[(int64_t)(g - 1) * q32.cap + b] =
+                make_float4((float)f, (float)L.r[k1][nd], (float)L.r[k1 + 1][nd], (float)L.r[g == 1 ? 12 : 16][nd]);
         }
     }
     lds_order();
@@ -634,6 +625,8 @@ __global__ __launch_bounds__(kStradT) void k_moments_straddle(int64_t n, int D, 
     __shared__ MomLds s_m[kStradT / 64];
     __shared__ int s_off[64];
     __shared__ unsigned s_levels;   // levels at which some unit has such a node
+    __shared__ int s_cand[kMaxLevels][kStradU];   // of the first kStradU units: the node and its range
+    __shared__ int4 s_rg[kMaxLevels][kStradU];
     const int t = threadIdx.x, g = t & 7;
     if (t < 64) level_offsets(table, ntile, D, cap, s_off);
     if (t == 0) s_levels = 0u;
@@ -655,8 +648,15 @@ __global__ __launch_bounds__(kStradT) void k_moments_straddle(int64_t n, int D, 
     };
     for (int64_t u = t >> 3; u < units; u += kStradU) {   // a lane group's levels, 8 at a time
         unsigned mask = 0;
-        int4 rg;
-        for (int l = g; l <= D; l += 8) mask |= candidate(u, l, rg) >= 0 ? 1u << l : 0u;
+        int4 rg = make_int4(0, 0, -1, 0);
+        for (int l = g; l <= D; l += 8) {
+            const int b = candidate(u, l, rg);
+            mask |= b >= 0 ? 1u << l : 0u;
+            if (u < kStradU) {
+                s_cand[l][u] = b;
+                s_rg[l][u] = rg;
+            }
+        }
         if (mask) atomicOr(&s_levels, mask);
     }
     __syncthreads();
@@ -668,7 +668,16 @@ __global__ __launch_bounds__(kStradT) void k_moments_straddle(int64_t n, int D, 
         for (int64_t u0 = (t >> 6) * 8; u0 < units; u0 += kStradU) {
             const int64_t u = u0 + ((t & 63) >> 3);
             int4 rg = make_int4(0, 0, -1, 0);
-            const int b = u < units ? candidate(u, l, rg) : -1;
+            int b = -1;
+            if (u < units) {
+                if (u < kStradU) {
+                    b = s_cand[l][u];
+                    rg = s_rg[l][u];
+                } else {
+                    b = candidate(u, l, rg);
+                }
+            }
+            if (b < 0) rg = make_int4(0, 0, -1, 0);
             if (__ballot(b >= 0))
                 moments_group(s_m[t >> 6], b >= 0, b, rg, kids_end, x, y, z, m, node, q64, q32);
         }
