@@ -29,9 +29,10 @@
 // those derivatives gives the first step; dt_max where its denominator is 0
 // (no pair inside r_out). Expressions are evaluated as written (no contraction).
 //
-// A block is two launches: the front (next block time, active list,
-// prediction) and the force with the corrector; particles are kept in one
-// bucket per level, so neither launch passes over all n particles.
+// A block is one launch: the next block time and its active particles from the
+// level counts, prediction of each active particle and its list members in
+// registers, force, corrector, new step, move to the new bucket. Particles are
+// kept in one bucket per level, so it does not pass over all n particles.
 #include "irr_pair.hpp"
 #include "pbh_internal.hpp"
 
@@ -57,45 +58,91 @@ __device__ inline double norm3(double x, double y, double z) {
 // >= k* - 1 (the step at most doubles): buckets >= k* are refilled from zero
 // and bucket k* - 1 is appended to.
 //
-// Level counts are double-buffered by block parity q: the front of a block
-// reads the counts of slot q (cnt, plus the appends newcnt of the previous
-// block, and that block's k*) and writes the merged counts to slot q ^ 1,
-// where the corrector of the same block appends. Every launch of a block
-// reads only what earlier launches wrote.
+// No launch reads what it writes. Level counts, block time and k* have two slots
+// by block parity q: a block reads slot q and writes q ^ 1. The counts of the
+// corrected particles per level (new) have four by block number: a block reads
+// its own, which the block before filled, appends to the next and clears the one
+// after that. Buckets of the active levels are read from one of two buffers
+// (bit k of the mask) and refilled in the other. And a particle's state has two
+// records: a block reads the newest with a time before its own, and writes the
+// corrected state over the older one, whose time (old or, once written, the
+// block's own) never qualifies, so members that are corrected at the same moment
+// are read as they were.
 //
 // Blocks are enqueued in batches without waiting; once every particle has
 // reached the end of the regular step the remaining blocks are empty
-// (kHermDone), and the front that finds it also sets a host-visible flag,
+// (kHermDone), and the block that finds it also sets a host-visible flag,
 // which the host reads after a batch while the next one runs.
-constexpr int kHermGrid = 1024;   // grid-stride launches
-constexpr int kHermLanes = 32;    // lanes per active particle in the prediction (the particle and its list)
-constexpr int kHermAllFrac = 8;   // predict all particles when n_active >= n / 8
+constexpr int kHermT = 512;       // threads per workgroup of a block
+constexpr int kHermGrid = 512;    // workgroups
+constexpr int kHermLanes = 8;     // lanes per active particle while that fits the grid, else one
 constexpr int kSlotShift = 26;    // per-item scratch: level << 26 | rank in its workgroup
 constexpr uint32_t kSlotMask = (1u << kSlotShift) - 1;
 static_assert(kHermK < 63, "levels fit one wave");
 
 __device__ inline unsigned long long* lev_cnt(const HermParams& p, int q) { return p.lev + kLevCnt + 64 * q; }
-__device__ inline unsigned long long* lev_new(const HermParams& p, int q) { return p.lev + kLevNew + 64 * q; }
+__device__ inline unsigned long long* lev_new(const HermParams& p, int b) { return p.lev + kLevNew + 64 * (b & 3); }
 
-__device__ inline void predict_one(const HermParams& p, int64_t i, int64_t tn) {
+// One particle's state at its own time, as 16-byte pieces of its record:
+// x y | z vx | vy vz | ax ay | az jx | jy jz | m tau | dt -
+struct HermState {
+    double x[3], v[3], a[3], j[3], m;
+    int64_t tau, dt;
+};
+
+__device__ inline HermState load_state(const double2* __restrict__ r) {
+    HermState s;
+    const double2 q0 = r[0], q1 = r[1], q2 = r[2], q3 = r[3], q4 = r[4], q5 = r[5], q6 = r[6], q7 = r[7];
+    s.x[0] = q0.x; s.x[1] = q0.y; s.x[2] = q1.x;
+    s.v[0] = q1.y; s.v[1] = q2.x; s.v[2] = q2.y;
+    s.a[0] = q3.x; s.a[1] = q3.y; s.a[2] = q4.x;
+    s.j[0] = q4.y; s.j[1] = q5.x; s.j[2] = q5.y;
+    s.m = q6.x;
+    s.tau = __double_as_longlong(q6.y);
+    s.dt = __double_as_longlong(q7.x);
+    return s;
+}
+
+__device__ inline void store_state(double2* r, const HermState& s) {
+    r[0] = make_double2(s.x[0], s.x[1]);
+    r[1] = make_double2(s.x[2], s.v[0]);
+    r[2] = make_double2(s.v[1], s.v[2]);
+    r[3] = make_double2(s.a[0], s.a[1]);
+    r[4] = make_double2(s.a[2], s.j[0]);
+    r[5] = make_double2(s.j[1], s.j[2]);
+    r[6] = make_double2(s.m, __longlong_as_double((long long)s.tau));
+    r[7] = make_double2(__longlong_as_double((long long)s.dt), 0.0);
+}
+
+constexpr int kRecPieces = 8;
+
+// The record of particle i to read at block time tn: the newest with an earlier
+// time (buffer 0 or 1).
+__device__ inline int state_buffer(const HermParams& p, int64_t i, int64_t tn) {
+    const int64_t t0 = __double_as_longlong(p.rec[kRecPieces * i + 6].y);
+    const int64_t t1 = __double_as_longlong(p.rec[kRecPieces * (p.n + i) + 6].y);
+    return t1 < tn && (t0 >= tn || t1 > t0) ? 1 : 0;
+}
+
+// The predicted position and velocity at time tn (the P3T predictor).
+__device__ inline void predict(const HermParams& p, const HermState& s, int64_t tn, double* xp, double* vp) {
 #pragma clang fp contract(off)
-    const double d = (double)(tn - p.tau[i]) * p.unit;
+    const double d = (double)(tn - s.tau) * p.unit;
     const double d2 = d * d, d3 = d2 * d;
     for (int k = 0; k < 3; ++k) {
-        const int64_t q = 3 * i + k;
-        p.xp[q] = p.x[q] + d * p.v[q] + 0.5 * d2 * p.a[q] + d3 / 6.0 * p.j[q];
-        p.vp[q] = p.v[q] + d * p.a[q] + 0.5 * d2 * p.j[q];
+        xp[k] = s.x[k] + d * s.v[k] + 0.5 * d2 * s.a[k] + d3 / 6.0 * s.j[k];
+        vp[k] = s.v[k] + d * s.a[k] + 0.5 * d2 * s.j[k];
     }
 }
 
-// The count of level k (lane k of a wave) after merging the previous block's
-// appends into slot q; `add` returns those appends.
-__device__ inline long long merged_count(const HermParams& p, int q, int k, long long& add) {
+// The count of level k (lane k of a wave) after merging the appends of the block
+// before; `add` returns those appends.
+__device__ inline long long merged_count(const HermParams& p, int b, int k, long long& add) {
     add = 0;
     if (k > kHermK) return 0;
-    const int kp = (int)p.lev[kLevKs + q];   // k* of the previous block
-    const long long old = (long long)lev_cnt(p, q)[k];
-    add = (long long)lev_new(p, q)[k];
+    const int kp = (int)p.lev[kLevKs + (b & 1)];   // k* of the previous block
+    const long long old = (long long)lev_cnt(p, b & 1)[k];
+    add = (long long)lev_new(p, b)[k];
     return k >= kp ? add : (k == kp - 1 ? old + add : old);
 }
 
@@ -128,152 +175,82 @@ __device__ inline BlockPlan plan_block(long long c, long long t, unsigned long l
     return b;
 }
 
-// entry t of the active list: level buckets ks, ks + 1, ... in turn
+__device__ inline int32_t* bucket_of(const HermParams& p, int buf, int k) {
+    return p.bucket + ((int64_t)buf * (kHermK + 1) + k) * p.n;
+}
+
+// entry t of the active list: level buckets ks, ks + 1, ... in turn, each in the
+// buffer of its mask bit
 __device__ inline int32_t active_at(const HermParams& p, const long long* off, const long long* cnt, int ks,
-                                    long long t) {
+                                    uint64_t mask, long long t) {
     int k = ks;
     while (k < kHermK && t >= off[k] + cnt[k]) ++k;
-    return p.bucket[(int64_t)k * p.n + (t - off[k])];
-}
-
-// predict the active particle i (item 0) or member g - 1, g - 1 + kHermLanes, ...
-// of its list (items g, g + kHermLanes, ...): lane g of its lane group
-__device__ inline void predict_items(const HermParams& p, int32_t i, int g, int64_t tn) {
-    if (g == 0) predict_one(p, i, tn);
-    const int64_t b0 = p.off[i], e = p.off[i + 1];
-    if (b0 < 0 || e < b0 || e > p.cap) return;   // flagged by the force kernel
-    for (int64_t m = b0 + (g == 0 ? kHermLanes - 1 : g - 1); m < e; m += kHermLanes) {
-        const int64_t j = p.idx[m];
-        if ((uint64_t)j < (uint64_t)p.n) predict_one(p, j, tn);
-    }
-}
-
-// Block front: the next block time and the active buckets (computed by every
-// workgroup from slot q; workgroup 0 publishes them), then the active list
-// (bucket order) with the prediction of each active particle and its list
-// members (a member shared by several lists is written with the same value
-// by each) -- the only states the irregular force of the block reads.
-__global__ __launch_bounds__(256) void k_herm_front(HermParams p, int q) {
-    __shared__ long long s_cnt[64], s_off[64];
-    __shared__ long long s_tn, s_nact;
-    __shared__ int s_ks;
-    if (threadIdx.x < 64) {
-        const int k = threadIdx.x;
-        long long add;
-        const long long c = merged_count(p, q, k, add);
-        // deepest new level of the previous corrector (its appends; the first
-        // block's appends are the start levels, not counted)
-        const uint64_t app = __ballot(add > 0);
-        const long long t = (long long)p.lev[kLevT + q];
-        const BlockPlan B = plan_block(c, t, p.tend);
-        s_cnt[k] = c;
-        s_off[k] = B.off;
-        if (k == 0) {
-            s_tn = B.tn;
-            s_nact = B.nact;
-            s_ks = B.ks;
-        }
-        if (blockIdx.x == 0) {
-            if (k == 0 && t > 0 && app) {
-                const unsigned long long dl = (unsigned long long)(63 - __clzll(app));
-                if (dl > p.ctl[kHermKmax]) p.ctl[kHermKmax] = dl;
-            }
-            if (k <= kHermK) {
-                lev_cnt(p, q ^ 1)[k] = (unsigned long long)c;
-                lev_new(p, q ^ 1)[k] = 0ull;
-            }
-            if (k == 0) {
-                p.lev[kLevT + (q ^ 1)] = (unsigned long long)B.tn;
-                p.lev[kLevKs + (q ^ 1)] = (unsigned long long)B.ks;
-                p.ctl[kHermTn] = B.done ? ~0ull : (unsigned long long)B.tn;
-                p.ctl[kHermNact] = (unsigned long long)B.nact;
-                if (B.done) {
-                    p.ctl[kHermDone] = 1ull;
-                    if (p.done_host) *p.done_host = 1ull;   // read by the host while later blocks run
-                } else {
-                    p.ctl[kHermBlocks] += 1ull;
-                    p.ctl[kHermSteps] += (unsigned long long)B.nact;
-                }
-            }
-        }
-    }
-    __syncthreads();
-    const long long nact = s_nact, tn = s_tn;
-    const int ks = s_ks;
-    const long long stride = (long long)gridDim.x * 256;
-    const long long t0 = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (nact * kHermAllFrac >= p.n) {
-        // a large active set: predict every particle once, in order (the
-        // others are not read by this block), and list the active ones
-        for (long long t = t0; t < p.n; t += stride) predict_one(p, t, tn);
-        for (long long t = t0; t < nact; t += stride) p.act[t] = active_at(p, s_off, s_cnt, ks, t);
-        return;
-    }
-    // kHermLanes lanes per active particle: item 0 is the particle, item
-    // m >= 1 the m-th member of its list
-    for (long long t = t0; t < nact * kHermLanes; t += stride) {
-        const long long a = t / kHermLanes;
-        const int g = (int)(t % kHermLanes);
-        const int32_t i = active_at(p, s_off, s_cnt, ks, a);
-        if (g == 0) p.act[a] = i;
-        predict_items(p, i, g, tn);
-    }
+    return bucket_of(p, (int)((mask >> k) & 1), k)[t - off[k]];
 }
 
 // Each workgroup takes one contiguous chunk of the n_items items (a multiple of
-// 256, so a small set is one workgroup): `step(k, i)` advances item k (the
-// particle i = list[k], or k without a list) and returns its new level; the
-// workgroup ranks its items per level in LDS, reserves room in each bucket
-// with one device atomic per level (buckets >= ks restart from zero, bucket
-// ks - 1 keeps its members), then stores the particles there. Same-address
-// device atomics serialise, so one per workgroup and level, not per wave; a
-// workgroup that holds every item stores its counts without atomics.
-template <class Step>
-__device__ inline void step_and_bucket(const HermParams& p, int q, int ks, int64_t n_items,
-                                       const int32_t* list, int32_t first, Step step) {
+// its lane groups, so a small set is one workgroup): `step(k, i)` advances item k
+// (the particle i = item(k)) and returns its new level in lane 0 of its group of
+// LH lanes; the workgroup ranks its items per level in LDS, reserves room in each
+// bucket with one device atomic per level (buckets >= ks restart from zero in
+// their other buffer, bucket ks - 1 keeps its `keep` members), then stores the
+// particles there. Same-address device atomics serialise, so one per workgroup
+// and level, not per wave; a workgroup that holds every item stores its counts
+// without atomics. `step` runs in every lane of a wave that holds an item.
+template <int LH, int T, class Item, class Step>
+__device__ inline void step_and_bucket(const HermParams& p, unsigned long long* newcnt, int ks, long long keep_cnt,
+                                       uint64_t mask_new, int64_t n_items, Item item, Step step) {
+    constexpr int TG = T / LH;
     __shared__ int s_h[64];
     __shared__ long long s_b[64];
-    const int64_t per = ((n_items + gridDim.x - 1) / gridDim.x + 255) / 256 * 256;
+    const int64_t per = ((n_items + gridDim.x - 1) / gridDim.x + TG - 1) / TG * TG;
     const int64_t c0 = (int64_t)blockIdx.x * per, c1 = c0 + per < n_items ? c0 + per : n_items;
     if (c0 >= c1) return;   // workgroup-uniform
     if (threadIdx.x < 64) s_h[threadIdx.x] = 0;
     __syncthreads();
-    // a thread's first item stays in registers; later ones go through p.slot
+    const int tg = threadIdx.x / LH;
+    const bool head = threadIdx.x % LH == 0;
+    // a group's first item stays in registers; later ones go through p.slot
     int lv0 = -1, r0 = 0;
     int32_t i0 = 0;
-    for (int64_t k = c0 + threadIdx.x; k < c1; k += 256) {
-        const bool head = k == c0 + threadIdx.x;
-        // (workgroup 0's first items are k = threadIdx.x: `first` holds list[k])
-        const int32_t i = list ? (head && c0 == 0 ? first : list[k]) : (int32_t)k;
-        const int level = step(k, i);
-        const int r = atomicAdd(&s_h[level], 1);
-        if (head) {
-            lv0 = level;
-            r0 = r;
-            i0 = i;
-        } else {
-            p.slot[k] = ((uint32_t)level << kSlotShift) | (uint32_t)r;
+    for (int64_t k0 = c0; k0 < c1; k0 += TG) {
+        const int64_t k = k0 + tg;
+        const bool have = k < c1;
+        if (__ballot(have) == 0) break;   // this wave holds no more items
+        const int32_t i = have ? item(k) : -1;
+        const int level = step(i);
+        if (have && head) {
+            const int r = atomicAdd(&s_h[level], 1);
+            if (k0 == c0) {
+                lv0 = level;
+                r0 = r;
+                i0 = i;
+            } else {
+                p.slot[k] = ((uint32_t)level << kSlotShift) | (uint32_t)r;
+            }
         }
     }
     __syncthreads();
     if (threadIdx.x <= kHermK && s_h[threadIdx.x] > 0) {
         const int k = threadIdx.x;
-        const long long keep = k == ks - 1 ? (long long)lev_cnt(p, q)[k] : 0;
+        const long long keep = k == ks - 1 ? keep_cnt : 0;
         if (c0 == 0 && c1 == n_items) {   // the only workgroup with items: no other appends
             s_b[k] = keep;
-            lev_new(p, q)[k] = (unsigned long long)s_h[k];
+            newcnt[k] = (unsigned long long)s_h[k];
         } else {
-            s_b[k] = keep + (long long)atomicAdd(lev_new(p, q) + k, (unsigned long long)s_h[k]);
+            s_b[k] = keep + (long long)atomicAdd(newcnt + k, (unsigned long long)s_h[k]);
         }
     }
     __syncthreads();
-    if (lv0 >= 0) p.bucket[(int64_t)lv0 * p.n + s_b[lv0] + r0] = i0;
-    for (int64_t k = c0 + threadIdx.x + 256; k < c1; k += 256) {   // the same later items per thread
-        const uint32_t v = p.slot[k];
-        const int level = (int)(v >> kSlotShift);
-        const int32_t i = list ? list[k] : (int32_t)k;
-        p.bucket[(int64_t)level * p.n + s_b[level] + (int64_t)(v & kSlotMask)] = i;
-    }
+    auto put = [&](int level, int64_t r, int32_t i) {
+        bucket_of(p, (int)((mask_new >> level) & 1), level)[s_b[level] + r] = i;
+    };
+    if (lv0 >= 0) put(lv0, r0, i0);
+    if (head)
+        for (int64_t k = c0 + TG + tg; k < c1; k += TG) {   // the same later items per group
+            const uint32_t v = p.slot[k];
+            put((int)(v >> kSlotShift), (int64_t)(v & kSlotMask), item(k));
+        }
 }
 
 // block step in ticks: dt_max / 2^k not above `want`, dividing tau (the
@@ -352,9 +329,10 @@ __device__ inline void pair_d23(const ClusterParams& cp, double eps2, const doub
 // First steps: one lane per particle sums the derivatives over its list (in
 // list order; lists from the regular-force walk are short), then eq. dt.
 __global__ __launch_bounds__(256) void k_herm_start(HermParams p, IrrParams ip) {
-    // slot 0, every level refilled (ks = 0)
-    step_and_bucket(p, 0, 0, p.n, nullptr, 0, [&](int64_t, int32_t i) {
+    // block 0's counts, every level filled (ks = 0) in buffer 0
+    step_and_bucket<1, 256>(p, lev_new(p, 0), 0, 0, 0ull, p.n, [](int64_t k) { return (int32_t)k; }, [&](int32_t i) {
 #pragma clang fp contract(off)
+        if (i < 0) return 0;   // a lane without an item
         const int64_t i3 = 3 * (int64_t)i;
         double xi[3], vi[3], ai[3], ji[3], f2[3] = {0.0, 0.0, 0.0}, f3[3] = {0.0, 0.0, 0.0};
         for (int c = 0; c < 3; ++c) {
@@ -394,49 +372,82 @@ __global__ __launch_bounds__(256) void k_herm_start(HermParams p, IrrParams ip) 
         const double num = n0 * n2 + n1 * n1, den = n1 * n3 + n2 * n2;
         const double want = den > 0.0 ? sqrt(p.eta * num / den) : p.dtmax;
         const int64_t t = block_step(want, p.dtmax, 0);
-        p.tau[i] = 0;
-        p.dt[i] = t;
-        if (p.dt0) p.dt0[i] = t;
+        HermState s;
+        for (int c = 0; c < 3; ++c) {
+            s.x[c] = xi[c];
+            s.v[c] = vi[c];
+            s.a[c] = ai[c];
+            s.j[c] = ji[c];
+        }
+        s.m = ip.mass[i];
+        s.tau = 0;
+        s.dt = t;
+        store_state(p.rec + kRecPieces * (int64_t)i, s);
+        // no second record yet: a time before any
+        p.rec[kRecPieces * (p.n + i) + 6] = make_double2(0.0, __longlong_as_double(-1ll));
+        p.dt0[i] = t;
         return step_level(t);
     });
 }
 
-// The irregular force of the block and the corrector, one lane per active
-// particle: F_I and its derivative a1, j1 at the predicted state (the pair
-// terms of the irregular-force kernel, summed over the list in order), then
-// the 4th-order corrector and the new block step; returns the new level. The force reads only
-// predicted states and masses; the corrector writes only the state of its own
-// particle, so neither reads what the other writes.
+// One active particle i (a group of LH lanes; i < 0: a group without one, which
+// takes part in the exchange): F_I and its derivative a1, j1 at the predicted
+// states (the pair terms of the irregular-force kernel; lane g sums list entries
+// g, g + LH, ... in order, then the group's butterfly), the 4th-order corrector
+// and the new block step; returns the new level.
+template <int LH>
 __device__ inline int force_correct(const HermParams& p, const IrrParams& ip, int32_t i, int64_t tn) {
 #pragma clang fp contract(off)
-    // the corrector's own inputs first: their loads overlap the force's gathers
-    const int64_t dti = p.dt[i];
-    double a0[3], j0[3], fr[3], xp[3], vp[3];
-    for (int c = 0; c < 3; ++c) {
-        const int64_t q3 = 3 * (int64_t)i + c;
-        a0[c] = p.a[q3];
-        j0[c] = p.j[q3];
-        fr[c] = p.fr ? p.fr[q3] : 0.0;
-        xp[c] = p.xp[q3];
-        vp[c] = p.vp[q3];
-    }
+    const int g = threadIdx.x % LH;
     IrrSums S;   // (the pair sums carry their own contraction setting)
-    unsigned long long bad = 0;
-    irr_sums<true, false, false, false>(ip, i, S, bad);
-    if (bad) atomicOr(ip.err, bad);
+    HermState s = {};
+    double xp[3] = {0.0, 0.0, 0.0}, vp[3] = {0.0, 0.0, 0.0}, fr[3] = {0.0, 0.0, 0.0};
+    int buf = 0;
+    if (i >= 0) {
+        const int64_t i3 = 3 * (int64_t)i;
+        int64_t b = p.off[i], e = p.off[i + 1];
+        buf = state_buffer(p, i, tn);
+        s = load_state(p.rec + kRecPieces * (buf * p.n + i));
+        if (p.fr)
+            for (int c = 0; c < 3; ++c) fr[c] = p.fr[i3 + c];
+        predict(p, s, tn, xp, vp);
+        const PartJ me = {xp[0], xp[1], xp[2], s.m, vp[0], vp[1], vp[2]};
+        const IrrK K = irr_constants(ip.cp0);
+        if (b < 0 || e < b || e > p.cap) {   // malformed offsets: flagged, list not read
+            atomicOr(ip.err, kIrrBadOffsets);
+            e = b;
+        }
+        for (int64_t m = b + g; m < e; m += LH) {
+            const int64_t j = p.idx[m];
+            if ((uint64_t)j >= (uint64_t)p.n) {
+                atomicOr(ip.err, kIrrBadIndex);
+                continue;
+            }
+            if (j == i) continue;
+            const HermState o = load_state(p.rec + kRecPieces * (state_buffer(p, j, tn) * p.n + j));
+            double xj[3], vj[3];
+            predict(p, o, tn, xj, vj);
+            pair_irr<true, false>(K, ip.eps2, me, PartJ{xj[0], xj[1], xj[2], o.m, vj[0], vj[1], vj[2]}, S);
+        }
+    }
+    if (LH > 1) {
+        double* const w[6] = {&S.ax, &S.ay, &S.az, &S.jx, &S.jy, &S.jz};
+        for (int k = 0; k < 6; ++k)
+            for (int o = LH / 2; o > 0; o >>= 1) *w[k] += __shfl_xor(*w[k], o, 64);
+    }
+    if (i < 0 || g != 0) return 0;
     const double a1v[3] = {S.ax, S.ay, S.az}, j1v[3] = {S.jx, S.jy, S.jz};
-    const double d = (double)dti * p.unit, d2 = d * d, d3 = d2 * d, d4 = d3 * d, d5 = d4 * d;
+    const double d = (double)s.dt * p.unit, d2 = d * d, d3 = d2 * d, d4 = d3 * d, d5 = d4 * d;
     double a2[3], a3[3], a2e[3], at[3];
     for (int c = 0; c < 3; ++c) {
-        const int64_t q3 = 3 * (int64_t)i + c;
         const double a1 = a1v[c], j1 = j1v[c];
-        const double da = a0[c] - a1;
-        a2[c] = (-6.0 * da - d * (4.0 * j0[c] + 2.0 * j1)) / d2;
-        a3[c] = (12.0 * da + 6.0 * d * (j0[c] + j1)) / d3;
-        p.x[q3] = xp[c] + d4 / 24.0 * a2[c] + d5 / 120.0 * a3[c];
-        p.v[q3] = vp[c] + d3 / 6.0 * a2[c] + d4 / 24.0 * a3[c];
-        p.a[q3] = a1;
-        p.j[q3] = j1;
+        const double da = s.a[c] - a1;
+        a2[c] = (-6.0 * da - d * (4.0 * s.j[c] + 2.0 * j1)) / d2;
+        a3[c] = (12.0 * da + 6.0 * d * (s.j[c] + j1)) / d3;
+        s.x[c] = xp[c] + d4 / 24.0 * a2[c] + d5 / 120.0 * a3[c];
+        s.v[c] = vp[c] + d3 / 6.0 * a2[c] + d4 / 24.0 * a3[c];
+        s.a[c] = a1;
+        s.j[c] = j1;
         a2e[c] = a2[c] + d * a3[c];
         at[c] = a1 + fr[c];
     }
@@ -448,20 +459,88 @@ __device__ inline int force_correct(const HermParams& p, const IrrParams& ip, in
     double want = den > 0.0 ? sqrt(p.eta * num / den) : p.dtmax;
     if (want > 2.0 * d) want = 2.0 * d;
     const int64_t t = block_step(want, p.dtmax, tn);
-    p.tau[i] = tn;
-    p.dt[i] = t;
+    s.tau = tn;
+    s.dt = t;
+    store_state(p.rec + kRecPieces * ((buf ^ 1) * p.n + i), s);
     return step_level(t);
 }
 
-__global__ __launch_bounds__(256) void k_herm_force_correct(HermParams p, IrrParams ip, int q) {
-    // workgroup 0's first active entries, read alongside the block's counts
-    // (act has n entries; an entry past n_active is never used)
-    const int32_t first = blockIdx.x == 0 && (int64_t)threadIdx.x < p.n ? p.act[threadIdx.x] : 0;
-    const int64_t nact = (int64_t)p.ctl[kHermNact];
-    const int ks = (int)p.lev[kLevKs + (q ^ 1)];
-    const int64_t tn = (int64_t)p.ctl[kHermTn];
-    step_and_bucket(p, q ^ 1, ks, nact, p.act, first,
-                    [&](int64_t, int32_t i) { return force_correct(p, ip, i, tn); });
+// One block (number b in its batch): every workgroup computes the next block
+// time and the active buckets from the level counts, workgroup 0 publishes them
+// for the next block.
+__global__ __launch_bounds__(kHermT) void k_herm_block(HermParams p, IrrParams ip, int b) {
+    __shared__ long long s_cnt[64], s_off[64];
+    __shared__ long long s_tn, s_nact;
+    __shared__ int s_ks;
+    const int q = b & 1;
+    const uint64_t mask = p.lev[kLevMask + q];
+    if (threadIdx.x < 64) {
+        const int k = threadIdx.x;
+        long long add;
+        const long long c = merged_count(p, b, k, add);
+        // deepest new level of the previous corrector (its appends; the first
+        // block's appends are the start levels, not counted)
+        const uint64_t app = __ballot(add > 0);
+        const long long t = (long long)p.lev[kLevT + q];
+        const BlockPlan B = plan_block(c, t, p.tend);
+        s_cnt[k] = c;
+        s_off[k] = B.off;
+        if (k == 0) {
+            s_tn = B.done ? -1 : B.tn;
+            s_nact = B.done ? 0 : B.nact;
+            s_ks = B.ks;
+        }
+        if (blockIdx.x == 0) {
+            if (k == 0 && t > 0 && app) {
+                const unsigned long long dl = (unsigned long long)(63 - __clzll(app));
+                if (dl > p.ctl[kHermKmax]) p.ctl[kHermKmax] = dl;
+            }
+            if (k <= kHermK) {
+                lev_cnt(p, q ^ 1)[k] = (unsigned long long)c;
+                lev_new(p, b + 2)[k] = 0ull;
+            }
+            if (k == 0) {
+                p.lev[kLevT + (q ^ 1)] = (unsigned long long)B.tn;
+                p.lev[kLevKs + (q ^ 1)] = (unsigned long long)B.ks;
+                p.lev[kLevMask + (q ^ 1)] = mask ^ (B.ks > kHermK ? 0ull : ~0ull << B.ks);
+                if (B.done) {
+                    p.ctl[kHermDone] = 1ull;
+                    if (p.done_host) *p.done_host = 1ull;   // read by the host while later blocks run
+                } else {
+                    p.ctl[kHermBlocks] += 1ull;
+                    p.ctl[kHermSteps] += (unsigned long long)B.nact;
+                }
+            }
+        }
+    }
+    __syncthreads();
+    const long long nact = s_nact, tn = s_tn;
+    const int ks = s_ks;
+    if (nact == 0) return;
+    const uint64_t mask_new = mask ^ (~0ull << ks);
+    const long long keep = ks > 0 ? s_cnt[ks - 1] : 0;
+    unsigned long long* const newcnt = lev_new(p, b + 1);
+    auto item = [&](int64_t k) { return active_at(p, s_off, s_cnt, ks, mask, k); };
+    // eight lanes share a particle's list while the grid has lanes for all
+    if (nact * kHermLanes <= (long long)gridDim.x * kHermT)
+        step_and_bucket<kHermLanes, kHermT>(p, newcnt, ks, keep, mask_new, nact, item,
+                                            [&](int32_t i) { return force_correct<kHermLanes>(p, ip, i, tn); });
+    else
+        step_and_bucket<1, kHermT>(p, newcnt, ks, keep, mask_new, nact, item,
+                                   [&](int32_t i) { return force_correct<1>(p, ip, i, tn); });
+}
+
+// the states of the end of the regular step into the caller's arrays
+__global__ __launch_bounds__(256) void k_herm_finish(HermParams p) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= p.n) return;
+    const int64_t t0 = __double_as_longlong(p.rec[kRecPieces * i + 6].y);
+    const int64_t t1 = __double_as_longlong(p.rec[kRecPieces * (p.n + i) + 6].y);
+    const HermState s = load_state(p.rec + kRecPieces * ((t1 > t0 ? p.n : 0) + i));
+    for (int c = 0; c < 3; ++c) {
+        p.x[3 * i + c] = s.x[c];
+        p.v[3 * i + c] = s.v[c];
+    }
 }
 
 // pot_tot = pot_r + pot_i
@@ -472,21 +551,18 @@ __global__ void k_add(int64_t n, const double* a, const double* b, double* out) 
 
 }  // namespace
 
-static unsigned herm_grid(int64_t n) {
-    const int64_t g = (n + 255) / 256;
-    return (unsigned)(g < kHermGrid ? (g < 1 ? 1 : g) : kHermGrid);
-}
-
 void launch_herm_start(const HermParams& p, const IrrParams& ip, hipStream_t s) {
-    hipLaunchKernelGGL(k_herm_start, dim3(herm_grid(p.n)), dim3(256), 0, s, p, ip);
+    const int64_t g = (p.n + 255) / 256;
+    hipLaunchKernelGGL(k_herm_start, dim3((unsigned)(g < 1024 ? g : 1024)), dim3(256), 0, s, p, ip);
 }
 
-void launch_herm_front(const HermParams& p, int parity, hipStream_t s) {
-    hipLaunchKernelGGL(k_herm_front, dim3(herm_grid(p.n)), dim3(256), 0, s, p, parity);
+void launch_herm_block(const HermParams& p, const IrrParams& ip, int b, hipStream_t s) {
+    const int64_t g = (p.n * kHermLanes + kHermT - 1) / kHermT;
+    hipLaunchKernelGGL(k_herm_block, dim3((unsigned)(g < kHermGrid ? g : kHermGrid)), dim3(kHermT), 0, s, p, ip, b);
 }
 
-void launch_herm_force_correct(const HermParams& p, const IrrParams& ip, int parity, hipStream_t s) {
-    hipLaunchKernelGGL(k_herm_force_correct, dim3(herm_grid(p.n)), dim3(256), 0, s, p, ip, parity);
+void launch_herm_finish(const HermParams& p, hipStream_t s) {
+    hipLaunchKernelGGL(k_herm_finish, dim3((unsigned)((p.n + 255) / 256)), dim3(256), 0, s, p);
 }
 
 void launch_add(int64_t n, const double* a, const double* b, double* out, hipStream_t s) {

@@ -128,9 +128,9 @@ struct pbh_ctx {
     struct {
         int64_t n = -1;
         int64_t last_n = 0;   // particles of the last integration
-        double *a = nullptr, *j = nullptr, *xp = nullptr, *vp = nullptr;
-        int64_t *tau = nullptr, *dt = nullptr, *dt0 = nullptr;
-        int32_t* act = nullptr;
+        double *a = nullptr, *j = nullptr;
+        double2* rec = nullptr;
+        int64_t* dt0 = nullptr;
         unsigned long long* ctl = nullptr;
         unsigned long long* lev = nullptr;
         int32_t* bucket = nullptr;
@@ -692,11 +692,9 @@ pbh_status ensure_herm(pbh_ctx* ctx, int64_t n) {
     h.idx = nullptr;
     const int nb = (int)std::min<int64_t>((n + 255) / 256, 4096);
     if (!halloc(ctx, &h.a, 3 * n) || !halloc(ctx, &h.j, 3 * n) ||
-        !halloc(ctx, &h.xp, 3 * n) || !halloc(ctx, &h.vp, 3 * n) ||
-        !halloc(ctx, &h.tau, n) || !halloc(ctx, &h.dt, n) || !halloc(ctx, &h.dt0, n) ||
-        !halloc(ctx, &h.act, n) ||
+        !halloc(ctx, &h.rec, 16 * n) || !halloc(ctx, &h.dt0, n) ||
         !halloc(ctx, &h.ctl, kHermCtl) || !halloc(ctx, &h.lev, kLevLen) ||
-        !halloc(ctx, &h.bucket, (int64_t)(kHermK + 1) * n) || !halloc(ctx, &h.slot, n) ||
+        !halloc(ctx, &h.bucket, 2 * (int64_t)(kHermK + 1) * n) || !halloc(ctx, &h.slot, n) ||
         !halloc(ctx, &h.fr, 3 * n) || !halloc(ctx, &h.potr, n) ||
         !halloc(ctx, &h.poti, n) || !halloc(ctx, &h.pott, n) || !halloc(ctx, &h.scr, 3 * n) ||
         !halloc(ctx, &h.epart, nb) || !halloc(ctx, &h.off, n + 1)) {
@@ -729,7 +727,7 @@ IrrParams herm_irr(pbh_ctx* ctx, int64_t n, double r_in, double r_out, double ep
 // One regular step of Hermite integration of F_I (see herm.hip), in place.
 constexpr int64_t kHermMaxBlocks = 1ll << 20;
 constexpr int kHermBatch = 16;   // blocks per graph launch
-static_assert(kHermBatch % 2 == 0, "block parity restarts at each batch");
+static_assert(kHermBatch % 4 == 0, "block numbers restart at each batch");
 
 pbh_status do_hermite(pbh_ctx* ctx, int64_t n, double* pos, double* vel, const double* mass,
                       const double* fr, double r_in, double r_out, double eps,
@@ -750,13 +748,9 @@ pbh_status do_hermite(pbh_ctx* ctx, int64_t n, double* pos, double* vel, const d
     hp.v = vel;
     hp.a = h.a;
     hp.j = h.j;
-    hp.xp = h.xp;
-    hp.vp = h.vp;
+    hp.rec = h.rec;
     hp.fr = fr;
-    hp.tau = h.tau;
-    hp.dt = h.dt;
     hp.dt0 = h.dt0;
-    hp.act = h.act;
     hp.ctl = h.ctl;
     if (!h.done) {
         HIP_TRY(hipHostMalloc((void**)&h.done, sizeof(unsigned long long), hipHostMallocCoherent));
@@ -776,11 +770,9 @@ pbh_status do_hermite(pbh_ctx* ctx, int64_t n, double* pos, double* vel, const d
     launch_zero_u64(h.lev, kLevLen, s);
     launch_herm_start(hp, ip, s);
     launch_zero_u64(h.ctl, kHermCtl, s);
-    ip.pos = h.xp;   // the block's force reads predicted states
-    ip.vel = h.vp;
     ip.acc = ip.jerk = nullptr;
     // Blocks run in batches of kHermBatch, each batch one graph launch. The
-    // front that finds every particle at the end sets a host flag; the host
+    // block that finds every particle at the end sets a host flag; the host
     // reads it once a batch has finished, while the next batch runs, so the GPU
     // does not wait for the host; the batch after the last busy one is empty.
     const std::vector<double> key = {(double)n, (double)(uintptr_t)pos, (double)(uintptr_t)vel,
@@ -794,10 +786,7 @@ pbh_status do_hermite(pbh_ctx* ctx, int64_t n, double* pos, double* vel, const d
         h.gkey.clear();
         hipStream_t cs = ctx->cap_stream;
         HIP_TRY(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-        for (int b = 0; b < kHermBatch; ++b) {   // kHermBatch is even: block parity b & 1
-            launch_herm_front(hp, b & 1, cs);
-            launch_herm_force_correct(hp, ip, b & 1, cs);
-        }
+        for (int b = 0; b < kHermBatch; ++b) launch_herm_block(hp, ip, b, cs);
         HIP_TRY(hipStreamEndCapture(cs, &h.graph));
         HIP_TRY(hipGraphInstantiate(&h.gexec, h.graph, nullptr, nullptr, 0));
         h.gkey = key;
@@ -816,6 +805,7 @@ pbh_status do_hermite(pbh_ctx* ctx, int64_t n, double* pos, double* vel, const d
         HIP_TRY(hipEventSynchronize(h.ev[batch & 1]));
         if (*flag) break;
     }
+    launch_herm_finish(hp, s);
     unsigned long long c[kHermCtl], err = 0;
     HIP_TRY(hipMemcpyAsync(c, h.ctl, sizeof(c), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipMemcpyAsync(&err, ctx->irr_err, sizeof(err), hipMemcpyDeviceToHost, s));

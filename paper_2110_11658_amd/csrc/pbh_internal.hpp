@@ -387,30 +387,25 @@ int64_t core_bsum_len(int64_t n);
 
 // herm.hip: Hermite integration of F_I with block steps over one regular step
 constexpr int kHermK = 40;   // block steps dt_max / 2^k, k <= kHermK; times in ticks of dt_max / 2^kHermK
-enum { kHermTn = 0, kHermNact = 1, kHermSteps = 2, kHermKmax = 3, kHermDone = 4, kHermBlocks = 5,
-       kHermCtl = 6 };
-// level bookkeeping, two slots by block parity: bucket counts, appends of the
-// last corrector, block time, k* of the last block
-enum { kLevCnt = 0, kLevNew = 128, kLevT = 256, kLevKs = 258, kLevLen = 260 };
+enum { kHermSteps = 0, kHermKmax = 1, kHermDone = 2, kHermBlocks = 3, kHermCtl = 4 };
+// level bookkeeping: bucket counts (two slots), appends of the correctors (four),
+// then block time, k* of the last block and bucket buffer per level (two each)
+enum { kLevCnt = 0, kLevNew = 128, kLevT = 384, kLevKs = 386, kLevMask = 388, kLevLen = 390 };
 struct HermParams {
     int64_t n = 0;
     double* x = nullptr;         // [n][3] positions (caller's, updated in place)
     double* v = nullptr;         // [n][3] velocities (caller's, updated in place)
-    double* a = nullptr;         // [n][3] F_I at tau_i
-    double* j = nullptr;         // [n][3] dF_I/dt at tau_i
-    double* xp = nullptr;        // [n][3] predicted
-    double* vp = nullptr;
+    double* a = nullptr;         // [n][3] F_I at the start
+    double* j = nullptr;         // [n][3] dF_I/dt at the start
+    double2* rec = nullptr;      // [2][n] records of 128 bytes (state, mass, time and step in ticks)
     const double* fr = nullptr;  // [n][3] regular force (step criterion), or null
-    int64_t* tau = nullptr;      // [n] ticks
-    int64_t* dt = nullptr;       // [n] ticks
-    int64_t* dt0 = nullptr;      // [n] first step of the regular step (ticks), or null
-    int32_t* act = nullptr;      // [n] active list
+    int64_t* dt0 = nullptr;      // [n] first step of the regular step (ticks)
     unsigned long long* ctl = nullptr;   // [kHermCtl]
     unsigned long long* lev = nullptr;   // [kLevLen]
-    int32_t* bucket = nullptr;           // [kHermK + 1][n] particles by level
+    int32_t* bucket = nullptr;           // [2][kHermK + 1][n] particles by level
     uint32_t* slot = nullptr;            // [n] per-item level and rank (bucket moves)
     unsigned long long* done_host = nullptr;   // host-coherent pinned flag, set once all are at tend
-    const int64_t* off = nullptr;        // neighbour lists (members are predicted with the active)
+    const int64_t* off = nullptr;        // neighbour lists
     const int32_t* idx = nullptr;
     int64_t cap = 0;
     unsigned long long tend = 0; // ticks of one regular step: 2^(kHermK + 2)
@@ -421,10 +416,9 @@ struct HermParams {
 // first steps (eq. dt with the computed second and third derivatives of F_I;
 // ip: masses, radii and softening of the irregular force, and its error word)
 void launch_herm_start(const HermParams& p, const IrrParams& ip, hipStream_t s);
-// one block: front (next time, active list, prediction), then the irregular
-// force of the active list with the corrector; parity = block number & 1
-void launch_herm_front(const HermParams& p, int parity, hipStream_t s);
-void launch_herm_force_correct(const HermParams& p, const IrrParams& ip, int parity, hipStream_t s);
+// one block, number b of its batch (batches hold a multiple of four blocks)
+void launch_herm_block(const HermParams& p, const IrrParams& ip, int b, hipStream_t s);
+void launch_herm_finish(const HermParams& p, hipStream_t s);
 void launch_add(int64_t n, const double* a, const double* b, double* out, hipStream_t s);
 
 // kdk.hip
