@@ -131,6 +131,33 @@ def test_hermite_larger_n(n, seed, T):
     assert np.abs(gv - ov).max() <= 1e-10 * np.abs(ov).max()
 
 
+@pytest.mark.parametrize("copies", [16, 17])
+def test_hermite_one_lane_per_list(copies):
+    # copies of one set of 2048 particles, each with its own lists: up to 32768
+    # active particles a block gives eight lanes to a list, beyond one; both
+    # take the oracle's schedule for the set, and every copy the same states
+    n = 2048
+    print(f"hermite copies={copies}", flush=True)
+    c, r_in, r_out = _setup(n, 96, 16.0)
+    eps, T, eta = 1e-4, 1.0 / 32, 0.02
+    r_buff = 3.0 * np.linalg.norm(c.vel, axis=1).max() * T
+    o_off, o_idx = oracle.nbr_brute(c.pos, r_out + r_buff)
+    ofr, _ = oracle.direct(c.pos, c.mass, r_in, r_out, eps)
+    ox, ov, ost = oracle.hermite(c.pos, c.vel, c.mass, r_in, r_out, eps, T, eta=eta, fr=ofr)
+    m = o_idx.size
+    off = np.concatenate([[0]] + [o_off[1:] + k * m for k in range(copies)]).astype(np.int64)
+    idx = np.concatenate([o_idx + k * n for k in range(copies)]).astype(np.int32)
+    pos, vel = _t(np.tile(c.pos, (copies, 1))), _t(np.tile(c.vel, (copies, 1)))
+    p = _pbh(prec="fp64")
+    st = p.hermite(pos, vel, _t(np.tile(c.mass, copies)), _t(np.tile(ofr, (copies, 1))), r_in, r_out, eps,
+                   _t(off), _t(idx), T, eta)
+    assert st["blocks"] == ost["blocks"] and st["kmax"] == ost["kmax"] and st["steps"] == copies * ost["steps"]
+    gx, gv = pos.cpu().numpy().reshape(copies, n, 3), vel.cpu().numpy().reshape(copies, n, 3)
+    assert (gx == gx[0]).all() and (gv == gv[0]).all()
+    assert np.abs(gx[0] - ox).max() <= 1e-10 * np.abs(ox).max()
+    assert np.abs(gv[0] - ov).max() <= 1e-10 * np.abs(ov).max()
+
+
 def test_p3t_larger_n():
     print("p3t n=1536", flush=True)
     c, r_in, r_out = _setup(1536, 98, 12.0)
