@@ -28,7 +28,13 @@ namespace pbh {
 
 namespace {
 
-constexpr int kCoreStack = 2048;   // LDS traversal stack of one wave (overflow is flagged)
+// LDS traversal stack of one wave. A round takes as many nodes as leave kCoreDeep
+// entries free with all their children on it, so a full stack is worked off a node
+// at a time, which needs 7 entries a level. The search waits for the loads of its
+// rounds, so waves in flight set its rate: 2048 entries without that rule let 18
+// share a CU, 1024 let 32 (2^20 particles, 72407 samples: 312 -> 228 us).
+constexpr int kCoreStack = 1024;
+constexpr int kCoreDeep = 256;     // > 7 levels x 21 + 8
 
 struct CoreParams {
     int64_t n;
@@ -51,12 +57,30 @@ __device__ inline double pair_r2(double xj, double yj, double zj, double xi, dou
     return dx * dx + dy * dy + dz * dz;
 }
 
+// smaller of v and the value DPP control CTRL brings from another lane (lanes
+// whose source lies outside keep their own)
+template <int CTRL, int ROWS>
+__device__ inline unsigned long long dpp_min_u64(unsigned long long v) {
+    const int lo = (int)(unsigned)v, hi = (int)(unsigned)(v >> 32);
+    const unsigned l = (unsigned)__builtin_amdgcn_update_dpp(lo, lo, CTRL, ROWS, 0xf, false);
+    const unsigned h = (unsigned)__builtin_amdgcn_update_dpp(hi, hi, CTRL, ROWS, 0xf, false);
+    const unsigned long long w = (unsigned long long)h << 32 | l;
+    return w < v ? w : v;
+}
+
+// minimum over the wave, in every lane: within rows of 16 lanes by row shifts,
+// then across the rows by row broadcasts into lane 63 (an exchange through LDS for
+// each of the six steps took four times as long)
 __device__ inline unsigned long long wave_min_u64(unsigned long long v) {
-    for (int o = 32; o > 0; o >>= 1) {
-        const unsigned long long w = __shfl_xor(v, o, 64);
-        v = w < v ? w : v;
-    }
-    return v;
+    v = dpp_min_u64<0x111, 0xf>(v);   // row_shr:1
+    v = dpp_min_u64<0x112, 0xf>(v);   // row_shr:2
+    v = dpp_min_u64<0x114, 0xf>(v);   // row_shr:4
+    v = dpp_min_u64<0x118, 0xf>(v);   // row_shr:8
+    v = dpp_min_u64<0x142, 0xa>(v);   // row_bcast:15
+    v = dpp_min_u64<0x143, 0xc>(v);   // row_bcast:31
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)v, 63);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(v >> 32), 63);
+    return (unsigned long long)hi << 32 | lo;
 }
 
 __device__ inline int wave_min_i32(int v) {
@@ -67,52 +91,67 @@ __device__ inline int wave_min_i32(int v) {
     return v;
 }
 
-// The wave's current 6 nearest (wave-uniform), ascending by (r^2, index).
+// value of another lane, as the compiler's lane reads take 32 bits
+__device__ inline double lane_f64(double v, int lane) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, lane);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), lane);
+    return __longlong_as_double((long long)((unsigned long long)hi << 32 | lo));
+}
+
+// value of the lane before (lane 0 of each row of 16 keeps its own)
+__device__ inline int from_lane_before(int v) {
+    return __builtin_amdgcn_update_dpp(v, v, 0x111, 0xf, 0xf, false);   // row_shr:1
+}
+
+// The wave's current 6 nearest, ascending by (r^2, index): lane t < 6 holds entry
+// t, empty entries are infinitely far with an index above any. An insertion is one
+// comparison in all lanes and a shift by one lane (the whole list in every lane,
+// with static selections, took 250 us against 228 at 2^20 particles, 72407
+// samples).
 struct Top6 {
-    double d[6];
-    int id[6];
-    int cnt;
-    __device__ double bound() const { return cnt < 6 ? __builtin_inf() : d[5]; }
+    double d = __builtin_inf();
+    int id = 0x7fffffff;
+    double d5 = __builtin_inf();   // entry 5, in every lane
+    int id5 = 0x7fffffff;
     // (r2, j) would enter the list
-    __device__ bool better(double r2, int j) const {
-        if (cnt < 6) return true;
-        return r2 < d[5] || (r2 == d[5] && j < id[5]);
-    }
-    __device__ bool has(int j) const {
-        bool h = false;
-        for (int t = 0; t < 6; ++t) h |= (t < cnt) && id[t] == j;
-        return h;
-    }
-    // insert at the rank of (r2, j), shifting the rest up (static indices only,
-    // so the list stays in registers); the 7th entry falls off
+    __device__ bool better(double r2, int j) const { return r2 < d5 || (r2 == d5 && j < id5); }
+    // insert the wave-uniform (r2, j); the 7th entry falls off
     __device__ void insert(double r2, int j) {
-        int pos = 0;
-#pragma unroll
-        for (int t = 0; t < 6; ++t)
-            pos += (t < cnt && (d[t] < r2 || (d[t] == r2 && id[t] < j))) ? 1 : 0;
-#pragma unroll
-        for (int t = 5; t > 0; --t) {
-            d[t] = t > pos ? d[t - 1] : (t == pos ? r2 : d[t]);
-            id[t] = t > pos ? id[t - 1] : (t == pos ? j : id[t]);
-        }
-        if (pos == 0) {
-            d[0] = r2;
-            id[0] = j;
-        }
-        cnt = cnt < 6 ? cnt + 1 : 6;
+        const int lane = threadIdx.x;
+        const uint64_t before = __ballot(d < r2 || (d == r2 && id < j)) & 0x3full;
+        const int pos = __popcll(before);
+        const unsigned long long b = (unsigned long long)__double_as_longlong(d);
+        const unsigned lo = (unsigned)from_lane_before((int)(unsigned)b);
+        const unsigned hi = (unsigned)from_lane_before((int)(unsigned)(b >> 32));
+        const int idb = from_lane_before(id);
+        const double db = __longlong_as_double((long long)((unsigned long long)hi << 32 | lo));
+        d = lane > pos ? db : (lane == pos ? r2 : d);
+        id = lane > pos ? idb : (lane == pos ? j : id);
+        d5 = lane_f64(d, 5);
+        id5 = __builtin_amdgcn_readlane(id, 5);
     }
-    // merge the lanes' candidates (valid lanes with distance r2, index j):
-    // the wave minimum enters until no candidate beats the 6th entry
+    // merge the lanes' candidates (valid lanes with distance r2, index j, each
+    // particle once in a search): the nearest enters until none beats entry 5
     __device__ void merge(bool valid, double r2, int j) {
-        bool c = valid && !has(j);
+        bool c = valid;
         for (int it = 0; it < 6; ++it) {
             c = c && better(r2, j);
-            if (!__ballot(c)) return;
-            const unsigned long long key = c ? (unsigned long long)__double_as_longlong(r2) : ~0ull;
-            const unsigned long long mk = wave_min_u64(key);
-            const int mj = wave_min_i32((c && key == mk) ? j : 0x7fffffff);
-            insert(__longlong_as_double((long long)mk), mj);
-            c = c && !(key == mk && j == mj);
+            uint64_t who = __ballot(c);
+            if (!who) return;
+            if (who & (who - 1)) {   // several: the nearest, of equal ones the lowest index
+                const unsigned long long key = c ? (unsigned long long)__double_as_longlong(r2) : ~0ull;
+                const unsigned long long mk = wave_min_u64(key);
+                const bool at = c && key == mk;
+                who = __ballot(at);
+                if (who & (who - 1)) {
+                    const int mj = wave_min_i32(at ? j : 0x7fffffff);
+                    who = __ballot(at && j == mj);
+                }
+            }
+            const int l = __ffsll((unsigned long long)who) - 1;
+            insert(lane_f64(r2, l), __builtin_amdgcn_readlane(j, l));
+            c = c && (int)threadIdx.x != l;
         }
     }
 };
@@ -132,16 +171,11 @@ __global__ __launch_bounds__(64) void k_core_knn(CoreParams p) {
     const int64_t k = p.rank[i];
     const double xi = p.x[k], yi = p.y[k], zi = p.z[k];
     Top6 T;
-    T.cnt = 0;
-    for (int t = 0; t < 6; ++t) {
-        T.d[t] = 0.0;
-        T.id[t] = 0;
-    }
     // seed: the 64 key positions around i (n >= 7 gives at least 6 others)
+    int64_t lo = k - 32;
+    if (lo + 64 > p.n) lo = p.n - 64;
+    if (lo < 0) lo = 0;
     {
-        int64_t lo = k - 32;
-        if (lo + 64 > p.n) lo = p.n - 64;
-        if (lo < 0) lo = 0;
         const int64_t q = lo + lane;
         const bool ok = q < p.n && q != k;
         const int64_t qq = q < p.n ? q : k;
@@ -154,7 +188,8 @@ __global__ __launch_bounds__(64) void k_core_knn(CoreParams p) {
     int top = 1;
     while (top > 0) {
         __syncthreads();
-        const int npop = uni(top < 64 ? top : 64);
+        const int room = (kCoreStack - kCoreDeep - top) / 7;
+        const int npop = uni(min(top, room < 1 ? 1 : (room < 64 ? room : 64)));
         top -= npop;
         const bool has = lane < npop;
         const int nd = has ? s_stack[top + lane] : 0;
@@ -164,7 +199,7 @@ __global__ __launch_bounds__(64) void k_core_knn(CoreParams p) {
         const int4 rg = p.node.range(nd);
         w.begin = rg.x; w.count = rg.y; w.first_child = rg.z; w.nchild = rg.w;
         const double c[3] = {xi, yi, zi};
-        const bool open = has && !(box_pt_d2(w.lo, w.hi, c) > T.bound());
+        const bool open = has && !(box_pt_d2(w.lo, w.hi, c) > T.d5);
         const bool leaf = w.nchild == 0;
         const int nch = (open && !leaf) ? w.nchild : 0;
         const int incl = wave_incl_scan(nch, lane);
@@ -193,16 +228,18 @@ __global__ __launch_bounds__(64) void k_core_knn(CoreParams p) {
             const bool ok = sidx < total;
             const int64_t q = ok ? (int64_t)s_beg[f] + (sidx - s_ex[f]) : k;
             const double r2 = pair_r2(p.x[q], p.y[q], p.z[q], xi, yi, zi);
-            T.merge(ok && q != k, r2, p.perm[q]);
+            T.merge(ok && (uint64_t)(q - lo) >= 64, r2, p.perm[q]);   // (the seed's are merged already)
         }
     }
     if (overflow) atomicOr(p.err, lane == 0 ? kCoreStackFull : 0ull);
-    if (lane == 0) {
+    {
 #pragma clang fp contract(off)
+        const double m = lane < 5 ? p.mass[T.id] : 0.0;
         double m5 = 0.0;
-        for (int t = 0; t < 5; ++t) m5 += p.mass[T.id[t]];
-        const double r6 = sqrt(T.d[5]);
-        p.rho[s] = overflow ? __builtin_nan("") : m5 / (4.0 / 3.0 * 3.14159265358979323846 * (T.d[5] * r6));
+        for (int t = 0; t < 5; ++t) m5 += lane_f64(m, t);
+        const double r6 = sqrt(T.d5);
+        if (lane == 0)
+            p.rho[s] = overflow ? __builtin_nan("") : m5 / (4.0 / 3.0 * 3.14159265358979323846 * (T.d5 * r6));
     }
 }
 
@@ -396,69 +433,82 @@ __global__ __launch_bounds__(kCrossBlk) void k_core_bsum(int64_t n, const int32_
     if (threadIdx.x == 0) bsum[blockIdx.x] = red[0];
 }
 
+// Replaces v[0 .. e - 1] by its running sums, added in order to cum, and returns
+// the last (one thread; v holds zeros from e to the next multiple of 16). The
+// chain of additions sets the pace: the next 16 values are read while it runs and
+// no branch or comparison stands in it.
+__device__ inline double run_in_order(double* v, int e, double cum) {
+    double x[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) x[u] = v[u];
+    for (int k0 = 0; k0 < e; k0 += 16) {
+        double nx[16];
+        const int k1 = k0 + 16 < e ? k0 + 16 : k0;
+#pragma unroll
+        for (int u = 0; u < 16; ++u) nx[u] = v[k1 + u];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            cum += x[u];
+            x[u] = cum;
+        }
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            v[k0 + u] = x[u];
+            x[u] = nx[u];
+        }
+    }
+    return cum;
+}
+
 // Half-mass radius (first distance at which the running mass reaches half the
-// total, scanning blocks then one block in order) and the regularisation
-// parameters. The scans are serial (thread 0, in order) over values that the
-// workgroup first stages in LDS, kCrossBlk at a time.
+// total) and the regularisation parameters, in one workgroup. Running sums are
+// taken in order by one thread, kCrossBlk values at a time in LDS: of the block
+// sums (left in bsum) and, once every thread has looked for the half among
+// those, of the masses of the block that holds it. Searching while summing, one
+// value read at a time, and a second pass of sums took 110 us at 2^20, this 34.
 __global__ __launch_bounds__(kCrossBlk) void k_core_final(int64_t n, int64_t nblk, const int32_t* __restrict__ order,
                                                           const uint64_t* __restrict__ key,
-                                                          const double* __restrict__ mass,
-                                                          const double* __restrict__ bsum,
+                                                          const double* __restrict__ mass, double* __restrict__ bsum,
                                                           const unsigned long long* ncore, double eta,
                                                           double* __restrict__ st) {
 #pragma clang fp contract(off)
     __shared__ double v[kCrossBlk];
-    __shared__ double s_tot, s_acc;
-    __shared__ int64_t s_b;
-    __shared__ int s_found;
+    __shared__ double s_cum;
+    __shared__ unsigned long long s_b, s_k;
     const int t = threadIdx.x;
     if (t == 0) {
-        s_tot = 0.0;
-        s_acc = 0.0;   // running mass of whole blocks before s_b
-        s_b = 0;
-        s_found = 0;
+        s_cum = 0.0;
+        s_b = (unsigned long long)(nblk - 1);
     }
-    for (int64_t c0 = 0; c0 < nblk; c0 += kCrossBlk) {   // total mass
+    for (int64_t c0 = 0; c0 < nblk; c0 += kCrossBlk) {
+        const bool in = c0 + t < nblk;
+        v[t] = in ? bsum[c0 + t] : 0.0;
         __syncthreads();
-        v[t] = c0 + t < nblk ? bsum[c0 + t] : 0.0;
+        if (t == 0) s_cum = run_in_order(v, nblk - c0 < kCrossBlk ? (int)(nblk - c0) : kCrossBlk, s_cum);
         __syncthreads();
-        if (t == 0) {
-            double m = s_tot;
-            const int64_t e = nblk - c0 < kCrossBlk ? nblk - c0 : kCrossBlk;
-            for (int64_t k = 0; k < e; ++k) m += v[k];
-            s_tot = m;
+        if (in) bsum[c0 + t] = v[t];
+        __syncthreads();
+    }
+    const double half = 0.5 * s_cum;
+    // the first block whose running sum is not below the half, or the last one
+    for (int64_t k = t; k < nblk - 1; k += kCrossBlk)
+        if (!(bsum[k] < half)) {
+            atomicMin(&s_b, (unsigned long long)k);
+            break;
         }
-    }
     __syncthreads();
-    const double half = 0.5 * s_tot;
-    for (int64_t c0 = 0; c0 < nblk; c0 += kCrossBlk) {   // block holding the half-mass point
-        __syncthreads();
-        if (s_found) break;   // workgroup-uniform
-        v[t] = c0 + t < nblk ? bsum[c0 + t] : 0.0;
-        __syncthreads();
-        if (t == 0) {
-            double cum = s_acc;
-            int64_t b = c0;
-            const int64_t e = c0 + kCrossBlk < nblk ? c0 + kCrossBlk : nblk;
-            while (b < nblk - 1 && b < e && cum + v[b - c0] < half) cum += v[(b++) - c0];
-            s_acc = cum;
-            s_b = b;
-            s_found = b < e;   // stopped inside this chunk (or at the last block)
-        }
-    }
+    const int64_t b = (int64_t)s_b;
+    const int64_t beg = b * kCrossBlk;
+    const int len = (int)((b + 1) * kCrossBlk < n ? kCrossBlk : n - beg);
+    v[t] = t < len ? mass[order[beg + t]] : 0.0;
+    if (t == 0) s_k = (unsigned long long)(len - 1);
     __syncthreads();
-    const int64_t b = s_b;
-    const int64_t beg = b * kCrossBlk, end = (b + 1) * kCrossBlk < n ? (b + 1) * kCrossBlk : n;
-    v[t] = beg + t < end ? mass[order[beg + t]] : 0.0;
+    if (t == 0) run_in_order(v, len, b > 0 ? bsum[b - 1] : 0.0);
+    __syncthreads();
+    if (t < len - 1 && v[t] >= half) atomicMin(&s_k, (unsigned long long)t);
     __syncthreads();
     if (t == 0) {
-        double cum = s_acc;
-        int64_t kk = beg;
-        for (; kk < end - 1; ++kk) {
-            cum += v[kk - beg];
-            if (cum >= half) break;
-        }
-        const double rh = sqrt(__longlong_as_double((long long)key[kk]));
+        const double rh = sqrt(__longlong_as_double((long long)key[beg + (int64_t)s_k]));
         const double rmin = 4.0 * rh / ((double)n * cbrt(st[3]));
         st[5] = (double)*ncore;
         st[6] = rh;
@@ -499,7 +549,7 @@ void launch_core(const CoreLaunch& c, hipStream_t s) {
     hipLaunchKernelGGL(k_core_bsum, dim3((unsigned)nblk), dim3(kCrossBlk), 0, s, n, (const int32_t*)c.vals,
                        c.mass, c.bsum);
     hipLaunchKernelGGL(k_core_final, dim3(1), dim3(kCrossBlk), 0, s, n, nblk, (const int32_t*)c.vals,
-                       (const uint64_t*)c.keys, c.mass, (const double*)c.bsum,
+                       (const uint64_t*)c.keys, c.mass, c.bsum,
                        (const unsigned long long*)c.ncore, c.eta, c.stats);
 }
 

@@ -89,6 +89,21 @@ def test_core_ties_and_small_inputs():
     _check(pos7, m7, smp7, rho7.cpu().numpy(), got7)
 
 
+@pytest.mark.parametrize("n,seed", [(8, 81), (64, 82), (1024, 83), (1025, 84), (2065, 85)])
+def test_core_half_mass_scan_edges(n, seed):
+    # one particle short of, at and past the blocks of the running mass; most of
+    # the mass in the outermost particles, so that the scan reaches the last block
+    rng = np.random.default_rng(seed)
+    pos = rng.normal(size=(n, 3))
+    mass = np.where((pos ** 2).sum(1) >= np.sort((pos ** 2).sum(1))[-3], float(n), 1.0)
+    smp = np.arange(n, dtype=np.int32)
+    p = _pbh()
+    pos_d, mass_d = _t(pos), _t(mass)
+    p.build(pos_d, mass_d)
+    rho, got = p.core(pos_d, mass_d, _t(smp))
+    _check(pos, mass, smp, rho.cpu().numpy(), got)
+
+
 def test_core_full_size_sampled():
     # the 2^20 Plummer/Kroupa workload with the paper's sample size
     # (sqrt(5000 N) = 72 407 particles); the oracle's O(S N) search checks 512
