@@ -29,12 +29,14 @@
 // those derivatives gives the first step; dt_max where its denominator is 0
 // (no pair inside r_out). Expressions are evaluated as written (no contraction).
 //
-// A block is one launch: the next block time and its active particles from the
-// level counts, prediction of each active particle and its list members in
+// A block is at most one launch: the next block time and its active particles from
+// the level counts, prediction of each active particle and its list members in
 // registers, force, corrector, new step, move to the new bucket. Particles are
-// kept in one bucket per level, so it does not pass over all n particles.
+// kept in one bucket per level, so it does not pass over all n particles. Blocks of
+// few particles, which are most, follow one another inside one workgroup.
 #include "irr_pair.hpp"
 #include "pbh_internal.hpp"
+#include "wave.hpp"
 
 namespace pbh {
 
@@ -58,24 +60,40 @@ __device__ inline double norm3(double x, double y, double z) {
 // >= k* - 1 (the step at most doubles): buckets >= k* are refilled from zero
 // and bucket k* - 1 is appended to.
 //
-// No launch reads what it writes. Level counts, block time and k* have two slots
-// by block parity q: a block reads slot q and writes q ^ 1. The counts of the
-// corrected particles per level (new) have four by block number: a block reads
-// its own, which the block before filled, appends to the next and clears the one
-// after that. Buckets of the active levels are read from one of two buffers
+// No workgroup reads what another one of its launch writes. Level counts, block
+// time and k* have two slots by launch parity q: a launch reads slot q and writes
+// q ^ 1. The counts of the corrected particles per level (new) have four by launch
+// number: a launch reads its own, which the one before filled, appends to the next
+// and clears the one after that. Buckets of the active levels are read from one of two buffers
 // (bit k of the mask) and refilled in the other. And a particle's state has two
 // records: a block reads the newest with a time before its own, and writes the
 // corrected state over the older one, whose time (old or, once written, the
 // block's own) never qualifies, so members that are corrected at the same moment
 // are read as they were.
 //
-// Blocks are enqueued in batches without waiting; once every particle has
-// reached the end of the regular step the remaining blocks are empty
-// (kHermDone), and the block that finds it also sets a host-visible flag,
+// A launch's first block may have any number of active particles. If they are few
+// (kHermSolo), workgroup 0 takes them all, the others end, and it goes on with the
+// following blocks as long as those are few as well, with nothing between them but
+// a barrier of the workgroup; it stops before a large block and leaves the counts
+// for the next launch. Deep levels hold few particles and make most of the blocks:
+// of 617 in a regular step at 2^20 three quarters have at most 18 active. A block
+// is a chain of dependent loads (bucket entry, list bounds, list entry, the times of
+// the member's records, its record) and the corrector's divisions and roots, about
+// 4 us in a row of small blocks; one of a launch of its own takes 7 to 12 us, and
+// took 19 when prediction and force were two launches (regular step at 2^20 with two
+// forces: 28.2 -> 20.6 ms; 16384 particles: 2.87 -> 1.23 ms). Two records side by
+// side and the record's number in the bucket entry leave out one load and most
+// of the address misses (22.0 -> 21.0 ms).
+//
+// Launches are enqueued in batches without waiting; once every particle has
+// reached the end of the regular step the remaining launches are empty
+// (kHermDone), and the one that finds it also sets a host-visible flag,
 // which the host reads after a batch while the next one runs.
 constexpr int kHermT = 512;       // threads per workgroup of a block
 constexpr int kHermGrid = 512;    // workgroups
 constexpr int kHermLanes = 8;     // lanes per active particle while that fits the grid, else one
+constexpr int kHermSolo = 128;    // active particles of a block that one workgroup takes (64: the same time, 256: 1 % more)
+constexpr int kHermInner = 64;    // blocks in a launch at most
 constexpr int kSlotShift = 26;    // per-item scratch: level << 26 | rank in its workgroup
 constexpr uint32_t kSlotMask = (1u << kSlotShift) - 1;
 static_assert(kHermK < 63, "levels fit one wave");
@@ -114,15 +132,21 @@ __device__ inline void store_state(double2* r, const HermState& s) {
     r[7] = make_double2(__longlong_as_double((long long)s.dt), 0.0);
 }
 
-constexpr int kRecPieces = 8;
+// Record `buf` (0 or 1) of particle i; the two are neighbours.
+__device__ inline double2* record(const HermParams& p, int64_t i, int buf) { return p.rec + 8 * (2 * i + buf); }
 
-// The record of particle i to read at block time tn: the newest with an earlier
-// time (buffer 0 or 1).
+__device__ inline int64_t record_time(const HermParams& p, int64_t i, int buf) {
+    return __double_as_longlong(record(p, i, buf)[6].y);
+}
+
+// The record of particle i to read at block time tn: the newest with an earlier time.
 __device__ inline int state_buffer(const HermParams& p, int64_t i, int64_t tn) {
-    const int64_t t0 = __double_as_longlong(p.rec[kRecPieces * i + 6].y);
-    const int64_t t1 = __double_as_longlong(p.rec[kRecPieces * (p.n + i) + 6].y);
+    const int64_t t0 = record_time(p, i, 0), t1 = record_time(p, i, 1);
     return t1 < tn && (t0 >= tn || t1 > t0) ? 1 : 0;
 }
+
+// A bucket entry: the particle, and in the sign bit which record holds its state.
+constexpr int32_t kInRec1 = (int32_t)0x80000000;
 
 // The predicted position and velocity at time tn (the P3T predictor).
 __device__ inline void predict(const HermParams& p, const HermState& s, int64_t tn, double* xp, double* vp) {
@@ -135,23 +159,18 @@ __device__ inline void predict(const HermParams& p, const HermState& s, int64_t 
     }
 }
 
-// The count of level k (lane k of a wave) after merging the appends of the block
-// before; `add` returns those appends.
-__device__ inline long long merged_count(const HermParams& p, int b, int k, long long& add) {
-    add = 0;
-    if (k > kHermK) return 0;
-    const int kp = (int)p.lev[kLevKs + (b & 1)];   // k* of the previous block
-    const long long old = (long long)lev_cnt(p, b & 1)[k];
-    add = (long long)lev_new(p, b)[k];
-    return k >= kp ? add : (k == kp - 1 ? old + add : old);
+// The count of level k after a block that took the levels >= ks, from the count
+// before it and the corrected particles `add` it left on the level.
+__device__ inline long long merged_count(long long old, long long add, int ks, int k) {
+    return k >= ks ? add : (k == ks - 1 ? old + add : old);
 }
 
 // The next block from the level counts (one wave, lane k holding count c of
 // level k) and the current time t: its time tn, k*, the number of active
-// particles and lane k's offset in the active list (levels >= k* in order).
+// particles and lane k's end in the active list (levels >= k* in order).
 struct BlockPlan {
-    long long tn, nact, off;
-    int ks;
+    long long tn;
+    int nact, end, ks;
     bool done;
 };
 
@@ -164,14 +183,10 @@ __device__ inline BlockPlan plan_block(long long c, long long t, unsigned long l
     b.tn = b.done ? (long long)tend : (((t >> sh) + 1) << sh);
     const int tz = __ffsll((unsigned long long)b.tn) - 1;
     b.ks = b.done ? kHermK + 1 : (tz >= kHermK ? 0 : kHermK - tz);
-    const long long a = k >= b.ks ? c : 0;
-    long long incl = a;
-    for (int o = 1; o < 64; o <<= 1) {
-        const long long w = __shfl_up(incl, o, 64);
-        if (k >= o) incl += w;
-    }
-    b.nact = __shfl(incl, 63, 64);
-    b.off = incl - a;
+    const int a = k >= b.ks ? (int)c : 0;   // (n < 2^31)
+    const int incl = wave_incl_scan(a, k);
+    b.nact = last_lane(incl);
+    b.end = incl;
     return b;
 }
 
@@ -180,31 +195,41 @@ __device__ inline int32_t* bucket_of(const HermParams& p, int buf, int k) {
 }
 
 // entry t of the active list: level buckets ks, ks + 1, ... in turn, each in the
-// buffer of its mask bit
-__device__ inline int32_t active_at(const HermParams& p, const long long* off, const long long* cnt, int ks,
-                                    uint64_t mask, long long t) {
-    int k = ks;
-    while (k < kHermK && t >= off[k] + cnt[k]) ++k;
-    return bucket_of(p, (int)((mask >> k) & 1), k)[t - off[k]];
+// buffer of its mask bit. end[k]: entries of levels up to k (0 below ks); its 16
+// groups of four are read until one ends past t.
+__device__ inline int32_t active_at(const HermParams& p, const int4* end, int ks, uint64_t mask, int t) {
+    int k = ks & ~3, first = 0;
+    int4 e = end[k >> 2];
+    while (e.w <= t) {   // t < nact = end[63]
+        first = e.w;
+        k += 4;
+        e = end[k >> 2];
+    }
+    if (t >= e.z) { k += 3; first = e.z; }
+    else if (t >= e.y) { k += 2; first = e.y; }
+    else if (t >= e.x) { k += 1; first = e.x; }
+    return bucket_of(p, (int)((mask >> k) & 1), k)[t - first];
 }
 
 // Each workgroup takes one contiguous chunk of the n_items items (a multiple of
-// its lane groups, so a small set is one workgroup): `step(k, i)` advances item k
-// (the particle i = item(k)) and returns its new level in lane 0 of its group of
-// LH lanes; the workgroup ranks its items per level in LDS, reserves room in each
+// its lane groups, so a small set is one workgroup): `step(have, i, buf)` advances
+// the particle of bucket entry item(k), whose state is in record buf, to the other
+// record and returns its new level in lane 0 of its group of LH lanes; the workgroup ranks its items per level in LDS, reserves room in each
 // bucket with one device atomic per level (buckets >= ks restart from zero in
 // their other buffer, bucket ks - 1 keeps its `keep` members), then stores the
 // particles there. Same-address device atomics serialise, so one per workgroup
-// and level, not per wave; a workgroup that holds every item stores its counts
-// without atomics. `step` runs in every lane of a wave that holds an item.
-template <int LH, int T, class Item, class Step>
+// and level, not per wave. SOLO: the calling workgroup takes every item and
+// newcnt, 64 counts, is LDS memory that it sets. `step` runs in every lane of a
+// wave that holds an item.
+template <int LH, int T, bool SOLO, class Item, class Step>
 __device__ inline void step_and_bucket(const HermParams& p, unsigned long long* newcnt, int ks, long long keep_cnt,
                                        uint64_t mask_new, int64_t n_items, Item item, Step step) {
     constexpr int TG = T / LH;
     __shared__ int s_h[64];
     __shared__ long long s_b[64];
     const int64_t per = ((n_items + gridDim.x - 1) / gridDim.x + TG - 1) / TG * TG;
-    const int64_t c0 = (int64_t)blockIdx.x * per, c1 = c0 + per < n_items ? c0 + per : n_items;
+    const int64_t c0 = SOLO ? 0 : (int64_t)blockIdx.x * per;
+    const int64_t c1 = SOLO || c0 + per > n_items ? n_items : c0 + per;
     if (c0 >= c1) return;   // workgroup-uniform
     if (threadIdx.x < 64) s_h[threadIdx.x] = 0;
     __syncthreads();
@@ -217,8 +242,8 @@ __device__ inline void step_and_bucket(const HermParams& p, unsigned long long* 
         const int64_t k = k0 + tg;
         const bool have = k < c1;
         if (__ballot(have) == 0) break;   // this wave holds no more items
-        const int32_t i = have ? item(k) : -1;
-        const int level = step(i);
+        const int32_t i = have ? item(k) : 0;
+        const int level = step(have, i & ~kInRec1, i & kInRec1 ? 1 : 0);
         if (have && head) {
             const int r = atomicAdd(&s_h[level], 1);
             if (k0 == c0) {
@@ -231,19 +256,19 @@ __device__ inline void step_and_bucket(const HermParams& p, unsigned long long* 
         }
     }
     __syncthreads();
-    if (threadIdx.x <= kHermK && s_h[threadIdx.x] > 0) {
-        const int k = threadIdx.x;
-        const long long keep = k == ks - 1 ? keep_cnt : 0;
-        if (c0 == 0 && c1 == n_items) {   // the only workgroup with items: no other appends
-            s_b[k] = keep;
+    if (SOLO) {
+        if (threadIdx.x < 64) {
+            const int k = threadIdx.x;
+            s_b[k] = k == ks - 1 ? keep_cnt : 0;
             newcnt[k] = (unsigned long long)s_h[k];
-        } else {
-            s_b[k] = keep + (long long)atomicAdd(newcnt + k, (unsigned long long)s_h[k]);
         }
+    } else if (threadIdx.x <= kHermK && s_h[threadIdx.x] > 0) {
+        const int k = threadIdx.x;
+        s_b[k] = (k == ks - 1 ? keep_cnt : 0) + (long long)atomicAdd(newcnt + k, (unsigned long long)s_h[k]);
     }
     __syncthreads();
     auto put = [&](int level, int64_t r, int32_t i) {
-        bucket_of(p, (int)((mask_new >> level) & 1), level)[s_b[level] + r] = i;
+        bucket_of(p, (int)((mask_new >> level) & 1), level)[s_b[level] + r] = i ^ kInRec1;
     };
     if (lv0 >= 0) put(lv0, r0, i0);
     if (head)
@@ -253,14 +278,15 @@ __device__ inline void step_and_bucket(const HermParams& p, unsigned long long* 
         }
 }
 
-// block step in ticks: dt_max / 2^k not above `want`, dividing tau (the
-// largest power of two dividing tau > 0 is its lowest set bit)
+// block step in ticks: dt_max / 2^k not above `want` (k <= kHermK), dividing tau
+// (the largest power of two dividing tau > 0 is its lowest set bit). With
+// dt_max >= want the exponents give k or k - 1.
 __device__ inline int64_t block_step(double want, double dtmax, int64_t tau) {
-    double d = dtmax;
     int k = 0;
-    while (d > want && k < kHermK) {
-        d *= 0.5;
-        ++k;
+    if (dtmax > want) {
+        k = want > 0.0 ? __builtin_amdgcn_frexp_exp(dtmax) - __builtin_amdgcn_frexp_exp(want) : kHermK;
+        if (k < kHermK && __builtin_ldexp(dtmax, -k) > want) ++k;
+        k = k < kHermK ? k : kHermK;
     }
     int64_t t = (int64_t)1 << (kHermK - k);
     const int64_t low = tau & -tau;
@@ -329,10 +355,11 @@ __device__ inline void pair_d23(const ClusterParams& cp, double eps2, const doub
 // First steps: one lane per particle sums the derivatives over its list (in
 // list order; lists from the regular-force walk are short), then eq. dt.
 __global__ __launch_bounds__(256) void k_herm_start(HermParams p, IrrParams ip) {
-    // block 0's counts, every level filled (ks = 0) in buffer 0
-    step_and_bucket<1, 256>(p, lev_new(p, 0), 0, 0, 0ull, p.n, [](int64_t k) { return (int32_t)k; }, [&](int32_t i) {
+    // block 0's counts, every level filled (ks = 0) in buffer 0, the states in record 0
+    step_and_bucket<1, 256, false>(p, lev_new(p, 0), 0, 0, 0ull, p.n,
+                                   [](int64_t k) { return (int32_t)k | kInRec1; }, [&](bool have, int32_t i, int) {
 #pragma clang fp contract(off)
-        if (i < 0) return 0;   // a lane without an item
+        if (!have) return 0;   // a lane without an item
         const int64_t i3 = 3 * (int64_t)i;
         double xi[3], vi[3], ai[3], ji[3], f2[3] = {0.0, 0.0, 0.0}, f3[3] = {0.0, 0.0, 0.0};
         for (int c = 0; c < 3; ++c) {
@@ -382,32 +409,29 @@ __global__ __launch_bounds__(256) void k_herm_start(HermParams p, IrrParams ip) 
         s.m = ip.mass[i];
         s.tau = 0;
         s.dt = t;
-        store_state(p.rec + kRecPieces * (int64_t)i, s);
-        // no second record yet: a time before any
-        p.rec[kRecPieces * (p.n + i) + 6] = make_double2(0.0, __longlong_as_double(-1ll));
+        store_state(record(p, i, 0), s);
+        record(p, i, 1)[6] = make_double2(0.0, __longlong_as_double(-1ll));   // none yet: a time before any
         p.dt0[i] = t;
         return step_level(t);
     });
 }
 
-// One active particle i (a group of LH lanes; i < 0: a group without one, which
-// takes part in the exchange): F_I and its derivative a1, j1 at the predicted
+// One active particle i with its state in record buf (a group of LH lanes; have
+// false: a group without one, which takes part in the exchange): F_I and its derivative a1, j1 at the predicted
 // states (the pair terms of the irregular-force kernel; lane g sums list entries
 // g, g + LH, ... in order, then the group's butterfly), the 4th-order corrector
 // and the new block step; returns the new level.
 template <int LH>
-__device__ inline int force_correct(const HermParams& p, const IrrParams& ip, int32_t i, int64_t tn) {
+__device__ inline int force_correct(const HermParams& p, const IrrParams& ip, bool have, int32_t i, int buf, int64_t tn) {
 #pragma clang fp contract(off)
     const int g = threadIdx.x % LH;
     IrrSums S;   // (the pair sums carry their own contraction setting)
     HermState s = {};
     double xp[3] = {0.0, 0.0, 0.0}, vp[3] = {0.0, 0.0, 0.0}, fr[3] = {0.0, 0.0, 0.0};
-    int buf = 0;
-    if (i >= 0) {
+    if (have) {
         const int64_t i3 = 3 * (int64_t)i;
         int64_t b = p.off[i], e = p.off[i + 1];
-        buf = state_buffer(p, i, tn);
-        s = load_state(p.rec + kRecPieces * (buf * p.n + i));
+        s = load_state(record(p, i, buf));
         if (p.fr)
             for (int c = 0; c < 3; ++c) fr[c] = p.fr[i3 + c];
         predict(p, s, tn, xp, vp);
@@ -424,7 +448,7 @@ __device__ inline int force_correct(const HermParams& p, const IrrParams& ip, in
                 continue;
             }
             if (j == i) continue;
-            const HermState o = load_state(p.rec + kRecPieces * (state_buffer(p, j, tn) * p.n + j));
+            const HermState o = load_state(record(p, j, state_buffer(p, j, tn)));
             double xj[3], vj[3];
             predict(p, o, tn, xj, vj);
             pair_irr<true, false>(K, ip.eps2, me, PartJ{xj[0], xj[1], xj[2], o.m, vj[0], vj[1], vj[2]}, S);
@@ -435,7 +459,7 @@ __device__ inline int force_correct(const HermParams& p, const IrrParams& ip, in
         for (int k = 0; k < 6; ++k)
             for (int o = LH / 2; o > 0; o >>= 1) *w[k] += __shfl_xor(*w[k], o, 64);
     }
-    if (i < 0 || g != 0) return 0;
+    if (!have || g != 0) return 0;
     const double a1v[3] = {S.ax, S.ay, S.az}, j1v[3] = {S.jx, S.jy, S.jz};
     const double d = (double)s.dt * p.unit, d2 = d * d, d3 = d2 * d, d4 = d3 * d, d5 = d4 * d;
     double a2[3], a3[3], a2e[3], at[3];
@@ -461,82 +485,136 @@ __device__ inline int force_correct(const HermParams& p, const IrrParams& ip, in
     const int64_t t = block_step(want, p.dtmax, tn);
     s.tau = tn;
     s.dt = t;
-    store_state(p.rec + kRecPieces * ((buf ^ 1) * p.n + i), s);
+    store_state(record(p, i, buf ^ 1), s);
     return step_level(t);
 }
 
-// One block (number b in its batch): every workgroup computes the next block
-// time and the active buckets from the level counts, workgroup 0 publishes them
-// for the next block.
+// One launch (number b in its batch): every workgroup computes the next block
+// time and the active buckets from the level counts; then the grid takes that
+// block, or workgroup 0 that one and those after it while they are few, and
+// workgroup 0 leaves counts, time and buckets for the next launch.
 __global__ __launch_bounds__(kHermT) void k_herm_block(HermParams p, IrrParams ip, int b) {
-    __shared__ long long s_cnt[64], s_off[64];
-    __shared__ long long s_tn, s_nact;
-    __shared__ int s_ks;
+    __shared__ long long s_cnt[64];
+    __shared__ int4 s_end[16];
+    __shared__ unsigned long long s_new[64];
+    __shared__ long long s_tn;
+    __shared__ int s_nact, s_ks;
     const int q = b & 1;
-    const uint64_t mask = p.lev[kLevMask + q];
-    if (threadIdx.x < 64) {
-        const int k = threadIdx.x;
-        long long add;
-        const long long c = merged_count(p, b, k, add);
-        // deepest new level of the previous corrector (its appends; the first
-        // block's appends are the start levels, not counted)
-        const uint64_t app = __ballot(add > 0);
-        const long long t = (long long)p.lev[kLevT + q];
+    uint64_t mask = p.lev[kLevMask + q];
+    // wave 0, lane k: the count of level k, the levels the last block filled
+    // (its corrected particles; the first block's are the start levels, which
+    // count for no statistics), and the statistics of this launch
+    const int lane = threadIdx.x;
+    const bool wave0 = lane < 64;
+    long long c = 0, t = 0;
+    int deepest = -1;
+    unsigned long long blocks = 0, steps = 0;
+    auto plan = [&](long long old, long long add, int kp) {
+        c = lane <= kHermK ? merged_count(old, add, kp, lane) : 0;
+        const uint64_t app = __ballot(lane <= kHermK && add > 0);
+        if (t > 0 && app) {
+            const int dl = 63 - __clzll(app);
+            deepest = dl > deepest ? dl : deepest;
+        }
         const BlockPlan B = plan_block(c, t, p.tend);
-        s_cnt[k] = c;
-        s_off[k] = B.off;
-        if (k == 0) {
+        s_cnt[lane] = c;
+        (&s_end[0].x)[lane] = B.end;
+        if (lane == 0) {
             s_tn = B.done ? -1 : B.tn;
             s_nact = B.done ? 0 : B.nact;
             s_ks = B.ks;
         }
-        if (blockIdx.x == 0) {
-            if (k == 0 && t > 0 && app) {
-                const unsigned long long dl = (unsigned long long)(63 - __clzll(app));
-                if (dl > p.ctl[kHermKmax]) p.ctl[kHermKmax] = dl;
-            }
-            if (k <= kHermK) {
-                lev_cnt(p, q ^ 1)[k] = (unsigned long long)c;
-                lev_new(p, b + 2)[k] = 0ull;
-            }
-            if (k == 0) {
-                p.lev[kLevT + (q ^ 1)] = (unsigned long long)B.tn;
-                p.lev[kLevKs + (q ^ 1)] = (unsigned long long)B.ks;
-                p.lev[kLevMask + (q ^ 1)] = mask ^ (B.ks > kHermK ? 0ull : ~0ull << B.ks);
-                if (B.done) {
-                    p.ctl[kHermDone] = 1ull;
-                    if (p.done_host) *p.done_host = 1ull;   // read by the host while later blocks run
-                } else {
-                    p.ctl[kHermBlocks] += 1ull;
-                    p.ctl[kHermSteps] += (unsigned long long)B.nact;
-                }
-            }
+        return B;
+    };
+    // for the next launch: the counts before the last block, its time, its k* and
+    // the buckets after it
+    auto publish = [&](long long tn, int ks, uint64_t mask_new, bool done) {
+        if (lane <= kHermK) {
+            lev_cnt(p, q ^ 1)[lane] = (unsigned long long)c;
+            lev_new(p, b + 2)[lane] = 0ull;
         }
+        if (lane != 0) return;
+        p.lev[kLevT + (q ^ 1)] = (unsigned long long)tn;
+        p.lev[kLevKs + (q ^ 1)] = (unsigned long long)ks;
+        p.lev[kLevMask + (q ^ 1)] = mask_new;
+        if (deepest >= 0 && (unsigned long long)deepest > p.ctl[kHermKmax])
+            p.ctl[kHermKmax] = (unsigned long long)deepest;
+        const unsigned long long all = p.ctl[kHermBlocks] + blocks;
+        p.ctl[kHermBlocks] = all;
+        p.ctl[kHermSteps] += steps;
+        if (done) p.ctl[kHermDone] = 1ull;
+        // read by the host while later launches run
+        if (p.done_host && (done || all > kHermMaxBlocks)) *p.done_host = all > kHermMaxBlocks ? 2ull : 1ull;
+    };
+    if (wave0) {
+        t = (long long)p.lev[kLevT + q];
+        const long long old = lane <= kHermK ? (long long)lev_cnt(p, q)[lane] : 0;
+        const long long add = lane <= kHermK ? (long long)lev_new(p, b)[lane] : 0;
+        plan(old, add, (int)p.lev[kLevKs + q]);
     }
     __syncthreads();
-    const long long nact = s_nact, tn = s_tn;
-    const int ks = s_ks;
-    if (nact == 0) return;
-    const uint64_t mask_new = mask ^ (~0ull << ks);
-    const long long keep = ks > 0 ? s_cnt[ks - 1] : 0;
-    unsigned long long* const newcnt = lev_new(p, b + 1);
-    auto item = [&](int64_t k) { return active_at(p, s_off, s_cnt, ks, mask, k); };
-    // eight lanes share a particle's list while the grid has lanes for all
-    if (nact * kHermLanes <= (long long)gridDim.x * kHermT)
-        step_and_bucket<kHermLanes, kHermT>(p, newcnt, ks, keep, mask_new, nact, item,
-                                            [&](int32_t i) { return force_correct<kHermLanes>(p, ip, i, tn); });
-    else
-        step_and_bucket<1, kHermT>(p, newcnt, ks, keep, mask_new, nact, item,
-                                   [&](int32_t i) { return force_correct<1>(p, ip, i, tn); });
+    long long tn = s_tn;
+    int nact = s_nact, ks = s_ks;
+    auto item = [&](int64_t k) { return active_at(p, s_end, ks, mask, (int)k); };
+    if (nact == 0) {
+        if (wave0 && blockIdx.x == 0) publish((long long)p.tend, kHermK + 1, mask, true);
+        return;
+    }
+    if (nact > kHermSolo) {
+        const uint64_t mask_new = mask ^ (~0ull << ks);
+        if (wave0 && blockIdx.x == 0) {
+            blocks = 1;
+            steps = (unsigned long long)nact;
+            publish(tn, ks, mask_new, false);
+        }
+        const long long keep = ks > 0 ? s_cnt[ks - 1] : 0;
+        unsigned long long* const newcnt = lev_new(p, b + 1);
+        // eight lanes share a particle's list while the grid has lanes for all
+        if ((long long)nact * kHermLanes <= (long long)gridDim.x * kHermT)
+            step_and_bucket<kHermLanes, kHermT, false>(
+                p, newcnt, ks, keep, mask_new, nact, item,
+                [&](bool have, int32_t i, int buf) { return force_correct<kHermLanes>(p, ip, have, i, buf, tn); });
+        else
+            step_and_bucket<1, kHermT, false>(p, newcnt, ks, keep, mask_new, nact, item,
+                                              [&](bool have, int32_t i, int buf) { return force_correct<1>(p, ip, have, i, buf, tn); });
+        return;
+    }
+    if (blockIdx.x != 0) return;
+    for (int it = 1;; ++it) {
+        const uint64_t mask_new = mask ^ (~0ull << ks);
+        step_and_bucket<kHermLanes, kHermT, true>(
+            p, s_new, ks, ks > 0 ? s_cnt[ks - 1] : 0, mask_new, nact, item,
+            [&](bool have, int32_t i, int buf) { return force_correct<kHermLanes>(p, ip, have, i, buf, tn); });
+        blocks += 1;
+        steps += (unsigned long long)nact;
+        __syncthreads();   // every record, bucket entry and count of the block is stored
+        const long long before = c;
+        if (wave0) {
+            t = tn;
+            plan(before, (long long)s_new[lane], ks);
+        }
+        __syncthreads();
+        if (it < kHermInner && s_nact > 0 && s_nact <= kHermSolo) {
+            nact = s_nact;
+            tn = s_tn;
+            ks = s_ks;
+            mask = mask_new;
+            continue;
+        }
+        if (wave0) {   // (the next launch plans that block again)
+            c = before;
+            if (lane <= kHermK) lev_new(p, b + 1)[lane] = s_new[lane];
+            publish(tn, ks, mask_new, false);
+        }
+        return;
+    }
 }
 
 // the states of the end of the regular step into the caller's arrays
 __global__ __launch_bounds__(256) void k_herm_finish(HermParams p) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= p.n) return;
-    const int64_t t0 = __double_as_longlong(p.rec[kRecPieces * i + 6].y);
-    const int64_t t1 = __double_as_longlong(p.rec[kRecPieces * (p.n + i) + 6].y);
-    const HermState s = load_state(p.rec + kRecPieces * ((t1 > t0 ? p.n : 0) + i));
+    const HermState s = load_state(record(p, i, record_time(p, i, 1) > record_time(p, i, 0) ? 1 : 0));
     for (int c = 0; c < 3; ++c) {
         p.x[3 * i + c] = s.x[c];
         p.v[3 * i + c] = s.v[c];

@@ -725,9 +725,8 @@ IrrParams herm_irr(pbh_ctx* ctx, int64_t n, double r_in, double r_out, double ep
 }
 
 // One regular step of Hermite integration of F_I (see herm.hip), in place.
-constexpr int64_t kHermMaxBlocks = 1ll << 20;
-constexpr int kHermBatch = 16;   // blocks per graph launch
-static_assert(kHermBatch % 4 == 0, "block numbers restart at each batch");
+constexpr int kHermBatch = 16;   // launches per graph, each of one block or several small ones
+static_assert(kHermBatch % 4 == 0, "launch numbers restart at each batch");
 
 pbh_status do_hermite(pbh_ctx* ctx, int64_t n, double* pos, double* vel, const double* mass,
                       const double* fr, double r_in, double r_out, double eps,
@@ -771,8 +770,8 @@ pbh_status do_hermite(pbh_ctx* ctx, int64_t n, double* pos, double* vel, const d
     launch_herm_start(hp, ip, s);
     launch_zero_u64(h.ctl, kHermCtl, s);
     ip.acc = ip.jerk = nullptr;
-    // Blocks run in batches of kHermBatch, each batch one graph launch. The
-    // block that finds every particle at the end sets a host flag; the host
+    // Block launches run in batches of kHermBatch, each batch one graph. The
+    // launch that finds every particle at the end sets a host flag; the host
     // reads it once a batch has finished, while the next batch runs, so the GPU
     // does not wait for the host; the batch after the last busy one is empty.
     const std::vector<double> key = {(double)n, (double)(uintptr_t)pos, (double)(uintptr_t)vel,
@@ -796,14 +795,14 @@ pbh_status do_hermite(pbh_ctx* ctx, int64_t n, double* pos, double* vel, const d
     HIP_TRY(hipGraphLaunch(h.gexec, s));
     HIP_TRY(hipEventRecord(h.ev[0], s));
     for (int64_t batch = 0;; ++batch) {
-        if ((batch + 1) * kHermBatch >= kHermMaxBlocks) {
-            HIP_TRY(hipStreamSynchronize(s));
-            return fail(ctx, PBH_E_INTERNAL, "Hermite block steps exceed the limit");
-        }
         HIP_TRY(hipGraphLaunch(h.gexec, s));
         HIP_TRY(hipEventRecord(h.ev[(batch + 1) & 1], s));
         HIP_TRY(hipEventSynchronize(h.ev[batch & 1]));
-        if (*flag) break;
+        if (*flag) break;   // every launch before it makes a block, so this comes
+    }
+    if (*flag == 2ull) {
+        HIP_TRY(hipStreamSynchronize(s));
+        return fail(ctx, PBH_E_INTERNAL, "Hermite block steps exceed the limit");
     }
     launch_herm_finish(hp, s);
     unsigned long long c[kHermCtl], err = 0;

@@ -388,6 +388,7 @@ int64_t core_bsum_len(int64_t n);
 // herm.hip: Hermite integration of F_I with block steps over one regular step
 constexpr int kHermK = 40;   // block steps dt_max / 2^k, k <= kHermK; times in ticks of dt_max / 2^kHermK
 enum { kHermSteps = 0, kHermKmax = 1, kHermDone = 2, kHermBlocks = 3, kHermCtl = 4 };
+constexpr unsigned long long kHermMaxBlocks = (1ull << 20) - 17;   // blocks of a regular step at most
 // level bookkeeping: bucket counts (two slots), appends of the correctors (four),
 // then block time, k* of the last block and bucket buffer per level (two each)
 enum { kLevCnt = 0, kLevNew = 128, kLevT = 384, kLevKs = 386, kLevMask = 388, kLevLen = 390 };

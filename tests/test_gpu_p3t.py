@@ -131,6 +131,27 @@ def test_hermite_larger_n(n, seed, T):
     assert np.abs(gv - ov).max() <= 1e-10 * np.abs(ov).max()
 
 
+@pytest.mark.parametrize("n", [64, 65, 128, 129, 257])
+def test_hermite_blocks_of_one_workgroup(n):
+    # blocks of up to 128 active particles follow one another in one workgroup
+    # (64 at a time), larger ones take a launch each
+    print(f"hermite n={n}", flush=True)
+    c, r_in, r_out = _setup(n, 94, 8.0)
+    eps, T, eta = 1e-4, 1.0 / 16, 0.02
+    r_buff = 3.0 * np.linalg.norm(c.vel, axis=1).max() * T
+    p = _pbh(prec="fp64")
+    pos, vel, mass = _t(c.pos), _t(c.vel), _t(c.mass)
+    p.build(pos, mass)
+    fr, _, off, idx = p.force(r_in, r_out, 0.0, eps, r_buff=r_buff)
+    st = p.hermite(pos, vel, mass, fr, r_in, r_out, eps, off, idx, T, eta)
+    ofr, _ = oracle.direct(c.pos, c.mass, r_in, r_out, eps)
+    ox, ov, ost = oracle.hermite(c.pos, c.vel, c.mass, r_in, r_out, eps, T, eta=eta, fr=ofr)
+    assert st == ost
+    gx, gv = pos.cpu().numpy(), vel.cpu().numpy()
+    assert np.abs(gx - ox).max() <= 1e-10 * np.abs(ox).max()
+    assert np.abs(gv - ov).max() <= 1e-10 * np.abs(ov).max()
+
+
 @pytest.mark.parametrize("copies", [16, 17])
 def test_hermite_one_lane_per_list(copies):
     # copies of one set of 2048 particles, each with its own lists: up to 32768
