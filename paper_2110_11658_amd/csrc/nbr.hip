@@ -175,7 +175,7 @@ __global__ __launch_bounds__(64) void k_nbr_fill(NbrParams p) {
     }
 }
 
-// Staged lists into the CSR. One wave per block of 64 consecutive sorted
+// Staged lists into the CSR. One workgroup per block of 64 consecutive sorted
 // particles (the interleaving unit of the staging rows); stage_k[p] = 1 if
 // the walk staged the list of p (0: the fill pass writes it). The block's
 // lists pass through an LDS tile of 64 entries per particle: entry t of all
@@ -183,22 +183,28 @@ __global__ __launch_bounds__(64) void k_nbr_fill(NbrParams p) {
 // consecutive CSR entries of one particle (lists in caller order lie
 // scattered over the CSR; one lane per list would write 64 unrelated lines
 // per instruction). Entries beyond the caller's capacity are dropped and
-// flagged.
+// flagged. Four waves share a tile, and with few blocks the tiles of a block are
+// dealt out over gridDim.y workgroups: a lone wave a block was a chain of 64 stores
+// a tile, 42 us at 4096 particles (now 6), 59 at 131072 (26), 195 at 2^20 (175, of
+// which 0.5 GB are read and written; two waves 181, eight 184).
 constexpr int kCopyTile = 64;   // 16 KB of LDS per block; 16, 32, 96 and 128 were slower at 2^20
+constexpr int kCopyWaves = 4;
+constexpr int kCopyGroups = 2048;   // workgroups the chip holds
 
-__global__ __launch_bounds__(64) void k_nbr_copy(int64_t n, const int8_t* __restrict__ stage_k,
-                                                 const int32_t* __restrict__ perm,
-                                                 const int32_t* __restrict__ stage, int scap,
-                                                 const int64_t* __restrict__ off,
-                                                 int32_t* __restrict__ idx, int64_t cap,
-                                                 unsigned long long* __restrict__ cnt) {
+__global__ __launch_bounds__(64 * kCopyWaves) void k_nbr_copy(int64_t n, const int8_t* __restrict__ stage_k,
+                                                              const int32_t* __restrict__ perm,
+                                                              const int32_t* __restrict__ stage, int scap,
+                                                              const int64_t* __restrict__ off,
+                                                              int32_t* __restrict__ idx, int64_t cap,
+                                                              unsigned long long* __restrict__ cnt) {
     __shared__ int s_tile[kStageStride][kCopyTile + 1];
     __shared__ int s_cnt[kStageStride];
     __shared__ int64_t s_off[kStageStride];
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63, wave = uni((int)threadIdx.x >> 6);
     const int64_t nblk = (n + kStageStride - 1) / kStageStride;
     bool overflow = false;
     for (int64_t blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
+        // (every wave reads the block's counts and offsets)
         const int64_t i = blk * kStageStride + lane;
         const bool staged = i < n && stage_k[i] != 0;
         int c = 0;
@@ -214,27 +220,28 @@ __global__ __launch_bounds__(64) void k_nbr_copy(int64_t n, const int8_t* __rest
             const int v = __shfl_xor(maxc, o, 64);
             maxc = v > maxc ? v : maxc;
         }
-        maxc = __builtin_amdgcn_readfirstlane(maxc);
+        maxc = uni(maxc);
         __syncthreads();
-        s_cnt[lane] = c;
-        s_off[lane] = at;
-        for (int t0 = 0; t0 < maxc; t0 += kCopyTile) {
+        if (wave == 0) {
+            s_cnt[lane] = c;
+            s_off[lane] = at;
+        }
+        for (int t0 = (int)blockIdx.y * kCopyTile; t0 < maxc; t0 += kCopyTile * (int)gridDim.y) {
             __syncthreads();
             // unconditional loads (index clamped into the row) so that all of
             // them are in flight together; unused tile entries are never read
 #pragma unroll
-            for (int u = 0; u < kCopyTile; ++u) {
+            for (int k = 0; k < kCopyTile / kCopyWaves; ++k) {
+                const int u = wave * (kCopyTile / kCopyWaves) + k;
                 const int t = t0 + u < c ? t0 + u : 0;
                 s_tile[lane][u] = row[(int64_t)t * kStageStride];
             }
             __syncthreads();
 #pragma unroll 4
-            for (int q = 0; q < kStageStride * kCopyTile / 64; ++q) {
-                const int slot = q * 64 + lane;
-                const int pp = slot / kCopyTile, u = slot % kCopyTile;
-                if (t0 + u < s_cnt[pp]) {
-                    const int64_t dst = s_off[pp] + t0 + u;
-                    if (dst < cap) idx[dst] = s_tile[pp][u];
+            for (int q = wave; q < kStageStride; q += kCopyWaves) {
+                if (t0 + lane < s_cnt[q]) {
+                    const int64_t dst = s_off[q] + t0 + lane;
+                    if (dst < cap) idx[dst] = s_tile[q][lane];
                     else overflow = true;
                 }
             }
@@ -270,12 +277,15 @@ NbrParams make_params(Dev& d, const BuildCfg& c, int stack_cap) {
 
 void launch_nbr_copy(Dev& d, const BuildCfg& c, int stage_cap, const int64_t* off, int32_t* idx,
                      int64_t cap, hipStream_t s) {
-    int64_t grid = (c.n + kStageStride - 1) / kStageStride;
-    if (grid > 16384) grid = 16384;
-    if (grid < 1) grid = 1;
-    hipLaunchKernelGGL(k_nbr_copy, dim3((unsigned)grid), dim3(64), 0, s, c.n, (const int8_t*)d.stage_k,
-                       (const int32_t*)d.perm, (const int32_t*)d.nbr_stage, stage_cap, off, idx, cap,
-                       d.cnt);
+    const int64_t nblk = (c.n + kStageStride - 1) / kStageStride;
+    const int64_t grid = nblk < 1 ? 1 : (nblk < 16384 ? nblk : 16384);
+    // tiles of a block side by side while that does not crowd the chip
+    const int64_t tiles = (stage_cap + kCopyTile - 1) / kCopyTile;
+    int64_t gy = kCopyGroups / grid;
+    gy = gy < 1 ? 1 : (gy < tiles ? gy : tiles);
+    hipLaunchKernelGGL(k_nbr_copy, dim3((unsigned)grid, (unsigned)gy), dim3(64 * kCopyWaves), 0, s, c.n,
+                       (const int8_t*)d.stage_k, (const int32_t*)d.perm, (const int32_t*)d.nbr_stage, stage_cap,
+                       off, idx, cap, d.cnt);
 }
 
 void launch_nbr_fill(Dev& d, const BuildCfg& c, int grid, int stack_cap, const int64_t* off,
