@@ -104,6 +104,7 @@ struct pbh_ctx {
     int64_t alloc_gen = 0;   // bumped whenever device buffers are reallocated
     int grid_mixed = 0, grid_fp64 = 0;   // persistent walk grids at the default tile (the largest)
     int grid_tile[2][3] = {{0, 0, 0}, {0, 0, 0}};   // [mixed][tile 64, 96, 128]
+    int grid_team = 0;
 
     // kdk
     double* k_acc = nullptr;
@@ -205,8 +206,9 @@ int64_t node_capacity(int64_t n, int D, int n_leaf, int C) {
 int walk_grid(pbh_ctx* ctx, int mixed) {
     const int tile = ctx->params.walk_tile;
     const int t = tile == 128 ? 2 : (tile == 96 ? 1 : 0);
-    int& g = ctx->grid_tile[mixed ? 1 : 0][t];
-    if (g == 0) g = walk_blocks_per_cu(mixed, tile) * ctx->cus;
+    const bool team = walk_team(mixed, tile, ctx->cfg.n);
+    int& g = team ? ctx->grid_team : ctx->grid_tile[mixed ? 1 : 0][t];
+    if (g == 0) g = walk_blocks_per_cu(mixed, tile, team) * ctx->cus;
     const int gmax = mixed ? ctx->grid_mixed : ctx->grid_fp64;   // the stacks are sized for this
     return g < gmax ? g : gmax;
 }
@@ -333,8 +335,8 @@ pbh_status setup_build(pbh_ctx* ctx, int64_t n, int32_t C, const int64_t* offset
     c.n_groups = n;   // capacity; the walk reads the actual count on the device
     ctx->nblk_box = (int)blk_cluster.size();
     if (ctx->grid_mixed == 0) {
-        ctx->grid_mixed = walk_blocks_per_cu(1, 64) * ctx->cus;
-        ctx->grid_fp64 = walk_blocks_per_cu(0, 64) * ctx->cus;
+        ctx->grid_mixed = walk_blocks_per_cu(1, 64, false) * ctx->cus;
+        ctx->grid_fp64 = walk_blocks_per_cu(0, 64, false) * ctx->cus;
     }
     pbh_status st = ensure_buffers(ctx);
     if (st != PBH_OK) return st;
@@ -531,6 +533,7 @@ pbh_status do_force(pbh_ctx* ctx, const double* pos, const double* mass,
     w.max_copies = ctx->params.lanes_per_particle ? ctx->params.lanes_per_particle : 64;
     w.cpos = pos;
     w.cmass = mass;
+    w.team = walk_team(w.mixed, w.tile, c.n);
     w.grid = walk_grid(ctx, w.mixed);   // persistent: workgroups leave when the group queue is empty
     w.stack_cap = kStackCap;
     w.count_nbr = nbr_off != nullptr;   // the walk counts the neighbours of every particle
@@ -1338,6 +1341,7 @@ static void kdk_force(pbh_ctx* ctx, const double* pos, const double* mass, doubl
     w.mixed = ctx->params.prec == PBH_MIXED;
     w.tile = ctx->params.walk_tile;
     w.max_copies = ctx->params.lanes_per_particle ? ctx->params.lanes_per_particle : 64;
+    w.team = walk_team(w.mixed, w.tile, ctx->cfg.n);
     w.grid = walk_grid(ctx, w.mixed);
     w.stack_cap = kStackCap;
     w.count_nbr = 0;

@@ -298,6 +298,7 @@ struct WalkCfg {
     double eps;
     int mixed;
     int tile = 64;         // LDS tile capacity (64, 96 or 128)
+    bool team = false;     // four waves a group (see walk_team)
     int max_copies = 64;   // most sub-wave copies of a small group
     const double* cpos = nullptr;    // caller's arrays for the stale-input check, or null
     const double* cmass = nullptr;
@@ -309,7 +310,8 @@ struct WalkCfg {
 void launch_rcrit(Dev& d, const BuildCfg& c, double theta, hipStream_t s);
 void launch_walk(Dev& d, const BuildCfg& c, const WalkCfg& w, double* acc, double* pot,
                  hipStream_t s);
-int walk_blocks_per_cu(int mixed, int tile);
+bool walk_team(int mixed, int tile, int64_t n);
+int walk_blocks_per_cu(int mixed, int tile, bool team);
 
 // nbr.hip
 void launch_nbr_copy(Dev& d, const BuildCfg& c, int stage_cap, const int64_t* off, int32_t* idx,

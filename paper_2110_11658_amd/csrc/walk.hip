@@ -8,7 +8,8 @@
 // Barnes-Hut with opening angle theta).
 //
 // One wavefront walks one group (a run of <= 64 sorted particles, one per
-// lane). Persistent workgroups of one wave pull groups from a global counter.
+// lane), or with few groups a team of four does (see TeamMem). Persistent
+// workgroups pull groups from global counters.
 // Per step the wave pops up to 64 nodes from its stack (one per lane) and
 // classifies them in FP64 without FMA, exactly like the definition:
 //   near   box-box distance^2 < R^2, or the boxes touch (R = r_out + r_buff,
@@ -16,11 +17,13 @@
 //   accept not near, theta > 0, distance^2(group box, COM) > rcrit^2
 //   open   otherwise: a leaf becomes particle-particle work, an inner node
 //          pushes its children.
-// Accepted nodes and leaf particles are compacted with ballot + prefix sums
-// into LDS tiles of TC entries (64, 96 or 128; FP32 in the mixed path: positions
-// relative to the group centre, formed in FP64 first); a tile is evaluated
-// just before it would overflow, every lane reading each entry by LDS
-// broadcast. Tile partial sums are
+// Accepted nodes are compacted with ballot + prefix sums into LDS tiles of TC
+// entries (64, 96 or 128; FP32 in the mixed path: positions relative to the group
+// centre, formed in FP64 first), leaf particles as runs of their tile; a tile is
+// evaluated just before it would overflow, every lane reading each entry by LDS
+// broadcast. Only then are the particles of its runs loaded, all in one go (a step
+// adds few, and loading them there cost it a search and a memory latency: 128k
+// particles 813 -> 803 us, 2^20 5.12 -> 5.07 ms, 4096 190 -> 184). Tile partial sums are
 // folded into FP32 (hi, lo) pairs with TwoSum and returned in FP64.
 #include <type_traits>
 
@@ -44,7 +47,7 @@ constexpr int kWalkStackLds = 640;
 // Near entries of the FP64 walk keep their original coordinates for the
 // neighbour test; the mixed walk keeps the sorted index instead and reads the
 // coordinates from global memory in the rare case the FP64 test is needed
-// (10 KB of LDS per wave with TC = 64: 16 waves per CU).
+// (under 10 KB of LDS per wave with TC = 64: 16 waves per CU).
 template <typename R, int TC>
 struct NearExtra {
     double nx[TC], ny[TC], nz[TC];
@@ -59,11 +62,18 @@ struct alignas(16) Tiles : NearExtra<R, TC> {
     static_assert(TC >= 64, "one traversal step adds up to 64 entries");
     static constexpr int kCap = TC;
     R pn[TC + 32][12];   // cx cy cz M | qxx qyy qzz qxy | qxz qyz - -  (room for one more step)
-    R far[TC][4];        // x y z m (relative to the group centre)
-    R nearp[TC][4];
+    // Far and near tiles are filled just before they are evaluated; until then their
+    // storage holds the runs of sorted particles that make them up: [0] a run's first
+    // entry, [1] its first particle minus that entry
+    union {
+        R far[TC][4];    // x y z m (relative to the group centre)
+        int far_run[2][TC];
+    };
+    union {
+        R nearp[TC][4];
+        int near_run[2][TC];
+    };
     int nearj[TC];       // caller index: skips the self pair, and is the neighbour index
-    int lf_ex[64];       // leaf expansion: exclusive prefix of particle counts
-    int lf_beg[64];
 };
 
 struct WalkParams {
@@ -477,6 +487,42 @@ __device__ inline Part<float> eval_near_f32(const Tiles<float, TC>& T, int cnt, 
     return Part<float>{ax, ay, az, ph};
 }
 
+// Only the neighbours of a near tile, in entry order, for the list wave of a team:
+// a lane's four next entries are read and tested together (one at a time, the LDS
+// reads and branches set its pace: walk of 4096 particles 146 us, 138 so; with four
+// groups on a SIMD that is covered and the larger code costs 2 to 5 %).
+template <int TC>
+__device__ inline void find_near_f32(const Tiles<float, TC>& T, int cnt, int ksub, int sub, float px, float py,
+                                     float pz, int self, const NearK<float>& K, int me, double rlist2, int& nbr,
+                                     int32_t* srow, int scap) {
+    for (int e0 = 0; e0 < cnt; e0 += 4 * ksub) {
+        float dr[4];
+        int oj[4];
+        bool band = false, any = false;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int e = e0 + u * ksub + sub, ec = e < cnt ? e : cnt - 1;
+            const float4 q = *reinterpret_cast<const float4*>(&T.nearp[ec][0]);
+            const float dx = q.x - px, dy = q.y - py, dz = q.z - pz;
+            oj[u] = T.nearj[ec];
+            dr[u] = e < cnt ? fmaf(dz, dz, fmaf(dy, dy, dx * dx)) - K.rlist2f : INFINITY;
+            band = band || (e < cnt && fabsf(dr[u]) <= K.band);
+            any = any || dr[u] < 0.f;
+        }
+        if (__ballot(band || any) == 0) continue;
+        const bool exact = __ballot(band) != 0;   // (wave-uniform)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int e = e0 + u * ksub + sub;
+            bool nb = dr[u] < 0.f;
+            if (exact && e < cnt) nb = near_listed(T, e, dr[u], K, me, rlist2);
+            nb = nb && oj[u] != self;
+            if (nb && nbr < scap) srow[nbr * kStageStride] = oj[u];
+            nbr += nb ? 1 : 0;
+        }
+    }
+}
+
 // The mixed walk's forms (explicit FMA chains above), chosen per precision.
 template <int TC>
 __device__ inline Part<float> eval_pn(const Tiles<float, TC>& T, int cnt, int ksub, int sub, float px,
@@ -521,11 +567,13 @@ __device__ inline Part<float> eval_near(const Tiles<float, TC>& T, int cnt, int 
 //   215 groups 245 / 205 / 205, 1523: 461 / 374 / 375, 3177: 552 / 521 / 576,
 //   6141: 892 / 805 / 899, 26611: 5128 / 5098 / -, FP64 4782: 2012 / 1786 / 1835
 // and with 103236 groups sharing only costs (14090 / 14150).
-template <bool MIXED>
+// A team (see TeamMem) shares all groups or none: 16384 particles 225 / 231, 32768
+// 339 (three eighths) / 322.
+template <bool MIXED, int TEAM>
 __device__ inline int walk_shared(int64_t G) {
     const int64_t q = (G + kQueues - 1) / kQueues, w = gridDim.x / kQueues;
     if (q > 8 * w) return 0;
-    const int64_t t = 8 * q <= 5 * w ? q : (MIXED ? q * 3 / 8 : q * 5 / 8);
+    const int64_t t = 8 * q <= 5 * w ? q : (TEAM > 1 ? 0 : (MIXED ? q * 3 / 8 : q * 5 / 8));
     return (int)(t < kWalkShared / kQueues ? t : kWalkShared / kQueues);
 }
 
@@ -592,83 +640,53 @@ __device__ inline WalkArgs walk_args() {
     return a;
 }
 
-// Four waves per SIMD (16 per compute unit, which the 64-entry mixed walk's
-// LDS allows): the register budget is held to 128, which this kernel fits
-// without spilling; left free, the compiler takes more and halves nothing but
-// occupancy. Larger tiles and the FP64 walk are held lower by their LDS.
-template <bool MIXED, int TC>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_walk(WalkParams p) {
-    using R = typename std::conditional<MIXED, float, double>::type;
-    constexpr int TCAP = TC;
-    __shared__ Tiles<R, TC> T;
-    __shared__ int s_stack[kWalkStackLds];
-    const int lane = threadIdx.x;
-    const Stack stack{s_stack, p.stack + (int64_t)blockIdx.x * (p.stack_cap - kWalkStackLds), p.stack_cap,
-                      kWalkStackLds};
-    int home = blockIdx.x % kQueues;
-    const R eps2 = (R)p.eps2;
-    const int64_t G = (int64_t)*p.G;
-    const unsigned long long t_start = wall_clock64();
-    const unsigned long long c_start = clock64();
-    const int tail = walk_shared<MIXED>(G);
-    int n_walked = 0;
-    // interaction counts of this wave, added to the counters once at its end
-    unsigned long long sum_pn = 0, sum_far = 0, sum_near = 0, slot_pn = 0, slot_far = 0, slot_near = 0;
-    bool first = true;
+// A lane's part in the walk of a group: which particles it evaluates for, and how
+// the tiles' entries are shared with its copies. By default a group of g particles
+// takes one pass over every tile with ksub = min(64 / g, cap) copies, lane = copy *
+// g + particle (see for_entries; lanes beyond ksub * g repeat copy 0 and are
+// ignored at the merge), and the copies are merged once per group. A group of
+// 33..53 particles takes two passes over every multipole tile instead (split):
+// pass A holds particles 0..31 in two copies (particle lane & 31, copy lane >> 5),
+// pass B the other rB = g - 32 in kB = min(64 / rB, cap, 8) >= 3 copies counted
+// from lane 32, so that lane 32 + q holds particle 32 + q in copy 0. Their copies
+// are merged after every tile into lane p < g, which owns particle p and takes the
+// group's far and near tiles in one pass.
+template <typename R>
+struct Role {
+    int gb, gcnt, cl;
+    double ctr[3];          // group centre
+    double rlist2;          // neighbour-list radius R = r_out + r_buff, squared
+    bool near_exact;        // every neighbour test in FP64 (see the band in tile_near)
+    bool active, split;
+    int rB, kB, ksubA, subA, copyA, subB;
+    int ksubN, subN, me;    // far and near pairs, neighbour list and outputs: this lane's particle
+    int wrow, scap;
+    bool real, hiB, ownerB;
+    R pAx, pAy, pAz, pBx, pBy, pBz;
 
-    for (;;) {
-        const WalkItem item = walk_next(p.queues, G, tail, home, first, lane);
-        first = false;
-        if (item.g < 0) break;
-        const int64_t g = item.g;
-        // A group's sums are kept in two: A0 takes three of five multipole tiles
-        // and the far tiles, A1 the other multipole tiles and the near ones, and
-        // the two are added at the end. In a shared group each wave computes one
-        // of them: both traverse the tree (the order of the tile entries is the
-        // traversal's), each fills and evaluates only the tiles of its own sum, and
-        // part 0 finds the neighbours. So the sums do not depend on which groups
-        // are shared.
-        const int part = uni(item.part), parts = uni(item.parts);
-        const bool lead = part == 0;
-        n_walked += lead ? 1 : 0;
-
-        const WalkArgs a = walk_args();
-        const int gb = uni(a->g_begin[g]), gcnt = uni(a->g_count[g]), root = uni(a->g_root[g]);
-        const int cl = uni(a->g_cluster[g]);
-        double glo[3], ghi[3], ctr[3];
-        for (int k = 0; k < 3; ++k) {
-            glo[k] = a->g_lo[3 * g + k];
-            ghi[k] = a->g_hi[3 * g + k];
-            ctr[k] = (glo[k] + ghi[k]) * 0.5;
-        }
-        // a group this large against the list radius R takes every neighbour test in
-        // FP64 (see the band in flush_near)
+    __device__ __forceinline__ void set(WalkArgs a, int64_t g, int lane, const double* glo, const double* ghi) {
+        gb = uni(a->g_begin[g]);
+        gcnt = uni(a->g_count[g]);
+        cl = uni(a->g_cluster[g]);
+        // a group this large against the list radius R takes every neighbour test in FP64
         double h = 0.0;
-        for (int k = 0; k < 3; ++k) h = fmax(h, (ghi[k] - glo[k]) * 0.5);
-        const bool near_exact = __builtin_amdgcn_readfirstlane((int)(h > 64.0 * a->cp[cl].rlist)) != 0;
-        const double rlist2 = a->cp[cl].rlist2;   // neighbour-list radius R = r_out + r_buff, squared
-        // Lane roles. By default a group of g particles takes one pass over
-        // every tile with ksub = min(64 / g, cap) copies, lane = copy * g +
-        // particle (see for_entries; lanes beyond ksub * g repeat copy 0 and
-        // are ignored at the merge), and the copies are merged once per group.
-        // A group of 33..53 particles takes two passes over every multipole
-        // tile instead (split): pass A holds particles 0..31 in two copies
-        // (particle lane & 31, copy lane >> 5), pass B the other rB = g - 32
-        // in kB = min(64 / rB, cap, 8) >= 3 copies counted from lane 32, so
-        // that lane 32 + q holds particle 32 + q in copy 0. Their copies are
-        // merged after every tile into lane p < g, which owns particle p and
-        // takes the group's far and near tiles in one pass.
-        const bool active = lane < gcnt;
-        const int rB = gcnt - 32;
-        int kB = 0;
+        for (int k = 0; k < 3; ++k) {
+            ctr[k] = (glo[k] + ghi[k]) * 0.5;
+            h = fmax(h, (ghi[k] - glo[k]) * 0.5);
+        }
+        near_exact = __builtin_amdgcn_readfirstlane((int)(h > 64.0 * a->cp[cl].rlist)) != 0;
+        rlist2 = a->cp[cl].rlist2;
+        active = lane < gcnt;
+        rB = gcnt - 32;
+        kB = 0;
         if (rB >= 1 && rB <= 21) {
             const int kfit = 64 / rB;
             kB = kfit < a->max_copies ? kfit : a->max_copies;
             kB = kB < 8 ? kB : 8;
         }
-        const bool split = kB >= 3;
-        int ksubA, subA, plA, copyA;
-        int subB = 0, plB = 0;
+        split = kB >= 3;
+        int plA, plB = 0;
+        subB = 0;
         if (split) {
             ksubA = 2;
             copyA = lane >> 5;
@@ -688,9 +706,340 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
         // the particle whose far and near pairs, neighbour list and outputs
         // this lane handles (a stand-in for the idle lanes of a split group)
         const int own = split ? (active ? lane : 0) : plA;
-        const int ksubN = split ? 1 : ksubA;
-        const int subN = split ? 0 : subA;
-        const int me = gb + own;
+        ksubN = split ? 1 : ksubA;
+        subN = split ? 0 : subA;
+        me = gb + own;
+        // Neighbour staging. A particle's row holds a->scap entries; a lane
+        // that holds it whole (ksubN = 1) uses it whole, copies of a small group
+        // each get a sub-row of wrow = a->scap / ksubN entries (joined into one
+        // list after the walk). Lanes that hold no particle of their own, or
+        // repeat copy 0, store nothing (scap = 0).
+        real = split ? active : copyA < ksubA;
+        wrow = a->scap / ksubN;
+        scap = (a->stage == nullptr || !real) ? 0 : (ksubN == 1 ? a->scap : wrow);
+        // positions relative to the group centre: pass A (also the far and
+        // near tiles, except on lanes >= 32 of a split group) and pass B
+        pAx = (R)(a->x[gb + plA] - ctr[0]);
+        pAy = (R)(a->y[gb + plA] - ctr[1]);
+        pAz = (R)(a->z[gb + plA] - ctr[2]);
+        const int pbi = split ? gb + plB : me;
+        pBx = (R)(a->x[pbi] - ctr[0]);
+        pBy = (R)(a->y[pbi] - ctr[1]);
+        pBz = (R)(a->z[pbi] - ctr[2]);
+        hiB = split && lane >= 32;   // lanes whose own particle is pass B's copy 0
+        ownerB = hiB && active;
+    }
+};
+
+// The LDS accesses of one wave complete in order; this keeps the compiler to it.
+__device__ inline void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// One evaluation of a tile of each kind by one wave (all lanes run it).
+template <typename R, int TC>
+__device__ __forceinline__ Part<R> tile_pn(Tiles<R, TC>& T, const Role<R>& r, int lane, int cnt, R eps2) {
+    Part<R> pa = eval_pn(T, cnt, r.ksubA, r.subA, r.pAx, r.pAy, r.pAz, eps2);
+    if (r.split) {
+        const Part<R> pb = eval_pn(T, cnt, r.kB, r.subB, r.pBx, r.pBy, r.pBz, eps2);
+        // pass A: copy 1 (lane p + 32) into lane p
+        pa.x += shfl_down32(pa.x);
+        pa.y += shfl_down32(pa.y);
+        pa.z += shfl_down32(pa.z);
+        pa.p += shfl_down32(pa.p);
+        // pass B: copies in copy order into lane 32 + q, through the
+        // tile's storage (every lane has read the tile)
+        wave_sync();
+        Part<R>* red = reinterpret_cast<Part<R>*>(&T.pn[0][0]);
+        red[lane] = pb;
+        wave_sync();
+        Part<R> sb{R(0), R(0), R(0), R(0)};
+        if (r.ownerB) {
+            for (int c = 0; c < r.kB; ++c) {
+                const Part<R> v = red[(lane + c * r.rB) & 63];
+                sb.x += v.x; sb.y += v.y; sb.z += v.z; sb.p += v.p;
+            }
+        }
+        wave_sync();
+        if (r.hiB) pa = sb;   // idle lanes add zero
+    }
+    return pa;
+}
+
+// Fills a far or near tile of cnt entries from its runs of particles.
+template <bool NEAR, typename R, int TC>
+__device__ __forceinline__ void fill_tile(Tiles<R, TC>& T, const WalkParams& p, const double (&ctr)[3], int lane,
+                                          int cnt, int runs) {
+    constexpr int H = (TC + 63) / 64;
+    int (&run)[2][TC] = NEAR ? T.near_run : T.far_run;
+    int j[H];
+    wave_sync();
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+        const int e = h * 64 + lane;
+        int f = 0;   // the last run that begins at or before entry e
+#pragma unroll
+        for (int st = H * 32; st > 0; st >>= 1)
+            if (f + st < runs && run[0][f + st] <= e) f += st;
+        j[h] = run[1][f] + e;
+    }
+    wave_sync();
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+        const int e = h * 64 + lane;
+        if (e >= cnt) continue;
+        const int64_t k = j[h];
+        R* q = NEAR ? T.nearp[e] : T.far[e];
+        q[0] = (R)(p.x[k] - ctr[0]);
+        q[1] = (R)(p.y[k] - ctr[1]);
+        q[2] = (R)(p.z[k] - ctr[2]);
+        q[3] = (R)p.m[k];
+        if (NEAR) {
+            T.nearj[e] = p.perm[k];
+            if constexpr (std::is_same<R, float>::value) {
+                T.nears[e] = (int)k;
+            } else {
+                T.nx[e] = p.x[k];
+                T.ny[e] = p.y[k];
+                T.nz[e] = p.z[k];
+            }
+        }
+    }
+    wave_sync();
+}
+
+template <typename R, int TC>
+__device__ __forceinline__ Part<R> tile_far(const Tiles<R, TC>& T, const Role<R>& r, int cnt, R eps2) {
+    return eval_far(T, cnt, r.ksubN, r.subN, r.hiB ? r.pBx : r.pAx, r.hiB ? r.pBy : r.pAy,
+                    r.hiB ? r.pBz : r.pAz, eps2);
+}
+
+template <bool LIST_WAVE, typename R, int TC>
+__device__ __forceinline__ Part<R> tile_near(const Tiles<R, TC>& T, const Role<R>& r, const WalkParams& p, int cnt,
+                                             R eps2, bool count_nbr, bool force, int& nbr) {
+    constexpr bool MIXED = std::is_same<R, float>::value;
+    // The changeover constants are read for each near tile (about ten a
+    // group): kept in registers they would crowd the multipole loop. The
+    // empty asm keeps the loads here.
+    const ClusterParams* cpp = p.cp + r.cl;
+    asm volatile("" : "+s"(cpp));
+    const ClusterParams& cp = *cpp;
+    NearK<R> K;
+    if (MIXED) {
+        K.r_in = cp.f_r_in; K.r_out = cp.f_r_out; K.inv_delta = cp.f_inv_delta;
+        K.c0 = cp.f_c0; K.d0 = cp.f_d0; K.l1 = cp.f_l1; K.inner = cp.f_inner;
+        for (int k = 0; k < 6; ++k) K.e[k] = cp.f_e[k];
+    } else {
+        K.r_in = cp.r_in; K.r_out = cp.r_out; K.inv_delta = cp.inv_delta;
+        K.c0 = cp.c0; K.d0 = cp.d0; K.l1 = cp.l1; K.inner = cp.inner;
+        for (int k = 0; k < 6; ++k) K.e[k] = cp.e[k];
+    }
+    K.pole = cp.d0 != 0.0;
+    {
+        // Band of the FP32 neighbour pre-test against the list radius R.
+        // Relative coordinates are FP64 differences rounded once to FP32, so
+        // with |p| <= h (group box half side) and a pair at r <= 2 R each
+        // component of d errs by at most 2^-24 (2h + 2.01 r); with h <= 64 R
+        // the error of r^2 (squares, FMA rounding, R^2 in FP32) stays below
+        // 928 * 2^-24 R^2, and for r > 2 R far below r^2 - R^2. The band is
+        // 2048 * 2^-24 R^2; larger groups always take the FP64 test.
+        K.rlist2f = (float)r.rlist2;
+        K.x = p.x; K.y = p.y; K.z = p.z;
+        K.band = r.near_exact ? INFINITY : (float)(2048.0 * 0x1p-24 * r.rlist2);
+    }
+    int32_t* srow = p.stage != nullptr
+                        ? p.stage + stage_index(r.me, (r.ksubN == 1 ? 0 : r.subN * r.wrow), p.scap)
+                        : nullptr;
+    if constexpr (LIST_WAVE && MIXED) {
+        find_near_f32(T, cnt, r.ksubN, r.subN, r.hiB ? r.pBx : r.pAx, r.hiB ? r.pBy : r.pAy, r.hiB ? r.pBz : r.pAz,
+                      p.perm[r.me], K, r.me, r.rlist2, nbr, srow, r.scap);
+        return Part<R>{0, 0, 0, 0};
+    }
+    return eval_near(T, cnt, r.ksubN, r.subN, r.hiB ? r.pBx : r.pAx, r.hiB ? r.pBy : r.pAy,
+                     r.hiB ? r.pBz : r.pAz, eps2, p.perm[r.me], K, count_nbr, force, r.me, r.rlist2, nbr, srow,
+                     r.scap);
+}
+
+// Team walk: with few groups a workgroup of four waves walks one group. The first
+// traverses and makes tiles; full tiles go as jobs to the others, who take them as
+// they come free. Neighbour lists are jobs of their own for the last wave, which
+// keeps the counts. Jobs are numbered in the order in which one wave alone would
+// evaluate them; a job's partial sums come back through slot (number mod
+// kTeamRing) and the first wave folds them into the accumulators in that order, so
+// the results are those of one wave. A tile of each kind has kTeamBufs buffers; the
+// first wave waits for a slot or buffer it needs, the others for jobs. Every wait is
+// for a wave of the same workgroup that runs on, and the end flag ends the others.
+constexpr int kTeamWaves = 4;
+constexpr int kTeamBufs = 3;
+constexpr int kTeamRing = 8;
+enum { kJobPn = 0, kJobFar = 1, kJobNear = 2 };
+
+template <typename R, int TEAM>
+struct TeamMem {
+    Part<R> res[kTeamRing][64];
+    int done[kTeamRing];       // number + 1 of the job whose sums the slot holds
+    int head, take;            // jobs given, jobs taken
+    int4 job[kTeamRing];       // kind, buffer, entries | runs << 16, list job that fills the tile (0: none)
+    int last[3][kTeamBufs];    // last job on each buffer of each kind
+    int list_head, list_filled, list_done;   // list jobs given, their tiles filled, ended
+    int2 list_job[kTeamBufs + 1];            // buffer, entries | runs << 16
+    int list_last[kTeamBufs];                // list jobs up to the last one on each near buffer
+    int nbr[64];               // neighbours found by the lanes of the last wave
+    int group, turn, end;      // group of the jobs, its turn; no more jobs
+};
+template <typename R>
+struct TeamMem<R, 1> {};
+
+__device__ inline int lds_load(int* p) {
+    return uni(__hip_atomic_load(p, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP));
+}
+__device__ inline void lds_store(int* p, int v) {   // (all lanes the same value)
+    __hip_atomic_store(p, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ inline void lds_wait(int* p, int v) {   // until *p >= v
+    while (lds_load(p) < v) __builtin_amdgcn_s_sleep(1);
+}
+
+__device__ inline void group_box(WalkArgs a, int64_t g, double* lo, double* hi) {
+    for (int k = 0; k < 3; ++k) {
+        lo[k] = a->g_lo[3 * g + k];
+        hi[k] = a->g_hi[3 * g + k];
+    }
+}
+
+// A wave that evaluates; `lists`: also the neighbour lists.
+template <typename R, int TC, int TEAM>
+__device__ __forceinline__ void team_evaluate(Tiles<R, TC>* T, TeamMem<R, TEAM>& tm, const WalkParams& p, bool lists,
+                                              int lane, R eps2) {
+    int turn = 0, list = 0, nbr = 0;
+    Role<R> r;
+    auto follow = [&]() {   // the group that jobs are given for
+        const int now = uni(tm.turn);
+        if (now == turn) return;
+        turn = now;
+        const WalkArgs a = walk_args();
+        const int64_t g = uni(tm.group);
+        double glo[3], ghi[3];
+        group_box(a, g, glo, ghi);
+        r.set(a, g, lane, glo, ghi);
+        nbr = 0;
+    };
+    for (;;) {
+        // (the jobs seen here come after the list jobs seen next, which fill their tiles)
+        const int head = lds_load(&tm.head);
+        if (lists && list < lds_load(&tm.list_head)) {
+            follow();
+            const int2 job = tm.list_job[list % (kTeamBufs + 1)];
+            Tiles<R, TC>& t = T[uni(job.x)];
+            const int cnt = uni(job.y) & 0xffff;
+            fill_tile<true>(t, p, r.ctr, lane, cnt, uni(job.y) >> 16);
+            lds_store(&tm.list_filled, ++list);
+            tile_near<true>(t, r, p, cnt, eps2, true, false, nbr);
+            tm.nbr[lane] = nbr;
+            lds_store(&tm.list_done, list);
+            continue;
+        }
+        const int num = lds_load(&tm.take);
+        if (num < head) {
+            if (uni(atomicCAS(&tm.take, lane == 0 ? num : -1, num + 1)) != num) continue;   // (another wave has it)
+            follow();
+            const int4 job = tm.job[num % kTeamRing];
+            const int kind = uni(job.x), cnt = uni(job.z) & 0xffff, runs = uni(job.z) >> 16, filler = uni(job.w);
+            Tiles<R, TC>& t = T[uni(job.y)];
+            Part<R> v;
+            if (kind == kJobPn) {
+                v = tile_pn(t, r, lane, cnt, eps2);
+            } else if (kind == kJobFar) {
+                fill_tile<false>(t, p, r.ctr, lane, cnt, runs);
+                v = tile_far(t, r, cnt, eps2);
+            } else {
+                if (filler) lds_wait(&tm.list_filled, filler);
+                else fill_tile<true>(t, p, r.ctr, lane, cnt, runs);
+                int none = 0;
+                v = tile_near<false>(t, r, p, cnt, eps2, false, true, none);
+            }
+            tm.res[num % kTeamRing][lane] = v;
+            lds_store(&tm.done[num % kTeamRing], num + 1);
+            continue;
+        }
+        if (lds_load(&tm.end)) break;
+        __builtin_amdgcn_s_sleep(1);
+    }
+}
+
+// Four waves per SIMD (16 per compute unit, which the 64-entry mixed walk's
+// LDS allows): the register budget is held to 128, which this kernel fits
+// without spilling; left free, the compiler takes more and halves nothing but
+// occupancy. Larger tiles and the FP64 walk are held lower by their LDS.
+template <bool MIXED, int TC, int TEAM>
+__global__ __launch_bounds__(64 * TEAM) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_walk(WalkParams p) {
+    using R = typename std::conditional<MIXED, float, double>::type;
+    constexpr int TCAP = TC;
+    __shared__ Tiles<R, TC> s_tiles[TEAM == 1 ? 1 : kTeamBufs];
+    __shared__ int s_stack[kWalkStackLds];
+    __shared__ TeamMem<R, TEAM> tm;
+    const int lane = threadIdx.x & 63;
+    const R eps2 = (R)p.eps2;
+    if constexpr (TEAM > 1) {
+        if (threadIdx.x < kTeamRing) tm.done[threadIdx.x] = 0;
+        if (threadIdx.x < 3 * kTeamBufs) (&tm.last[0][0])[threadIdx.x] = -1;
+        if (threadIdx.x < kTeamBufs) tm.list_last[threadIdx.x] = 0;
+        if (threadIdx.x == 0) tm.head = tm.take = tm.list_head = tm.list_filled = tm.list_done = tm.turn = tm.end = 0;
+        __syncthreads();
+        // the traversing waves of a CU's teams are spread over its SIMDs
+        const int w = uni((int)(threadIdx.x / 64 + blockIdx.x / 256) & (kTeamWaves - 1));
+        if (w > 0) {
+            team_evaluate<R, TC, TEAM>(s_tiles, tm, p, w == kTeamWaves - 1, lane, eps2);
+            return;
+        }
+    }
+    Tiles<R, TC>& T = s_tiles[0];
+    const Stack stack{s_stack, p.stack + (int64_t)blockIdx.x * (p.stack_cap - kWalkStackLds), p.stack_cap,
+                      kWalkStackLds};
+    int home = blockIdx.x % kQueues;
+    const int64_t G = (int64_t)*p.G;
+    const unsigned long long t_start = wall_clock64();
+    const unsigned long long c_start = clock64();
+    const int tail = walk_shared<MIXED, TEAM>(G);
+    int n_walked = 0;
+    // interaction counts of this wave, added to the counters once at its end
+    unsigned long long sum_pn = 0, sum_far = 0, sum_near = 0, slot_pn = 0, slot_far = 0, slot_near = 0;
+    bool first = true;
+    // the team's jobs: next number, first one not yet folded in, those for A1 (a bit
+    // per slot), list jobs, the group's turn, and the buffers being filled
+    int j_next = 0, j_tail = 0, j_list = 0, j_turn = 0;
+    unsigned j_a1 = 0;
+    int b_pn = 0, b_far = 0, b_near = 0;
+    (void)j_next, (void)j_tail, (void)j_list, (void)j_turn, (void)j_a1;
+
+    for (;;) {
+        const WalkItem item = walk_next(p.queues, G, tail, home, first, lane);
+        first = false;
+        if (item.g < 0) break;
+        const int64_t g = item.g;
+        // A group's sums are kept in two: A0 takes three of five multipole tiles
+        // and the far tiles, A1 the other multipole tiles and the near ones, and
+        // the two are added at the end. In a shared group each wave computes one
+        // of them: both traverse the tree (the order of the tile entries is the
+        // traversal's), each fills and evaluates only the tiles of its own sum, and
+        // part 0 finds the neighbours. So the sums do not depend on which groups
+        // are shared.
+        const int part = uni(item.part), parts = uni(item.parts);
+        const bool lead = part == 0;
+        n_walked += lead ? 1 : 0;
+
+        const WalkArgs a = walk_args();
+        const int root = uni(a->g_root[g]);
+        double glo[3], ghi[3];
+        group_box(a, g, glo, ghi);
+        Role<R> r;
+        r.set(a, g, lane, glo, ghi);
+        const double (&ctr)[3] = r.ctr;
+        const double rlist2 = r.rlist2;
+        const bool active = r.active, split = r.split, real = r.real;
+        const int gcnt = r.gcnt, ksubA = r.ksubA, ksubN = r.ksubN, kB = r.kB, me = r.me, wrow = r.wrow,
+                  scap = r.scap;
         const int orig_me = a->perm[me];
         if (a->cpos && lead) {
             // the caller's arrays must still hold what the build sorted
@@ -699,32 +1048,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
                                           a->cpos[o3 + 2] != a->z[me] || a->cmass[orig_me] != a->m[me]);
             if (__ballot(stale)) atomicOr(&a->cnt[kErr], lane == 0 ? kErrStale : 0ull);
         }
-        // Neighbour staging. A particle's row holds a->scap entries; a lane
-        // that holds it whole (ksubN = 1) uses it whole, copies of a small group
-        // each get a sub-row of wrow = a->scap / ksubN entries (joined into one
-        // list after the walk). Lanes that hold no particle of their own, or
-        // repeat copy 0, store nothing (scap = 0).
-        const bool real = split ? active : copyA < ksubA;
-        const int wrow = a->scap / ksubN;
-        const int scap = (a->stage == nullptr || !real) ? 0 : (ksubN == 1 ? a->scap : wrow);
-        // positions relative to the group centre: pass A (also the far and
-        // near tiles, except on lanes >= 32 of a split group) and pass B
-        const R pAx = (R)(a->x[gb + plA] - ctr[0]);
-        const R pAy = (R)(a->y[gb + plA] - ctr[1]);
-        const R pAz = (R)(a->z[gb + plA] - ctr[2]);
-        const int pbi = split ? gb + plB : me;
-        const R pBx = (R)(a->x[pbi] - ctr[0]);
-        const R pBy = (R)(a->y[pbi] - ctr[1]);
-        const R pBz = (R)(a->z[pbi] - ctr[2]);
         const unsigned rcpA = rounds_rcp(ksubA), rcpB = split ? rounds_rcp(kB) : 0u,
                        rcpN = rounds_rcp(ksubN);
-        const bool hiB = split && lane >= 32;   // lanes whose own particle is pass B's copy 0
-        const bool ownerB = hiB && active;
         const bool count_nbr = a->nbr_cnt != nullptr && lead;
         // the tiles this wave fills and evaluates
         int pn_tile = 0, pn_own = 0;                     // multipole tile being filled and its accumulator
         const bool far_mine = lead, near_force = parts == 1 || !lead, near_mine = near_force || count_nbr;
-        int npn = 0, nfar = 0, nnear = 0;
+        int npn = 0, nfar = 0, nnear = 0, rfar = 0, rnear = 0;   // tile entries, runs of the far and near tile
         unsigned c_pn = 0, c_far = 0, c_near = 0;   // per group: far below 2^32
         // loop iterations of the evaluations (each occupies all 64 lanes)
         unsigned it_pn = 0, it_far = 0, it_near = 0;
@@ -732,78 +1062,83 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
         Acc<R> A0, A1;
         // one flush of each tile kind; every lane runs it (it_* counts the
         // loop iterations, each of which occupies the 64 lanes)
+        auto fold = [&]() {   // the next job's sums
+            if constexpr (TEAM > 1) {
+                const int slot = j_tail % kTeamRing;
+                lds_wait(&tm.done[slot], j_tail + 1);
+                const Part<R> v = tm.res[slot][lane];
+                if ((j_a1 >> slot) & 1) A1.add(v);
+                else A0.add(v);
+                ++j_tail;
+            }
+        };
+        // gives buffer b of a kind out as a job, then takes the next buffer
+        auto give = [&](int kind, int b, int cnt, int filler, int acc) {
+            if constexpr (TEAM > 1) {
+                if (j_next - j_tail == kTeamRing) fold();
+                const int slot = j_next % kTeamRing;
+                j_a1 = (j_a1 & ~(1u << slot)) | ((unsigned)acc << slot);
+                tm.job[slot] = make_int4(kind, b, cnt, filler);
+                tm.last[kind][b] = j_next;
+                lds_store(&tm.head, ++j_next);
+            }
+        };
+        auto next_buffer = [&](int kind, int& b) {
+            if constexpr (TEAM > 1) {
+                b = b + 1 < kTeamBufs ? b + 1 : 0;
+                const int busy = uni(tm.last[kind][b]);
+                while (j_tail <= busy) fold();
+            }
+        };
         auto flush_pn = [&](int cnt) {
             it_pn += entry_rounds(cnt, ksubA, rcpA);
-            Part<R> pa = eval_pn(T, cnt, ksubA, subA, pAx, pAy, pAz, eps2);
-            if (split) {
-                it_pn += entry_rounds(cnt, kB, rcpB);
-                const Part<R> pb = eval_pn(T, cnt, kB, subB, pBx, pBy, pBz, eps2);
-                // pass A: copy 1 (lane p + 32) into lane p
-                pa.x += shfl_down32(pa.x);
-                pa.y += shfl_down32(pa.y);
-                pa.z += shfl_down32(pa.z);
-                pa.p += shfl_down32(pa.p);
-                // pass B: copies in copy order into lane 32 + q, through the
-                // tile's storage (every lane has read the tile)
-                __syncthreads();
-                Part<R>* red = reinterpret_cast<Part<R>*>(&T.pn[0][0]);
-                red[lane] = pb;
-                __syncthreads();
-                Part<R> sb{R(0), R(0), R(0), R(0)};
-                if (ownerB) {
-                    for (int c = 0; c < kB; ++c) {
-                        const Part<R> v = red[(lane + c * rB) & 63];
-                        sb.x += v.x; sb.y += v.y; sb.z += v.z; sb.p += v.p;
-                    }
-                }
-                __syncthreads();
-                if (hiB) pa = sb;   // idle lanes add zero
-            }
-            if (pn_own == 0) A0.add(pa);
-            else A1.add(pa);
-        };
-        auto flush_far = [&](int cnt) {
-            it_far += entry_rounds(cnt, ksubN, rcpN);
-            A0.add(eval_far(T, cnt, ksubN, subN, hiB ? pBx : pAx, hiB ? pBy : pAy, hiB ? pBz : pAz, eps2));
-        };
-        auto flush_near = [&](int cnt) {
-            // The changeover constants are read for each flush of a near tile (about ten a
-            // group): kept in registers they would crowd the multipole loop. The
-            // empty asm keeps the loads here.
-            const ClusterParams* cpp = p.cp + cl;
-            asm volatile("" : "+s"(cpp));
-            const ClusterParams& cp = *cpp;
-            NearK<R> K;
-            if (MIXED) {
-                K.r_in = cp.f_r_in; K.r_out = cp.f_r_out; K.inv_delta = cp.f_inv_delta;
-                K.c0 = cp.f_c0; K.d0 = cp.f_d0; K.l1 = cp.f_l1; K.inner = cp.f_inner;
-                for (int k = 0; k < 6; ++k) K.e[k] = cp.f_e[k];
+            if (split) it_pn += entry_rounds(cnt, kB, rcpB);
+            if constexpr (TEAM > 1) {
+                give(kJobPn, b_pn, cnt, 0, pn_own);
+                next_buffer(kJobPn, b_pn);
             } else {
-                K.r_in = cp.r_in; K.r_out = cp.r_out; K.inv_delta = cp.inv_delta;
-                K.c0 = cp.c0; K.d0 = cp.d0; K.l1 = cp.l1; K.inner = cp.inner;
-                for (int k = 0; k < 6; ++k) K.e[k] = cp.e[k];
+                const Part<R> pa = tile_pn(T, r, lane, cnt, eps2);
+                if (pn_own == 0) A0.add(pa);
+                else A1.add(pa);
             }
-            K.pole = cp.d0 != 0.0;
-            {
-                // Band of the FP32 neighbour pre-test against the list radius R.
-                // Relative coordinates are FP64 differences rounded once to FP32, so
-                // with |p| <= h (group box half side) and a pair at r <= 2 R each
-                // component of d errs by at most 2^-24 (2h + 2.01 r); with h <= 64 R
-                // the error of r^2 (squares, FMA rounding, R^2 in FP32) stays below
-                // 928 * 2^-24 R^2, and for r > 2 R far below r^2 - R^2. The band is
-                // 2048 * 2^-24 R^2; larger groups always take the FP64 test.
-                K.rlist2f = (float)rlist2;
-                K.x = p.x; K.y = p.y; K.z = p.z;
-                K.band = near_exact ? INFINITY : (float)(2048.0 * 0x1p-24 * rlist2);
-            }
-            if (near_force) it_near += entry_rounds(cnt, ksubN, rcpN);
-            int32_t* srow = p.stage != nullptr
-                                ? p.stage + stage_index(me, (ksubN == 1 ? 0 : subN * wrow), p.scap)
-                                : nullptr;
-            const Part<R> v = eval_near(T, cnt, ksubN, subN, hiB ? pBx : pAx, hiB ? pBy : pAy, hiB ? pBz : pAz,
-                                        eps2, p.perm[me], K, count_nbr, near_force, me, rlist2, nbr, srow, scap);
-            if (near_force) A1.add(v);
         };
+        auto flush_far = [&](int cnt, int runs) {
+            it_far += entry_rounds(cnt, ksubN, rcpN);
+            if constexpr (TEAM > 1) {
+                give(kJobFar, b_far, cnt | runs << 16, 0, 0);
+                next_buffer(kJobFar, b_far);
+            } else {
+                fill_tile<false>(T, p, ctr, lane, cnt, runs);
+                A0.add(tile_far(T, r, cnt, eps2));
+            }
+        };
+        bool had_lists = false;
+        auto flush_near = [&](int cnt, int runs) {
+            if (near_force) it_near += entry_rounds(cnt, ksubN, rcpN);
+            if constexpr (TEAM > 1) {
+                if (count_nbr) {
+                    had_lists = true;
+                    tm.list_job[j_list % (kTeamBufs + 1)] = make_int2(b_near, cnt | runs << 16);
+                    lds_store(&tm.list_head, ++j_list);
+                    tm.list_last[b_near] = j_list;
+                }
+                if (near_force) give(kJobNear, b_near, cnt | runs << 16, count_nbr ? j_list : 0, 1);
+                next_buffer(kJobNear, b_near);
+                lds_wait(&tm.list_done, uni(tm.list_last[b_near]));
+            } else {
+                fill_tile<true>(T, p, ctr, lane, cnt, runs);
+                const Part<R> v = tile_near<false>(T, r, p, cnt, eps2, count_nbr, near_force, nbr);
+                if (near_force) A1.add(v);
+            }
+        };
+        auto group_sync = []() {   // between the lanes of this wave
+            if constexpr (TEAM > 1) wave_sync();
+            else __syncthreads();
+        };
+        if constexpr (TEAM > 1) {   // (no job of another group is under way)
+            tm.group = (int)g;
+            tm.turn = ++j_turn;
+        }
         stack.put(0, root);   // every lane stores the same value
         int top = 1;
         bool overflow = false;
@@ -813,9 +1148,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
             // once it could not take another step's entries (up to 64)
             if (npn > TCAP - 32) {
                 if (parts == 1 || pn_own == part) {
-                    __syncthreads();
+                    group_sync();
                     flush_pn(npn);
-                    __syncthreads();
+                    group_sync();
                 }
                 npn = 0;
                 pn_tile = pn_tile < 4 ? pn_tile + 1 : 0;
@@ -843,7 +1178,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
             if (mk) {
                 const int k = uni(__popcll(mk));
                 if (accept && (parts == 1 || pn_own == part)) {
-                    R* e = T.pn[npn + popc_below(mk)];
+                    R* e = s_tiles[b_pn].pn[npn + popc_below(mk)];
                     e[0] = (R)(w.com[0] - ctr[0]);
                     e[1] = (R)(w.com[1] - ctr[1]);
                     e[2] = (R)(w.com[2] - ctr[2]);
@@ -887,57 +1222,57 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
                 const int v = flag ? w.count : 0;
                 const int li = wave_incl_scan(v, lane);
                 const int total = last_lane(li);
-                __syncthreads();
-                T.lf_ex[lane] = li - v;
-                T.lf_beg[lane] = w.begin;
-                __syncthreads();
                 if (cls == 0) c_far += total; else c_near += total;
+                int fill = cls == 0 ? nfar : nnear, runs = cls == 0 ? rfar : rnear;
+                const bool mine = cls == 0 ? far_mine : near_mine;
                 for (int base = 0; base < total; base += 64) {
-                    const int s = base + lane;
-                    int k = 0;
-#pragma unroll
-                    for (int st = 32; st > 0; st >>= 1)
-                        if (T.lf_ex[k + st] <= s) k += st;
-                    const int j = T.lf_beg[k] + (s - T.lf_ex[k]);
-                    int& fill = cls == 0 ? nfar : nnear;
                     const int add = (total - base) < 64 ? (total - base) : 64;
                     if (fill + add > TCAP) {
-                        __syncthreads();
+                        group_sync();
                         if (cls == 0) {
-                            if (far_mine) flush_far(fill);
+                            if (far_mine) flush_far(fill, runs);
                         } else {
-                            if (near_mine) flush_near(fill);
+                            if (near_mine) flush_near(fill, runs);
                         }
                         fill = 0;
-                        __syncthreads();
+                        runs = 0;
+                        group_sync();
                     }
-                    if (s < total && (cls == 0 ? far_mine : near_mine)) {
-                        R* e = cls == 0 ? T.far[fill + lane] : T.nearp[fill + lane];
-                        e[0] = (R)(p.x[j] - ctr[0]);
-                        e[1] = (R)(p.y[j] - ctr[1]);
-                        e[2] = (R)(p.z[j] - ctr[2]);
-                        e[3] = (R)p.m[j];
-                        if (cls == 1) {
-                            T.nearj[fill + lane] = p.perm[j];
-                            if constexpr (MIXED) {
-                                T.nears[fill + lane] = j;
-                            } else {
-                                T.nx[fill + lane] = p.x[j];
-                                T.ny[fill + lane] = p.y[j];
-                                T.nz[fill + lane] = p.z[j];
-                            }
+                    if (mine) {
+                        // the part of the lane's leaf among these entries
+                        const int ex = li - v;
+                        const int lo = ex > base ? ex : base, hi = li < base + add ? li : base + add;
+                        const uint64_t rm = __ballot(lo < hi);
+                        if (lo < hi) {
+                            Tiles<R, TC>& F = s_tiles[cls == 0 ? b_far : b_near];
+                            int (&run)[2][TC] = cls == 0 ? F.far_run : F.near_run;
+                            const int k = runs + popc_below(rm), at = fill + lo - base;
+                            run[0][k] = at;
+                            run[1][k] = w.begin + (lo - ex) - at;
                         }
+                        runs = uni(runs + __popcll(rm));
                     }
                     fill = uni(fill + add);
                 }
-                __syncthreads();
+                if (cls == 0) {
+                    nfar = fill;
+                    rfar = runs;
+                } else {
+                    nnear = fill;
+                    rnear = runs;
+                }
             }
         }
-        __syncthreads();
+        group_sync();
         if (npn && (parts == 1 || pn_own == part)) flush_pn(npn);
-        if (nfar && far_mine) flush_far(nfar);
-        if (nnear && near_mine) flush_near(nnear);
-        __syncthreads();
+        if (nfar && far_mine) flush_far(nfar, rfar);
+        if (nnear && near_mine) flush_near(nnear, rnear);
+        if constexpr (TEAM > 1) {
+            while (j_tail < j_next) fold();
+            lds_wait(&tm.list_done, j_list);
+            nbr = had_lists ? tm.nbr[lane] : 0;
+        }
+        group_sync();
 
         const WalkArgs e = walk_args();
         // a row that overflowed sends the group's lists to the fill pass
@@ -951,7 +1286,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
             A0.store(red + W * lane);
             A1.store(red + W * (64 + lane));
             T.nearj[lane] = nbr;
-            __syncthreads();
+            group_sync();
             // (the barrier also makes the copies' staged entries visible)
             if (active) {
                 const bool join = count_nbr && !need_fill;
@@ -978,7 +1313,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
                     nbr += nc;
                 }
             }
-            __syncthreads();
+            group_sync();
         }
         if (overflow) atomicOr(&e->cnt[kErr], lane == 0 ? kErrWalkStack : 0ull);
         if (count_nbr) {
@@ -1045,6 +1380,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
         slot_far += it_far;
         slot_near += it_near;
     }
+    if constexpr (TEAM > 1) lds_store(&tm.end, 1);   // (no jobs are left)
     const WalkArgs z = walk_args();
     if (!first && (slot_pn | slot_far | slot_near)) {
         // one contribution per wave (lane 0, the others add 0), spread over lines
@@ -1106,12 +1442,23 @@ void launch_rcrit(Dev& d, const BuildCfg& c, double theta, hipStream_t s) {
 
 template <bool MIXED>
 static auto walk_kernel(int tile) {
-    return tile == 128 ? k_walk<MIXED, 128> : (tile == 96 ? k_walk<MIXED, 96> : k_walk<MIXED, 64>);
+    return tile == 128 ? k_walk<MIXED, 128, 1> : (tile == 96 ? k_walk<MIXED, 96, 1> : k_walk<MIXED, 64, 1>);
 }
 
-int walk_blocks_per_cu(int mixed, int tile) {
+// Up to here a team walks each group. Few groups leave the chip idle but for the
+// longest ones, whose walk is a chain of latencies that four waves shorten; with
+// more, four groups on a SIMD cover each other's latencies and a team's idle waves
+// are lost. Walk in us, one wave a group / a team: 700 particles 87 / 73, 4096 184
+// / 138, 16384 301 / 226, 32768 358 / 322, 40960 409 / 366 (nbar 200: 827 / 745),
+// 49152 440 / 436, 65536 505 / 550, 131072 812 / 970.
+constexpr int64_t kTeamMaxN = 40960;
+
+bool walk_team(int mixed, int tile, int64_t n) { return mixed && tile == 64 && n <= kTeamMaxN; }
+
+int walk_blocks_per_cu(int mixed, int tile, bool team) {
     int nb = 0;
-    if (mixed) hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, walk_kernel<true>(tile), 64, 0);
+    if (team) hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_walk<true, 64, kTeamWaves>, 64 * kTeamWaves, 0);
+    else if (mixed) hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, walk_kernel<true>(tile), 64, 0);
     else hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, walk_kernel<false>(tile), 64, 0);
     return nb > 0 ? nb : 1;
 }
@@ -1149,7 +1496,8 @@ void launch_walk(Dev& d, const BuildCfg& c, const WalkCfg& w, double* acc, doubl
     p.cmass = w.cmass;
     p.part_sum = d.part_sum;
     p.part_done = d.part_done;
-    if (w.mixed) hipLaunchKernelGGL(walk_kernel<true>(w.tile), dim3(w.grid), dim3(64), 0, s, p);
+    if (w.team) hipLaunchKernelGGL((k_walk<true, 64, kTeamWaves>), dim3(w.grid), dim3(64 * kTeamWaves), 0, s, p);
+    else if (w.mixed) hipLaunchKernelGGL(walk_kernel<true>(w.tile), dim3(w.grid), dim3(64), 0, s, p);
     else hipLaunchKernelGGL(walk_kernel<false>(w.tile), dim3(w.grid), dim3(64), 0, s, p);
 }
 

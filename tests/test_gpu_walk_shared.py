@@ -49,3 +49,26 @@ def test_results_do_not_depend_on_the_sharing(prec, filler):
             if lists:
                 assert np.array_equal(go[s.start:s.stop + 1] - go[s.start], off)
                 assert np.array_equal(gi[go[s.start]:go[s.stop]], idx + s.start)
+
+
+@pytest.mark.parametrize("n,n_crit,theta,r_out", [(2, 64, 0.5, 0.1), (64, 64, 0.5, 2.0), (700, 64, 0.0, 0.1),
+                                                  (2900, 64, 0.5, 0.06), (2900, 48, 0.7, 0.3), (900, 64, 0.5, 9.0)])
+def test_four_waves_a_group_equal_one(n, n_crit, theta, r_out):
+    # a walk of few particles gives four waves to a group, of many one: the
+    # cluster alone and in an ensemble of more than 40960 particles, bit for bit
+    # (far, near and multipole tiles missing or many, lists that overflow their rows)
+    from paper_2110_11658_amd.api import Pbh
+    kw = dict(prec="mixed", key_bits=18, n_crit=n_crit)
+    a, b = ic.plummer(n, seed=5, masses="kroupa"), ic.plummer(45000, seed=6)
+    r_in, eps = 0.1 * r_out, 1e-5
+    print(f"team n={n} n_crit={n_crit} theta={theta} r_out={r_out}", flush=True)
+    alone, p = Pbh(0, **kw), Pbh(0, **kw)
+    alone.build(_t(a.pos), _t(a.mass))
+    acc, pot, off, idx = (t.cpu().numpy() for t in alone.force(r_in, r_out, theta, eps))
+    offsets = np.array([0, n, n + b.n])
+    p.build_batched(offsets, _t(np.concatenate([a.pos, b.pos])), _t(np.concatenate([a.mass, b.mass])))
+    ga, gp, go, gi = (t.cpu().numpy() for t in p.force_batched([r_in, 0.001], [r_out, 0.01], theta, eps))
+    assert np.array_equal(ga[:n], acc) and np.array_equal(gp[:n], pot)
+    assert np.array_equal(go[:n + 1], off) and np.array_equal(gi[:off[-1]], idx)
+    ga, gp, _, _ = alone.force(r_in, r_out, theta, eps, neighbours=False)
+    assert np.array_equal(ga.cpu().numpy(), acc) and np.array_equal(gp.cpu().numpy(), pot)
