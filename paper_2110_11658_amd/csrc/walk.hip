@@ -977,7 +977,7 @@ __global__ __launch_bounds__(64 * TEAM) __attribute__((amdgpu_waves_per_eu(4, 4)
     using R = typename std::conditional<MIXED, float, double>::type;
     constexpr int TCAP = TC;
     __shared__ Tiles<R, TC> s_tiles[TEAM == 1 ? 1 : kTeamBufs];
-    __shared__ int s_stack[kWalkStackLds];
+    __shared__ int s_stack[kWalkStackLds + 1];   // (and an entry for what is not pushed)
     __shared__ TeamMem<R, TEAM> tm;
     const int lane = threadIdx.x & 63;
     const R eps2 = (R)p.eps2;
@@ -1160,16 +1160,23 @@ __global__ __launch_bounds__(64 * TEAM) __attribute__((amdgpu_waves_per_eu(4, 4)
             const int npop = uni(top < 64 ? top : 64);
             top -= npop;
             const bool has = lane < npop;
-            const int nd = has ? stack.get(top + lane) : root;
+            int nd = root;
+            if (top + npop <= kWalkStackLds) {   // (wave-uniform; the usual case)
+                if (has) nd = s_stack[top + lane];
+            } else {
+                if (has) nd = stack.get(top + lane);
+            }
             __threadfence_block();
             const WNode w = p.node.load(nd);
             // (the moments along with the node: one latency a step, and siblings' moments
             // lie side by side, whether or not all of them are accepted)
             Mom32 q32 = {};
             if (MIXED) q32 = p.q32.load(nd);
+            double rcrit2 = w.rcrit2;
+            asm volatile("" : "+v"(rcrit2));   // (with the other loads, not where it is compared)
             const double dbox2 = box_box_d2(glo, ghi, w.lo, w.hi);
             const bool near = (dbox2 < rlist2) || (dbox2 == 0.0);
-            const bool accept = has && !near && p.use_theta && (box_pt_d2(glo, ghi, w.com) > w.rcrit2);
+            const bool accept = has && !near && p.use_theta && (box_pt_d2(glo, ghi, w.com) > rcrit2);
             const bool open = has && !accept;
             const bool leaf = w.nchild == 0;
 
@@ -1208,7 +1215,7 @@ __global__ __launch_bounds__(64 * TEAM) __attribute__((amdgpu_waves_per_eu(4, 4)
                 int* dst = s_stack + top + incl - nch;
 #pragma unroll
                 for (int k = 0; k < 8; ++k)
-                    if (k < nch) dst[k] = w.first_child + k;
+                    *(k < nch ? dst + k : s_stack + kWalkStackLds) = w.first_child + k;   // (no branches)
             } else {
                 for (int k = 0; k < nch; ++k) stack.put(top + incl - nch + k, w.first_child + k);
             }
