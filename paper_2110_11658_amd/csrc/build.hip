@@ -15,7 +15,7 @@
 //            (parallel-axis sums over children), tight box
 //   groups   tree-bounded runs of <= n_crit sorted particles (rule at k_group_pass)
 //
-// A build is 13 launches up to 8192 particles and 20 beyond (there were 43 and
+// A build is 12 launches up to 8192 particles and 20 beyond (there were 43 and
 // 53): with kernels of a few microseconds the launches, and the scans between
 // them, were most of its time.
 //
@@ -868,6 +868,7 @@ __global__ __launch_bounds__(kLimitT) void k_group_limit(const unsigned* __restr
 constexpr int kGrpT = 256;
 constexpr int kGrpI = 4;
 constexpr int kGrpTile = kGrpT * kGrpI;
+constexpr int kGrpFew = 8;
 
 __global__ __launch_bounds__(kGrpT) void k_group_count(const int32_t* __restrict__ flag, int64_t n,
                                                        int32_t* __restrict__ tmp) {
@@ -898,8 +899,14 @@ __global__ __launch_bounds__(kGrpT) void k_group_fill(const int32_t* __restrict_
     __shared__ int s_w[kGrpT / 64];
     __shared__ int s_first[kGrpTile];   // the tile's groups: first particle in the tile
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const int64_t base = (int64_t)blockIdx.x * kGrpTile;
     int part = 0;
-    for (int64_t k = t; k < (int64_t)blockIdx.x; k += kGrpT) part += tmp[k];
+    if (tmp) {
+        for (int64_t k = t; k < (int64_t)blockIdx.x; k += kGrpT) part += tmp[k];
+    } else {   // few tiles: counted here
+#pragma unroll 8
+        for (int64_t k = t; k < base; k += kGrpT) part += flag[k] != 0 ? 1 : 0;
+    }
     for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o, 64);
     if (lane == 0) s_w[w] = part;
     __syncthreads();
@@ -907,7 +914,6 @@ __global__ __launch_bounds__(kGrpT) void k_group_fill(const int32_t* __restrict_
     for (int q = 0; q < kGrpT / 64; ++q) off += s_w[q];
     __syncthreads();
     // a wave holds kGrpI * 64 consecutive particles
-    const int64_t base = (int64_t)blockIdx.x * kGrpTile;
     const int p0 = w * (kGrpI * 64) + lane;
     uint64_t ball[kGrpI];
     int c = 0;
@@ -1024,9 +1030,15 @@ void launch_groups(Dev& d, const BuildCfg& c, hipStream_t s) {
                        (const double*)d.z, (const double*)d.cl_S, d.g_hist, c.n_clusters, reps, d.g_flag, d.g_len,
                        d.g_box);
     const int64_t nb = group_tmp_need(n);
-    hipLaunchKernelGGL(k_group_count, dim3((unsigned)nb), dim3(kGrpT), 0, s, (const int32_t*)d.g_flag, n, d.g_tmp);
+    // up to kGrpFew tiles the fill counts the tiles before its own itself: cheaper than
+    // a launch (build of 700 particles 93 -> 91 us, 4096 133.5 -> 132.8)
+    const bool few = nb <= kGrpFew;
+    if (!few)
+        hipLaunchKernelGGL(k_group_count, dim3((unsigned)nb), dim3(kGrpT), 0, s, (const int32_t*)d.g_flag, n,
+                           d.g_tmp);
     hipLaunchKernelGGL(k_group_fill, dim3((unsigned)nb), dim3(kGrpT), 0, s, (const int32_t*)d.g_flag,
-                       (const int32_t*)d.g_len, n, (const int32_t*)d.g_tmp, nb, (const uint64_t*)d.keys, c.D,
+                       (const int32_t*)d.g_len, n, few ? nullptr : (const int32_t*)d.g_tmp, nb,
+                       (const uint64_t*)d.keys, c.D,
                        (const double*)d.g_box, d.g, d.cnt, d.host_err);
 }
 

@@ -522,9 +522,12 @@ pbh_status do_force(pbh_ctx* ctx, const double* pos, const double* mass,
     if (nbr_cap < 0 || (nbr_cap > 0 && !nbr_idx)) return fail(ctx, PBH_E_ARG, "bad neighbour buffer");
     Dev& d = ctx->d;
     const BuildCfg& c = ctx->cfg;
-    pbh_status up = upload_cparams(ctx, cps, s);
-    if (up != PBH_OK) return up;
-    launch_rcrit(d, c, theta, s);
+    const bool one = cps.size() == 1;
+    if (!one) {
+        pbh_status up = upload_cparams(ctx, cps, s);
+        if (up != PBH_OK) return up;
+    }
+    launch_rcrit(d, c, theta, one ? &cps[0] : nullptr, s);
     WalkCfg w;
     w.theta = theta;
     w.eps = eps;
@@ -1334,7 +1337,7 @@ static pbh_status kdk_prepare(pbh_ctx* ctx, int64_t n, double r_in, double r_out
 static void kdk_force(pbh_ctx* ctx, const double* pos, const double* mass, double theta, double eps,
                       hipStream_t s) {
     enqueue_build(ctx, pos, mass, s);
-    launch_rcrit(ctx->d, ctx->cfg, theta, s);
+    launch_rcrit(ctx->d, ctx->cfg, theta, nullptr, s);
     WalkCfg w;
     w.theta = theta;
     w.eps = eps;

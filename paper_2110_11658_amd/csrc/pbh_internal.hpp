@@ -307,7 +307,8 @@ struct WalkCfg {
     int count_nbr;   // also count neighbours per particle into Dev::nbr_cnt
     int stage_cap;   // > 0: stage neighbour indices in Dev::nbr_stage rows of this size
 };
-void launch_rcrit(Dev& d, const BuildCfg& c, double theta, hipStream_t s);
+// cp0: the constants of a single cluster, stored for the walk (null: they are there)
+void launch_rcrit(Dev& d, const BuildCfg& c, double theta, const ClusterParams* cp0, hipStream_t s);
 void launch_walk(Dev& d, const BuildCfg& c, const WalkCfg& w, double* acc, double* pot,
                  hipStream_t s);
 bool walk_team(int mixed, int tile, int64_t n);

@@ -132,6 +132,7 @@ __global__ __launch_bounds__(SCAN_T) void k_scan_down(const T* in, int64_t n,
 // it (tmp[0 .. blockIdx.x), in index order per thread, then across the
 // workgroup); the last tile also writes the total to out[n].
 constexpr int64_t kScanFuseTiles = 4096;
+constexpr int64_t kScanFewTiles = 8;
 
 template <typename T, typename O>
 __global__ __launch_bounds__(SCAN_T) void k_scan_down_fused(const T* in, int64_t n,
@@ -140,15 +141,20 @@ __global__ __launch_bounds__(SCAN_T) void k_scan_down_fused(const T* in, int64_t
     __shared__ int64_t s_val[SCAN_TILE];
     __shared__ int64_t s_wave[SCAN_T / 64];
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const int64_t base = (int64_t)blockIdx.x * SCAN_TILE;
     int64_t part = 0;
-    for (int64_t k = t; k < (int64_t)blockIdx.x; k += SCAN_T) part += tmp[k];
+    if (tmp) {
+        for (int64_t k = t; k < (int64_t)blockIdx.x; k += SCAN_T) part += tmp[k];
+    } else {   // few tiles, and `in` is not `out`: summed here
+#pragma unroll 8
+        for (int64_t k = t; k < base; k += SCAN_T) part += (int64_t)in[k];
+    }
     for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o, 64);
     if (lane == 0) s_wave[w] = part;
     __syncthreads();
     int64_t off = 0;
     for (int k = 0; k < SCAN_T / 64; ++k) off += s_wave[k];
     __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * SCAN_TILE;
 #pragma unroll
     for (int k = 0; k < SCAN_I; ++k) {
         int64_t i = base + k * SCAN_T + t;
@@ -182,9 +188,12 @@ template <typename T, typename O>
 void scan_impl(const T* in, O* out, int64_t n, int64_t* tmp, hipStream_t s) {
     const int64_t nb = (n + SCAN_TILE - 1) / SCAN_TILE;
     if (nb >= 1 && nb <= kScanFuseTiles) {
-        hipLaunchKernelGGL((k_scan_reduce<T>), dim3(nb), dim3(SCAN_T), 0, s, in, n, tmp);
+        // up to kScanFewTiles a workgroup sums the tiles before its own itself: cheaper than
+        // a launch (lists of 700 particles 19 -> 16 us, 4096 19.8 -> 17.5). Not in place, where those are being overwritten.
+        const bool few = nb <= kScanFewTiles && (const void*)in != (const void*)out;
+        if (!few) hipLaunchKernelGGL((k_scan_reduce<T>), dim3(nb), dim3(SCAN_T), 0, s, in, n, tmp);
         hipLaunchKernelGGL((k_scan_down_fused<T, O>), dim3(nb), dim3(SCAN_T), 0, s, in, n,
-                           (const int64_t*)tmp, out, nb);
+                           few ? nullptr : (const int64_t*)tmp, out, nb);
         return;
     }
     if (nb == 0) {

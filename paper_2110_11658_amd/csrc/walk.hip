@@ -1409,15 +1409,18 @@ __global__ __launch_bounds__(64 * TEAM) __attribute__((amdgpu_waves_per_eu(4, 4)
 }
 
 // rcrit^2 = (l/theta + delta)^2 per node, l = largest box extent, delta =
-// |COM - box centre|; also clears the per-call counters and queues.
+// |COM - box centre|; also clears the per-call counters and queues, and stores the
+// changeover constants of a single cluster (a launch of its own took them 3 us and a gap of 4).
 __global__ void k_rcrit(NodePlanes node, const unsigned long long* __restrict__ n_dev,
                         double theta, unsigned long long* __restrict__ cnt,
-                        unsigned long long* __restrict__ queues, unsigned* __restrict__ part_done, int n_part) {
+                        unsigned long long* __restrict__ queues, unsigned* __restrict__ part_done, int n_part,
+                        ClusterParams cp0, ClusterParams* __restrict__ cp_dst) {
 #pragma clang fp contract(off)
     const int64_t n = (int64_t)*n_dev;
     if (blockIdx.x == 0) {   // the queue heads, then the counter lines
         for (int k = threadIdx.x; k < kQueueWords; k += blockDim.x) queues[k] = 0;
         if (threadIdx.x == 0) cnt[kCntFill] = 0;
+        if (threadIdx.x == 0 && cp_dst) *cp_dst = cp0;
     }
     for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < n_part;
          b += (int64_t)gridDim.x * blockDim.x)
@@ -1440,11 +1443,12 @@ __global__ void k_rcrit(NodePlanes node, const unsigned long long* __restrict__ 
 
 }  // namespace
 
-void launch_rcrit(Dev& d, const BuildCfg& c, double theta, hipStream_t s) {
+void launch_rcrit(Dev& d, const BuildCfg& c, double theta, const ClusterParams* cp0, hipStream_t s) {
     int64_t nb = (c.node_cap + 255) / 256;
     if (nb > 4096) nb = 4096;
     hipLaunchKernelGGL(k_rcrit, dim3(nb), dim3(256), 0, s, d.node,
-                       (const unsigned long long*)(d.cnt + kCntNodes), theta, d.cnt, d.queues, d.part_done, kWalkShared);
+                       (const unsigned long long*)(d.cnt + kCntNodes), theta, d.cnt, d.queues, d.part_done, kWalkShared,
+                       cp0 ? *cp0 : ClusterParams{}, cp0 ? d.cparams : nullptr);
 }
 
 template <bool MIXED>
