@@ -138,7 +138,7 @@ pbh_status pbh_get_params(const pbh_ctx* ctx, pbh_params* out);
 
 /*
  * Build the octree of one cluster (Section 2.4): bounding box and finiteness
- * check, Morton keys, stable radix sort, octree topology, FP64 monopole and
+ * check, Morton keys, stable sort, octree topology, FP64 monopole and
  * traceless quadrupole moments about each node's centre of mass, and walk
  * groups. n >= 1. pos/mass are read during the call's stream work only; the
  * library keeps its own sorted copy. Returns PBH_E_NONFINITE (after waiting

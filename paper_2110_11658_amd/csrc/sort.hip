@@ -1,4 +1,4 @@
-// sort.hip -- device-wide exclusive scan and stable LSD radix sort (gfx950).
+// sort.hip -- device-wide exclusive scan and stable sorts of 64-bit keys (gfx950).
 //
 // Scan: launches of fixed size (so they can be captured in a graph): per-tile
 // sums, then per-tile scans, each tile adding the sums of the tiles before it

@@ -563,7 +563,7 @@ __device__ inline Part<float> eval_near(const Tiles<float, TC>& T, int cnt, int 
 // the last ones makes the end of the walk finer-grained (a group is up to a
 // millisecond of one wave) at the price of traversing for them twice, which costs
 // the FP64 walk less. q: groups per queue, w: waves per queue (512 for the mixed
-// walk). Walk times in us, sharing none / the rule's / all:
+// walk). Walk times in us, one wave a group, sharing none / the rule's / all:
 //   215 groups 245 / 205 / 205, 1523: 461 / 374 / 375, 3177: 552 / 521 / 576,
 //   6141: 892 / 805 / 899, 26611: 5128 / 5098 / -, FP64 4782: 2012 / 1786 / 1835
 // and with 103236 groups sharing only costs (14090 / 14150).
@@ -970,7 +970,7 @@ __device__ __forceinline__ void team_evaluate(Tiles<R, TC>* T, TeamMem<R, TEAM>&
 
 // Four waves per SIMD (16 per compute unit, which the 64-entry mixed walk's
 // LDS allows): the register budget is held to 128, which this kernel fits
-// without spilling; left free, the compiler takes more and halves nothing but
+// but for a few registers of its set-up; left free, the compiler takes more and halves nothing but
 // occupancy. Larger tiles and the FP64 walk are held lower by their LDS.
 template <bool MIXED, int TC, int TEAM>
 __global__ __launch_bounds__(64 * TEAM) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_walk(WalkParams p) {
