@@ -451,7 +451,7 @@ __device__ inline int force_correct(const HermParams& p, const IrrParams& ip, bo
             const HermState o = load_state(record(p, j, state_buffer(p, j, tn)));
             double xj[3], vj[3];
             predict(p, o, tn, xj, vj);
-            pair_irr<true, false>(K, ip.eps2, me, PartJ{xj[0], xj[1], xj[2], o.m, vj[0], vj[1], vj[2]}, S);
+            pair_irr<true, false, false>(K, ip.eps2, me, PartJ{xj[0], xj[1], xj[2], o.m, vj[0], vj[1], vj[2]}, true, S);
         }
     }
     if (LH > 1) {

@@ -88,12 +88,14 @@ __device__ inline void store_sums(const IrrParams& p, int64_t slot, const IrrSum
 // a target or past their list take part with no record of their own.
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));   // one 16-byte piece
 
-// Entries per lane and round on the key-order route: 2 with the jerk (120
-// registers, 4 waves per SIMD; 3 entries need 136 and drop to 3 waves), 6 for
-// the force alone (94 registers, 5 waves). Measured at 2^20 against 1 to 3
-// and 2 to 6.
+// Entries per lane and round on the key-order route: 3 with the jerk (123
+// registers, 4 waves per SIMD), 6 for the force alone (90 registers, 5 waves).
+// Loads in flight set the rate: 2^20 particles with 64 neighbours, jerk and
+// potential, whole call: 1, 2, 3, 4 entries 765, 718, 704, 750 us (3 entries took
+// 136 registers before the logarithm's constants moved to scalar ones: 2 entries,
+// 730 us); force alone 5, 6, 7 entries 501, 496, 495.
 template <bool JERK>
-constexpr int coop_lane_batch() { return JERK ? 2 : 6; }
+constexpr int coop_lane_batch() { return JERK ? 3 : 6; }
 
 template <bool JERK>
 struct CoopPieces {
@@ -181,7 +183,7 @@ __device__ inline bool irr_sums_coop(const IrrParams& p, int64_t i, bool have, i
 #pragma unroll
         for (int u = 0; u < B; ++u) {
             const PartJ q = coop_take<JERK>(P, u, xch, lane);
-            if (ok[u]) pair_irr<JERK, POT>(K, p.eps2, me, q, S);
+            pair_irr<JERK, POT, true>(K, p.eps2, me, q, ok[u], S);
         }
         m += STEP;
     }

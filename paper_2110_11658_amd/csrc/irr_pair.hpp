@@ -28,6 +28,15 @@ __device__ inline IrrK irr_constants(const ClusterParams& c) {
     return k;
 }
 
+// fma(a, b, c) for a constant c, read from scalar registers. Left to itself the
+// compiler keeps c in a vector register and copies it for every step of a
+// polynomial, since the two-operand form overwrites it.
+__device__ inline double fma_c(double a, double b, double c) {
+    double r;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(c));
+    return r;
+}
+
 // Natural logarithm of a positive normal s. With s = m 2^e and m in
 // [1/sqrt 2, sqrt 2), ln s = e ln 2 + 2 atanh(t) for t = (m - 1)/(m + 1),
 // |t| <= 0.1716, and atanh t = t + t^3/3 + t^5/5 + ... (the terms through t^19
@@ -51,14 +60,14 @@ __device__ inline double log_pos(double s) {
     r = fma(r, fma(-den, r, 1.0), r);
     const double t = num * r, t2 = t * t;
     double q = 1.0 / 19.0;
-    q = fma(q, t2, 1.0 / 17.0);
-    q = fma(q, t2, 1.0 / 15.0);
-    q = fma(q, t2, 1.0 / 13.0);
-    q = fma(q, t2, 1.0 / 11.0);
-    q = fma(q, t2, 1.0 / 9.0);
-    q = fma(q, t2, 1.0 / 7.0);
-    q = fma(q, t2, 1.0 / 5.0);
-    q = fma(q, t2, 1.0 / 3.0);
+    q = fma_c(q, t2, 1.0 / 17.0);
+    q = fma_c(q, t2, 1.0 / 15.0);
+    q = fma_c(q, t2, 1.0 / 13.0);
+    q = fma_c(q, t2, 1.0 / 11.0);
+    q = fma_c(q, t2, 1.0 / 9.0);
+    q = fma_c(q, t2, 1.0 / 7.0);
+    q = fma_c(q, t2, 1.0 / 5.0);
+    q = fma_c(q, t2, 1.0 / 3.0);
     const double at = fma(t * t2, q, t);
     const double ln2_hi = 0x1.62e42fee00000p-1, ln2_lo = 0x1.a39ef35793c76p-33;
     const double de = (double)e;
@@ -67,7 +76,6 @@ __device__ inline double log_pos(double s) {
 
 __device__ inline double phi_regular(const IrrK& cp, double s, double inv) {
 #pragma clang fp contract(off)
-    if (s < cp.r_in) return cp.inner;
     const double t = s * cp.inv_delta;
     double poly = fma(t, cp.e[5], cp.e[4]);
     poly = fma(t, poly, cp.e[3]);
@@ -75,8 +83,8 @@ __device__ inline double phi_regular(const IrrK& cp, double s, double inv) {
     poly = fma(t, poly, cp.e[1]);
     poly = fma(t, poly, cp.e[0]);
     double mid = fma(t, poly, cp.c0);
-    if (cp.r_in > 0.0) mid = fma(cp.l1, log_pos(s), fma(-cp.d0, inv, mid));   // s >= r_in > 0
-    return mid;
+    if (cp.r_in > 0.0) mid = fma(cp.l1, log_pos(s), fma(-cp.d0, inv, mid));
+    return s < cp.r_in ? cp.inner : mid;
 }
 
 struct PartJ {
@@ -115,30 +123,37 @@ struct IrrSums {
     double ax = 0, ay = 0, az = 0, jx = 0, jy = 0, jz = 0, ph = 0;
 };
 
-// One pair (j != i): the terms of F_I, dF_I/dt and Phi_I.
-template <bool JERK, bool POT>
-__device__ inline void pair_irr(const IrrK& cp, double eps2, const PartJ& me, const PartJ& q,
+// One pair, summed where ok (j != i): the terms of F_I, dF_I/dt and Phi_I. SELECT:
+// the changeover band's terms are computed for every pair and selected, as almost
+// every pair inside r_out lies in the band; with branches for the pair, for r_out
+// and for the band the sums were copied at each. (The Hermite corrector, short of
+// registers and with a few pairs a lane, is 2 % faster with the branch.)
+template <bool JERK, bool POT, bool SELECT>
+__device__ inline void pair_irr(const IrrK& cp, double eps2, const PartJ& me, const PartJ& q, bool ok,
                                 IrrSums& S) {
 #pragma clang fp contract(off)
     const double dx = q.x - me.x;
     const double dy = q.y - me.y;
     const double dz = q.z - me.z;
     const double s2 = fma(dz, dz, fma(dy, dy, fma(dx, dx, eps2)));
-    if (!(s2 < cp.rout2)) return;   // K = 0, Phi_I = 0
+    if (!(ok && s2 < cp.rout2)) return;   // K = 0, Phi_I = 0
     const double m = q.m;
     const double inv = rsqrt(s2);
     const double s = s2 * inv;
     const double inv2 = inv * inv;
     const double inv3 = inv * inv2;
+    // changeover band s >= r_in (a step changeover has inv_delta = 0: K = 1)
     double K = 1.0, slope = 0.0;
-    if (s >= cp.r_in) {   // changeover band (a step changeover has inv_delta = 0: K = 1)
+    const bool band = s >= cp.r_in;
+    if (SELECT || band) {
         const double x = (s - cp.r_in) * cp.inv_delta;
         const double omx = 1.0 - x;
         const double x2 = x * x;
-        const double g = x2 * x2 * fma(x, fma(x, fma(-20.0, x, 70.0), -84.0), 35.0);
-        K = 1.0 - g;
+        const double h = fma(-20.0, x, 70.0);
+        const double g = x2 * x2 * (SELECT ? fma_c(x, fma_c(x, h, -84.0), 35.0) : fma(x, fma(x, h, -84.0), 35.0));
         const double o3 = omx * omx * omx;
-        slope = 140.0 * (x2 * x) * o3 * cp.inv_delta;
+        K = band ? 1.0 - g : K;
+        slope = band ? 140.0 * (x2 * x) * o3 * cp.inv_delta : slope;
     }
     const double mk3 = m * K * inv3;
     S.ax = fma(mk3, dx, S.ax);
@@ -229,7 +244,7 @@ __device__ inline bool irr_sums(const IrrParams& p, int64_t i, IrrSums& S, unsig
             }
 #pragma unroll
             for (int u = 0; u < kIrrBatch; ++u)
-                if (ok[u]) pair_irr<JERK, POT>(K, p.eps2, me, q[u], S);
+                pair_irr<JERK, POT, true>(K, p.eps2, me, q[u], ok[u], S);
         }
     }
     return valid;
@@ -296,7 +311,7 @@ __device__ inline bool irr_sums_lanes(const IrrParams& p, int64_t i, int g, IrrS
             }
 #pragma unroll
             for (int u = 0; u < kIrrLaneBatch; ++u)
-                if (ok[u]) pair_irr<JERK, POT>(K, p.eps2, me, q[u], S);
+                pair_irr<JERK, POT, true>(K, p.eps2, me, q[u], ok[u], S);
         }
     }
     S.ax = group_sum(S.ax);
