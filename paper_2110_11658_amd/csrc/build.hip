@@ -612,9 +612,11 @@ __global__ __launch_bounds__(kMomT) void k_moments_tile(int64_t n, int D, int64_
 // one of `outer`: of a level, only the last node that starts in a unit can reach
 // beyond it. One workgroup per outer unit, eight lanes per inner unit, level by
 // level; levels without such nodes are skipped.
-constexpr int kStradT = 512;
-constexpr int kStradU = kStradT / 8;   // inner units at a time
-__global__ __launch_bounds__(kStradT) void k_moments_straddle(int64_t n, int D, int64_t ntile, int64_t cap,
+// kStradU of them at a time: 64, or 128 where that saves a second launch (65537 to
+// 131072 particles: 100003 build in 202 us with two, 187 with one of 1024 threads;
+// with more units than that the larger workgroups cost 6 us at 524288).
+template <int kStradU>
+__global__ __launch_bounds__(8 * kStradU) void k_moments_straddle(int64_t n, int D, int64_t ntile, int64_t cap,
                                                               int64_t inner, int64_t outer,
                                                               const int32_t* __restrict__ table,
                                                               const double* __restrict__ x,
@@ -622,7 +624,7 @@ __global__ __launch_bounds__(kStradT) void k_moments_straddle(int64_t n, int D, 
                                                               const double* __restrict__ z,
                                                               const double* __restrict__ m, NodePlanes node,
                                                               Mom64Planes q64, Mom32Planes q32) {
-    __shared__ MomLds s_m[kStradT / 64];
+    __shared__ MomLds s_m[kStradU / 8];
     __shared__ int s_off[64];
     __shared__ unsigned s_levels;   // levels at which some unit has such a node
     __shared__ int s_cand[kMaxLevels][kStradU];   // of the first kStradU units: the node and its range
@@ -1001,14 +1003,19 @@ void launch_moments(Dev& d, const BuildCfg& c, hipStream_t s) {
                        c.n, c.D, ntile, c.node_cap, (const int32_t*)d.topo_table, (const double*)d.x,
                        (const double*)d.y, (const double*)d.z, (const double*)d.m, d.node, d.q64, d.q32);
     // units of 1024 particles, then of 64 times that; the last launch takes all
-    for (int64_t inner = kMomTiles; inner < ntile; inner *= kStradU) {
-        const int64_t outer = inner * kStradU;
-        const bool all = outer >= ntile || inner > kMomTiles;
-        hipLaunchKernelGGL(k_moments_straddle, dim3(all ? 1u : (unsigned)((ntile + outer - 1) / outer)),
-                           dim3(kStradT), 0, s, c.n, c.D, ntile, c.node_cap, inner, all ? ntile : outer,
-                           (const int32_t*)d.topo_table, (const double*)d.x, (const double*)d.y,
+    auto straddle = [&](auto kernel, int64_t u, int64_t inner, int64_t outer) {
+        const int64_t blocks = (ntile + outer - 1) / outer;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3((unsigned)(8 * u)), 0, s, c.n, c.D, ntile, c.node_cap,
+                           inner, outer, (const int32_t*)d.topo_table, (const double*)d.x, (const double*)d.y,
                            (const double*)d.z, (const double*)d.m, d.node, d.q64, d.q32);
-        if (all) break;
+    };
+    constexpr int64_t kU = 64;
+    if (ntile > kMomTiles * kU && ntile <= 2 * kMomTiles * kU) {
+        straddle(k_moments_straddle<2 * kU>, 2 * kU, kMomTiles, ntile);
+    } else if (ntile > kMomTiles) {
+        const bool one = ntile <= kMomTiles * kU;
+        straddle(k_moments_straddle<kU>, kU, kMomTiles, one ? ntile : kMomTiles * kU);
+        if (!one) straddle(k_moments_straddle<kU>, kU, kMomTiles * kU, ntile);
     }
 }
 
