@@ -218,18 +218,15 @@ __device__ inline int32_t active_at(const HermParams& p, const int4* end, int ks
 // bucket with one device atomic per level (buckets >= ks restart from zero in
 // their other buffer, bucket ks - 1 keeps its `keep` members), then stores the
 // particles there. Same-address device atomics serialise, so one per workgroup
-// and level, not per wave. SOLO: the calling workgroup takes every item and
-// newcnt, 64 counts, is LDS memory that it sets. `step` runs in every lane of a
-// wave that holds an item.
-template <int LH, int T, bool SOLO, class Item, class Step>
+// and level, not per wave. `step` runs in every lane of a wave that holds an item.
+template <int LH, int T, class Item, class Step>
 __device__ inline void step_and_bucket(const HermParams& p, unsigned long long* newcnt, int ks, long long keep_cnt,
                                        uint64_t mask_new, int64_t n_items, Item item, Step step) {
     constexpr int TG = T / LH;
     __shared__ int s_h[64];
     __shared__ long long s_b[64];
     const int64_t per = ((n_items + gridDim.x - 1) / gridDim.x + TG - 1) / TG * TG;
-    const int64_t c0 = SOLO ? 0 : (int64_t)blockIdx.x * per;
-    const int64_t c1 = SOLO || c0 + per > n_items ? n_items : c0 + per;
+    const int64_t c0 = (int64_t)blockIdx.x * per, c1 = c0 + per < n_items ? c0 + per : n_items;
     if (c0 >= c1) return;   // workgroup-uniform
     if (threadIdx.x < 64) s_h[threadIdx.x] = 0;
     __syncthreads();
@@ -256,13 +253,7 @@ __device__ inline void step_and_bucket(const HermParams& p, unsigned long long* 
         }
     }
     __syncthreads();
-    if (SOLO) {
-        if (threadIdx.x < 64) {
-            const int k = threadIdx.x;
-            s_b[k] = k == ks - 1 ? keep_cnt : 0;
-            newcnt[k] = (unsigned long long)s_h[k];
-        }
-    } else if (threadIdx.x <= kHermK && s_h[threadIdx.x] > 0) {
+    if (threadIdx.x <= kHermK && s_h[threadIdx.x] > 0) {
         const int k = threadIdx.x;
         s_b[k] = (k == ks - 1 ? keep_cnt : 0) + (long long)atomicAdd(newcnt + k, (unsigned long long)s_h[k]);
     }
@@ -276,6 +267,25 @@ __device__ inline void step_and_bucket(const HermParams& p, unsigned long long* 
             const uint32_t v = p.slot[k];
             put((int)(v >> kSlotShift), (int64_t)(v & kSlotMask), item(k));
         }
+}
+
+// The same by one workgroup for every item: ranks are places in the buckets at
+// once, without a barrier. count[64] (LDS): particles per new level, zero at first.
+template <int LH, int T, class Item, class Step>
+__device__ inline void step_solo(const HermParams& p, int* count, int ks, long long keep_cnt, uint64_t mask_new,
+                                 int n_items, Item item, Step step) {
+    constexpr int TG = T / LH;
+    for (int k0 = 0; k0 < n_items; k0 += TG) {
+        const int k = k0 + (int)threadIdx.x / LH;
+        const bool have = k < n_items;
+        if (__ballot(have) == 0) break;   // this wave holds no more items
+        const int32_t i = have ? item(k) : 0;
+        const int level = step(have, i & ~kInRec1, i & kInRec1 ? 1 : 0);
+        if (have && threadIdx.x % LH == 0) {
+            const long long at = (level == ks - 1 ? keep_cnt : 0) + atomicAdd(&count[level], 1);
+            bucket_of(p, (int)((mask_new >> level) & 1), level)[at] = i ^ kInRec1;
+        }
+    }
 }
 
 // block step in ticks: dt_max / 2^k not above `want` (k <= kHermK), dividing tau
@@ -356,7 +366,7 @@ __device__ inline void pair_d23(const ClusterParams& cp, double eps2, const doub
 // list order; lists from the regular-force walk are short), then eq. dt.
 __global__ __launch_bounds__(256) void k_herm_start(HermParams p, IrrParams ip) {
     // block 0's counts, every level filled (ks = 0) in buffer 0, the states in record 0
-    step_and_bucket<1, 256, false>(p, lev_new(p, 0), 0, 0, 0ull, p.n,
+    step_and_bucket<1, 256>(p, lev_new(p, 0), 0, 0, 0ull, p.n,
                                    [](int64_t k) { return (int32_t)k | kInRec1; }, [&](bool have, int32_t i, int) {
 #pragma clang fp contract(off)
         if (!have) return 0;   // a lane without an item
@@ -496,7 +506,7 @@ __device__ inline int force_correct(const HermParams& p, const IrrParams& ip, bo
 __global__ __launch_bounds__(kHermT) void k_herm_block(HermParams p, IrrParams ip, int b) {
     __shared__ long long s_cnt[64];
     __shared__ int4 s_end[16];
-    __shared__ unsigned long long s_new[64];
+    __shared__ int s_new[64];   // of the last block of a row
     __shared__ long long s_tn;
     __shared__ int s_nact, s_ks;
     const int q = b & 1;
@@ -507,7 +517,7 @@ __global__ __launch_bounds__(kHermT) void k_herm_block(HermParams p, IrrParams i
     const int lane = threadIdx.x;
     const bool wave0 = lane < 64;
     long long c = 0, t = 0;
-    int deepest = -1;
+    int last = 0, deepest = -1;
     unsigned long long blocks = 0, steps = 0;
     auto plan = [&](long long old, long long add, int kp) {
         c = lane <= kHermK ? merged_count(old, add, kp, lane) : 0;
@@ -547,6 +557,7 @@ __global__ __launch_bounds__(kHermT) void k_herm_block(HermParams p, IrrParams i
         if (p.done_host && (done || all > kHermMaxBlocks)) *p.done_host = all > kHermMaxBlocks ? 2ull : 1ull;
     };
     if (wave0) {
+        s_new[lane] = 0;
         t = (long long)p.lev[kLevT + q];
         const long long old = lane <= kHermK ? (long long)lev_cnt(p, q)[lane] : 0;
         const long long add = lane <= kHermK ? (long long)lev_new(p, b)[lane] : 0;
@@ -571,18 +582,18 @@ __global__ __launch_bounds__(kHermT) void k_herm_block(HermParams p, IrrParams i
         unsigned long long* const newcnt = lev_new(p, b + 1);
         // eight lanes share a particle's list while the grid has lanes for all
         if ((long long)nact * kHermLanes <= (long long)gridDim.x * kHermT)
-            step_and_bucket<kHermLanes, kHermT, false>(
+            step_and_bucket<kHermLanes, kHermT>(
                 p, newcnt, ks, keep, mask_new, nact, item,
                 [&](bool have, int32_t i, int buf) { return force_correct<kHermLanes>(p, ip, have, i, buf, tn); });
         else
-            step_and_bucket<1, kHermT, false>(p, newcnt, ks, keep, mask_new, nact, item,
+            step_and_bucket<1, kHermT>(p, newcnt, ks, keep, mask_new, nact, item,
                                               [&](bool have, int32_t i, int buf) { return force_correct<1>(p, ip, have, i, buf, tn); });
         return;
     }
     if (blockIdx.x != 0) return;
     for (int it = 1;; ++it) {
         const uint64_t mask_new = mask ^ (~0ull << ks);
-        step_and_bucket<kHermLanes, kHermT, true>(
+        step_solo<kHermLanes, kHermT>(
             p, s_new, ks, ks > 0 ? s_cnt[ks - 1] : 0, mask_new, nact, item,
             [&](bool have, int32_t i, int buf) { return force_correct<kHermLanes>(p, ip, have, i, buf, tn); });
         blocks += 1;
@@ -590,8 +601,10 @@ __global__ __launch_bounds__(kHermT) void k_herm_block(HermParams p, IrrParams i
         __syncthreads();   // every record, bucket entry and count of the block is stored
         const long long before = c;
         if (wave0) {
+            last = s_new[lane];
+            s_new[lane] = 0;
             t = tn;
-            plan(before, (long long)s_new[lane], ks);
+            plan(before, last, ks);
         }
         __syncthreads();
         if (it < kHermInner && s_nact > 0 && s_nact <= kHermSolo) {
@@ -603,7 +616,7 @@ __global__ __launch_bounds__(kHermT) void k_herm_block(HermParams p, IrrParams i
         }
         if (wave0) {   // (the next launch plans that block again)
             c = before;
-            if (lane <= kHermK) lev_new(p, b + 1)[lane] = s_new[lane];
+            if (lane <= kHermK) lev_new(p, b + 1)[lane] = (unsigned long long)last;
             publish(tn, ks, mask_new, false);
         }
         return;
