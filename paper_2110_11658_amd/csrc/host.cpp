@@ -201,12 +201,23 @@ int64_t node_capacity(int64_t n, int D, int n_leaf, int C) {
     return 2 * n + (int64_t)D * ((n + n_leaf) / (n_leaf + 1)) + C + 64;
 }
 
+// Whether a walk takes a team of four waves a group (see walk_team). Groups of fewer
+// than 32 particles leave a team's evaluating waves little to do for the same
+// traversal, and there are more of them, so the line falls with the square of
+// n_crit. Walk in us, one wave a group / a team, n_crit 4, 8, 16, 32, 64: 5000
+// particles 150/198, 134/139, 154/128, 356/255, 353/253; 20000 347/614, 274/374,
+// 262/274, 305/257, 449/345; 40000 574/1206, 413/702, 342/446, 417/385, 564/471.
+bool use_team(const pbh_ctx* ctx, int mixed) {
+    const int64_t c = std::min(ctx->cfg.n_crit, 32);
+    return walk_team(mixed, ctx->params.walk_tile, ctx->cfg.n) && ctx->cfg.n <= 40 * c * c;
+}
+
 // persistent walk grid for the context's precision and tile: resident
 // workgroups per compute unit (LDS and registers) times the compute units
 int walk_grid(pbh_ctx* ctx, int mixed) {
     const int tile = ctx->params.walk_tile;
     const int t = tile == 128 ? 2 : (tile == 96 ? 1 : 0);
-    const bool team = walk_team(mixed, tile, ctx->cfg.n);
+    const bool team = use_team(ctx, mixed);
     int& g = team ? ctx->grid_team : ctx->grid_tile[mixed ? 1 : 0][t];
     if (g == 0) g = walk_blocks_per_cu(mixed, tile, team) * ctx->cus;
     const int gmax = mixed ? ctx->grid_mixed : ctx->grid_fp64;   // the stacks are sized for this
@@ -536,7 +547,7 @@ pbh_status do_force(pbh_ctx* ctx, const double* pos, const double* mass,
     w.max_copies = ctx->params.lanes_per_particle ? ctx->params.lanes_per_particle : 64;
     w.cpos = pos;
     w.cmass = mass;
-    w.team = walk_team(w.mixed, w.tile, c.n);
+    w.team = use_team(ctx, w.mixed);
     w.grid = walk_grid(ctx, w.mixed);   // persistent: workgroups leave when the group queue is empty
     w.stack_cap = kStackCap;
     w.count_nbr = nbr_off != nullptr;   // the walk counts the neighbours of every particle
@@ -1344,7 +1355,7 @@ static void kdk_force(pbh_ctx* ctx, const double* pos, const double* mass, doubl
     w.mixed = ctx->params.prec == PBH_MIXED;
     w.tile = ctx->params.walk_tile;
     w.max_copies = ctx->params.lanes_per_particle ? ctx->params.lanes_per_particle : 64;
-    w.team = walk_team(w.mixed, w.tile, ctx->cfg.n);
+    w.team = use_team(ctx, w.mixed);
     w.grid = walk_grid(ctx, w.mixed);
     w.stack_cap = kStackCap;
     w.count_nbr = 0;
