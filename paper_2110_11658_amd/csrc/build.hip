@@ -498,12 +498,16 @@ __device__ inline void moments_group(MomLds& L, bool on, int b, int4 rg, int kid
             e = p < n8 ? fmin(e, v[p] * flip) : e;
         }
         if (on && leaf) {
-            for (int p = 8; p < nsub; ++p) {   // (leaves of more than 8 particles)
-                const int j = rg.x + p;
-                const double mj = m[j], xs = g == 1 ? x[j] : (g == 2 ? y[j] : z[j]);
-                const double xb = kb % 3 == 1 ? x[j] : (kb % 3 == 2 ? y[j] : z[j]);
-                a = g == 0 ? a + mj : a + mj * xs;
-                e = fmin(e, xb * flip);
+            // leaves of more than 8 particles: the loads of four at a time, in flight together
+            // (build of 131072 particles in leaves of up to 32 in 319 -> 270 us, of 1048576
+            // 567 -> 504; eight at a time, in more registers, 311 and 554)
+            const double* ps = (g == 1 ? x : (g == 2 ? y : z)) + rg.x;
+            const double* pb = (kb % 3 == 1 ? x : (kb % 3 == 2 ? y : z)) + rg.x;
+#pragma unroll 4
+            for (int p = 8; p < nsub; ++p) {
+                const double mj = m[rg.x + p], xs = ps[p];
+                a = a + (g == 0 ? mj : mj * xs);
+                e = fmin(e, pb[p] * flip);
             }
         }
         if (g < 4) L.r[g][nd] = a;
@@ -538,6 +542,7 @@ __device__ inline void moments_group(MomLds& L, bool on, int b, int4 rg, int kid
         for (int p = 0; p < 8; ++p)
             if (p < n8) a = a + u[p];
         if (on && leaf) {
+#pragma unroll 4
             for (int p = 8; p < nsub; ++p) {
                 const int j = rg.x + p;
                 const double dx = x[j] - com[0], dy = y[j] - com[1], dz = z[j] - com[2];
@@ -732,6 +737,42 @@ __device__ inline void emit_group(int begin, int count, const double* lo, const 
     }
 }
 
+// The runs of the wave's big leaves (run: their length, 0 for lanes without one; slot:
+// their histogram), a lane a run: leaf of 20000 particles in one cell of the finest
+// level 2809 -> 40 us, and 2623 -> 35 for the pass that writes the groups (a lane a leaf
+// waited for every particle in turn).
+template <bool HIST>
+__device__ inline void big_leaf_runs(int lane, int begin, int count, int run, int64_t slot,
+                                     const double* __restrict__ x, const double* __restrict__ y,
+                                     const double* __restrict__ z, unsigned* __restrict__ hist,
+                                     int32_t* __restrict__ flag, int32_t* __restrict__ len,
+                                     double* __restrict__ box) {
+    const int runs = run ? (count + run - 1) / run : 0;
+    const int incl = wave_incl_scan(runs, lane);   // (at most n + 64)
+    const int total = last_lane(incl);
+    for (int q0 = 0; q0 < total; q0 += 64) {
+        const int q = q0 + lane;
+        int src = 0;   // the first lane with q < incl
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) src += __shfl(incl, src + o - 1, 64) <= q ? o : 0;
+        const int rl = __shfl(run, src, 64), first = __shfl(incl - runs, src, 64);
+        const int lb = __shfl(begin, src, 64), le = lb + __shfl(count, src, 64);
+        const int64_t sl = __shfl((long long)slot, src, 64);
+        if (q >= total) continue;   // (past the last run)
+        const int s0 = lb + (q - first) * rl, e0 = min(s0 + rl, le);
+        double lo[3] = {x[s0], y[s0], z[s0]}, hi[3] = {lo[0], lo[1], lo[2]};
+#pragma unroll 4
+        for (int j = s0 + 1; j < e0; ++j) {
+            const double v[3] = {x[j], y[j], z[j]};
+            for (int k = 0; k < 3; ++k) {
+                if (v[k] < lo[k]) lo[k] = v[k];
+                if (v[k] > hi[k]) hi[k] = v[k];
+            }
+        }
+        emit_group<HIST>(s0, e0 - s0, lo, hi, hist + sl * kOctaves, flag, len, box);
+    }
+}
+
 template <bool HIST>
 __global__ __launch_bounds__(256) void k_group_pass(NodePlanes node,
                              const unsigned long long* __restrict__ n_dev,
@@ -741,41 +782,32 @@ __global__ __launch_bounds__(256) void k_group_pass(NodePlanes node,
                              unsigned* __restrict__ hist, int nc, int reps, int32_t* __restrict__ flag,
                              int32_t* __restrict__ len, double* __restrict__ box) {
     const int64_t nn = (int64_t)*n_dev;
-    for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < nn;
-         b += (int64_t)gridDim.x * blockDim.x) {
+    const int lane = threadIdx.x & 63;
+    // (the loop is wave-uniform: all lanes take part in big_leaf_runs)
+    for (int64_t b0 = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x - lane); b0 < nn;
+         b0 += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t b = b0 + lane;
+        const bool on = b < nn;
         WNode w;
-        node.box(b, w.lo, w.hi);
-        const int4 rg = node.range(b);
-        w.begin = rg.x; w.count = rg.y; w.first_child = rg.z; w.nchild = rg.w;
-        const int c = cluster_of(keys[w.begin], D);
-        const double S = HIST ? INFINITY : cl_S[c];
-        unsigned* h = hist + ((int64_t)(b % reps) * nc + c) * kOctaves;
-        const double ext = box_extent(w.lo, w.hi);
-        const bool big = w.count > n_crit || ext > S;
-        if (b < nc && !big) emit_group<HIST>(w.begin, w.count, w.lo, w.hi, h, flag, len, box);
-        if (!big) continue;
-        if (w.nchild == 0) {
-            if (ext > S) {
-                for (int j = w.begin; j < w.begin + w.count; ++j) {
-                    const double v[3] = {x[j], y[j], z[j]};
-                    emit_group<HIST>(j, 1, v, v, h, flag, len, box);
-                }
-            } else {
-                for (int s0 = w.begin; s0 < w.begin + w.count; s0 += n_crit) {
-                    const int e0 = min(s0 + n_crit, w.begin + w.count);
-                    double lo[3], hi[3];
-                    for (int j = s0; j < e0; ++j) {
-                        const double v[3] = {x[j], y[j], z[j]};
-                        for (int k = 0; k < 3; ++k) {
-                            if (j == s0 || v[k] < lo[k]) lo[k] = v[k];
-                            if (j == s0 || v[k] > hi[k]) hi[k] = v[k];
-                        }
-                    }
-                    emit_group<HIST>(s0, e0 - s0, lo, hi, h, flag, len, box);
-                }
-            }
-            continue;
+        w.begin = w.count = w.nchild = 0;
+        int64_t slot = 0;
+        double S = INFINITY, ext = 0.0;
+        bool big = false;
+        if (on) {
+            node.box(b, w.lo, w.hi);
+            const int4 rg = node.range(b);
+            w.begin = rg.x; w.count = rg.y; w.first_child = rg.z; w.nchild = rg.w;
+            const int c = cluster_of(keys[w.begin], D);
+            if (!HIST) S = cl_S[c];
+            slot = (int64_t)(b % reps) * nc + c;
+            ext = box_extent(w.lo, w.hi);
+            big = w.count > n_crit || ext > S;
         }
+        unsigned* h = hist + slot * kOctaves;
+        if (on && b < nc && !big) emit_group<HIST>(w.begin, w.count, w.lo, w.hi, h, flag, len, box);
+        const int run = !big || w.nchild != 0 ? 0 : (ext > S ? 1 : n_crit);   // of a big leaf
+        if (__ballot(run != 0)) big_leaf_runs<HIST>(lane, w.begin, w.count, run, slot, x, y, z, hist, flag, len, box);
+        if (!big || run != 0) continue;
         int run_begin = 0, run_count = 0;
         double rlo[3] = {0, 0, 0}, rhi[3] = {0, 0, 0};
         // the children's boxes and counts are loaded together (one memory
