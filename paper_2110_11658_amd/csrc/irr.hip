@@ -28,6 +28,8 @@
 // are taken in batches whose loads issue together (a gather costs cache
 // latency, not arithmetic). Lists, targets and offsets are range-checked: a
 // bad entry is skipped and flagged, never dereferenced.
+#include <type_traits>
+
 #include "irr_pair.hpp"
 #include "pbh_internal.hpp"
 #include "wave.hpp"
@@ -88,18 +90,20 @@ __device__ inline void store_sums(const IrrParams& p, int64_t slot, const IrrSum
 // a target or past their list take part with no record of their own.
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));   // one 16-byte piece
 
-// Entries per lane and round on the key-order route: 3 with the jerk (123
-// registers, 4 waves per SIMD), 6 for the force alone (90 registers, 5 waves).
-// Loads in flight set the rate: 2^20 particles with 64 neighbours, jerk and
-// potential, whole call: 1, 2, 3, 4 entries 765, 718, 704, 750 us (3 entries took
-// 136 registers before the logarithm's constants moved to scalar ones: 2 entries,
-// 730 us); force alone 5, 6, 7 entries 501, 496, 495.
-template <bool JERK>
-constexpr int coop_lane_batch() { return JERK ? 3 : 6; }
-
-template <bool JERK>
+// Entries per lane and round (N) on the key-order route: 6 for the force alone (then
+// 2 where no lane of the wave has more left), 3 with the jerk or 2 for short lists.
+// Loads in flight set the rate of long lists; on short ones the entries of a round
+// that no lane has cost their loads and exchanges. 2^20 particles, whole call in us,
+// mean list 8, 24, 64:
+//   jerk             2 entries 227, 337, 634; 3 entries 243, 352, 621
+//   jerk, potential  2 entries 270, 396, 718; 3 entries 274, 393, 700
+//   force            6 entries 181 (8), 488 (64); with the rounds of 2 163, 492
+//   force, potential 6 entries 294 (24), 553 (64); with the rounds of 2 283, 556
+// An entry that no lane of the wave has is not exchanged (jerk, 3 entries, mean list 8
+// 254 -> 244 us).
+template <bool JERK, int N>
 struct CoopPieces {
-    static constexpr int B = coop_lane_batch<JERK>();
+    static constexpr int B = N;
     static constexpr int CH = JERK ? 4 : 2;   // 16-byte pieces per record
     static constexpr int RPI = 64 / CH;       // records per load instruction
     u32x4 piece[B][CH];
@@ -109,10 +113,10 @@ struct CoopPieces {
 // lane % CH of the records of lanes RPI k + lane / CH (k < CH). rk holds the
 // key rank of each lane's record, or 0 where the lane has no pair: those
 // slots all load record 0, one shared line per instruction, and are ignored.
-template <bool JERK>
+template <bool JERK, int N>
 __device__ inline void coop_load(const IrrRec* __restrict__ rec, const int32_t* rk, int lane,
-                                 CoopPieces<JERK>& P) {
-    using C = CoopPieces<JERK>;
+                                 CoopPieces<JERK, N>& P) {
+    using C = CoopPieces<JERK, N>;
     const int c = lane % C::CH;
     int rt[C::B][C::CH];
 #pragma unroll
@@ -128,9 +132,9 @@ __device__ inline void coop_load(const IrrRec* __restrict__ rec, const int32_t* 
 }
 
 // Entry u's record of this lane, passed through the wave's LDS slot.
-template <bool JERK>
-__device__ inline PartJ coop_take(const CoopPieces<JERK>& P, int u, IrrRec* xch, int lane) {
-    using C = CoopPieces<JERK>;
+template <bool JERK, int N>
+__device__ inline PartJ coop_take(const CoopPieces<JERK, N>& P, int u, IrrRec* xch, int lane) {
+    using C = CoopPieces<JERK, N>;
     const int c = lane % C::CH;
 #pragma unroll
     for (int k = 0; k < C::CH; ++k)
@@ -141,7 +145,7 @@ __device__ inline PartJ coop_take(const CoopPieces<JERK>& P, int u, IrrRec* xch,
     return q;
 }
 
-template <bool JERK, bool POT, bool MULTI>
+template <bool JERK, bool POT, bool MULTI, int N>
 __device__ inline bool irr_sums_coop(const IrrParams& p, int64_t i, bool have, int g, IrrSums& S,
                                      unsigned long long& bad, IrrRec* xch) {
     const int lane = (int)(threadIdx.x & 63);
@@ -152,8 +156,6 @@ __device__ inline bool irr_sums_coop(const IrrParams& p, int64_t i, bool have, i
     const IrrK K = irr_constants(MULTI ? *cp : p.cp0);
     PartJ me = {};
     if (valid) me = load_rec<JERK>(p.rec, p.rank[i]);
-    constexpr int B = coop_lane_batch<JERK>();
-    constexpr int64_t STEP = (int64_t)kIrrLanes * B;
     int64_t m = b + g;
     if (!valid) m = e = 0;
     // While any lane of the wave has entries left, some list holds an entry
@@ -161,7 +163,8 @@ __device__ inline bool irr_sums_coop(const IrrParams& p, int64_t i, bool have, i
     // a lane without an entry loads those, and its loads stay in bounds. A
     // lane with entries clamps to its own last one, e - 1 in [b, cap).
     const int64_t last = m < e ? e - 1 : 0;
-    while (__builtin_amdgcn_ballot_w64(m < e) != 0) {
+    auto round = [&](auto entries) {   // the next B entries of every lane
+        constexpr int B = decltype(entries)::value;
         int32_t jv[B], rk[B];
         bool ok[B];
 #pragma unroll
@@ -178,14 +181,20 @@ __device__ inline bool irr_sums_coop(const IrrParams& p, int64_t i, bool have, i
             rk[u] = p.rank[ok[u] ? jv[u] : 0];
             if (!ok[u]) rk[u] = 0;
         }
-        CoopPieces<JERK> P;
-        coop_load<JERK>(p.rec, rk, lane, P);
+        CoopPieces<JERK, B> P;
+        coop_load<JERK, B>(p.rec, rk, lane, P);
 #pragma unroll
         for (int u = 0; u < B; ++u) {
-            const PartJ q = coop_take<JERK>(P, u, xch, lane);
+            if (u > 0 && __builtin_amdgcn_ballot_w64(ok[u]) == 0) continue;
+            const PartJ q = coop_take<JERK, B>(P, u, xch, lane);
             pair_irr<JERK, POT, true>(K, p.eps2, me, q, ok[u], S);
         }
-        m += STEP;
+        m += (int64_t)kIrrLanes * B;
+    };
+    using std::integral_constant;
+    while (__builtin_amdgcn_ballot_w64(m < e) != 0) {
+        if (!JERK && __builtin_amdgcn_ballot_w64(m + 2 * (int64_t)kIrrLanes < e) == 0) round(integral_constant<int, 2>());
+        else round(integral_constant<int, N>());
     }
     S.ax = group_sum(S.ax);
     S.ay = group_sum(S.ay);
@@ -205,20 +214,21 @@ constexpr unsigned kIrrChunk = 16;
 
 // One target k (a lane group, lane g of it): the group's sums over its list,
 // stored at its output slot by lane 0.
-template <bool JERK, bool POT, bool SORTED, bool MULTI>
+template <bool JERK, bool POT, bool MULTI>
 __device__ inline void irr_target(const IrrParams& p, int64_t k, int g) {
     unsigned long long bad = 0;
     const int64_t i = p.tgt ? (int64_t)p.tgt[k] : (p.order ? (int64_t)p.order[k] : k);
     IrrSums S;
-    const bool valid = irr_sums_lanes<JERK, POT, SORTED, MULTI>(p, i, g, S, bad);
+    const bool valid = irr_sums_lanes<JERK, POT, false, MULTI>(p, i, g, S, bad);
     if (g == 0 && (valid || p.tgt)) store_sums<JERK, POT>(p, p.tgt ? k : i, S);   // no slot of its own otherwise
     if (bad) atomicOr(p.err, bad);
 }
 
-template <bool JERK, bool POT, bool SORTED, bool MULTI>
+// N: entries per lane and round of the key-order route, 0 for the caller-array route
+template <bool JERK, bool POT, bool MULTI, int N>
 __global__ __launch_bounds__(256) void k_irregular(IrrParams p) {
     const int g = threadIdx.x % kIrrLanes;   // lane groups never straddle a workgroup
-    if (SORTED) {
+    if constexpr (N > 0) {
         // key-order targets in chunks per XCD (cache locality and load balance);
         // every lane takes part in the cooperative loads, with a target or not
         __shared__ IrrRec xch[256 / 64][64];
@@ -229,7 +239,7 @@ __global__ __launch_bounds__(256) void k_irregular(IrrParams p) {
         const int64_t kk = have ? k : 0;
         const int64_t i = p.tgt ? (int64_t)p.tgt[kk] : (p.order ? (int64_t)p.order[kk] : kk);
         IrrSums S;
-        const bool valid = irr_sums_coop<JERK, POT, MULTI>(p, i, have, g, S, bad, xch[threadIdx.x / 64]);
+        const bool valid = irr_sums_coop<JERK, POT, MULTI, N>(p, i, have, g, S, bad, xch[threadIdx.x / 64]);
         if (have && g == 0 && (valid || p.tgt)) store_sums<JERK, POT>(p, p.tgt ? k : i, S);
         if (bad) atomicOr(p.err, bad);
         return;
@@ -238,7 +248,7 @@ __global__ __launch_bounds__(256) void k_irregular(IrrParams p) {
     const int64_t nt = p.n_tgt;
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < nt * kIrrLanes;
          v += (int64_t)gridDim.x * blockDim.x)
-        irr_target<JERK, POT, SORTED, MULTI>(p, v / kIrrLanes, g);
+        irr_target<JERK, POT, MULTI>(p, v / kIrrLanes, g);
 }
 
 template <bool JERK, bool POT, bool MULTI>
@@ -251,10 +261,17 @@ void launch_route(const IrrParams& p, hipStream_t s) {
     if (p.rec && fits) {   // grid padded to whole rounds of chunks over the XCDs
         const int64_t round = (int64_t)kQueues * kIrrChunk;
         const dim3 grid((unsigned)((nb + round - 1) / round * round));
-        hipLaunchKernelGGL((k_irregular<JERK, POT, true, MULTI>), grid, block, 0, s, p);
+        // short lists with the jerk, by the list buffer's entries a particle (at least the
+        // mean list): the times at coop's entries cross between 24 and 64 without the
+        // potential and between 8 and 24 with it
+        constexpr int kMany = JERK ? 3 : 6, kFew = JERK ? 2 : kMany;
+        if (JERK && p.cap <= (POT ? 16 : 40) * p.n)
+            hipLaunchKernelGGL((k_irregular<JERK, POT, MULTI, kFew>), grid, block, 0, s, p);
+        else
+            hipLaunchKernelGGL((k_irregular<JERK, POT, MULTI, kMany>), grid, block, 0, s, p);
     } else {
         const int64_t g = nb < (1 << 16) ? nb : (1 << 16);
-        hipLaunchKernelGGL((k_irregular<JERK, POT, false, MULTI>), dim3((unsigned)g), block, 0, s, p);
+        hipLaunchKernelGGL((k_irregular<JERK, POT, MULTI, 0>), dim3((unsigned)g), block, 0, s, p);
     }
 }
 
