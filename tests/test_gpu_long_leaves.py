@@ -1,7 +1,8 @@
 """Leaves of more particles than a walk group: runs of points in one cell of the
 finest level (longest a few thousand), and large leaves whose boxes exceed the size
 limit of groups. Nodes, moments and groups equal the CPU oracle's (the oracle's
-order of FP64 operations and of particles)."""
+order of FP64 operations and of particles). Points many times over, exactly or
+nearly, are sorted in the stable order of their keys."""
 import numpy as np
 import pytest
 import torch
@@ -43,3 +44,27 @@ def test_nodes_and_groups_of_long_leaves(kind, n_leaf, n_crit):
     lo = np.minimum.reduceat(xs, ob, axis=0)
     hi = np.maximum.reduceat(xs, ob, axis=0)
     assert np.array_equal(gbox, np.concatenate([lo, hi], axis=1))
+
+
+# copies of each point and how far they lie apart: the same key; keys that differ in
+# their last bits only, in short runs and in runs too long to insert
+@pytest.mark.parametrize("n,copies,apart", [(5000, 100, 0.0), (5000, 9, 3e-7), (5000, 100, 3e-7), (40000, 30, 0.0),
+                                            (40000, 100, 3e-7), (300000, 12, 3e-7), (300000, 100, 0.0)])
+def test_order_of_points_many_times_over(n, copies, apart):
+    from paper_2110_11658_amd.api import Pbh
+    print(f"order n={n} copies={copies} apart={apart}", flush=True)
+    rng = np.random.default_rng(n + copies)
+    pos = np.repeat(ic.plummer(n // copies, seed=5).pos, copies, axis=0)
+    pos = (pos + apart * rng.normal(size=pos.shape))[rng.permutation(pos.shape[0])]
+    if copies == 9:   # equal keys among them as well
+        pos[::2][:pos[1::2].shape[0]] = pos[1::2]
+    p = Pbh(0)
+    for again in range(2):   # the second time in key order
+        mass = np.full(pos.shape[0], 1.0 / pos.shape[0])
+        p.build(torch.from_numpy(np.ascontiguousarray(pos)).cuda(), torch.from_numpy(mass).cuda())
+        order, keys, _, _ = p.debug_tree()
+        assert np.array_equal(np.sort(order), np.arange(pos.shape[0]))
+        by_caller = np.empty(pos.shape[0], dtype=np.uint64)
+        by_caller[order] = keys
+        assert np.array_equal(order, np.argsort(by_caller, kind="stable"))
+        pos = pos[order]
