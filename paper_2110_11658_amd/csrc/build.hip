@@ -703,7 +703,6 @@ __global__ __launch_bounds__(8 * kStradU) void k_moments_straddle(int64_t n, int
 // (2^e <= x < 2^(e+1)) holding the median box size of the groups formed with
 // S = infinity (first pass, histogram only). The first particle of each group
 // is flagged; a scan of the flags numbers the groups in particle order.
-constexpr int kOctaves = 128;
 constexpr int kGroupLimitLog2 = 5;
 
 __device__ inline double box_extent(const double* lo, const double* hi) {

@@ -247,7 +247,7 @@ pbh_status ensure_buffers(pbh_ctx* ctx) {
               dalloc(ctx, &d.q64.p, cap * Mom64Planes::kPlanes) &&
               dalloc(ctx, &d.q32.p, cap * Mom32Planes::kPlanes) &&
               dalloc(ctx, &d.g_flag, n) && dalloc(ctx, &d.g_tmp, group_tmp_need(n)) && dalloc(ctx, &d.g_len, n) && dalloc(ctx, &d.g_box, 6 * n) &&
-              dalloc(ctx, &d.g_hist, (int64_t)128 * C * group_hist_reps((int)C)) && dalloc(ctx, &d.cl_S, C) &&
+              dalloc(ctx, &d.g_hist, group_hist_words(C)) && dalloc(ctx, &d.cl_S, C) &&
               dalloc(ctx, &d.g.begin, G) && dalloc(ctx, &d.g.count, G) &&
               dalloc(ctx, &d.g.root, G) && dalloc(ctx, &d.g.cluster, G) &&
               dalloc(ctx, &d.g.lo, 3 * G) && dalloc(ctx, &d.g.hi, 3 * G) && dalloc(ctx, &d.fill_list, G) &&

@@ -165,6 +165,12 @@ struct BuildCfg {
 inline int group_hist_reps(int n_clusters) {
     return n_clusters >= 256 ? 1 : (n_clusters > 4 ? 256 / n_clusters : 64);
 }
+constexpr int kOctaves = 128;
+// Histogram words that serve every build of up to n_clusters clusters: the copies do
+// not grow with them (130 clusters have 130 in all, 128 have 256).
+inline int64_t group_hist_words(int64_t n_clusters) {
+    return kOctaves * (n_clusters > 256 ? n_clusters : 256);
+}
 
 // Most groups of a walk that two waves share, and their (group, part) pairs.
 constexpr int kWalkShared = 8192;
