@@ -14,6 +14,7 @@
 // digit bit (match by bits) and the waves of a workgroup are ordered through
 // LDS.
 #include "pbh_internal.hpp"
+#include "sample_sort.hpp"
 #include "wave.hpp"
 
 namespace pbh {
@@ -332,12 +333,13 @@ __global__ void k_copy_pairs(const uint64_t* __restrict__ ks, const int32_t* __r
 // Stable sort of up to kSsMaxN (key, index) pairs, the indices being 0..n-1 on
 // entry. Up to kSsCap keys: one workgroup sorts them in LDS. More: the keys are
 // split into S buckets of 1024 to 2048 keys on average by S - 1 splitters (every
-// kSsOver-th of S * kSsOver evenly spaced samples in sorted order), scattered
-// to their buckets in a stable order, and one workgroup sorts each bucket in
-// LDS. Keys are compared as (key, index) pairs, so equal keys spread over
-// buckets like any others and a bucket's size depends on the sampling alone
-// (beyond kSsCap with probability 3e-6 a bucket; such a bucket is sorted by its
-// workgroup in global memory).
+// kSsOver-th of S * kSsOver samples in sorted order, a sample drawn from each of
+// as many equal stretches of the keys, see ss_sample_at), scattered to their
+// buckets in a stable order, and one workgroup sorts each bucket in LDS. Keys are
+// compared as (key, index) pairs, so equal keys spread over buckets like any
+// others. A bucket passes kSsCap, 4 to 8 times the average, where the samples drawn
+// misrepresent the keys that much: with probability 3e-6 a bucket for places drawn
+// at random. Such a bucket is sorted by its workgroup in global memory.
 //
 // Against the 8-bit LSD radix sort (8 passes of 4 launches over the whole array
 // for 63-bit keys) a key moves through global memory twice instead of sixteen
@@ -345,21 +347,17 @@ __global__ void k_copy_pairs(const uint64_t* __restrict__ ks, const int32_t* __r
 // keys, 53 against 200 for 2^17, 29 against 165 for 4096 (kernel times). What is
 // left is latency: the sort of the buckets takes half of it, five digit passes
 // of barriers and LDS round trips in each of 512 workgroups.
-constexpr int kSsCap = 8192;        // keys one workgroup sorts in LDS
-constexpr int kSsT = 1024;          // its threads
+constexpr int kSsT = 1024;          // threads of a workgroup that sorts in LDS
 constexpr int kSsR = kSsCap / kSsT; // keys per thread
-constexpr int kSsOver = 8;
-constexpr int kSsMaxS = 2048;
-constexpr int64_t kSsMaxN = (int64_t)kSsMaxS * 2048;
 
 __device__ inline uint64_t ss_lanes_below(int lane) { return (lane == 0) ? 0ull : (~0ull >> (64 - lane)); }
 
-// the m evenly spaced samples, side by side (read in place by every workgroup
-// of the ranking, each on a 128-byte line of its own)
+// the m samples, side by side (read in place by every workgroup of the ranking,
+// each on a 128-byte line of its own)
 __global__ __launch_bounds__(256) void k_ss_gather(const uint64_t* __restrict__ keys, int64_t n, int m,
                                                    uint64_t* __restrict__ sample) {
     const int j = blockIdx.x * 256 + threadIdx.x;
-    if (j < m) sample[j] = keys[(int64_t)j * n / m];
+    if (j < m) sample[j] = keys[ss_sample_at(j, n, m)];
 }
 
 // Ranks 32 of the m samples per workgroup by counting, 32 threads a sample,
@@ -396,7 +394,7 @@ __global__ __launch_bounds__(1024) void k_ss_split(const uint64_t* __restrict__ 
         const int r = s_cnt[t];
         if (r > 0 && r % kSsOver == 0) {
             sp_key[r / kSsOver] = mk;
-            sp_idx[r / kSsOver] = (int32_t)((int64_t)me * n / m);
+            sp_idx[r / kSsOver] = (int32_t)ss_sample_at(me, n, m);
         }
     }
 }
@@ -881,12 +879,6 @@ __global__ __launch_bounds__(kSsT) void k_ss_local(uint64_t* __restrict__ kin_al
             vout[i] = iota ? (int32_t)(b0 + at) : vin[at];
         }
     }
-}
-
-inline int ss_buckets(int64_t n) {
-    int s = 4;
-    while (s < kSsMaxS && (int64_t)s * 2048 < n) s <<= 1;
-    return s;
 }
 
 }  // namespace
