@@ -1413,6 +1413,8 @@ static pbh_status kdk_impl(pbh_ctx* ctx, int64_t n, double* pos, double* vel, co
                                          (double)(uintptr_t)vel, (double)(uintptr_t)mass,
                                          (double)(uintptr_t)energy_out, (double)ctx->params.prec,
                                          (double)ctx->params.leaf_size, (double)ctx->params.n_crit,
+                                         (double)ctx->params.walk_tile,
+                                         (double)ctx->params.lanes_per_particle,
                                          (double)ctx->params.key_bits, (double)ctx->alloc_gen,
                                          (double)(uintptr_t)ctx->k_acc, (double)n};
         if (!ctx->gexec || ctx->gkey != key) {

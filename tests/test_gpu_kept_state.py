@@ -1,0 +1,48 @@
+"""What a context keeps between calls follows the parameters of the call at hand."""
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2110_11658_amd import ic
+
+pytestmark = pytest.mark.gpu
+
+
+def _t(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def _p(t):
+    return C.c_void_p(t.data_ptr())
+
+
+@pytest.mark.parametrize("change", [dict(walk_tile=128), dict(lanes_per_particle=1)])
+def test_leapfrog_graph_takes_new_walk_parameters(change):
+    # the same arrays before and after the change: a graph captured with the former
+    # tile or lanes must not be replayed
+    from paper_2110_11658_amd.api import Pbh
+    print(f"leapfrog, then {change}, then again", flush=True)
+    c = ic.plummer(3000, seed=41, masses="kroupa")
+    pos, vel, mass = _t(c.pos), _t(c.vel), _t(c.mass)
+    energy = torch.empty(4, dtype=torch.float64, device="cuda")
+
+    def leapfrog(p):
+        pos.copy_(_t(c.pos))
+        vel.copy_(_t(c.vel))
+        st = p.L.pbh_kdk_graph(p.ctx, c.n, _p(pos), _p(vel), _p(mass), 1.0 / 256, 3, 0.01, 0.1, 0.5, 1e-3, _p(energy),
+                               C.c_void_p(torch.cuda.current_stream().cuda_stream))
+        assert st == 0
+        torch.cuda.synchronize()
+        return [t.cpu().numpy().copy() for t in (pos, vel, energy)]
+
+    kept, fresh = Pbh(0), Pbh(0, **change)
+    first = leapfrog(kept)
+    kept.set_params(**change)
+    second, want = leapfrog(kept), leapfrog(fresh)
+    assert not np.array_equal(first[1], want[1])   # (the parameter is seen in the sums' rounding)
+    for a, b in zip(second, want):
+        assert np.array_equal(a, b)
+    kept.close()
+    fresh.close()
