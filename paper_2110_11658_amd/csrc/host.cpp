@@ -201,15 +201,25 @@ int64_t node_capacity(int64_t n, int D, int n_leaf, int C) {
     return 2 * n + (int64_t)D * ((n + n_leaf) / (n_leaf + 1)) + C + 64;
 }
 
-// Whether a walk takes a team of four waves a group (see walk_team). Groups of fewer
-// than 32 particles leave a team's evaluating waves little to do for the same
-// traversal, and there are more of them, so the line falls with the square of
-// n_crit. Walk in us, one wave a group / a team, n_crit 4, 8, 16, 32, 64: 5000
-// particles 150/198, 134/139, 154/128, 356/255, 353/253; 20000 347/614, 274/374,
-// 262/274, 305/257, 449/345; 40000 574/1206, 413/702, 342/446, 417/385, 564/471.
+// Whether a walk takes a team of four waves a group (see walk_team). A team shortens
+// the chain of one group's walk, so it pays where groups have much to do.
+// - Groups of fewer than 32 particles leave a team's evaluating waves little to do for
+//   the same traversal, and there are more of them, so the line falls with the square of
+//   n_crit. Walk in us, one wave a group / a team, n_crit 4, 8, 16, 32, 64: 5000
+//   particles 150/198, 134/139, 154/128, 356/255, 353/253; 20000 347/614, 274/374,
+//   262/274, 305/257, 449/345; 40000 574/1206, 413/702, 342/446, 417/385, 564/471.
+// - A group meets its own cluster only: in small clusters its walk is over in a few
+//   tiles, and with many of them the waves that a team binds are missed by other groups.
+//   C equal clusters of s particles take teams while s >= 48 C (unequal ones by the size
+//   of the cluster that a particle is in on average). s x C: 20 x 2000 49/70, 160 x 250
+//   79/122, 320 x 6 65/59, 320 x 31 72/91, 640 x 7 89/84, 640 x 15 95/102, 1280 x 15
+//   133/116, 1280 x 31 174/188, 1920 x 15 189/186, 1920 x 20 198/213, 2560 x 15 240/222;
+//   one cluster of 10 29/30, 100 42/41, 500 76/68.
 bool use_team(const pbh_ctx* ctx, int mixed) {
-    const int64_t c = std::min(ctx->cfg.n_crit, 32);
-    return walk_team(mixed, ctx->params.walk_tile, ctx->cfg.n) && ctx->cfg.n <= 40 * c * c;
+    const BuildCfg& b = ctx->cfg;
+    const int64_t c = std::min(b.n_crit, 32);
+    return walk_team(mixed, ctx->params.walk_tile, b.n) && b.n <= 40 * c * c &&
+           48.0 * (double)b.n <= b.mean_cluster * b.mean_cluster;
 }
 
 // persistent walk grid for the context's precision and tile: resident
@@ -333,8 +343,10 @@ pbh_status setup_build(pbh_ctx* ctx, int64_t n, int32_t C, const int64_t* offset
     std::vector<int32_t> cblk(C + 1, 0);
     int64_t chunk = kBoxChunk;
     while (chunk > kBoxChunkMin && n < 256 * chunk) chunk >>= 1;
+    int64_t squares = 0;   // (below 2^62)
     for (int k = 0; k < C; ++k) {
         const int64_t a = offsets[k], b = offsets[k + 1];
+        squares += (b - a) * (b - a);
         cblk[k] = (int32_t)blk_cluster.size();
         for (int64_t q = a; q < b; q += chunk) {
             blk_cluster.push_back(k);
@@ -343,6 +355,7 @@ pbh_status setup_build(pbh_ctx* ctx, int64_t n, int32_t C, const int64_t* offset
         }
     }
     cblk[C] = (int32_t)blk_cluster.size();
+    c.mean_cluster = (double)squares / (double)n;
     c.n_groups = n;   // capacity; the walk reads the actual count on the device
     ctx->nblk_box = (int)blk_cluster.size();
     if (ctx->grid_mixed == 0) {

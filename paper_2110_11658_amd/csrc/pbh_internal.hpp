@@ -156,6 +156,7 @@ struct BuildCfg {
     int32_t n_crit = 64;
     int64_t node_cap = 0;
     int64_t n_groups = 0;
+    double mean_cluster = 0.0;   // size of the cluster that a particle is in, on average
 };
 
 // Scratch and arrays of one built forest.

@@ -1461,7 +1461,8 @@ static auto walk_kernel(int tile) {
 // more, four groups on a SIMD cover each other's latencies and a team's idle waves
 // are lost. Walk in us, one wave a group / a team: 700 particles 87 / 73, 4096 184
 // / 138, 16384 301 / 226, 32768 358 / 322, 40960 409 / 366 (nbar 200: 827 / 745),
-// 49152 440 / 436, 65536 505 / 550, 131072 812 / 970.
+// 49152 440 / 436, 65536 505 / 550, 131072 812 / 970; uniform 28000 159 / 139, 36000
+// 180 / 174, 40000 201 / 186; lattice 32768 96 / 91, 35937 113 / 124, 39304 117 / 135.
 constexpr int64_t kTeamMaxN = 40960;
 
 bool walk_team(int mixed, int tile, int64_t n) { return mixed && tile == 64 && n <= kTeamMaxN; }
