@@ -90,17 +90,19 @@ __device__ inline void store_sums(const IrrParams& p, int64_t slot, const IrrSum
 // a target or past their list take part with no record of their own.
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));   // one 16-byte piece
 
-// Entries per lane and round (N) on the key-order route: 6 for the force alone (then
-// 2 where no lane of the wave has more left), 3 with the jerk or 2 for short lists.
-// Loads in flight set the rate of long lists; on short ones the entries of a round
-// that no lane has cost their loads and exchanges. 2^20 particles, whole call in us,
-// mean list 8, 24, 64:
+// Entries per lane and round on the key-order route: with the jerk 3, or 2 for short
+// lists; for the force alone 6, then one round of 2 where no lane of the wave has more
+// left (short lists: looked for before every round, long ones: once the rounds of 6
+// are done). Loads in flight set the rate of long lists; on short ones the entries of
+// a round that no lane has cost their loads and exchanges. 2^20 particles, whole call
+// in us, mean list 8, 24, 64, 100:
 //   jerk             2 entries 227, 337, 634; 3 entries 243, 352, 621
 //   jerk, potential  2 entries 270, 396, 718; 3 entries 274, 393, 700
-//   force            6 entries 181 (8), 488 (64); with the rounds of 2 163, 492
-//   force, potential 6 entries 294 (24), 553 (64); with the rounds of 2 283, 556
+//   force            6 entries 178, 227, 478, 705; short form 161, 216, 485, 724; long 163, 219, 476, 707
+//   force, potential 6 entries 216, 278, 537, 764; short form 199, 260, 539, 779; long 203, 263, 522, 751
 // An entry that no lane of the wave has is not exchanged (jerk, 3 entries, mean list 8
 // 254 -> 244 us).
+enum class Route { caller, few, many };   // caller arrays; key order: short lists, long lists
 template <bool JERK, int N>
 struct CoopPieces {
     static constexpr int B = N;
@@ -145,7 +147,7 @@ __device__ inline PartJ coop_take(const CoopPieces<JERK, N>& P, int u, IrrRec* x
     return q;
 }
 
-template <bool JERK, bool POT, bool MULTI, int N>
+template <bool JERK, bool POT, bool MULTI, Route ROUTE>
 __device__ inline bool irr_sums_coop(const IrrParams& p, int64_t i, bool have, int g, IrrSums& S,
                                      unsigned long long& bad, IrrRec* xch) {
     const int lane = (int)(threadIdx.x & 63);
@@ -191,10 +193,20 @@ __device__ inline bool irr_sums_coop(const IrrParams& p, int64_t i, bool have, i
         }
         m += (int64_t)kIrrLanes * B;
     };
+    auto left = [&](int entries) {   // some lane has more than these
+        return __builtin_amdgcn_ballot_w64(m + (int64_t)entries * kIrrLanes < e) != 0;
+    };
     using std::integral_constant;
-    while (__builtin_amdgcn_ballot_w64(m < e) != 0) {
-        if (!JERK && __builtin_amdgcn_ballot_w64(m + 2 * (int64_t)kIrrLanes < e) == 0) round(integral_constant<int, 2>());
-        else round(integral_constant<int, N>());
+    if constexpr (JERK) {
+        while (left(0)) round(integral_constant<int, ROUTE == Route::few ? 2 : 3>());
+    } else if constexpr (ROUTE == Route::few) {
+        while (left(0)) {
+            if (left(2)) round(integral_constant<int, 6>());
+            else round(integral_constant<int, 2>());
+        }
+    } else {
+        while (left(2)) round(integral_constant<int, 6>());
+        if (left(0)) round(integral_constant<int, 2>());
     }
     S.ax = group_sum(S.ax);
     S.ay = group_sum(S.ay);
@@ -224,11 +236,10 @@ __device__ inline void irr_target(const IrrParams& p, int64_t k, int g) {
     if (bad) atomicOr(p.err, bad);
 }
 
-// N: entries per lane and round of the key-order route, 0 for the caller-array route
-template <bool JERK, bool POT, bool MULTI, int N>
+template <bool JERK, bool POT, bool MULTI, Route ROUTE>
 __global__ __launch_bounds__(256) void k_irregular(IrrParams p) {
     const int g = threadIdx.x % kIrrLanes;   // lane groups never straddle a workgroup
-    if constexpr (N > 0) {
+    if constexpr (ROUTE != Route::caller) {
         // key-order targets in chunks per XCD (cache locality and load balance);
         // every lane takes part in the cooperative loads, with a target or not
         __shared__ IrrRec xch[256 / 64][64];
@@ -239,7 +250,7 @@ __global__ __launch_bounds__(256) void k_irregular(IrrParams p) {
         const int64_t kk = have ? k : 0;
         const int64_t i = p.tgt ? (int64_t)p.tgt[kk] : (p.order ? (int64_t)p.order[kk] : kk);
         IrrSums S;
-        const bool valid = irr_sums_coop<JERK, POT, MULTI, N>(p, i, have, g, S, bad, xch[threadIdx.x / 64]);
+        const bool valid = irr_sums_coop<JERK, POT, MULTI, ROUTE>(p, i, have, g, S, bad, xch[threadIdx.x / 64]);
         if (have && g == 0 && (valid || p.tgt)) store_sums<JERK, POT>(p, p.tgt ? k : i, S);
         if (bad) atomicOr(p.err, bad);
         return;
@@ -261,17 +272,17 @@ void launch_route(const IrrParams& p, hipStream_t s) {
     if (p.rec && fits) {   // grid padded to whole rounds of chunks over the XCDs
         const int64_t round = (int64_t)kQueues * kIrrChunk;
         const dim3 grid((unsigned)((nb + round - 1) / round * round));
-        // short lists with the jerk, by the list buffer's entries a particle (at least the
-        // mean list): the times at coop's entries cross between 24 and 64 without the
-        // potential and between 8 and 24 with it
-        constexpr int kMany = JERK ? 3 : 6, kFew = JERK ? 2 : kMany;
-        if (JERK && p.cap <= (POT ? 16 : 40) * p.n)
-            hipLaunchKernelGGL((k_irregular<JERK, POT, MULTI, kFew>), grid, block, 0, s, p);
+        // short lists, by the list buffer's entries a particle (at least the mean list; a
+        // roomy buffer of short lists takes the form for long ones): the times above cross
+        // between 24 and 64 with the jerk, between 8 and 24 with the potential too, and for
+        // the force alone near 40
+        if (p.cap <= (JERK && POT ? 16 : 40) * p.n)
+            hipLaunchKernelGGL((k_irregular<JERK, POT, MULTI, Route::few>), grid, block, 0, s, p);
         else
-            hipLaunchKernelGGL((k_irregular<JERK, POT, MULTI, kMany>), grid, block, 0, s, p);
+            hipLaunchKernelGGL((k_irregular<JERK, POT, MULTI, Route::many>), grid, block, 0, s, p);
     } else {
         const int64_t g = nb < (1 << 16) ? nb : (1 << 16);
-        hipLaunchKernelGGL((k_irregular<JERK, POT, MULTI, 0>), dim3((unsigned)g), block, 0, s, p);
+        hipLaunchKernelGGL((k_irregular<JERK, POT, MULTI, Route::caller>), dim3((unsigned)g), block, 0, s, p);
     }
 }
 
