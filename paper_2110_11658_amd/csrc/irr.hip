@@ -231,7 +231,7 @@ __device__ inline void irr_target(const IrrParams& p, int64_t k, int g) {
     unsigned long long bad = 0;
     const int64_t i = p.tgt ? (int64_t)p.tgt[k] : (p.order ? (int64_t)p.order[k] : k);
     IrrSums S;
-    const bool valid = irr_sums_lanes<JERK, POT, false, MULTI>(p, i, g, S, bad);
+    const bool valid = irr_sums_lanes<JERK, POT, MULTI>(p, i, g, S, bad);
     if (g == 0 && (valid || p.tgt)) store_sums<JERK, POT>(p, p.tgt ? k : i, S);   // no slot of its own otherwise
     if (bad) atomicOr(p.err, bad);
 }

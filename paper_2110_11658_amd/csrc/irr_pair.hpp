@@ -173,7 +173,7 @@ __device__ inline void pair_irr(const IrrK& cp, double eps2, const PartJ& me, co
     if (POT) S.ph = fma(m, -inv - phi_regular(cp, s, inv), S.ph);
 }
 
-// Target setup shared by both kernels: validates i and its list range, and
+// Target setup shared by both routes: validates i and its list range, and
 // finds its cluster constants. Returns false when i is out of range.
 __device__ inline bool target_setup(const IrrParams& p, int64_t i, const ClusterParams*& cp,
                                     int64_t& b, int64_t& e, unsigned long long& bad) {
@@ -201,56 +201,6 @@ __device__ inline bool target_setup(const IrrParams& p, int64_t i, const Cluster
     return true;
 }
 
-// List entries per batch: their list, rank and particle loads are independent
-// and issue together (one dependent chain per batch instead of per entry).
-constexpr int kIrrBatch = 8;
-
-// The sums of target i (caller index) over its list, in list order; false when
-// i is out of range. MULTI: clusters with their own constants (per lane);
-// otherwise one set, read from the kernel arguments (wave-uniform, so it stays
-// in scalar registers). SORTED: particles from the key-order records.
-template <bool JERK, bool POT, bool SORTED, bool MULTI>
-__device__ inline bool irr_sums(const IrrParams& p, int64_t i, IrrSums& S, unsigned long long& bad) {
-    const ClusterParams* cp;
-    int64_t b, e;
-    const bool valid = target_setup(p, i, cp, b, e, bad);
-    if (valid) {
-        const IrrK K = irr_constants(MULTI ? *cp : p.cp0);
-        const PartJ me = SORTED ? load_rec<JERK>(p.rec, p.rank[i]) : load_caller<JERK>(p, i);
-        for (; b < e; b += kIrrBatch) {
-            int32_t jv[kIrrBatch];
-            bool ok[kIrrBatch];
-#pragma unroll
-            for (int u = 0; u < kIrrBatch; ++u)   // clamped: inside the list whenever b < e
-                jv[u] = p.idx[b + u < e ? b + u : e - 1];
-#pragma unroll
-            for (int u = 0; u < kIrrBatch; ++u) {
-                const bool live = b + u < e;
-                const bool inr = (uint64_t)(int64_t)jv[u] < (uint64_t)p.n;
-                if (live && !inr) bad |= kIrrBadIndex;
-                ok[u] = live && inr && jv[u] != i;
-                if (!ok[u]) jv[u] = (int32_t)i;   // a valid index; its pair is not summed
-            }
-            PartJ q[kIrrBatch];
-            if (SORTED) {
-                int32_t rk[kIrrBatch];
-#pragma unroll
-                for (int u = 0; u < kIrrBatch; ++u) rk[u] = p.rank[jv[u]];
-#pragma unroll
-                for (int u = 0; u < kIrrBatch; ++u) q[u] = load_rec<JERK>(p.rec, rk[u]);
-            } else {
-#pragma unroll
-                for (int u = 0; u < kIrrBatch; ++u) q[u] = load_caller<JERK>(p, jv[u]);
-            }
-#pragma unroll
-            for (int u = 0; u < kIrrBatch; ++u)
-                pair_irr<JERK, POT, true>(K, p.eps2, me, q[u], ok[u], S);
-        }
-    }
-    return valid;
-}
-
-
 // Lane groups: kIrrLanes lanes share one target. Lane g takes list entries
 // g, g + kIrrLanes, g + 2 kIrrLanes, ... in that order (irr_lane_batch of
 // them per round, their loads issued together), and the group adds its partial
@@ -271,7 +221,10 @@ __device__ inline double group_sum(double v) {
     return v;
 }
 
-template <bool JERK, bool POT, bool SORTED, bool MULTI>
+// The sums of target i (caller index) from the caller's arrays; false when i is out of
+// range. MULTI: clusters with their own constants (per lane); otherwise one set, read
+// from the kernel arguments (wave-uniform, so it stays in scalar registers).
+template <bool JERK, bool POT, bool MULTI>
 __device__ inline bool irr_sums_lanes(const IrrParams& p, int64_t i, int g, IrrSums& S,
                                       unsigned long long& bad) {
     const ClusterParams* cp;
@@ -280,7 +233,7 @@ __device__ inline bool irr_sums_lanes(const IrrParams& p, int64_t i, int g, IrrS
     if (g != 0) bad = 0;   // target and offset flags once per group
     if (valid) {
         const IrrK K = irr_constants(MULTI ? *cp : p.cp0);
-        const PartJ me = SORTED ? load_rec<JERK>(p.rec, p.rank[i]) : load_caller<JERK>(p, i);
+        const PartJ me = load_caller<JERK>(p, i);
         constexpr int kIrrLaneBatch = irr_lane_batch<JERK>();
         for (int64_t m = b + g; m < e; m += kIrrLanes * kIrrLaneBatch) {
             int32_t jv[kIrrLaneBatch];
@@ -299,16 +252,8 @@ __device__ inline bool irr_sums_lanes(const IrrParams& p, int64_t i, int g, IrrS
                 if (!ok[u]) jv[u] = (int32_t)i;   // a valid index; its pair is not summed
             }
             PartJ q[kIrrLaneBatch];
-            if (SORTED) {
-                int32_t rk[kIrrLaneBatch];
 #pragma unroll
-                for (int u = 0; u < kIrrLaneBatch; ++u) rk[u] = p.rank[jv[u]];
-#pragma unroll
-                for (int u = 0; u < kIrrLaneBatch; ++u) q[u] = load_rec<JERK>(p.rec, rk[u]);
-            } else {
-#pragma unroll
-                for (int u = 0; u < kIrrLaneBatch; ++u) q[u] = load_caller<JERK>(p, jv[u]);
-            }
+            for (int u = 0; u < kIrrLaneBatch; ++u) q[u] = load_caller<JERK>(p, jv[u]);
 #pragma unroll
             for (int u = 0; u < kIrrLaneBatch; ++u)
                 pair_irr<JERK, POT, true>(K, p.eps2, me, q[u], ok[u], S);
