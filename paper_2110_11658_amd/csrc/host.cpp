@@ -325,6 +325,7 @@ int ensure_stage(pbh_ctx* ctx) {
 // Host part of a build: sizes, tables, uploads. No kernel runs here.
 pbh_status setup_build(pbh_ctx* ctx, int64_t n, int32_t C, const int64_t* offsets, hipStream_t s) {
     BuildCfg& c = ctx->cfg;
+    ctx->built = false;   // the sizes below are no longer those of the tree and its buffers
     c.n = n;
     c.n_clusters = C;
     c.cbits = cluster_bits(C);

@@ -46,3 +46,27 @@ def test_leapfrog_graph_takes_new_walk_parameters(change):
         assert np.array_equal(a, b)
     kept.close()
     fresh.close()
+
+
+def test_refused_leapfrog_leaves_no_build():
+    # more particles than node indices can name: refused once the sizes are set. The
+    # tree of the build before must not be walked with them
+    from paper_2110_11658_amd import _lib
+    from paper_2110_11658_amd.api import Pbh
+    print("leapfrog refused, then a force of the build before", flush=True)
+    c = ic.plummer(1000, seed=42, masses="kroupa")
+    pos, vel, mass = _t(c.pos), _t(c.vel), _t(c.mass)
+    p = Pbh(0)
+    p.build(pos, mass)
+    want = [t.cpu().numpy() for t in p.force(0.01, 0.1, 0.5, 1e-3)]
+    energy = torch.empty(2, dtype=torch.float64, device="cuda")
+    st = p.L.pbh_kdk_graph(p.ctx, (1 << 31) - 2, _p(pos), _p(vel), _p(mass), 1.0 / 256, 1, 0.01, 0.1, 0.5, 1e-3,
+                           _p(energy), C.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert st == _lib.PBH_E_ARG
+    with pytest.raises(_lib.PbhError) as e:
+        p.force(0.01, 0.1, 0.5, 1e-3)
+    assert e.value.status == _lib.PBH_E_STATE
+    p.build(pos, mass)
+    for a, b in zip(p.force(0.01, 0.1, 0.5, 1e-3), want):
+        assert np.array_equal(a.cpu().numpy(), b)
+    p.close()
