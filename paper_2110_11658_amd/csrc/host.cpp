@@ -717,6 +717,7 @@ bool halloc(pbh_ctx* ctx, T** p, int64_t count) {
 pbh_status ensure_herm(pbh_ctx* ctx, int64_t n) {
     auto& h = ctx->herm;
     if (h.n >= n) return PBH_OK;
+    h.gkey.clear();   // the captured batch names the buffers freed here, more of them than its key does
     for (void* q : h.mem) (void)hipFree(q);
     h.mem.clear();
     h.cap = 0;

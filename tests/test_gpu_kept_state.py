@@ -70,3 +70,35 @@ def test_refused_leapfrog_leaves_no_build():
     for a, b in zip(p.force(0.01, 0.1, 0.5, 1e-3), want):
         assert np.array_equal(a.cpu().numpy(), b)
     p.close()
+
+
+def test_hermite_after_its_buffers_were_replaced():
+    # a call that ends between the allocation of larger Hermite buffers and the capture
+    # of its batch: the batch captured before must not be replayed on the freed ones
+    from paper_2110_11658_amd import _lib
+    from paper_2110_11658_amd.api import Pbh
+    print("hermite, a refused p3t of more particles, hermite", flush=True)
+    c, big = ic.plummer(700, seed=43, masses="kroupa"), ic.plummer(2000, seed=44, masses="kroupa")
+    r_out = ic.r_out_for_nbar(c.n, 12.0)
+    r_in, eps = 0.1 * r_out, 1e-4
+    pos, vel, mass = _t(c.pos), _t(c.vel), _t(c.mass)
+    p = Pbh(0, prec="fp64")
+    p.build(pos, mass)
+    fr, _, off, idx = p.force(r_in, r_out, 0.0, eps, r_buff=0.5 * r_out)
+
+    def hermite():
+        pos.copy_(_t(c.pos))
+        vel.copy_(_t(c.vel))
+        st = p.hermite(pos, vel, mass, fr, r_in, r_out, eps, off, idx, 1.0 / 256)
+        torch.cuda.synchronize()
+        return pos.cpu().numpy(), vel.cpu().numpy(), st
+
+    first = hermite()
+    bad = big.pos.copy()
+    bad[1234, 1] = np.nan
+    with pytest.raises(_lib.PbhError) as e:
+        p.p3t(_t(bad), _t(big.vel), _t(big.mass), r_in, r_out, 0.5 * r_out, 0.5, eps, 1.0 / 256, 1)
+    assert e.value.status == _lib.PBH_E_NONFINITE
+    again = hermite()
+    assert np.array_equal(first[0], again[0]) and np.array_equal(first[1], again[1]) and first[2] == again[2]
+    p.close()
