@@ -630,7 +630,9 @@ static_assert((1 << kSsPos) >= kSsCap, "a place fits its bits");
 __device__ inline void ss_local_pass(SsLds& L, uint64_t (&k)[kSsR], int rounds, int len, int shift) {
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     const uint64_t below = ss_lanes_below(lane);
-    for (int q = lane; q < 128; q += 64) reinterpret_cast<uint32_t*>(L.wc[w])[q] = 0u;
+    // (two counters a store; the type keeps their loads behind it)
+    typedef uint32_t __attribute__((may_alias)) pair_of_counts;
+    for (int q = lane; q < 128; q += 64) reinterpret_cast<pair_of_counts*>(L.wc[w])[q] = 0u;
     __builtin_amdgcn_wave_barrier();
     int rank[kSsR];
 #pragma unroll
