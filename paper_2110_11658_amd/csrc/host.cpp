@@ -215,11 +215,19 @@ int64_t node_capacity(int64_t n, int D, int n_leaf, int C) {
 //   79/122, 320 x 6 65/59, 320 x 31 72/91, 640 x 7 89/84, 640 x 15 95/102, 1280 x 15
 //   133/116, 1280 x 31 174/188, 1920 x 15 189/186, 1920 x 20 198/213, 2560 x 15 240/222;
 //   one cluster of 10 29/30, 100 42/41, 500 76/68.
+// - Leaves of thousands of particles come with groups of one particle (a big leaf wider
+//   than the size limit), all of whose tiles are handed over and filled for one entry a
+//   lane. Leaf size x particles: 1000 x 3000 201/174, 2000 x 2000 164/133, 4000 x 30000
+//   1887/2123, 16000 x 30000 2155/2824, one leaf of 3000 191/373, 10000 859/2472, 40000
+//   7818/34003.
+constexpr int64_t kTeamMaxLeaf = 2048;
+
 bool use_team(const pbh_ctx* ctx, int mixed) {
     const BuildCfg& b = ctx->cfg;
     const int64_t c = std::min(b.n_crit, 32);
     return walk_team(mixed, ctx->params.walk_tile, b.n) && b.n <= 40 * c * c &&
-           48.0 * (double)b.n <= b.mean_cluster * b.mean_cluster;
+           48.0 * (double)b.n <= b.mean_cluster * b.mean_cluster &&
+           std::min((int64_t)b.n_leaf, b.n) <= kTeamMaxLeaf;
 }
 
 // persistent walk grid for the context's precision and tile: resident

@@ -47,3 +47,26 @@ def test_team_line_of_ensembles(sizes, team):
         assert np.array_equal(idx[off[s.start]:off[s.stop]], i + s.start)
     ref.close()
     p.close()
+
+
+@pytest.mark.parametrize("n,leaf,team", [(2600, 2048, True), (2600, 2049, False), (2048, 100000, True),
+                                         (2049, 100000, False)])
+def test_team_line_of_large_leaves(n, leaf, team):
+    # (an ensemble of more than 40960 particles takes one wave a group)
+    from paper_2110_11658_amd.api import Pbh
+    print(f"{n} particles in leaves of up to {leaf}, team {team}", flush=True)
+    kw = dict(prec="mixed", key_bits=18, n_crit=32, leaf_size=leaf)
+    c, big, one = ic.plummer(n, seed=23, masses="kroupa"), ic.plummer(41000, seed=24), ic.plummer(2000, seed=22)
+    r_in, r_out, theta, eps = 0.01, 0.1, 0.5, 1e-5
+    ref, p, q = Pbh(0, prec="mixed"), Pbh(0, **kw), Pbh(0, **kw)
+    ref.build(_t(one.pos), _t(one.mass))
+    ref.force(r_in, r_out, theta, eps)
+    p.build(_t(c.pos), _t(c.mass))
+    acc, pot, off, idx = (t.cpu().numpy() for t in p.force(r_in, r_out, theta, eps))
+    assert (_grid(p) == _grid(ref)) == team
+    q.build_batched([0, n, n + big.n], _t(np.concatenate([c.pos, big.pos])), _t(np.concatenate([c.mass, big.mass])))
+    a, f, o, i = (t.cpu().numpy() for t in q.force_batched([r_in, 0.0], [r_out, 0.001], theta, eps))
+    assert np.array_equal(a[:n], acc) and np.array_equal(f[:n], pot)
+    assert np.array_equal(o[:n + 1], off) and np.array_equal(i[:o[n]], idx)
+    for h in (ref, p, q):
+        h.close()
