@@ -568,11 +568,14 @@ __device__ inline Part<float> eval_near(const Tiles<float, TC>& T, int cnt, int 
 //   6141: 892 / 805 / 899, 26611: 5128 / 5098 / -, FP64 4782: 2012 / 1786 / 1835
 // and with 103236 groups sharing only costs (14090 / 14150).
 // A team (see TeamMem) shares all groups or none: 16384 particles 225 / 231, 32768
-// 339 (three eighths) / 322.
-template <bool MIXED, int TEAM>
+// 339 (three eighths) / 322. With tiles of 128 entries ten waves share a CU, not
+// sixteen, and the second traversal costs them more: none are shared beyond 1.5 groups
+// a wave (1.2 groups a wave, none / three eighths: 571 / 529; 1.5: 1309 / 1368; 1.9:
+// 754 / 797; 2.4: 901 / 986; 3.6: 1202 / 1327).
+template <bool MIXED, int TC, int TEAM>
 __device__ inline int walk_shared(int64_t G) {
     const int64_t q = (G + kQueues - 1) / kQueues, w = gridDim.x / kQueues;
-    if (q > 8 * w) return 0;
+    if (q > 8 * w || (MIXED && TC == 128 && 2 * q > 3 * w)) return 0;
     const int64_t t = 8 * q <= 5 * w ? q : (TEAM > 1 ? 0 : (MIXED ? q * 3 / 8 : q * 5 / 8));
     return (int)(t < kWalkShared / kQueues ? t : kWalkShared / kQueues);
 }
@@ -973,9 +976,14 @@ __device__ __forceinline__ void team_evaluate(Tiles<R, TC>* T, TeamMem<R, TEAM>&
 // Four waves per SIMD (16 per compute unit, which the 64-entry mixed walk's
 // LDS allows): the register budget is held to 128, which this kernel fits
 // but for a few registers of its set-up; left free, the compiler takes more and halves nothing but
-// occupancy. Larger tiles and the FP64 walk are held lower by their LDS.
+// occupancy. Larger tiles and the FP64 walk are held lower by their LDS; the mixed
+// 96-entry tiles leave room for 13 waves, which the compiler takes for four a SIMD as
+// well: held to three they keep 148 registers and spill none (131072 particles, theta
+// 0.3, 2053 -> 1743 us; the 128-entry tiles are better left alone, 2059 / 2188).
+constexpr int walk_waves(bool mixed, int tc) { return mixed && tc == 96 ? 3 : 4; }
+
 template <bool MIXED, int TC, int TEAM>
-__global__ __launch_bounds__(64 * TEAM) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_walk(WalkParams p) {
+__global__ __launch_bounds__(64 * TEAM) __attribute__((amdgpu_waves_per_eu(walk_waves(MIXED, TC), walk_waves(MIXED, TC)))) void k_walk(WalkParams p) {
     using R = typename std::conditional<MIXED, float, double>::type;
     constexpr int TCAP = TC;
     __shared__ Tiles<R, TC> s_tiles[TEAM == 1 ? 1 : kTeamBufs];
@@ -1003,7 +1011,7 @@ __global__ __launch_bounds__(64 * TEAM) __attribute__((amdgpu_waves_per_eu(4, 4)
     const int64_t G = (int64_t)*p.G;
     const unsigned long long t_start = wall_clock64();
     const unsigned long long c_start = clock64();
-    const int tail = walk_shared<MIXED, TEAM>(G);
+    const int tail = walk_shared<MIXED, TC, TEAM>(G);
     int n_walked = 0;
     // interaction counts of this wave, added to the counters once at its end
     unsigned long long sum_pn = 0, sum_far = 0, sum_near = 0, slot_pn = 0, slot_far = 0, slot_near = 0;
