@@ -1,7 +1,7 @@
 """Benchmark of the P3T distant-force path on one MI355X.
 
 One step = one pass of the whole path over resident synthetic input:
-tree build (bounding box, Morton keys, radix sort, octree, FP64 moments,
+tree build (bounding box, Morton keys, a stable sort, octree, FP64 moments,
 groups) + grouped walk (regular force and potential, written in caller order)
 + neighbour lists inside r_out (count, scan, fill).
 

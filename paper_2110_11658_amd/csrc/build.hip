@@ -15,9 +15,10 @@
 //            (parallel-axis sums over children), tight box
 //   groups   tree-bounded runs of <= n_crit sorted particles (rule at k_group_pass)
 //
-// A build is 12 launches up to 8192 particles and 20 beyond (there were 43 and
-// 53): with kernels of a few microseconds the launches, and the scans between
-// them, were most of its time.
+// A build is 11 launches up to 1024 particles, 12 up to 8192, 18 up to 2^17 and 19
+// up to 2^22 (there were 43 to 53; beyond, the radix sort alone has 32 or more):
+// with kernels of a few microseconds the launches, and the scans between them, were
+// most of its time.
 //
 // FP64 arithmetic that decides the tree (keys, moments) is evaluated without
 // fused multiply-add so it rounds exactly as written.
@@ -52,8 +53,8 @@ __device__ inline void block_box(double (&v)[6], double (*s)[6]) {
     }
 }
 
-// Partial boxes of the blocks of the cluster table, and the zeroing of the
-// build's counters (see launch_zero_counts).
+// Partial boxes of the blocks of the cluster table, and the zeroing of the counters
+// but for those that outlive a build.
 __global__ __launch_bounds__(BB_T) void k_bbox_part(const double* __restrict__ pos,
                                                     const double* __restrict__ mass,
                                                     const int64_t* __restrict__ range,
@@ -62,7 +63,7 @@ __global__ __launch_bounds__(BB_T) void k_bbox_part(const double* __restrict__ p
     __shared__ double s_v[BB_T / 64][6];
     const int t = threadIdx.x;
     for (int i = blockIdx.x * BB_T + t; i < kNumCounters + kQueueWords; i += gridDim.x * BB_T)
-        if (i < 11 || i >= kNumCounters) cnt[i] = 0ull;   // slots 11 .. outlive a build
+        if (i < kCntKept || i >= kNumCounters) cnt[i] = 0ull;
     const int64_t b0 = range[2 * blockIdx.x], b1 = range[2 * blockIdx.x + 1];
     double v[6] = {INFINITY, INFINITY, INFINITY, INFINITY, INFINITY, INFINITY};
     int nf = 0;

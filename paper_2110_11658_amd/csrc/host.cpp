@@ -24,7 +24,6 @@ namespace {
 // particles per bbox/key block: 256 blocks or more from 2^17 particles on
 constexpr int kBoxChunk = 2048, kBoxChunkMin = 512;
 constexpr int kStackCap = 16384;     // traversal stack entries per persistent wave (LDS + spill)
-constexpr int kCntKdkStep = 11;      // counter slot: KDK energy output index
 constexpr int64_t kIrrPackRatio = 32;  // target lists of >= n/32 use the key-order records
 
 struct Buf {
@@ -393,7 +392,7 @@ pbh_status setup_build(pbh_ctx* ctx, int64_t n, int32_t C, const int64_t* offset
 
 void enqueue_build(pbh_ctx* ctx, const double* pos, const double* mass, hipStream_t s);
 
-// The build is 13 to 20 small kernels; launched one by one, the host's launch
+// The build is 11 to 19 small kernels (see build.hip); launched one by one, the host's launch
 // rate rather than the GPU would set the build time. The sequence is captured
 // into a graph once per set of buffers, sizes and parameters (the block tables
 // it reads are uploaded before each launch) and replayed.

@@ -35,9 +35,10 @@ enum : unsigned long long {
     kErrStale = 32ull,        // pos or mass changed since the build (force call)
 };
 
-// slots of the device counter array
-enum { kCntNodes = 0, kCntNbrTotal = 4, kErr = 5,
-       kCntMaxLevel = 9, kCntLeaves = 10, kCntGroups = 12, kCntFill = 13, kNumCounters = 16 };
+// slots of the device counter array; those from kCntKept on are not cleared by a build
+// (the leapfrog's energy index lives across builds, the other two are stored whole)
+enum { kCntNodes = 0, kErr = 5, kCntMaxLevel = 9, kCntLeaves = 10, kCntKept = 11,
+       kCntKdkStep = 11, kCntGroups = 12, kCntFill = 13, kNumCounters = 16 };
 
 // Behind the counters, on lines of their own (thousands of waves meet there):
 // the heads of the walk's group queues (one per XCD), the walk's interaction

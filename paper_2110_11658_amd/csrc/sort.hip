@@ -990,8 +990,10 @@ void sort_iota(uint64_t* keys, int32_t* vals, uint64_t* keys_alt, int32_t* vals_
     q.table = q.base + S + 8;
     hipLaunchKernelGGL(k_ss_gather, dim3((m + 255) / 256), dim3(256), 0, s, (const uint64_t*)keys, n, m, sample);
     hipLaunchKernelGGL(k_ss_split, dim3(m / 32), dim3(1024), 0, s, (const uint64_t*)sample, n, m, sp_key, sp_idx);
-    // Tiles: 512 keys up to 2^18 keys (to occupy the chip), then up to 4096; as
-    // many waves a tile as leave the tile and their S counters each within 64 KB.
+    // Tiles: 512 keys up to 2^18 keys (to occupy the chip), then 2048, then 4096. A tile
+    // takes 12 bytes of LDS a key and each bucket 8 and 2 a wave: 60 KB for 4096 keys in
+    // eight waves and 512 buckets, four waves beyond (64 KB for 1024 buckets, 80 for 2048
+    // of the 160 a CU has).
     if (n <= (1 << 18)) ss_partition<256, 2>(q, n, S, s);
     else if (n <= (1 << 19)) ss_partition<512, 4>(q, n, S, s);
     else if (S <= 512) ss_partition<512, 8>(q, n, S, s);
