@@ -782,11 +782,9 @@ __device__ __forceinline__ void fill_tile(Tiles<R, TC>& T, const WalkParams& p, 
     for (int h = 0; h < H; ++h) {
         const int e = h * 64 + lane;
         int f = 0;   // the last run that begins at or before entry e
-        if (runs > 1) {   // (of one run every tile of a large leaf)
 #pragma unroll
-            for (int st = H * 32; st > 0; st >>= 1)
-                if (f + st < runs && run[0][f + st] <= e) f += st;
-        }
+        for (int st = H * 32; st > 0; st >>= 1)
+            if (f + st < runs && run[0][f + st] <= e) f += st;
         j[h] = run[1][f] + e;
     }
     wave_sync();
